@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libkbuild.so")
-SOURCES = [os.path.join(CSRC, "kb_api.hip")]
+SOURCES = [os.path.join(CSRC, f) for f in ("kb_api.hip", "kb_f64.hip", "kb_f32.hip", "kb_f32fb.hip")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -18,7 +18,6 @@ FLAGS = [
     "-O3",
     "-std=c++17",
     "-fPIC",
-    "-shared",
     # packed FP32 instructions are kept out of every kernel
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-command-line-argument",
@@ -26,18 +25,38 @@ FLAGS = [
 
 
 def build(verbose: bool = False, extra: list[str] | None = None) -> str:
-    cmd = [HIPCC, *FLAGS, *(extra or []), "-I", INCLUDE, "-I", CSRC, "-o", LIB + ".tmp", *SOURCES]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    # the host pass does not know the packed-fp32 target feature; that warning is expected
-    err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l and l.strip())
-    if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({r.returncode}):\n{err}")
-    if verbose and err:
-        print(err, file=sys.stderr)
+    """Compile the sources side by side, then link."""
+    jobs = []
+    for src in SOURCES:
+        obj = os.path.splitext(src)[0] + ".o"
+        cmd = [HIPCC, *FLAGS, *(extra or []), "-I", INCLUDE, "-I", CSRC, "-c", "-o", obj, src]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        jobs.append((obj, cmd, subprocess.Popen(cmd, stdout=subprocess.DEVNULL, stderr=subprocess.PIPE, text=True)))
+    link = [HIPCC, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB + ".tmp", *(obj for obj, _, _ in jobs)]
+    failed = []
+    for _, cmd, p in jobs:
+        err = _errors(p.communicate()[1])
+        if p.returncode != 0:
+            failed.append(f"hipcc failed ({p.returncode}):\n{err}")
+        elif verbose and err:
+            print(err, file=sys.stderr)
+    if not failed:
+        r = subprocess.run(link, capture_output=True, text=True)
+        if r.returncode != 0:
+            failed.append(f"link failed ({r.returncode}):\n{r.stderr}")
+    for obj, _, _ in jobs:
+        if os.path.exists(obj):
+            os.remove(obj)
+    if failed:
+        raise RuntimeError("\n".join(failed))
     os.replace(LIB + ".tmp", LIB)
     return LIB
+
+
+def _errors(err: str) -> str:
+    # the host pass does not know the packed-fp32 target feature; that warning is expected
+    return "\n".join(l for l in err.splitlines() if "packed-fp32-ops" not in l and l.strip())
 
 
 if __name__ == "__main__":

@@ -10,58 +10,19 @@
 #include <atomic>
 
 #include "kb_adjoint.hpp"
-#include "kb_assemble.hpp"
 #include "kb_batch.hpp"
-#include "kb_kernels.hpp"
+#include "kb_launch.hpp"
 #include "kbuild.h"
+
+namespace kb {
+KB_INSTANCES(extern, Prec::F64)
+KB_INSTANCES(extern, Prec::F32)
+KB_INSTANCES(extern, Prec::F32FB)
+}  // namespace kb
 
 namespace {
 
 using namespace kb;
-
-constexpr size_t kAlign = 256;
-constexpr float kDefaultTau = 16.0f;
-constexpr int kDefaultBlock = 256;
-// pairs per pass-2 segment: the short one keeps three scatter workgroups per CU, the long
-// one (one per CU) is taken for tetrahedra when a segment would otherwise give runs of
-// fewer than kMinRun pairs per sub-bucket (measured: 18% faster scatter on the 20M-tet
-// mesh, 35% slower on brick meshes with the same sub-bucket counts)
-constexpr int kSeg = 4096, kSegLong = 8192, kMinRun = 16;
-constexpr int kSegThreads = 512;   // threads per pass-2 scatter workgroup
-constexpr int kTargetBuckets = 256;  // first-level buckets (pass-1 run length)
-constexpr double kSubEntries = 300;   // target distinct entries per sub-bucket
-constexpr int kHTMin = 512, kHTMax = 4096;
-constexpr int kHeavyGrid = 64;  // workgroups of k_pass3_heavy (each takes whole sub-buckets)
-static_assert(kHeavyGrid >= kHeavyPar, "k_pass3_heavy's first kHeavyPar workgroups clear the split tables");
-constexpr unsigned kFinalHeavyGrid = 256;  // workgroups copying the entries of heavy sub-buckets
-constexpr double kHalfTileRatio = 16;   // pairs per tile x bucket histogram entry
-constexpr size_t kWideStage = 112640;  // staged pair bytes per pass-1 tile, elements of > 8 rows
-
-size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
-int64_t div_up(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
-struct Plan {
-  int nen = 0, te = 0, prec = 0, block = kDefaultBlock;
-  int op = KB_OP_STIFFNESS;            // element integrand
-  int dof = 1;                         // degrees of freedom per node (assembly only)
-  float tau = kDefaultTau;
-  int64_t nel = 0, nn = 0, T = 0;
-  size_t vbytes = 8;
-  // assembly geometry
-  int s1 = 0, s2 = 0, p2 = 1, nb = 0;  // bucket / sub-bucket shifts, sub-buckets per bucket, buckets
-  int colbits = 1;                     // bits of a column index
-  int ht = 2048;                       // pass-3 hash slots
-  int seg = kSeg;                      // pairs per pass-2 segment
-  int tile = 0;                        // elements (= threads) per pass-1 workgroup
-  int cus = 256;                       // compute units of the current device (launch time)
-  int64_t ntiles = 0, nsub = 0, nhist = 0, nseg_max = 0;
-  int64_t csr_cap = 0, ntiles_csr = 0;  // running sums read back as pairs (grouped builds)
-  size_t lds1 = 0, lds2 = 0;
-  // workspace offsets
-  size_t o_coords4 = 0, o_hist = 0, o_csum = 0, o_tot = 0, o_part = 0, o_total = 0, o_bstart = 0, o_segbase = 0, o_hist2 = 0, o_seg2b = 0, o_emax = 0,
-         o_dconn = 0, o_ovl = 0, o_hvy = 0, o_tres = 0, o_row1 = 0, o_col1 = 0, o_val1 = 0, o_key2 = 0, o_val2 = 0, o_sbb = 0, o_rowoff = 0, o_usub = 0, o_ubase = 0,
-         total = 0;
-};
 
 // compute units of the current device, cached per device ordinal
 int device_cus(int* out) {
@@ -191,6 +152,14 @@ int make_plan(const kb_mesh* m, int prec, const kb_tuning* tu, Plan* p, int dof 
   // element per lane, `block` may pick the half-size tile (two workgroups per CU);
   // more rows (several DOFs per node): as many elements as keep the staged pairs near
   // 110 KB, on kWideThreads threads
+  auto lds_of = [&](int tile, int mode) {
+    const size_t slots = 4 * PairOut<double>::slot_words(mode, p->nb, p->nsub);
+    if (p->nen <= 8)  // (scan words for up to two lanes per element)
+      return (size_t)tile * p->te * (8 + p->vbytes) + slots + 4 * (2 * (size_t)tile / 64 + 2);
+    return (size_t)tile * p->te * (8 + p->vbytes) + slots + 4 * (kWideThreads / 64 + 2) +
+           (size_t)tile * p->nen * 12 + 4 * (size_t)tile + 2 * (size_t)p->te;
+  };
+  bool tile_set = false;
   if (p->nen <= 8) {
     const int big = p->nen == 4 ? (prec == KB_FP64 ? 768 : 1024) : 256;
     const int small = big / 2 % 64 == 0 ? big / 2 : 64 * ((big / 2 + 63) / 64);
@@ -199,9 +168,6 @@ int make_plan(const kb_mesh* m, int prec, const kb_tuning* tu, Plan* p, int dof 
     // (measured on the 27M bricks, FP64: 256 lanes, one wave on each SIMD, pass 1
     // 12.2 -> 9.5 ms against 192)
     const int mid = (p->nen == 8 && prec == KB_FP64) ? 192 : 0;
-    auto lds_of = [&](int tile) {  // (scan words for up to two lanes per element)
-      return (size_t)tile * p->te * (8 + p->vbytes) + 2 * 4 * (size_t)p->nb + 4 * (2 * (size_t)tile / 64 + 2);
-    };
     p->tile = big;
     // bricks: the half tile (two workgroups per CU, one's gathers under the other's
     // writes) when the tile x bucket histogram it doubles stays small next to the pairs
@@ -210,20 +176,33 @@ int make_plan(const kb_mesh* m, int prec, const kb_tuning* tu, Plan* p, int dof 
     if (m->elem == KB_HEX8 && p->dof == 1 && p->nb > 0 &&
         (double)p->T >= kHalfTileRatio * (double)p->nb * (double)div_up(p->nel, small))
       p->tile = small;
-    if (tu && (tu->block == big || tu->block == small || (mid && tu->block == mid))) p->tile = tu->block;
-    if (mid && p->tile == big && lds_of(big) > 163840) p->tile = mid;
-    if (lds_of(p->tile) > 163840) p->tile = small;  // many buckets: the counters need the room
-    p->lds1 = lds_of(p->tile);
+    tile_set = tu && (tu->block == big || tu->block == small || (mid && tu->block == mid));
+    if (tile_set) p->tile = tu->block;
+    if (mid && p->tile == big && lds_of(big, kTwoLevel) > 163840) p->tile = mid;
+    if (lds_of(p->tile, kTwoLevel) > 163840) p->tile = small;  // many buckets: the counters need the room
   } else {
     p->tile = (int)wide_tile;
-    p->lds1 = (size_t)p->tile * p->te * (8 + p->vbytes) + 2 * 4 * (size_t)p->nb + 4 * (kWideThreads / 64 + 2) +
-              (size_t)p->tile * p->nen * 12 + 4 * (size_t)p->tile + 2 * (size_t)p->te;
   }
+  // where pass 1 sends its pairs (kb_assemble.hpp): widths set by hand mean the two levels
+  p->mode = kTwoLevel;
+  if (p->nel > 0 && p->nb > 0 && !(tu && (tu->bucket_bits || tu->seg_pairs))) {
+    if (csr_cap == 0 && p->nsub <= kSlotsArray) {
+      int tile = p->tile;
+      if (p->nen <= 8 && !tile_set && div_up(p->nel, tile) < kDirectTiles) tile = kSmallTile;
+      if (div_up(p->nel, tile) * p->nsub <= kDirectRuns && lds_of(tile, kDirect) <= 163840) {
+        p->mode = kDirect;
+        p->tile = tile;
+      }
+    }
+    if (p->mode == kTwoLevel && lds_of(p->tile, kAsk) <= 163840) p->mode = kAsk;
+  }
+  p->lds1 = lds_of(p->tile, p->mode);
   p->ntiles = div_up(p->nel, p->tile);
   p->ntiles_csr = div_up(csr_cap, kCsrTile);
-  p->nhist = (int64_t)p->nb * (p->ntiles + p->ntiles_csr);
-  if (csr_cap > 0 && 2 * (size_t)kCsrTile * (8 + p->vbytes) + 2 * 4 * (size_t)p->nb + 4 * (256 / 64 + 2) > 163840)
-    return KB_EINVAL;
+  p->nhist = p->mode == kDirect ? 0 : (int64_t)p->nb * (p->ntiles + p->ntiles_csr);
+  p->lds_csr = 2 * (size_t)kCsrTile * (8 + p->vbytes) + 4 * PairOut<double>::slot_words(p->mode, p->nb, p->nsub) +
+               4 * (kCsrThreads / 64 + 2);
+  if (csr_cap > 0 && p->lds_csr > 163840) return KB_EINVAL;
   if (tu && tu->seg_pairs)
     p->seg = tu->seg_pairs;
   else
@@ -238,20 +217,17 @@ int make_plan(const kb_mesh* m, int prec, const kb_tuning* tu, Plan* p, int dof 
     return o;
   };
   const size_t T = (size_t)p->T;
-  const int64_t scan_n = std::max<int64_t>(p->nb, p->nsub + 1);
   p->o_coords4 = take(p->dof > 1 ? 0 : 32 * (size_t)p->nn);  // assembly with several DOFs: no geometry
-  // scan outputs hold n + 1 words: the scan writes its total after the last entry
   p->o_hist = take(4 * (size_t)p->nhist);
   p->o_csum = take(4 * (size_t)div_up(p->ntiles + p->ntiles_csr, kColChunk) * (size_t)p->nb);
   p->o_tot = take(4 * (size_t)p->nb);
-  p->o_part = take(4 * (size_t)(div_up(scan_n, kScanChunk) + 1));
-  p->o_total = take(8);
+  p->o_part = take(4 * (size_t)(div_up(p->nsub, kScanChunk) + 1));
   p->o_bstart = take(4 * ((size_t)p->nb + 1));
   p->o_segbase = take(4 * ((size_t)p->nb + 1));
-  p->o_hist2 = take(4 * (size_t)(p->nseg_max * p->p2));
+  p->o_hist2 = take(4 * (size_t)(p->nseg_max * p->p2));  // (direct: the nsub sub-bucket counters)
   p->o_seg2b = take(4 * (size_t)p->nseg_max);
-  p->o_emax = take(8);  // largest value exponent, then the count of heavy sub-buckets
-  p->o_ovl = take(4 * (size_t)p->nsub);  // heavy sub-buckets (k_pass3_heavy)
+  p->o_head = take(4 * kHeadWords);      // largest value exponent, heavy sub-buckets, ... (k_begin)
+  p->o_ovl = take(4 * (size_t)p->nsub);  // heavy sub-buckets (k_heavy)
   p->o_hvy = take(4 * ((size_t)kHeavyPar * kHvyWords + kBigWords));  // their split tables and big leaves
   p->o_dconn = take(p->dof > 1 ? 4 * (size_t)p->nen * (size_t)p->nel : 0);  // expanded connectivity
   p->o_tres = take(csr_cap > 0 ? p->vbytes * T : 0);  // residuals of the reduced entries
@@ -266,389 +242,6 @@ int make_plan(const kb_mesh* m, int prec, const kb_tuning* tu, Plan* p, int dof 
   p->o_ubase = take(4 * ((size_t)p->nsub + 1));
   p->total = off;
   return KB_OK;
-}
-
-struct Events {
-  void** ev;
-  hipStream_t s;
-  int rec(int i) {
-    if (!ev) return KB_OK;
-    return hipEventRecord((hipEvent_t)ev[i], s) == hipSuccess ? KB_OK : KB_EHIP;
-  }
-};
-
-#define KB_LAUNCH_CHECK()                                   \
-  do {                                                      \
-    if (hipGetLastError() != hipSuccess) return KB_EHIP;    \
-  } while (0)
-#define KB_TRY(x)                  \
-  do {                             \
-    int _r = (x);                  \
-    if (_r != KB_OK) return _r;    \
-  } while (0)
-
-unsigned grid_for(int64_t n, int block) { return (unsigned)div_up(n, block); }
-
-// exclusive scan in[0..n) -> out[0..n] (out holds n + 1 words), total64 optional
-// (in-place allowed)
-int scan(const int32_t* in, int64_t n, int32_t* part, int32_t* out, int64_t* total64, hipStream_t s) {
-  if (n == 0) {
-    k_scan_empty<<<1, 1, 0, s>>>(out, total64);
-    KB_LAUNCH_CHECK();
-    return KB_OK;
-  }
-  const int64_t nb = div_up(n, kScanChunk);
-  k_scan_partials<<<(unsigned)nb, kScanThreads, 0, s>>>(in, n, part);
-  KB_LAUNCH_CHECK();
-  k_scan_top<<<1, kScanThreads, 0, s>>>(part, nb);
-  KB_LAUNCH_CHECK();
-  k_scan_down<<<(unsigned)nb, kScanThreads, 0, s>>>(in, n, part, out, total64);
-  KB_LAUNCH_CHECK();
-  return KB_OK;
-}
-
-template <typename K>
-bool set_lds(K kernel, size_t bytes) {
-  return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) ==
-         hipSuccess;
-}
-
-template <int NEN, Prec P, bool FROM_VALUES, int BLOCK, Op OP>
-int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsigned char* ws, uint32_t* status,
-                       hipStream_t s) {
-  using V = typename PrecTraits<P>::V;
-  if constexpr (NEN == 8 && !FROM_VALUES && OP == Op::Stiffness && P != Prec::F64) {
-    // bricks in FP32: a lane pair per element, 2 * BLOCK lanes for a tile of BLOCK elements
-    // (in FP64 the pair kernel sits at the register limit and was slower on 1M bricks)
-    auto kern = k_pass1_pair<P, 2 * BLOCK>;
-    if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<(unsigned)p.ntiles, 2 * BLOCK, p.lds1, s>>>(m->conn, (const double4*)(ws + p.o_coords4), m->coef, p.nel,
-                                                       p.nn, p.tau, p.s1, p.nb, (const uint32_t*)(ws + p.o_hist),
-                                                       (uint16_t*)(ws + p.o_row1), (uint32_t*)(ws + p.o_col1),
-                                                       (V*)(ws + p.o_val1), (uint32_t*)(ws + p.o_emax), status);
-    KB_LAUNCH_CHECK();
-    return KB_OK;
-  }
-  if constexpr (NEN == 8 && !FROM_VALUES && P == Prec::F64) {
-    // bricks in FP64: two tiles per workgroup (two waves per SIMD while integrating)
-    auto kern = k_pass1_two<NEN, P, BLOCK, OP>;
-    if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<(unsigned)div_up(p.ntiles, 2), 2 * BLOCK, p.lds1, s>>>(
-        m->conn, (const double4*)(ws + p.o_coords4), m->coef, p.nel, p.nn, p.tau, p.s1, p.nb, p.ntiles,
-        (const uint32_t*)(ws + p.o_hist), (uint16_t*)(ws + p.o_row1), (uint32_t*)(ws + p.o_col1),
-        (V*)(ws + p.o_val1), (uint32_t*)(ws + p.o_emax), status);
-    KB_LAUNCH_CHECK();
-    return KB_OK;
-  }
-  auto kern = [] {
-    if constexpr (NEN == 4)
-      return k_pass1_tet<P, FROM_VALUES, BLOCK, OP>;
-    else
-      return k_pass1<NEN, P, FROM_VALUES, BLOCK, OP>;
-  }();
-  if (!set_lds(kern, p.lds1)) return KB_EHIP;
-  // tetrahedra: persistent, the workgroups that fit on the device at once (LDS-bound),
-  // at least one per XCD slot (b % 8) that owns tiles; bricks: one tile per workgroup
-  const int per_cu = std::max(1, (int)(163840 / std::max<size_t>(p.lds1, 1)));
-  const int64_t g1 =
-      NEN == 8 ? p.ntiles
-               : std::min<int64_t>(p.ntiles, std::max<int64_t>(8, (int64_t)p.cus * std::min(per_cu, 2048 / BLOCK)));
-  kern<<<(unsigned)g1, BLOCK, p.lds1, s>>>(m->conn, (const double4*)(ws + p.o_coords4), m->coef, (const V*)klow, p.nel,
-                                           p.nn, p.tau, p.s1, p.nb, p.ntiles, (const uint32_t*)(ws + p.o_hist),
-                                           (uint16_t*)(ws + p.o_row1), (uint32_t*)(ws + p.o_col1),
-                                           (V*)(ws + p.o_val1), (uint32_t*)(ws + p.o_emax), status);
-  KB_LAUNCH_CHECK();
-  return KB_OK;
-}
-
-// pass-1 tile sizes (elements = lanes per workgroup): {small, default} per element and
-// value size; the staging LDS is tile * pairs * (8 + value bytes)
-template <int NEN, Prec P>
-struct TileSizes {
-  static constexpr int big = NEN == 4 ? (P == Prec::F64 ? 768 : 1024) : 256;
-  static constexpr int mid = NEN == 8 && P == Prec::F64 ? 192 : 0;  // FP64, many buckets
-  static constexpr int small = big / 2 >= 64 && (big / 2) % 64 == 0 ? big / 2 : 64 * ((big / 2 + 63) / 64);
-};
-
-// elements of more than 8 rows: `tile` elements on kWideThreads threads, one tile per workgroup
-template <int NEN, typename V>
-int launch_pass1_wide(const Plan& p, const kb_mesh* m, const void* klow, unsigned char* ws, uint32_t* status,
-                      hipStream_t s) {
-  auto kern = k_pass1_wide<NEN, V>;
-  if (!set_lds(kern, p.lds1)) return KB_EHIP;
-  kern<<<(unsigned)p.ntiles, kWideThreads, p.lds1, s>>>(m->conn, (const V*)klow, p.nel, p.nn, p.tile, p.s1, p.nb,
-                                              (const uint32_t*)(ws + p.o_hist), (uint16_t*)(ws + p.o_row1),
-                                              (uint32_t*)(ws + p.o_col1), (V*)(ws + p.o_val1),
-                                              (uint32_t*)(ws + p.o_emax), status);
-  KB_LAUNCH_CHECK();
-  return KB_OK;
-}
-
-// OP: the integrand of pass 1 when the values are not given
-template <int NEN, Prec P, bool FROM_VALUES, Op OP = Op::Stiffness>
-int launch_pass1(const Plan& p, const kb_mesh* m, const void* klow, unsigned char* ws, uint32_t* status,
-                 hipStream_t s) {
-  if constexpr (NEN > 8) {
-    static_assert(FROM_VALUES, "elements of more than 8 rows are assembled from given values");
-    return launch_pass1_wide<NEN, typename PrecTraits<P>::V>(p, m, klow, ws, status, s);
-  } else {
-    if (p.tile == TileSizes<NEN, P>::big)
-      return launch_pass1_block<NEN, P, FROM_VALUES, TileSizes<NEN, P>::big, OP>(p, m, klow, ws, status, s);
-    if (p.tile == TileSizes<NEN, P>::small)
-      return launch_pass1_block<NEN, P, FROM_VALUES, TileSizes<NEN, P>::small, OP>(p, m, klow, ws, status, s);
-    if constexpr (TileSizes<NEN, P>::mid > 0) {
-      if (p.tile == TileSizes<NEN, P>::mid)
-        return launch_pass1_block<NEN, P, FROM_VALUES, TileSizes<NEN, P>::mid, OP>(p, m, klow, ws, status, s);
-    }
-    return KB_EINVAL;
-  }
-}
-
-// Running sums of a grouped build: read back as a second source of pairs (in), and the
-// pass's entries written with their residuals and rows (out).
-struct Carry {
-  bool first = true;              // first pass: the status words are initialised
-  const int32_t* rows = nullptr;  // in: rows, columns, values, residuals of the entries
-  const int32_t* cols = nullptr;
-  const void* vals = nullptr;
-  const void* res = nullptr;
-  const int64_t* nnz = nullptr;   // in: number of entries (device); nullptr: no input
-  void* res_out = nullptr;        // out: residuals and rows of the pass's entries
-  int32_t* rows_out = nullptr;
-};
-
-// pass 3, then the sub-buckets it could not hold (k_pass3_heavy: a small grid whose
-// workgroups return at once when there are none)
-template <typename V, bool RES>
-int launch_pass3(const Plan& p, uint32_t* key2, V* val2, uint32_t* sbb, uint32_t* emax, int32_t* tcol, V* tval,
-                 V* tres, uint32_t* rowoff, uint32_t* usub, uint32_t* ov_list, uint32_t* hvy, hipStream_t s) {
-  const unsigned g3 = (unsigned)p.nsub;
-  uint32_t* ov_count = emax + 1;
-  switch (p.ht) {
-    case 512:
-      k_pass3<V, 512, RES><<<g3, 256, (size_t)12 << p.s2, s>>>(key2, val2, sbb, p.s2, p.colbits, p.nn, emax, tcol, tval, tres, rowoff,
-                                              usub, ov_list, ov_count);
-      break;
-    case 1024:
-      k_pass3<V, 1024, RES><<<g3, 256, (size_t)12 << p.s2, s>>>(key2, val2, sbb, p.s2, p.colbits, p.nn, emax, tcol, tval, tres,
-                                               rowoff, usub, ov_list, ov_count);
-      break;
-    case 2048:
-      k_pass3<V, 2048, RES><<<g3, 256, (size_t)12 << p.s2, s>>>(key2, val2, sbb, p.s2, p.colbits, p.nn, emax, tcol, tval, tres,
-                                               rowoff, usub, ov_list, ov_count);
-      break;
-    default:
-      k_pass3<V, 4096, RES><<<g3, 256, (size_t)12 << p.s2, s>>>(key2, val2, sbb, p.s2, p.colbits, p.nn, emax, tcol, tval, tres,
-                                               rowoff, usub, ov_list, ov_count);
-      break;
-  }
-  KB_LAUNCH_CHECK();
-  auto kh = k_pass3_heavy<V, RES>;
-  if (!set_lds(kh, HeavySmem::bytes())) return KB_EHIP;
-  const unsigned gh = (unsigned)std::min<int64_t>(p.nsub, kHeavyGrid);
-  kh<<<gh, kHeavyThreads, HeavySmem::bytes(), s>>>(key2, val2, (uint32_t*)tcol, tval, sbb, p.s2, p.colbits, p.nn, emax,
-                                                   tres, rowoff, usub, ov_list, ov_count, hvy);
-  KB_LAUNCH_CHECK();
-  // up to kHeavyPar of them split by many workgroups, their big leaves summed by many
-  // workgroups, their first-level ranges reduced by one workgroup per compute unit, then
-  // their entry counts scanned (all return at once when there are none)
-  const unsigned gsplit = (unsigned)std::max(1, 2 * p.cus);
-  k_heavy_rows<<<gsplit, kHeavyThreads, 0, s>>>(key2, sbb, p.colbits, ov_list, ov_count, hvy);
-  KB_LAUNCH_CHECK();
-  k_heavy_layout<<<(unsigned)kHeavyPar, kHvyRows, 0, s>>>(sbb, p.colbits, ov_list, ov_count, hvy);
-  KB_LAUNCH_CHECK();
-  k_heavy_hist<<<gsplit, kHeavyThreads, 0, s>>>(key2, sbb, p.colbits, ov_list, ov_count, hvy);
-  KB_LAUNCH_CHECK();
-  k_heavy_starts<<<(unsigned)kHeavyPar, kHeavyThreads, 0, s>>>(sbb, p.colbits, ov_list, ov_count, hvy);
-  KB_LAUNCH_CHECK();
-  k_heavy_scatter<V><<<gsplit, kHeavyThreads, 0, s>>>(key2, val2, (uint32_t*)tcol, tval, sbb, p.colbits, ov_list,
-                                                      ov_count, hvy);
-  KB_LAUNCH_CHECK();
-  auto kl = k_heavy_bigleaf<V>;
-  if (!set_lds(kl, HeavySmem::bytes())) return KB_EHIP;
-  kl<<<(unsigned)std::max(1, p.cus), kHeavyThreads, HeavySmem::bytes(), s>>>((uint32_t*)tcol, tval, emax, ov_count,
-                                                                           hvy);
-  KB_LAUNCH_CHECK();
-  auto kr = k_pass3_heavy_ranges<V, RES>;
-  if (!set_lds(kr, HeavySmem::bytes())) return KB_EHIP;
-  kr<<<(unsigned)std::max(1, p.cus), kHeavyThreads, HeavySmem::bytes(), s>>>(key2, val2, (uint32_t*)tcol, tval,
-                                                                           p.colbits, emax, tres, ov_count, hvy);
-  KB_LAUNCH_CHECK();
-  k_pass3_heavy_finish<V, RES><<<(unsigned)kHeavyPar, kFinishThreads, 0, s>>>((uint32_t*)tcol, tval, tres, sbb, p.s2,
-                                                                            p.nn, rowoff, usub, ov_list, ov_count, hvy);
-  KB_LAUNCH_CHECK();
-  return KB_OK;
-}
-
-template <typename V>
-int assemble_tail(const Plan& p, unsigned char* ws, int32_t* row_ptr, int32_t* col_idx, V* vals, int64_t cap,
-                  int64_t* nnz_dev, uint32_t* status, Events& ev, hipStream_t s, const Carry* cr) {
-  auto* bstart = (uint32_t*)(ws + p.o_bstart);
-  auto* segbase = (uint32_t*)(ws + p.o_segbase);
-  auto* hist2 = (uint32_t*)(ws + p.o_hist2);
-  auto* seg2b = (uint32_t*)(ws + p.o_seg2b);
-  auto* emax = (uint32_t*)(ws + p.o_emax);
-  auto* row1 = (uint16_t*)(ws + p.o_row1);
-  auto* col1 = (uint32_t*)(ws + p.o_col1);
-  auto* val1 = (V*)(ws + p.o_val1);
-  auto* key2 = (uint32_t*)(ws + p.o_key2);
-  auto* val2 = (V*)(ws + p.o_val2);
-  auto* sbb = (uint32_t*)(ws + p.o_sbb);
-  auto* rowoff = (uint32_t*)(ws + p.o_rowoff);
-  auto* usub = (uint32_t*)(ws + p.o_usub);
-  auto* ubase = (uint32_t*)(ws + p.o_ubase);
-  auto* part = (int32_t*)(ws + p.o_part);
-  // pass-3 output reuses the pass-1 buffers (dead after pass 2)
-  auto* tcol = (int32_t*)col1;
-  auto* tval = val1;
-  KB_TRY(ev.rec(KB_STAGE_HISTOGRAM));
-  if (p.nb > 0) {
-    const unsigned gs = (unsigned)p.nseg_max;
-    k_seg_map<<<(unsigned)p.nb, 256, 0, s>>>(segbase, seg2b);
-    KB_LAUNCH_CHECK();
-    if (p.seg == kSegLong)
-      k_hist2<kSegLong><<<gs, 256, 4 * (size_t)p.p2, s>>>(row1, bstart, segbase, seg2b, p.nb, p.s2, p.p2, hist2);
-    else
-      k_hist2<kSeg><<<gs, 256, 4 * (size_t)p.p2, s>>>(row1, bstart, segbase, seg2b, p.nb, p.s2, p.p2, hist2);
-    KB_LAUNCH_CHECK();
-    k_colscan<<<(unsigned)p.nb, 256, 0, s>>>(hist2, bstart, segbase, p.nb, p.p2, sbb);
-    KB_LAUNCH_CHECK();
-  }
-  KB_TRY(ev.rec(KB_STAGE_PARTITION));
-  if (p.nb > 0) {
-    const unsigned gs = (unsigned)p.nseg_max;
-    auto k2 = p.seg == kSegLong ? k_scatter2<V, kSegLong, kSegThreads> : k_scatter2<V, kSeg, kSegThreads>;
-    if (!set_lds(k2, p.lds2)) return KB_EHIP;
-    k2<<<gs, kSegThreads, p.lds2, s>>>(row1, col1, val1, bstart, segbase, seg2b, hist2, sbb, p.nb, p.s2, p.p2,
-                                      p.colbits, key2, val2);
-    KB_LAUNCH_CHECK();
-  }
-  auto* tres = (V*)(ws + p.o_tres);
-  KB_TRY(ev.rec(KB_STAGE_REDUCE));
-  if (p.nsub > 0) {
-    auto* ov_list = (uint32_t*)(ws + p.o_ovl);
-    auto* hvy = (uint32_t*)(ws + p.o_hvy);
-    if (cr)
-      KB_TRY((launch_pass3<V, true>(p, key2, val2, sbb, emax, tcol, tval, tres, rowoff, usub, ov_list, hvy, s)));
-    else
-      KB_TRY((launch_pass3<V, false>(p, key2, val2, sbb, emax, tcol, tval, nullptr, rowoff, usub, ov_list, hvy, s)));
-  }
-  KB_TRY(ev.rec(KB_STAGE_COMPRESS));
-  KB_TRY(scan((const int32_t*)usub, p.nsub, part, (int32_t*)ubase, nnz_dev, s));
-  if (p.nsub > 0) {
-    const unsigned gf = (unsigned)div_up(p.nsub, 4);
-    auto* ov_list = (const uint32_t*)(ws + p.o_ovl);
-    auto* hvy = (const uint32_t*)(ws + p.o_hvy);
-    const uint32_t* ov_count = emax + 1;
-    if (cr) {
-      k_final<V, true><<<gf, 256, 0, s>>>(sbb, ubase, tcol, tval, tres, rowoff, p.s2, p.nn, p.nsub, row_ptr, col_idx,
-                                          vals, (V*)cr->res_out, cr->rows_out, cap, status);
-      KB_LAUNCH_CHECK();
-      k_final_heavy<V, true><<<kFinalHeavyGrid, 256, 0, s>>>(sbb, ubase, tcol, tval, tres, rowoff, p.s2, p.nn, p.nsub,
-                                                            ov_list, ov_count, hvy, col_idx, vals, (V*)cr->res_out,
-                                                            cr->rows_out, cap);
-    } else {
-      k_final<V><<<gf, 256, 0, s>>>(sbb, ubase, tcol, tval, nullptr, rowoff, p.s2, p.nn, p.nsub, row_ptr, col_idx,
-                                    vals, nullptr, nullptr, cap, status);
-      KB_LAUNCH_CHECK();
-      k_final_heavy<V><<<kFinalHeavyGrid, 256, 0, s>>>(sbb, ubase, tcol, tval, nullptr, rowoff, p.s2, p.nn, p.nsub,
-                                                      ov_list, ov_count, hvy, col_idx, vals, nullptr, nullptr, cap);
-    }
-    KB_LAUNCH_CHECK();
-  } else {
-    k_scan_empty<<<1, 1, 0, s>>>(row_ptr, nullptr);
-    KB_LAUNCH_CHECK();
-  }
-  KB_TRY(ev.rec(KB_N_STAGES));
-  return KB_OK;
-}
-
-template <int NEN, Prec P>
-int build_impl(const Plan& p, const kb_mesh* m, const void* klow, unsigned char* ws, int32_t* row_ptr,
-               int32_t* col_idx, void* vals, int64_t cap, int64_t* nnz_dev, uint32_t* status, Events& ev,
-               hipStream_t s, const Carry* cr = nullptr) {
-  using V = typename PrecTraits<P>::V;
-  auto* hist = (uint32_t*)(ws + p.o_hist);
-  auto* csum = (uint32_t*)(ws + p.o_csum);
-  auto* tot = (uint32_t*)(ws + p.o_tot);
-  auto* part = (int32_t*)(ws + p.o_part);
-  auto* total = (int64_t*)(ws + p.o_total);
-  auto* bstart = (uint32_t*)(ws + p.o_bstart);
-  auto* segbase = (uint32_t*)(ws + p.o_segbase);
-
-  // tiles of running sums read back (grouped builds) follow the element tiles
-  const int64_t ntc = (cr && cr->nnz && p.nb > 0) ? p.ntiles_csr : 0;
-  const int64_t nt_all = p.ntiles + ntc;
-  KB_TRY(ev.rec(KB_STAGE_INIT));
-  if (!cr || cr->first) {
-    k_init_status<<<1, 64, 0, s>>>(status, nnz_dev);
-    KB_LAUNCH_CHECK();
-  }
-  k_fill_i32<<<1, 64, 0, s>>>((int32_t*)(ws + p.o_emax), 2, 0);
-  KB_LAUNCH_CHECK();
-
-  KB_TRY(ev.rec(KB_STAGE_COUNT));
-  if (p.ntiles > 0) {
-    // with no nodes every element has an index error: flagged, nothing counted
-    const int nb = p.nb > 0 ? p.nb : 0;
-    k_hist_buckets<NEN><<<(unsigned)p.ntiles, 256, 4 * (size_t)(nb > 0 ? nb : 1), s>>>(
-        m->conn, p.nel, p.nn, p.tile, nb > 0 ? p.s1 : 30, nb, hist, status);
-    KB_LAUNCH_CHECK();
-  }
-  if (ntc > 0) {
-    k_hist_csr<<<(unsigned)ntc, 256, 4 * (size_t)p.nb, s>>>(cr->rows, cr->nnz, p.csr_cap, p.nn, p.s1, p.nb,
-                                                            hist + p.ntiles * p.nb);
-    KB_LAUNCH_CHECK();
-  }
-  KB_TRY(ev.rec(KB_STAGE_OFFSETS));
-  if (p.nb > 0) {
-    // tile offsets: column sums per chunk of tiles, their scan per bucket, bucket starts,
-    // then the offsets in place (the histogram stays tile-major)
-    const int64_t nchunk = div_up(nt_all, kColChunk);
-    const dim3 gc((unsigned)nchunk, (unsigned)div_up(p.nb, 256));
-    if (nchunk > 0) {
-      k_col_chunks<<<gc, 256, 0, s>>>(hist, nt_all, p.nb, csum);
-      KB_LAUNCH_CHECK();
-    }
-    k_col_scan<<<(unsigned)p.nb, 256, 0, s>>>(csum, nchunk, p.nb, tot);
-    KB_LAUNCH_CHECK();
-    KB_TRY(scan((const int32_t*)tot, p.nb, part, (int32_t*)bstart, total, s));
-    if (nchunk > 0) {
-      k_col_offsets<<<gc, 256, 0, s>>>(hist, csum, bstart, nt_all, p.nb);
-      KB_LAUNCH_CHECK();
-    }
-    k_segments<<<1, 256, 0, s>>>(bstart, p.nb, p.seg, segbase);
-    KB_LAUNCH_CHECK();
-  }
-  if (p.ntiles > 0 && p.nb > 0 && !klow && p.nn > 0) {
-    k_pad_coords<<<(unsigned)std::min<int64_t>(div_up(p.nn, 256), 8192), 256, 0, s>>>(m->coords, p.nn,
-                                                                                     (double4*)(ws + p.o_coords4));
-    KB_LAUNCH_CHECK();
-  }
-  // the integrate stage is exactly one kernel (pass 1), for either integrand
-  KB_TRY(ev.rec(KB_STAGE_INTEGRATE));
-  if (p.ntiles > 0 && p.nb > 0) {
-    if (klow) {
-      KB_TRY((launch_pass1<NEN, P, true>(p, m, klow, ws, status, s)));
-    } else if constexpr (NEN <= 8) {
-      if (p.op == KB_OP_MASS)
-        KB_TRY((launch_pass1<NEN, P, false, Op::Mass>(p, m, nullptr, ws, status, s)));
-      else
-        KB_TRY((launch_pass1<NEN, P, false>(p, m, nullptr, ws, status, s)));
-    } else {
-      return KB_EINVAL;  // several DOFs per node: values are always given
-    }
-  }
-  if (ntc > 0) {
-    const size_t lds = 2 * (size_t)kCsrTile * (8 + sizeof(V)) + 2 * 4 * (size_t)p.nb + 4 * (256 / 64 + 2);
-    if (!set_lds(k_pass1_csr<V>, lds)) return KB_EHIP;
-    k_pass1_csr<V><<<(unsigned)ntc, 256, lds, s>>>(cr->rows, cr->cols, (const V*)cr->vals, (const V*)cr->res, cr->nnz,
-                                                   p.csr_cap, p.nn, p.s1, p.nb, hist + p.ntiles * p.nb,
-                                                   (uint16_t*)(ws + p.o_row1), (uint32_t*)(ws + p.o_col1),
-                                                   (V*)(ws + p.o_val1), (uint32_t*)(ws + p.o_emax));
-    KB_LAUNCH_CHECK();
-  }
-  return assemble_tail<V>(p, ws, row_ptr, col_idx, (V*)vals, cap, nnz_dev, status, ev, s, cr);
 }
 
 template <int NEN>
@@ -701,27 +294,6 @@ int make_group_plan(const kb_mesh* m, int prec, const kb_tuning* tu, int64_t gro
   gp->o_resA = take(vb * c);
   gp->o_rowsA = take(4 * c);
   gp->total = off;
-  return KB_OK;
-}
-
-template <int NEN, Prec P>
-int integrate_impl(const Plan& p, const kb_mesh* m, void* vals, uint32_t* status, Events& ev, hipStream_t s) {
-  using V = typename PrecTraits<P>::V;
-  KB_TRY(ev.rec(KB_STAGE_INIT));
-  k_init_status<<<1, 64, 0, s>>>(status, nullptr);
-  KB_LAUNCH_CHECK();
-  for (int i = KB_STAGE_COUNT; i <= KB_STAGE_INTEGRATE; ++i) KB_TRY(ev.rec(i));
-  if (p.nel > 0) {
-    const int blk = std::min(p.block, 256);  // the kernel is built for at most 256 lanes
-    if (p.op == KB_OP_MASS)
-      k_integrate_store<NEN, P, Op::Mass><<<grid_for(p.nel, blk), blk, 0, s>>>(m->conn, m->coords, m->coef, p.nel,
-                                                                              p.nn, p.tau, (V*)vals, status);
-    else
-      k_integrate_store<NEN, P><<<grid_for(p.nel, blk), blk, 0, s>>>(m->conn, m->coords, m->coef, p.nel, p.nn, p.tau,
-                                                                    (V*)vals, status);
-    KB_LAUNCH_CHECK();
-  }
-  for (int i = KB_STAGE_HISTOGRAM; i <= KB_N_STAGES; ++i) KB_TRY(ev.rec(i));
   return KB_OK;
 }
 

@@ -1,32 +1,33 @@
-// kb_assemble.hpp -- atomic-free assembly of lower-triangular CSR K on gfx950.
+// kb_assemble.hpp -- assembly of lower-triangular CSR K on gfx950.
 //
 // Every element contributes nen(nen+1)/2 lower pairs (Alg. 1 mapping): the node of
 // rank r in its element (by global id) owns the r+1 pairs (itself, smaller ids) whose
 // global row is that node.  Assembly (Eq. 6) sums the pairs with equal (row, col).
 //
-// Data movement: two partition passes, then a streaming reduction in LDS.
-//   hist     per tile of elements: pairs per row bucket (row >> s1), tile-major.
-//   offsets  transpose + exclusive scan + transpose back: each tile's write offset in
-//            each bucket; bucket boundaries.
+// Data movement: a partition by row, then a streaming reduction in LDS.
+//   begin    status and counters cleared, padded coordinates (32 bytes per node), and a
+//            sample of the elements that tells whether they are numbered with locality.
+//   count    per tile of elements: pairs per row bucket (row >> s1), tile-major; or, the
+//            direct way (few sub-buckets, or locality), pairs per sub-bucket (row >> s2).
+//   offsets  column scan of the tile-major counts: each tile's write offset in each
+//            bucket; or the scan of the sub-bucket counts.
 //   pass 1   per tile (one element per lane): integrate the element (or read given
-//            values; coordinates come from a padded 32-byte-per-node copy made by
-//            k_pad_coords), stage its pairs in LDS grouped by bucket, write each bucket's run
-//            at the tile's offset as (row, col, value) arrays.  Also the largest value
-//            exponent, which fixes the exact-sum scale below.
-//   pass 2   per fixed-size segment of a bucket: histogram of sub-buckets
-//            (row >> s2); per bucket, a prefix over its segments for each sub-bucket;
+//            values), stage its pairs in LDS grouped by bucket or sub-bucket, write each
+//            group's run as (row, col, value) arrays, or (row_local << colbits | col,
+//            value).  Also the largest value exponent, which fixes the exact-sum scale.
+//   pass 2   (not the direct way) per fixed-size segment of a bucket: histogram of
+//            sub-buckets; per bucket, a prefix over its segments for each sub-bucket;
 //            then LDS-staged scatter into contiguous sub-bucket ranges; pairs are
 //            repacked as (row_local << colbits | col, value).
 //   pass 3   per sub-bucket: stream its pairs into an LDS hash table keyed by the
 //            packed (row, col); each value is added as a 128-bit fixed-point integer
 //            (scale 2^F from the largest exponent), so every sum is exact and its
 //            result does not depend on the order of the additions: the output is
-//            bitwise deterministic although the partition passes order pairs through
-//            LDS atomics.  Entries are then ordered by (row, col) and converted once
-//            (correct rounding of the exact sum to FP64, then to the value type).
+//            bitwise deterministic although the partition orders pairs through
+//            atomics.  Entries are then ordered by (row, col) and converted once
+//            (correct rounding of the exact sum to the value type).
 //   final    scan of per-sub-bucket unique counts; row_ptr and the compacted col/vals.
-// A sub-bucket whose distinct entries overflow the table takes a slow single-lane path
-// in global memory (heap sort, then the same exact sums).
+// Sub-buckets whose distinct entries overflow the table are reduced by k_heavy.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -86,6 +87,33 @@ __device__ __forceinline__ uint32_t block_scan_array(T* a, int n, uint32_t* smem
     }
   __syncthreads();
   return total;
+}
+
+// Called by every workgroup (256 threads) of a grid of `blocks` once it has added to
+// cnt[0 .. n) (atomics): the last one to arrive turns the counts into exclusive offsets,
+// starts[0 .. n] and, in place, cnt.  *done starts at zero.
+__device__ __forceinline__ void last_block_starts(uint32_t* cnt, int n, uint32_t* starts, uint32_t* done,
+                                                  uint32_t blocks) {
+  __shared__ uint32_t s_scan[8], s_last;
+  __threadfence();  // this thread's additions before the arrival
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(done, 1u) == blocks - 1 ? 1u : 0u;
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  uint32_t carry = 0;
+  for (int b0 = 0; b0 < n; b0 += blockDim.x) {
+    const int b = b0 + threadIdx.x;
+    const uint32_t v = b < n ? __hip_atomic_load(&cnt[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    uint32_t total;
+    const uint32_t ex = carry + block_scan_u32(v, s_scan, &total);
+    if (b < n) {
+      starts[b] = ex;
+      cnt[b] = ex;
+    }
+    carry += total;
+  }
+  if (threadIdx.x == 0) starts[n] = carry;
 }
 
 // ------------------------------------------------------- exact fixed-point sums
@@ -209,39 +237,216 @@ __device__ __forceinline__ V fixed_residual(uint64_t lo, uint64_t hi, int F, V h
   return from_fixed_as<V>(dl, dh, F);
 }
 
-// ---------------------------------------------------------------------- histogram
-// Per tile of `te` elements: pairs per bucket (row >> s1), written tile-major
-// hist[t * nb + b].  Flags index errors; invalid elements contribute nothing.
-// Reserve the pairs of local rows OFF .. OFF+N-1 of an element in their buckets' LDS
-// counters: each run of consecutive rows in one bucket takes one atomic for its total
+// ---------------------------------------------------------------- where pairs go
+// Pass 1 partitions its tile's pairs by bucket (row >> s1, then pass 2 splits each bucket
+// into sub-buckets) or sends them straight to their sub-buckets (row >> s2), which skips
+// pass 2: its histogram, offsets and scatter, a read and a write of every pair.  A tile's
+// run in a sub-bucket takes one global atomic for its places, so the direct way pays when
+// a tile's pairs fall in few sub-buckets:
+//   - kDirect, few sub-buckets in the whole mesh (host: at most kSlotsArray, and at most
+//     kDirectRuns runs in all): one LDS counter per sub-bucket;
+//   - kAsk: elements and nodes numbered with locality.  k_begin counts the sub-buckets
+//     that kSamples evenly spaced tiles touch, and every kernel after it takes the direct
+//     way if the sampled runs average at least kDirectRun pairs.  An LDS hash of
+//     kSlotsHash slots then maps a tile's sub-buckets to counters; a row whose sub-bucket
+//     finds no slot takes its places one by one.
+// The sums are exact, so both ways give the same matrix bit for bit.
+enum { kTwoLevel = 0, kDirect = 1, kAsk = 2 };
+constexpr int kSlotsHash = 512, kSlotsArray = 1024, kSlotProbes = 16;
+constexpr int kSamples = 8;
+constexpr uint32_t kDirectRun = 32;
+constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
+
+// head words of a build: [0] largest exponent, [1] heavy sub-buckets, [2] and [3]
+// workgroups done (k_heavy, k_count), then the way taken (kAsk) and the samples
+constexpr int kHeadWay = 15, kHeadVotes = 16, kHeadWords = 64;
+
+// the way sampled: votes[2 i], votes[2 i + 1] are the sub-buckets and the pairs of tile i
+__device__ __forceinline__ bool votes_direct(const uint32_t* __restrict__ votes) {
+  uint64_t runs = 0, pairs = 0;
+#pragma unroll
+  for (int i = 0; i < kSamples; ++i) {
+    runs += votes[2 * i];
+    pairs += votes[2 * i + 1];
+  }
+  return runs * kDirectRun <= pairs;
+}
+
+// *way: written by k_count
+__device__ __forceinline__ bool goes_direct(int mode, const uint32_t* __restrict__ way) {
+  return mode == kAsk ? *way != 0 : mode == kDirect;
+}
+
+// The LDS counters of a tile: one per bucket (two levels), per sub-bucket of the mesh
+// (direct, array), or per sub-bucket that the tile touches (direct, hash: key[] holds the
+// sub-bucket of each slot).  The ways are separate code under one branch at the top of
+// each kernel: as run-time cases of the same code they cost the two-level kernels 5%
+// (20.25M tets, pass 1 2.03 -> 2.12 ms) in scalar registers.
+template <bool DIRECT>
+struct TileSlots {
+  uint32_t* cnt;  // [n] pairs per slot, then local run starts
+  uint32_t* key;  // [n] sub-bucket of the slot (hash)
+  int n;          // counters in use
+  int shift;      // row -> bucket or sub-bucket
+  bool hash;
+  __device__ __forceinline__ TileSlots(uint32_t* cnt_, uint32_t* key_, int mode, int s1, int nb, int s2, int nsub) {
+    hash = DIRECT && mode == kAsk;
+    cnt = cnt_;
+    key = key_;
+    n = DIRECT ? (hash ? kSlotsHash : nsub) : nb;
+    shift = DIRECT ? s2 : s1;
+  }
+  __device__ __forceinline__ void clear(int nthreads) const {
+    for (int b = threadIdx.x; b < n; b += nthreads) {
+      cnt[b] = 0;
+      if (hash) key[b] = kEmptyKey;
+    }
+  }
+  // the slot of (sub-)bucket x, or kNoSlot (hash: no free slot within kSlotProbes probes)
+  __device__ __forceinline__ uint32_t find(uint32_t x) const {
+    if (!DIRECT || !hash) return x;
+    constexpr int bits = __builtin_ctz(kSlotsHash);
+    uint32_t h = (x * 0x9E3779B1u) >> (32 - bits);
+#pragma unroll 1
+    for (int p = 0; p < kSlotProbes; ++p) {
+      uint32_t k = __hip_atomic_load(&key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (k == kEmptyKey) k = atomicCAS(&key[h], kEmptyKey, x);
+      if (k == x || k == kEmptyKey) return h;
+      h = (h + 1) & (kSlotsHash - 1);
+    }
+    return kNoSlot;
+  }
+  // a row's places as reserve_rows returns them: its slot and its first place in the
+  // slot's part of the tile
+  __device__ __forceinline__ uint32_t slot(uint32_t q, int32_t row) const {
+    return DIRECT ? q >> 16 : (uint32_t)(row >> shift);
+  }
+  __device__ __forceinline__ uint32_t place(uint32_t q) const { return DIRECT ? q & 0xFFFFu : q; }
+};
+
+// Reserve the pairs of local rows OFF .. OFF+N-1 of an element in their slots' LDS
+// counters: each run of consecutive rows in one slot takes one atomic for its total
 // (under a natural numbering an element's neighbouring nodes mostly share a bucket, and
 // per-row increments from neighbouring lanes would serialise on one address); a row
-// after the first of its run starts where its predecessor's pairs end.  q: first place
-// of each row's r+1 pairs within the bucket's part of the tile.
-template <int N, int OFF, int NE>
-__device__ __forceinline__ void reserve_rows(uint32_t* cnt, const int32_t (&E)[NE], const int (&r)[NE], int s1,
+// after the first of its run starts where its predecessor's pairs end.  q: first place of
+// the row's r+1 pairs within the slot's part of the tile; direct: slot << 16 | that, or
+// kNoSlot.
+template <int N, int OFF, int NE, bool DIRECT>
+__device__ __forceinline__ void reserve_rows(const TileSlots<DIRECT>& sl, const int32_t (&E)[NE], const int (&r)[NE],
                                              uint32_t (&q)[N]) {
   uint32_t tot[N];  // pairs from row a to the end of its run
   tot[N - 1] = (uint32_t)(r[OFF + N - 1] + 1);
 #pragma unroll
   for (int a = N - 2; a >= 0; --a)
-    tot[a] = (uint32_t)(r[OFF + a] + 1) + ((E[OFF + a] >> s1) == (E[OFF + a + 1] >> s1) ? tot[a + 1] : 0u);
+    tot[a] = (uint32_t)(r[OFF + a] + 1) +
+             ((E[OFF + a] >> sl.shift) == (E[OFF + a + 1] >> sl.shift) ? tot[a + 1] : 0u);
 #pragma unroll
   for (int a = 0; a < N; ++a) {
-    if (a > 0 && (E[OFF + a] >> s1) == (E[OFF + a - 1] >> s1))
-      q[a] = q[a - 1] + (uint32_t)(r[OFF + a - 1] + 1);
-    else
-      q[a] = atomicAdd(&cnt[E[OFF + a] >> s1], tot[a]);
+    if (a > 0 && (E[OFF + a] >> sl.shift) == (E[OFF + a - 1] >> sl.shift)) {
+      q[a] = DIRECT && q[a - 1] == kNoSlot ? kNoSlot : q[a - 1] + (uint32_t)(r[OFF + a - 1] + 1);
+    } else if constexpr (DIRECT) {
+      const uint32_t s = sl.find((uint32_t)(E[OFF + a] >> sl.shift));
+      q[a] = s == kNoSlot ? kNoSlot : (s << 16 | atomicAdd(&sl.cnt[s], tot[a]));
+    } else {
+      q[a] = atomicAdd(&sl.cnt[E[OFF + a] >> sl.shift], tot[a]);
+    }
   }
 }
 
+// ---------------------------------------------------------------------- begin, count
+// First kernel of a build.  Workgroups 0 .. kSamples-1: workgroup 0 clears the status (if
+// not null), the entry count and the head words; with kAsk, workgroup i samples the tile at
+// i / kSamples of the elements.  The others clear n_zero words at every stride-th word of
+// zero (n_tab times: the row counts of the heavy sub-buckets' tables), and the sub-bucket counters and copy the coordinates into
+// 32-byte records (out4 null: none).
 template <int NEN>
-__global__ __launch_bounds__(256) void k_hist_buckets(const int32_t* __restrict__ conn, int64_t n_elem, int64_t n_node,
-                                                      int te, int s1, int nb, uint32_t* __restrict__ hist,
-                                                      uint32_t* __restrict__ status) {
-  extern __shared__ uint32_t s_h[];  // [nb]
+__global__ __launch_bounds__(256) void k_begin(const int32_t* __restrict__ conn, int64_t n_elem, int64_t n_node,
+                                               int tile, int64_t ntiles, int s2, int mode,
+                                               uint32_t* __restrict__ status, int64_t* __restrict__ nnz,
+                                               uint32_t* __restrict__ head, uint32_t* __restrict__ subcnt,
+                                               int64_t nsub, const double* __restrict__ coords,
+                                               double4* __restrict__ out4, uint32_t* __restrict__ zero, int n_tab,
+                                               int stride, int n_zero) {
+  constexpr int kSet = 2048;
+  __shared__ uint32_t s_set[kSet];
+  __shared__ uint32_t s_runs, s_pairs;
+  if (blockIdx.x >= kSamples) {
+    const int64_t i0 = (int64_t)(blockIdx.x - kSamples) * blockDim.x + threadIdx.x;
+    const int64_t step = (int64_t)(gridDim.x - kSamples) * blockDim.x;
+    for (int64_t i = i0; i < (int64_t)n_tab * n_zero; i += step) zero[i / n_zero * stride + i % n_zero] = 0u;
+    if (mode != kTwoLevel)
+      for (int64_t i = i0; i < nsub; i += step) subcnt[i] = 0u;
+    if (out4)
+      for (int64_t i = i0; i < n_node; i += step)
+        out4[i] = make_double4(coords[3 * i], coords[3 * i + 1], coords[3 * i + 2], 0.0);
+    return;
+  }
+  if (blockIdx.x == 0) {
+    if (status && threadIdx.x < KB_STATUS_WORDS) status[threadIdx.x] = 0u;
+    if (nnz && threadIdx.x == 0) *nnz = 0;
+    if (threadIdx.x < kHeadVotes) head[threadIdx.x] = 0u;
+  }
+  if (mode != kAsk) return;
+  for (int h = threadIdx.x; h < kSet; h += blockDim.x) s_set[h] = kEmptyKey;
+  if (threadIdx.x == 0) {
+    s_runs = 0u;
+    s_pairs = 0u;
+  }
+  __syncthreads();
+  const int64_t t = ntiles * blockIdx.x / kSamples;
+  const int64_t e0 = t * tile, e1 = e0 + tile < n_elem ? e0 + tile : n_elem;
+  uint32_t runs = 0, pairs = 0;
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
+    int32_t E[NEN];
+    load_conn<NEN>(conn, e, E);
+    if (check_conn<NEN>(E, n_node)) continue;
+    pairs += NEN * (NEN + 1) / 2;
+#pragma unroll
+    for (int a = 0; a < NEN; ++a) {
+      const uint32_t x = (uint32_t)(E[a] >> s2);
+      if (a > 0 && x == (uint32_t)(E[a > 0 ? a - 1 : 0] >> s2)) continue;
+      uint32_t h = (x * 0x9E3779B1u) >> (32 - __builtin_ctz(kSet));
+      int p = 0;
+#pragma unroll 1
+      for (; p < 16; ++p) {
+        const uint32_t k = atomicCAS(&s_set[h], kEmptyKey, x);
+        if (k == kEmptyKey) ++runs;
+        if (k == kEmptyKey || k == x) break;
+        h = (h + 1) & (kSet - 1);
+      }
+      if (p == 16) ++runs;  // a full set: no locality
+    }
+  }
+  if (runs) atomicAdd(&s_runs, runs);
+  if (pairs) atomicAdd(&s_pairs, pairs);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    head[kHeadVotes + 2 * blockIdx.x] = s_runs;
+    head[kHeadVotes + 2 * blockIdx.x + 1] = s_pairs;
+  }
+}
+
+// A tile's counts added to the sub-bucket counters (direct): one atomic per run.
+__device__ __forceinline__ void flush_counts(const TileSlots<true>& sl, uint32_t* __restrict__ subcnt) {
+  for (int b = threadIdx.x; b < sl.n; b += blockDim.x) {
+    const uint32_t c = sl.cnt[b];
+    if (c) atomicAdd(&subcnt[sl.hash ? sl.key[b] : (uint32_t)b], c);
+  }
+}
+
+// Per tile of `te` elements: pairs per bucket (row >> s1), written tile-major
+// hist[t * nb + b]; or, direct, pairs per sub-bucket added to subcnt.  Flags index errors;
+// invalid elements contribute nothing.  With kDirect the last workgroup to finish turns
+// the counts into the sub-bucket starts sbb[0 .. nsub] and, in place, the write cursors.
+// With kAsk the samples decide, and the first workgroup tells the kernels after this one.
+template <int NEN, bool DIRECT>
+__device__ __forceinline__ void count_tile(uint32_t* s_h, const int32_t* __restrict__ conn, int64_t n_elem,
+                                           int64_t n_node, int te, int s1, int nb, int s2, int nsub, int mode,
+                                           uint32_t* __restrict__ hist, uint32_t* __restrict__ subcnt,
+                                           uint32_t* __restrict__ status) {
+  const TileSlots<DIRECT> sl(s_h, s_h + kSlotsHash, mode, s1, nb, s2, nsub);
   const int64_t t = blockIdx.x;
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) s_h[b] = 0;
+  sl.clear(blockDim.x);
   __syncthreads();
   const int64_t e0 = t * te, e1 = (e0 + te < n_elem) ? e0 + te : n_elem;
   uint32_t flags = 0;
@@ -256,25 +461,62 @@ __global__ __launch_bounds__(256) void k_hist_buckets(const int32_t* __restrict_
     int r[NEN];
     node_ranks<NEN>(E, r);
     uint32_t q[NEN];
-    reserve_rows<NEN, 0>(s_h, E, r, s1, q);
+    reserve_rows<NEN, 0>(sl, E, r, q);
+    if constexpr (DIRECT) {
+#pragma unroll
+      for (int a = 0; a < NEN; ++a)
+        if (q[a] == kNoSlot) atomicAdd(&subcnt[E[a] >> s2], (uint32_t)(r[a] + 1));
+    }
   }
   if (flags) raise_flag(status, flags);
   __syncthreads();
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) hist[t * nb + b] = s_h[b];
+  if constexpr (DIRECT) {
+    flush_counts(sl, subcnt);
+  } else {
+    for (int b = threadIdx.x; b < nb; b += blockDim.x) hist[t * nb + b] = s_h[b];
+  }
 }
 
-// Tile offsets from the tile-major histogram hist[t][b] (tiles x buckets) without
+template <int NEN>
+__global__ __launch_bounds__(256) void k_count(const int32_t* __restrict__ conn, int64_t n_elem, int64_t n_node,
+                                               int te, int s1, int nb, int s2, int nsub, int mode,
+                                               uint32_t* head, uint32_t* __restrict__ hist,
+                                               uint32_t* __restrict__ subcnt, uint32_t* __restrict__ sbb,
+                                               uint32_t* __restrict__ status) {
+  extern __shared__ uint32_t s_h[];  // the slots' counters, then (hash) their keys
+  const bool direct = mode == kAsk ? votes_direct(head + kHeadVotes) : mode == kDirect;
+  if (mode == kAsk && blockIdx.x == 0 && threadIdx.x == 0) head[kHeadWay] = direct ? 1u : 0u;
+  if (direct) {
+    count_tile<NEN, true>(s_h, conn, n_elem, n_node, te, s1, nb, s2, nsub, mode, hist, subcnt, status);
+    if (mode == kDirect) last_block_starts(subcnt, nsub, sbb, &head[3], gridDim.x);
+  } else {
+    count_tile<NEN, false>(s_h, conn, n_elem, n_node, te, s1, nb, s2, nsub, mode, hist, subcnt, status);
+  }
+}
+
+// Offsets of pass 1's writes, in four kernels.
+// Two levels: from the tile-major histogram hist[t][b] (tiles x buckets) without
 // transposing it: column sums over chunks of kColChunk tiles, a scan of those per bucket,
-// then each chunk's columns walked again, counts turned into offsets in place:
-// hist[t][b] = bstart[b] + (pairs of bucket b in tiles before t).
+// the bucket starts, then each chunk's columns walked again, counts turned into offsets in
+// place: hist[t][b] = bstart[b] + (pairs of bucket b in tiles before t).
+// Direct (kAsk): the exclusive scan of the sub-bucket counts in the first two kernels, to
+// sbb and (in place) to the write cursors; the other two return at once.
 constexpr int kColChunk = 64;
 
-// grid (chunks, ceil(nb / 256)): csum[c][b] = sum of hist[t][b] over the tiles of chunk c
-__global__ __launch_bounds__(256) void k_col_chunks(const uint32_t* __restrict__ hist, int64_t ntiles, int nb,
-                                                    uint32_t* __restrict__ csum) {
-  const int64_t c = blockIdx.x;
-  const int b = blockIdx.y * blockDim.x + threadIdx.x;
-  if (b >= nb) return;
+// csum[c][b] = sum of hist[t][b] over the tiles of chunk c (grid: chunks x ceil(nb / 256),
+// flattened, bucket blocks fastest), or the chunk sums of subcnt
+static __global__ __launch_bounds__(kScanThreads) void k_offsets_sums(const uint32_t* __restrict__ hist, int64_t ntiles,
+                                                               int nb, int64_t nchunk, uint32_t* __restrict__ csum,
+                                                               const uint32_t* __restrict__ subcnt, int64_t nsub,
+                                                               int32_t* __restrict__ part, int mode,
+                                                               const uint32_t* __restrict__ way) {
+  if (goes_direct(mode, way)) {
+    if ((int64_t)blockIdx.x * kScanChunk < nsub) scan_chunk_sum((const int32_t*)subcnt, nsub, part);
+    return;
+  }
+  const int64_t nbb = (nb + 255) / 256, c = blockIdx.x / nbb;
+  const int b = (int)(blockIdx.x % nbb) * blockDim.x + threadIdx.x;
+  if (c >= nchunk || b >= nb) return;
   const int64_t t0 = c * kColChunk, t1 = t0 + kColChunk < ntiles ? t0 + kColChunk : ntiles;
   uint32_t sum = 0;
 #pragma unroll 8
@@ -283,11 +525,20 @@ __global__ __launch_bounds__(256) void k_col_chunks(const uint32_t* __restrict__
 }
 
 // one workgroup per bucket b: exclusive scan of csum[.][b] over the chunks, in place; the
-// bucket's total to tot[b]
-__global__ __launch_bounds__(256) void k_col_scan(uint32_t* __restrict__ csum, int64_t nchunk, int nb,
-                                                  uint32_t* __restrict__ tot) {
+// bucket's total to tot[b].  Direct: one workgroup per chunk of subcnt.
+static __global__ __launch_bounds__(kScanThreads) void k_offsets_scan(uint32_t* __restrict__ csum, int64_t nchunk, int nb,
+                                                               uint32_t* __restrict__ tot, uint32_t* subcnt,
+                                                               int64_t nsub, const int32_t* __restrict__ part,
+                                                               uint32_t* __restrict__ sbb, int mode,
+                                                               const uint32_t* __restrict__ way) {
+  if (goes_direct(mode, way)) {
+    if ((int64_t)blockIdx.x * kScanChunk < nsub)
+      scan_chunk_down((const int32_t*)subcnt, nsub, part, (int32_t*)sbb, (int32_t*)subcnt, nullptr);
+    return;
+  }
   __shared__ uint32_t s_scan[8];
   const int b = blockIdx.x;
+  if (b >= nb) return;
   uint32_t carry = 0;
   for (int64_t c0 = 0; c0 < nchunk; c0 += blockDim.x) {
     const int64_t c = c0 + threadIdx.x;
@@ -300,11 +551,48 @@ __global__ __launch_bounds__(256) void k_col_scan(uint32_t* __restrict__ csum, i
   if (threadIdx.x == 0) tot[b] = carry;
 }
 
-// grid (chunks, ceil(nb / 256)): counts of chunk c turned into offsets in place
-__global__ __launch_bounds__(256) void k_col_offsets(uint32_t* __restrict__ hist, const uint32_t* __restrict__ csum,
-                                                     const uint32_t* __restrict__ bstart, int64_t ntiles, int nb) {
-  const int64_t c = blockIdx.x;
-  const int b = blockIdx.y * blockDim.x + threadIdx.x;
+// single block: bucket starts bstart[0 .. nb] from the bucket totals, and segbase[b] =
+// number of pass-2 segments in buckets before b (segbase[nb] = total), a bucket of n
+// pairs having ceil(n / seg) segments
+static __global__ __launch_bounds__(1024) void k_bucket_starts(const uint32_t* __restrict__ tot, int nb, int seg,
+                                                        uint32_t* __restrict__ bstart, uint32_t* __restrict__ segbase,
+                                                        int mode, const uint32_t* __restrict__ way) {
+  if (goes_direct(mode, way)) return;
+  __shared__ uint32_t s_scan[1024 / 64 + 1];
+  uint32_t carry = 0, scarry = 0;
+  for (int b0 = 0; b0 < nb; b0 += blockDim.x) {
+    const int b = b0 + threadIdx.x;
+    const uint32_t n = b < nb ? tot[b] : 0u;
+    uint32_t total;
+    const uint32_t ex = block_scan_u32(n, s_scan, &total);
+    if (b < nb) bstart[b] = carry + ex;
+    carry += total;
+    const uint32_t sex = block_scan_u32((n + seg - 1) / seg, s_scan, &total);
+    if (b < nb) segbase[b] = scarry + sex;
+    scarry += total;
+  }
+  if (threadIdx.x == 0) {
+    bstart[nb] = carry;
+    segbase[nb] = scarry;
+  }
+}
+
+// counts of chunk c turned into offsets in place (grid as k_offsets_sums); the nb
+// workgroups after those write seg2b[s] = bucket of segment s
+static __global__ __launch_bounds__(256) void k_offsets_down(uint32_t* __restrict__ hist, const uint32_t* __restrict__ csum,
+                                                      const uint32_t* __restrict__ bstart, int64_t ntiles, int nb,
+                                                      int64_t nchunk, const uint32_t* __restrict__ segbase,
+                                                      uint32_t* __restrict__ seg2b, int mode,
+                                                      const uint32_t* __restrict__ way) {
+  if (goes_direct(mode, way)) return;
+  const int64_t nbb = (nb + 255) / 256, c = blockIdx.x / nbb;
+  if (c >= nchunk) {
+    const int64_t b = blockIdx.x - nchunk * nbb;
+    if (b < nb)
+      for (uint32_t s = segbase[b] + threadIdx.x; s < segbase[b + 1]; s += blockDim.x) seg2b[s] = (uint32_t)b;
+    return;
+  }
+  const int b = (int)(blockIdx.x % nbb) * blockDim.x + threadIdx.x;
   if (b >= nb) return;
   uint32_t run = bstart[b] + csum[c * nb + b];
   const int64_t t0 = c * kColChunk, t1 = t0 + kColChunk < ntiles ? t0 + kColChunk : ntiles;
@@ -316,87 +604,141 @@ __global__ __launch_bounds__(256) void k_col_offsets(uint32_t* __restrict__ hist
   }
 }
 
-// single block: segbase[b] = number of pass-2 segments in buckets before b
-// (segbase[nb] = total), a bucket of n pairs having ceil(n / seg) segments
-__global__ __launch_bounds__(256) void k_segments(const uint32_t* __restrict__ bstart, int nb, int seg,
-                                                  uint32_t* __restrict__ segbase) {
-  __shared__ uint32_t s_scan[8];
-  uint32_t carry = 0;
-  for (int b0 = 0; b0 < nb; b0 += blockDim.x) {
-    const int b = b0 + threadIdx.x;
-    const uint32_t n = (b < nb) ? (bstart[b + 1] - bstart[b] + seg - 1) / seg : 0u;
-    uint32_t total;
-    const uint32_t ex = block_scan_u32(n, s_scan, &total);
-    if (b < nb) segbase[b] = carry + ex;
-    carry += total;
-  }
-  if (threadIdx.x == 0) segbase[nb] = carry;
-}
-
 // ------------------------------------------------------------------------ pass 1
-// A tile is BLOCK elements, one per lane.  Its pairs are grouped by bucket (row >> s1)
-// in LDS and each bucket's run is written at the tile's offset in that bucket.
-template <typename V, int BLOCK>
-struct Pass1Smem {
-  uint64_t* key;  // [cap] staged (row << 32 | col)
-  V* val;         // [cap] staged values
-  uint32_t* cnt;  // [nb] pairs per bucket, then local run starts
-  uint32_t* base; // [nb] global offset of this tile in bucket b
-  uint32_t* scan; // [BLOCK/64 + 1]
-  uint32_t* emax; // [1]
-  __device__ Pass1Smem(unsigned char* smem, int cap, int nb) {
-    key = (uint64_t*)smem;
-    val = (V*)(key + cap);
-    cnt = (uint32_t*)(val + cap);
-    base = cnt + nb;
-    scan = base + nb;
-    emax = scan + (BLOCK / 64 + 1);
+// A tile is BLOCK elements, one per lane.  Its pairs are grouped by bucket (row >> s1) or
+// sub-bucket (row >> s2) in LDS and each group's run is written at the tile's offset there.
+template <typename V>
+struct PairOut {
+  uint16_t* row1;        // two levels: bucket arrays (row within its bucket, column, value)
+  uint32_t* col1;
+  V* val1;
+  const uint32_t* off1;  // [tile][nb] offsets
+  uint32_t* key2;        // direct: sub-bucket arrays (row within its sub-bucket << colbits | column, value)
+  V* val2;
+  uint32_t* cursor;      // [nsub] next free place
+  const uint32_t* way;
+  int mode, s1, nb, s2, nsub, colbits;
+  // LDS words of the counters: counts and bases (and keys) of the slots
+  static size_t slot_words(int mode, int nb, int64_t nsub) {
+    const size_t two = 2 * (size_t)nb, hash = 3 * (size_t)kSlotsHash;
+    return mode == kTwoLevel ? two : mode == kDirect ? 2 * (size_t)nsub : two > hash ? two : hash;
   }
 };
 
-// count the tile's pairs per bucket, keeping each (element, row) group's offset
-// within its bucket in q; then scan: sm.cnt = local run starts.  Returns the tile's
-// pair count.  Block-wide (barriers).
-template <int NEN, typename SM>
-__device__ __forceinline__ uint32_t pass1_count(const SM& sm, const int32_t (&E)[NEN], const int (&r)[NEN], bool valid,
-                                                int s1, int nb, uint32_t (&q)[NEN]) {
-  if (valid) reserve_rows<NEN, 0>(sm.cnt, E, r, s1, q);
-  __syncthreads();
-  return block_scan_array(sm.cnt, nb, sm.scan);
-}
-
-// stage one element's pairs: the r+1 pairs of row E[a] go contiguously into its bucket
-template <int NEN, typename V, typename SM>
-__device__ __forceinline__ void pass1_stage(const SM& sm, const int32_t (&E)[NEN], const uint32_t (&q)[NEN],
-                                            const V (&k)[ElemTraits<NEN>::T], int s1) {
+template <typename V, int BLOCK, bool DIRECT>
+struct Pass1Smem {
+  uint64_t* key;  // [cap] staged (row << 32 | col), direct (slot << 32 | key2)
+  V* val;         // [cap] staged values
+  uint32_t* scan; // [BLOCK/64 + 1]
+  uint32_t* emax; // [1]
+  uint32_t* base; // [n] global offset of this tile in each slot
+  TileSlots<DIRECT> sl;  // counters (base: n words, cnt: n words, hash: n words of keys)
+  static constexpr int kPerLane = DIRECT ? (kSlotsArray + BLOCK - 1) / BLOCK : 1;  // counters per lane at most
+  __device__ __forceinline__ Pass1Smem(unsigned char* smem, int cap, const PairOut<V>& o)
+      : sl(nullptr, nullptr, o.mode, o.s1, o.nb, o.s2, o.nsub) {
+    key = (uint64_t*)smem;
+    val = (V*)(key + cap);
+    scan = (uint32_t*)(val + cap);
+    emax = scan + (BLOCK / 64 + 1);
+    base = emax + 1;
+    sl.cnt = base + sl.n;
+    sl.key = sl.cnt + sl.n;
+  }
+  // counters cleared; two levels: the tile's offsets read
+  __device__ __forceinline__ void begin(const PairOut<V>& o, int64_t t) const {
+    if constexpr (DIRECT) {
+      sl.clear(BLOCK);
+    } else {
+      for (int b = threadIdx.x; b < o.nb; b += BLOCK) {
+        sl.cnt[b] = 0;
+        base[b] = o.off1[t * o.nb + b];
+      }
+    }
+  }
+  // direct, after the scan: the tile's places in each sub-bucket, one atomic per run.  The
+  // results stay in registers (the caller has other work to do) until put_bases.
+  __device__ __forceinline__ void take_bases(const PairOut<V>& o, uint32_t total, uint32_t (&g)[kPerLane]) const {
+    if constexpr (!DIRECT) return;
 #pragma unroll
-  for (int a = 0; a < NEN; ++a) {
-    uint32_t pos = sm.cnt[E[a] >> s1] + q[a];
-    const uint64_t rk = (uint64_t)(uint32_t)E[a] << 32;
+    for (int u = 0; u < kPerLane; ++u) {
+      const int b = u * BLOCK + threadIdx.x;
+      if (b < sl.n) {
+        const uint32_t c = (b + 1 < sl.n ? sl.cnt[b + 1] : total) - sl.cnt[b];
+        if (c) g[u] = atomicAdd(&o.cursor[sl.hash ? sl.key[b] : (uint32_t)b], c);
+      }
+    }
+  }
+  __device__ __forceinline__ void put_bases(const uint32_t (&g)[kPerLane]) const {
+    if constexpr (!DIRECT) return;
+#pragma unroll
+    for (int u = 0; u < kPerLane; ++u) {
+      const int b = u * BLOCK + threadIdx.x;
+      if (b < sl.n) base[b] = g[u];
+    }
+  }
+};
+
+// stage the pairs of local rows R0 .. R0+N-1: the r+1 pairs of row E[a] go contiguously
+// into its slot's run (a row without a slot takes its places at once)
+template <int N, int R0, int NEN, typename V, int BLOCK, bool DIRECT>
+__device__ __forceinline__ void pass1_stage(const Pass1Smem<V, BLOCK, DIRECT>& sm, const PairOut<V>& o, const int32_t (&E)[NEN],
+                                            const uint32_t (&q)[N], const V (&k)[ElemTraits<NEN>::T]) {
+#pragma unroll
+  for (int a = 0; a < N; ++a) {
+    const int row = R0 + a;
+    const uint32_t rl = DIRECT ? ((uint32_t)E[row] & ((1u << o.s2) - 1)) << o.colbits : 0u;
+    if (DIRECT && q[a] == kNoSlot) {
+      uint32_t n = 0;
+#pragma unroll
+      for (int b = 0; b < NEN; ++b) n += E[b] <= E[row] ? 1u : 0u;
+      uint32_t g = atomicAdd(&o.cursor[E[row] >> o.s2], n);
+#pragma unroll
+      for (int b = 0; b < NEN; ++b) {
+        if (E[b] <= E[row]) {
+          o.key2[g] = rl | (uint32_t)E[b];
+          o.val2[g] = row >= b ? k[lidx(row, b)] : k[lidx(b, row)];
+          ++g;
+        }
+      }
+      continue;
+    }
+    const uint32_t slot = sm.sl.slot(q[a], E[row]);
+    uint32_t pos = sm.sl.cnt[slot] + sm.sl.place(q[a]);
+    const uint64_t rk = (uint64_t)(DIRECT ? slot : (uint32_t)E[row]) << 32 | rl;
 #pragma unroll
     for (int b = 0; b < NEN; ++b) {
-      if (E[b] <= E[a]) {
+      if (E[b] <= E[row]) {
         sm.key[pos] = rk | (uint32_t)E[b];
-        sm.val[pos] = (a >= b) ? k[lidx(a, b)] : k[lidx(b, a)];
+        sm.val[pos] = row >= b ? k[lidx(row, b)] : k[lidx(b, row)];
         ++pos;
       }
     }
   }
 }
 
-// write the staged pairs: index i lies in bucket b = row >> s1, local start sm.cnt[b]
-template <typename V, typename SM>
-__device__ __forceinline__ void pass1_write(const SM& sm, uint32_t n_items, int s1, int nthreads,
-                                            uint16_t* __restrict__ orow, uint32_t* __restrict__ ocol,
-                                            V* __restrict__ oval) {
+// write the staged pairs: index i lies in slot b, local start cnt[b]
+template <typename V, int BLOCK, bool DIRECT>
+__device__ __forceinline__ void pass1_write(const Pass1Smem<V, BLOCK, DIRECT>& sm, const PairOut<V>& o,
+                                            uint32_t n_items) {
+  constexpr int nthreads = BLOCK;
+  if constexpr (DIRECT) {
+    for (uint32_t i = threadIdx.x; i < n_items; i += nthreads) {
+      const uint64_t key = sm.key[i];
+      const uint32_t b = (uint32_t)(key >> 32);
+      const uint32_t g = sm.base[b] + (i - sm.sl.cnt[b]);
+      o.key2[g] = (uint32_t)key;
+      o.val2[g] = sm.val[i];
+    }
+    return;
+  }
   for (uint32_t i = threadIdx.x; i < n_items; i += nthreads) {
     const uint64_t key = sm.key[i];
     const uint32_t row = (uint32_t)(key >> 32);
-    const int b = (int)(row >> s1);
-    const uint32_t g = sm.base[b] + (i - sm.cnt[b]);
-    orow[g] = (uint16_t)(row & ((1u << s1) - 1));  // row within its bucket
-    ocol[g] = (uint32_t)key;
-    oval[g] = sm.val[i];
+    const int b = (int)(row >> o.s1);
+    const uint32_t g = sm.base[b] + (i - sm.sl.cnt[b]);
+    o.row1[g] = (uint16_t)(row & ((1u << o.s1) - 1));  // row within its bucket
+    o.col1[g] = (uint32_t)key;
+    o.val1[g] = sm.val[i];
   }
 }
 
@@ -427,51 +769,72 @@ __device__ __forceinline__ void read_values(const V* __restrict__ klow, int64_t 
 // Bricks: one tile per workgroup; tiles are assigned XCD-contiguously, so the runs that
 // neighbouring tiles write side by side meet in one L2.  OP: the integrand (unless the
 // values are given).
-template <int NEN, Prec P, bool FROM_VALUES, int BLOCK, Op OP = Op::Stiffness>
-__global__ __launch_bounds__(BLOCK) void k_pass1(const int32_t* __restrict__ conn, const double4* __restrict__ coords4,
-                                               const double* __restrict__ coef,
-                                               const typename PrecTraits<P>::V* __restrict__ klow, int64_t n_elem,
-                                               int64_t n_node, float tau, int s1, int nb, int64_t ntiles,
-                                               const uint32_t* __restrict__ off1, uint16_t* __restrict__ orow,
-                                               uint32_t* __restrict__ ocol, typename PrecTraits<P>::V* __restrict__ oval,
-                                               uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+template <int NEN, Prec P, bool FROM_VALUES, int BLOCK, Op OP, bool DIRECT>
+__device__ __forceinline__ void pass1_tile(unsigned char* smem, const int32_t (&E)[NEN], const double4* __restrict__ coords4,
+    const double* __restrict__ coef, const typename PrecTraits<P>::V* __restrict__ klow,
+    int64_t n_elem, int64_t n_node, float tau, const PairOut<typename PrecTraits<P>::V>& o,
+    uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   using V = typename PrecTraits<P>::V;
+  using SM = Pass1Smem<V, BLOCK, DIRECT>;
   constexpr int T = ElemTraits<NEN>::T;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const Pass1Smem<V, BLOCK> sm(smem, BLOCK * T, nb);
+  const SM sm(smem, BLOCK * T, o);
   const int64_t t = xcd_item(blockIdx.x, gridDim.x);
-  for (int b = threadIdx.x; b < nb; b += BLOCK) {
-    sm.cnt[b] = 0;
-    sm.base[b] = off1[t * nb + b];
-  }
-  if (threadIdx.x == 0) *sm.emax = 0;
-  __syncthreads();
   const int64_t e = t * BLOCK + threadIdx.x;
-  int32_t E[NEN];
-  bool valid = false;
-  if (e < n_elem) {
-    load_conn<NEN>(conn, e, E);
-    valid = check_conn<NEN>(E, n_node) == 0;
+  sm.begin(o, t);
+  if (threadIdx.x == 0) *sm.emax = 0;
+  const bool valid = e < n_elem && check_conn<NEN>(E, n_node) == 0;
+  double Xn[NEN][3];
+  double c_e = 0.0;
+  if constexpr (!FROM_VALUES) {
+    if (valid) {
+      gather_nodes<NEN>(NodesPadded{coords4}, E, Xn);
+      c_e = coef[e];
+    }
   }
-  int r[NEN];
+  __syncthreads();
   uint32_t q[NEN];
-  if (valid) node_ranks<NEN>(E, r);
-  const uint32_t n_items = pass1_count<NEN>(sm, E, r, valid, s1, nb, q);
+  if (valid) {
+    int r[NEN];
+    node_ranks<NEN>(E, r);
+    reserve_rows<NEN, 0>(sm.sl, E, r, q);
+  }
+  __syncthreads();
+  const uint32_t n_items = block_scan_array(sm.sl.cnt, sm.sl.n, sm.scan);
+  uint32_t gb[SM::kPerLane];
+  sm.take_bases(o, n_items, gb);
   uint32_t flags = 0, fb = 0;
   if (valid) {
     V k[T];
     if constexpr (FROM_VALUES)
       read_values<T>(klow, e, k, &flags);
     else
-      element_values<NEN, P, NodesPadded, OP>(NodesPadded{coords4}, coef, e, E, tau, k, &flags, &fb);
+      element_values_at<NEN, P, OP>(Xn, c_e, tau, k, &flags, &fb);
     atomicMax(sm.emax, values_emax<T>(k));
-    pass1_stage<NEN>(sm, E, q, k, s1);
+    pass1_stage<NEN, 0>(sm, o, E, q, k);
   }
   if (flags) raise_flag(status, flags);
   if (fb) atomicAdd(&status[1], fb);
+  sm.put_bases(gb);
   __syncthreads();
   if (threadIdx.x == 0 && *sm.emax) atomicMax(emax, *sm.emax);
-  pass1_write(sm, n_items, s1, BLOCK, orow, ocol, oval);
+  pass1_write(sm, o, n_items);
+}
+
+template <int NEN, Prec P, bool FROM_VALUES, int BLOCK, Op OP = Op::Stiffness>
+__global__ __launch_bounds__(BLOCK) void k_pass1(const int32_t* __restrict__ conn, const double4* __restrict__ coords4,
+                                               const double* __restrict__ coef,
+                                               const typename PrecTraits<P>::V* __restrict__ klow, int64_t n_elem,
+                                               int64_t n_node, float tau,
+                                               const PairOut<typename PrecTraits<P>::V> o,
+                                               uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  int32_t E[NEN] = {};
+  const int64_t e = xcd_item(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
+  if (e < n_elem) load_conn<NEN>(conn, e, E);  // under way while the branch waits for its word
+  if (goes_direct(o.mode, o.way))
+    pass1_tile<NEN, P, FROM_VALUES, BLOCK, OP, true>(smem, E, coords4, coef, klow, n_elem, n_node, tau, o, emax, status);
+  else
+    pass1_tile<NEN, P, FROM_VALUES, BLOCK, OP, false>(smem, E, coords4, coef, klow, n_elem, n_node, tau, o, emax, status);
 }
 
 // Bricks in FP64 from coordinates (one element per lane at the register limit): two
@@ -479,75 +842,87 @@ __global__ __launch_bounds__(BLOCK) void k_pass1(const int32_t* __restrict__ con
 // elements are gathered and integrated.  The two tiles are then counted, staged and
 // written one after the other through the one staging area (BLOCK elements' pairs).
 // Workgroup w takes tiles 2w and 2w + 1, XCD-contiguously as k_pass1.
-template <int NEN, Prec P, int BLOCK, Op OP = Op::Stiffness>
-__global__ __launch_bounds__(2 * BLOCK) void k_pass1_two(const int32_t* __restrict__ conn,
-                                                       const double4* __restrict__ coords4,
-                                                       const double* __restrict__ coef, int64_t n_elem, int64_t n_node,
-                                                       float tau, int s1, int nb, int64_t ntiles,
-                                                       const uint32_t* __restrict__ off1, uint16_t* __restrict__ orow,
-                                                       uint32_t* __restrict__ ocol,
-                                                       typename PrecTraits<P>::V* __restrict__ oval,
-                                                       uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+template <int NEN, Prec P, int BLOCK, Op OP, bool DIRECT>
+__device__ __forceinline__ void pass1_two(unsigned char* smem, const int32_t (&E)[NEN], const double4* __restrict__ coords4,
+    const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau, int64_t ntiles,
+    const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
+    uint32_t* __restrict__ status) {
   using V = typename PrecTraits<P>::V;
+  using SM = Pass1Smem<V, 2 * BLOCK, DIRECT>;
   constexpr int T = ElemTraits<NEN>::T;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const Pass1Smem<V, 2 * BLOCK> sm(smem, BLOCK * T, nb);
+  const SM sm(smem, BLOCK * T, o);
   const int64_t w = xcd_item(blockIdx.x, gridDim.x);
   const int half = threadIdx.x >= BLOCK ? 1 : 0;
   const int64_t e = (2 * w + half) * BLOCK + (threadIdx.x - half * BLOCK);
   if (threadIdx.x == 0) *sm.emax = 0;
-  int32_t E[NEN];
-  bool valid = false;
-  if (e < n_elem) {
-    load_conn<NEN>(conn, e, E);
-    valid = check_conn<NEN>(E, n_node) == 0;
+  const bool valid = e < n_elem && check_conn<NEN>(E, n_node) == 0;
+  double Xn[NEN][3];
+  double c_e = 0.0;
+  if (valid) {
+    gather_nodes<NEN>(NodesPadded{coords4}, E, Xn);
+    c_e = coef[e];
   }
-  int r[NEN];
-  if (valid) node_ranks<NEN>(E, r);
   uint32_t flags = 0, fb = 0;
   V k[T];
-  if (valid) element_values<NEN, P, NodesPadded, OP>(NodesPadded{coords4}, coef, e, E, tau, k, &flags, &fb);
-  if (flags) raise_flag(status, flags);
-  if (fb) atomicAdd(&status[1], fb);
-  __syncthreads();
-  if (valid) atomicMax(sm.emax, values_emax<T>(k));
   for (int h = 0; h < 2; ++h) {
     const int64_t t = 2 * w + h;
     if (t >= ntiles) break;
-    for (int b = threadIdx.x; b < nb; b += 2 * BLOCK) {
-      sm.cnt[b] = 0;
-      sm.base[b] = off1[t * nb + b];
-    }
+    sm.begin(o, t);
     __syncthreads();
     uint32_t q[NEN];
     const bool mine = valid && half == h;
-    if (mine) reserve_rows<NEN, 0>(sm.cnt, E, r, s1, q);
+    if (mine) {
+      int r[NEN];
+      node_ranks<NEN>(E, r);
+      reserve_rows<NEN, 0>(sm.sl, E, r, q);
+    }
     __syncthreads();
-    const uint32_t n_items = block_scan_array(sm.cnt, nb, sm.scan);
-    if (mine) pass1_stage<NEN>(sm, E, q, k, s1);
+    const uint32_t n_items = block_scan_array(sm.sl.cnt, sm.sl.n, sm.scan);
+    uint32_t gb[SM::kPerLane];
+    sm.take_bases(o, n_items, gb);
+    if (h == 0 && valid) {  // both tiles' elements (the first tile's counts hide the gathers)
+      element_values_at<NEN, P, OP>(Xn, c_e, tau, k, &flags, &fb);
+      atomicMax(sm.emax, values_emax<T>(k));
+    }
+    if (mine) pass1_stage<NEN, 0>(sm, o, E, q, k);
+    sm.put_bases(gb);
     __syncthreads();
-    pass1_write(sm, n_items, s1, 2 * BLOCK, orow, ocol, oval);
+    pass1_write(sm, o, n_items);
     __syncthreads();  // the staging area is reused by the next tile
   }
+  if (flags) raise_flag(status, flags);
+  if (fb) atomicAdd(&status[1], fb);
   if (threadIdx.x == 0 && *sm.emax) atomicMax(emax, *sm.emax);
 }
 
-// stage the pairs of rows R0 .. R0+3 of a brick (the lane's half of a lane pair)
-template <int R0, typename V, typename SM>
-__device__ __forceinline__ void pair_stage_half(const SM& sm, const int32_t (&E)[8], const uint32_t (&q)[4],
-                                                const V (&k)[36], int s1) {
+template <int NEN, Prec P, int BLOCK, Op OP = Op::Stiffness>
+__global__ __launch_bounds__(2 * BLOCK) void k_pass1_two(const int32_t* __restrict__ conn,
+                                                       const double4* __restrict__ coords4,
+                                                       const double* __restrict__ coef, int64_t n_elem, int64_t n_node,
+                                                       float tau, int64_t ntiles,
+                                                       const PairOut<typename PrecTraits<P>::V> o,
+                                                       uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  int32_t E[NEN] = {};
+  const int64_t e = xcd_item(blockIdx.x, gridDim.x) * (2 * BLOCK) + threadIdx.x;
+  if (e < n_elem) load_conn<NEN>(conn, e, E);  // under way while the branch waits for its word
+  if (goes_direct(o.mode, o.way))
+    pass1_two<NEN, P, BLOCK, OP, true>(smem, E, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+  else
+    pass1_two<NEN, P, BLOCK, OP, false>(smem, E, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+}
+
+// offsets of the lane's four rows R0 .. R0+3 in their slots (two levels: per-row atomics
+// measured 1-2% faster here than one per run of rows)
+template <int R0, bool DIRECT>
+__device__ __forceinline__ void pair_reserve_half(const TileSlots<DIRECT>& sl, const int32_t (&E)[8], const int (&r)[8],
+                                                  uint32_t (&q)[4]) {
+  if constexpr (DIRECT) {
+    reserve_rows<4, R0>(sl, E, r, q);
+  } else {
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int row = R0 + a;
-    uint32_t pos = sm.cnt[E[row] >> s1] + q[a];
-    const uint64_t rk = (uint64_t)(uint32_t)E[row] << 32;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      if (E[b] <= E[row]) {
-        sm.key[pos] = rk | (uint32_t)E[b];
-        sm.val[pos] = row >= b ? k[lidx(row, b)] : k[lidx(b, row)];
-        ++pos;
-      }
+    for (int a = 0; a < 4; ++a) {
+      q[a] = atomicAdd(&sl.cnt[E[R0 + a] >> sl.shift], (uint32_t)(r[R0 + a] + 1));
     }
   }
 }
@@ -556,84 +931,90 @@ __device__ __forceinline__ void pair_stage_half(const SM& sm, const int32_t (&E)
 // and BLOCK / 2 elements per tile.  Twice the waves of one lane per element for the same
 // staging LDS, and half the quadrature per lane; lane h counts and stages the pairs of
 // rows 4h .. 4h+3.
-template <Prec P, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_pass1_pair(const int32_t* __restrict__ conn,
-                                                    const double4* __restrict__ coords4,
-                                                    const double* __restrict__ coef, int64_t n_elem, int64_t n_node,
-                                                    float tau, int s1, int nb, const uint32_t* __restrict__ off1,
-                                                    uint16_t* __restrict__ orow, uint32_t* __restrict__ ocol,
-                                                    typename PrecTraits<P>::V* __restrict__ oval,
-                                                    uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+template <Prec P, int BLOCK, bool DIRECT>
+__device__ __forceinline__ void pass1_pair(unsigned char* smem, const int32_t (&E)[8], const double4* __restrict__ coords4,
+    const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau,
+    const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
+    uint32_t* __restrict__ status) {
   using V = typename PrecTraits<P>::V;
+  using SM = Pass1Smem<V, BLOCK, DIRECT>;
   constexpr int NEN = 8, T = ElemTraits<NEN>::T, TE = BLOCK / 2;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const Pass1Smem<V, BLOCK> sm(smem, TE * T, nb);
+  const SM sm(smem, TE * T, o);
   const int64_t t = xcd_item(blockIdx.x, gridDim.x);
-  for (int b = threadIdx.x; b < nb; b += BLOCK) {
-    sm.cnt[b] = 0;
-    sm.base[b] = off1[t * nb + b];
-  }
-  if (threadIdx.x == 0) *sm.emax = 0;
-  __syncthreads();
   const int h = (int)(threadIdx.x & 1);
   const int64_t e = t * TE + (threadIdx.x >> 1);
-  int32_t E[NEN];
-  bool valid = false;
-  if (e < n_elem) {
-    load_conn<NEN>(conn, e, E);
-    valid = check_conn<NEN>(E, n_node) == 0;
+  sm.begin(o, t);
+  if (threadIdx.x == 0) *sm.emax = 0;
+  const bool valid = e < n_elem && check_conn<NEN>(E, n_node) == 0;
+  double xo[4][3];
+  double c_e = 0.0;
+  if (valid) {
+    gather_pair(NodesPadded{coords4}, E, h, xo);
+    c_e = coef[e];
   }
-  // offsets of the lane's four rows in their buckets (a branch per half keeps every
-  // index into E and r a constant)
+  __syncthreads();
+  // (a branch per half keeps every index into E and r a constant)
   uint32_t q[4];
   if (valid) {
     int r[NEN];
     node_ranks<NEN>(E, r);
-    if (h) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a) q[a] = atomicAdd(&sm.cnt[E[4 + a] >> s1], (uint32_t)(r[4 + a] + 1));
-    } else {
-#pragma unroll
-      for (int a = 0; a < 4; ++a) q[a] = atomicAdd(&sm.cnt[E[a] >> s1], (uint32_t)(r[a] + 1));
-    }
+    if (h)
+      pair_reserve_half<4>(sm.sl, E, r, q);
+    else
+      pair_reserve_half<0>(sm.sl, E, r, q);
   }
   __syncthreads();
-  const uint32_t n_items = block_scan_array(sm.cnt, nb, sm.scan);
+  const uint32_t n_items = block_scan_array(sm.sl.cnt, sm.sl.n, sm.scan);
+  uint32_t gb[SM::kPerLane];
+  sm.take_bases(o, n_items, gb);
   uint32_t flags = 0, fb = 0;
   if (valid) {
     V k[T];
-    element_values_pair<P>(NodesPadded{coords4}, coef, e, E, tau, h, k, &flags, &fb);
+    element_values_pair<P>(xo, c_e, tau, h, k, &flags, &fb);
     atomicMax(sm.emax, values_emax<T>(k));
     if (h)
-      pair_stage_half<4>(sm, E, q, k, s1);
+      pass1_stage<4, 4>(sm, o, E, q, k);
     else
-      pair_stage_half<0>(sm, E, q, k, s1);
+      pass1_stage<4, 0>(sm, o, E, q, k);
   }
   if (flags) raise_flag(status, flags);
   if (fb) atomicAdd(&status[1], fb);
+  sm.put_bases(gb);
   __syncthreads();
   if (threadIdx.x == 0 && *sm.emax) atomicMax(emax, *sm.emax);
-  pass1_write(sm, n_items, s1, BLOCK, orow, ocol, oval);
+  pass1_write(sm, o, n_items);
+}
+
+template <Prec P, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_pass1_pair(const int32_t* __restrict__ conn,
+                                                    const double4* __restrict__ coords4,
+                                                    const double* __restrict__ coef, int64_t n_elem, int64_t n_node,
+                                                    float tau, const PairOut<typename PrecTraits<P>::V> o,
+                                                    uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  int32_t E[8] = {};
+  const int64_t e = xcd_item(blockIdx.x, gridDim.x) * (BLOCK / 2) + (threadIdx.x >> 1);
+  if (e < n_elem) load_conn<8>(conn, e, E);  // under way while the branch waits for its word
+  if (goes_direct(o.mode, o.way))
+    pass1_pair<P, BLOCK, true>(smem, E, coords4, coef, n_elem, n_node, tau, o, emax, status);
+  else
+    pass1_pair<P, BLOCK, false>(smem, E, coords4, coef, n_elem, n_node, tau, o, emax, status);
 }
 
 // Tetrahedra: persistent workgroups.  XCD x owns one contiguous range of tiles and its
 // workgroups walk it interleaved (neighbouring runs again meet in one L2).  The next
 // tile's connectivity is loaded while the current tile is integrated, and its node
 // coordinates while the current tile is written.
-template <Prec P, bool FROM_VALUES, int BLOCK, Op OP = Op::Stiffness>
-__global__ __launch_bounds__(BLOCK) void k_pass1_tet(const int32_t* __restrict__ conn,
-                                                   const double4* __restrict__ coords4,
-                                                   const double* __restrict__ coef,
-                                                   const typename PrecTraits<P>::V* __restrict__ klow, int64_t n_elem,
-                                                   int64_t n_node, float tau, int s1, int nb, int64_t ntiles,
-                                                   const uint32_t* __restrict__ off1, uint16_t* __restrict__ orow,
-                                                   uint32_t* __restrict__ ocol,
-                                                   typename PrecTraits<P>::V* __restrict__ oval,
-                                                   uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+template <Prec P, bool FROM_VALUES, int BLOCK, Op OP, bool DIRECT>
+__device__ __forceinline__ void pass1_tet(unsigned char* smem, const int32_t* __restrict__ conn, const double4* __restrict__ coords4,
+    const double* __restrict__ coef, const typename PrecTraits<P>::V* __restrict__ klow,
+    int64_t n_elem, int64_t n_node, float tau, int64_t ntiles,
+    const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
+    uint32_t* __restrict__ status) {
   using V = typename PrecTraits<P>::V;
+  using SM = Pass1Smem<V, BLOCK, DIRECT>;
   constexpr int NEN = 4, T = ElemTraits<NEN>::T;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const Pass1Smem<V, BLOCK> sm(smem, BLOCK * T, nb);
+  const SM sm(smem, BLOCK * T, o);
   const int64_t G = gridDim.x, x = blockIdx.x % kXcds, w = blockIdx.x / kXcds;
   const int64_t nw = G / kXcds + (x < G % kXcds ? 1 : 0);
   const int64_t lo = x * (ntiles / kXcds) + min(x, ntiles % kXcds);
@@ -663,15 +1044,18 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_tet(const int32_t* __restrict__
   uint32_t em = 0;  // largest value exponent seen by this lane
   while (true) {
     const int64_t e = t * BLOCK + threadIdx.x;
-    for (int b = threadIdx.x; b < nb; b += BLOCK) {
-      sm.cnt[b] = 0;
-      sm.base[b] = off1[t * nb + b];
+    sm.begin(o, t);
+    __syncthreads();
+    uint32_t q[NEN];
+    if (valid) {
+      int r[NEN];
+      node_ranks<NEN>(E, r);
+      reserve_rows<NEN, 0>(sm.sl, E, r, q);
     }
     __syncthreads();
-    int r[NEN];
-    uint32_t q[NEN];
-    if (valid) node_ranks<NEN>(E, r);
-    const uint32_t n_items = pass1_count<NEN>(sm, E, r, valid, s1, nb, q);
+    const uint32_t n_items = block_scan_array(sm.sl.cnt, sm.sl.n, sm.scan);
+    uint32_t gb[SM::kPerLane];
+    sm.take_bases(o, n_items, gb);
     const int64_t tn = t + nw;
     int32_t En[NEN];
     const bool vn = fetch(tn, En);
@@ -684,10 +1068,11 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_tet(const int32_t* __restrict__
         element_values_at<NEN, P, OP>(Xn, c_e, tau, k, &flags, &fb);
       const uint32_t me = values_emax<T>(k);
       em = me > em ? me : em;
-      pass1_stage<NEN>(sm, E, q, k, s1);
+      pass1_stage<NEN, 0>(sm, o, E, q, k);
     }
     if (flags) raise_flag(status, flags);
     if (fb) atomicAdd(&status[1], fb);
+    sm.put_bases(gb);
 #pragma unroll
     for (int a = 0; a < NEN; ++a) E[a] = En[a];
     valid = vn;
@@ -698,7 +1083,7 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_tet(const int32_t* __restrict__
       }
     }
     __syncthreads();
-    pass1_write(sm, n_items, s1, BLOCK, orow, ocol, oval);
+    pass1_write(sm, o, n_items);
     t = tn;
     if (t >= hi) break;
     __syncthreads();
@@ -706,6 +1091,21 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_tet(const int32_t* __restrict__
   if (em) atomicMax(sm.emax, em);
   __syncthreads();
   if (threadIdx.x == 0 && *sm.emax) atomicMax(emax, *sm.emax);
+}
+
+template <Prec P, bool FROM_VALUES, int BLOCK, Op OP = Op::Stiffness>
+__global__ __launch_bounds__(BLOCK) void k_pass1_tet(const int32_t* __restrict__ conn,
+                                                   const double4* __restrict__ coords4,
+                                                   const double* __restrict__ coef,
+                                                   const typename PrecTraits<P>::V* __restrict__ klow, int64_t n_elem,
+                                                   int64_t n_node, float tau, int64_t ntiles,
+                                                   const PairOut<typename PrecTraits<P>::V> o,
+                                                   uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  if (goes_direct(o.mode, o.way))
+    pass1_tet<P, FROM_VALUES, BLOCK, OP, true>(smem, conn, coords4, coef, klow, n_elem, n_node, tau, ntiles, o, emax, status);
+  else
+    pass1_tet<P, FROM_VALUES, BLOCK, OP, false>(smem, conn, coords4, coef, klow, n_elem, n_node, tau, ntiles, o, emax, status);
 }
 
 // Elements of more than eight rows (nodes with several degrees of freedom), values
@@ -719,27 +1119,22 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_tet(const int32_t* __restrict__
 //   - the staged pairs, grouped by bucket, are written as runs (as for 4 and 8 rows).
 constexpr int kWideThreads = 1024;  // threads per wide pass-1 workgroup (one per CU: LDS)
 
-template <int NEN, typename V>
-__global__ __launch_bounds__(kWideThreads) void k_pass1_wide(const int32_t* __restrict__ conn, const V* __restrict__ klow,
-                                                  int64_t n_elem, int64_t n_node, int te, int s1, int nb,
-                                                  const uint32_t* __restrict__ off1, uint16_t* __restrict__ orow,
-                                                  uint32_t* __restrict__ ocol, V* __restrict__ oval,
-                                                  uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+template <int NEN, typename V, bool DIRECT>
+__device__ __forceinline__ void pass1_wide(unsigned char* smem, const int32_t* __restrict__ conn, const V* __restrict__ klow, int64_t n_elem, int64_t n_node,
+    int te, const PairOut<V>& o, uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   constexpr int T = ElemTraits<NEN>::T, NT = kWideThreads;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const Pass1Smem<V, NT> sm(smem, te * T, nb);
-  int32_t* s_E = (int32_t*)(sm.emax + 1);    // [te * NEN] the tile's connectivity
+  using SM = Pass1Smem<V, NT, DIRECT>;
+  const SM sm(smem, te * T, o);
+  // [te * NEN] the tile's connectivity, after the slots' words
+  int32_t* s_E = (int32_t*)(sm.base + (DIRECT && sm.sl.hash ? 3 : 2) * sm.sl.n);
   uint32_t* s_q = (uint32_t*)(s_E + te * NEN);  // [te * NEN] run offset of each row in its bucket
-  uint32_t* s_rank = s_q + te * NEN;            // [te * NEN] rank of each corner's id
+  uint32_t* s_rank = s_q + te * NEN;            // [te * NEN] slot << 8 (0xFFFF: none) | rank of each corner's id
   uint32_t* s_ok = s_rank + te * NEN;           // [te] element valid
   uint16_t* s_pq = (uint16_t*)(s_ok + te);      // [T] packed index -> (p << 8 | q)
   const int64_t t = xcd_item(blockIdx.x, gridDim.x);
   const int64_t e0 = t * te;
   const int ne = (int)(n_elem - e0 < te ? n_elem - e0 : te);
-  for (int b = threadIdx.x; b < nb; b += NT) {
-    sm.cnt[b] = 0;
-    sm.base[b] = off1[t * nb + b];
-  }
+  sm.begin(o, t);
   if (threadIdx.x == 0) *sm.emax = 0;
   for (int i = threadIdx.x; i < T; i += NT) {
     int p = 0;
@@ -765,11 +1160,15 @@ __global__ __launch_bounds__(kWideThreads) void k_pass1_wide(const int32_t* __re
     uint32_t r = 0;
 #pragma unroll
     for (int b = 0; b < NEN; ++b) r += (s_E[el * NEN + b] < Ea) ? 1u : 0u;
-    s_rank[j] = r;
-    s_q[j] = atomicAdd(&sm.cnt[Ea >> s1], r + 1);
+    const uint32_t s = sm.sl.find((uint32_t)(Ea >> sm.sl.shift));
+    // (a row without a slot: its places in its sub-bucket taken at once)
+    s_q[j] = s == kNoSlot ? atomicAdd(&o.cursor[Ea >> o.s2], r + 1) : atomicAdd(&sm.sl.cnt[s], r + 1);
+    s_rank[j] = (s & 0xFFFFu) << 8 | r;
   }
   __syncthreads();
-  const uint32_t n_items = block_scan_array(sm.cnt, nb, sm.scan);  // cnt: local run starts
+  const uint32_t n_items = block_scan_array(sm.sl.cnt, sm.sl.n, sm.scan);  // cnt: local run starts
+  uint32_t gb[SM::kPerLane];
+  sm.take_bases(o, n_items, gb);
   uint32_t em = 0;
   bool finite = true;
   const V* __restrict__ k = klow + e0 * T;
@@ -782,20 +1181,39 @@ __global__ __launch_bounds__(kWideThreads) void k_pass1_wide(const int32_t* __re
     const bool up = Ep >= Eq;
     const int a = up ? p : q, b = up ? q : p;
     const int32_t Ea = up ? Ep : Eq, Eb = up ? Eq : Ep;
-    const uint32_t pos = sm.cnt[Ea >> s1] + s_q[el * NEN + a] + s_rank[el * NEN + b];
+    const uint32_t slot = s_rank[el * NEN + a] >> 8, at = s_q[el * NEN + a] + (s_rank[el * NEN + b] & 255u);
     const V v = k[i];
     finite = finite && isfinite((double)v);
     const uint32_t ep = (uint32_t)biased_exponent((double)v);
     em = (ep > em && ep < 0x7FF) ? ep : em;
-    sm.key[pos] = (uint64_t)(uint32_t)Ea << 32 | (uint32_t)Eb;
+    const uint32_t key2 = ((uint32_t)Ea & ((1u << o.s2) - 1)) << o.colbits | (uint32_t)Eb;
+    if (DIRECT && slot == 0xFFFFu) {
+      o.key2[at] = key2;
+      o.val2[at] = v;
+      continue;
+    }
+    const uint32_t pos = sm.sl.cnt[slot] + at;
+    sm.key[pos] = DIRECT ? (uint64_t)slot << 32 | key2 : (uint64_t)(uint32_t)Ea << 32 | (uint32_t)Eb;
     sm.val[pos] = v;
   }
   if (!finite) flags |= KB_F_NONFINITE;
   if (flags) raise_flag(status, flags);
   if (em) atomicMax(sm.emax, em);
+  sm.put_bases(gb);
   __syncthreads();
   if (threadIdx.x == 0 && *sm.emax) atomicMax(emax, *sm.emax);
-  pass1_write(sm, n_items, s1, NT, orow, ocol, oval);
+  pass1_write(sm, o, n_items);
+}
+
+template <int NEN, typename V>
+__global__ __launch_bounds__(kWideThreads) void k_pass1_wide(const int32_t* __restrict__ conn, const V* __restrict__ klow,
+                                                  int64_t n_elem, int64_t n_node, int te, const PairOut<V> o,
+                                                  uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  if (goes_direct(o.mode, o.way))
+    pass1_wide<NEN, V, true>(smem, conn, klow, n_elem, n_node, te, o, emax, status);
+  else
+    pass1_wide<NEN, V, false>(smem, conn, klow, n_elem, n_node, te, o, emax, status);
 }
 
 // ----------------------------------------------------- running sums as a source
@@ -812,38 +1230,58 @@ __device__ __forceinline__ int64_t csr_entries(const int64_t* nnz_dev, int64_t c
   return (n >= 0 && n <= cap) ? n : 0;
 }
 
-__global__ __launch_bounds__(256) void k_hist_csr(const int32_t* __restrict__ rows, const int64_t* __restrict__ nnz_dev,
-                                                  int64_t cap, int64_t n_node, int s1, int nb,
-                                                  uint32_t* __restrict__ hist) {
-  extern __shared__ uint32_t s_h[];  // [nb]
+constexpr int kCsrThreads = 256, kCsrPer = kCsrTile / kCsrThreads;
+
+template <bool DIRECT>
+__device__ __forceinline__ void count_csr(uint32_t* s_h, const int32_t* __restrict__ rows,
+                                          const int64_t* __restrict__ nnz_dev, int64_t cap, int64_t n_node, int s1,
+                                          int nb, int s2, int nsub, int mode, uint32_t* __restrict__ hist,
+                                          uint32_t* __restrict__ subcnt) {
+  const TileSlots<DIRECT> sl(s_h, s_h + kSlotsHash, mode, s1, nb, s2, nsub);
   const int64_t t = blockIdx.x;
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) s_h[b] = 0;
+  sl.clear(kCsrThreads);
   __syncthreads();
   const int64_t n = csr_entries(nnz_dev, cap);
   const int64_t e0 = t * kCsrTile, e1 = e0 + kCsrTile < n ? e0 + kCsrTile : n;
-  for (int64_t i = e0 + threadIdx.x; i < e1; i += blockDim.x) {
+  for (int64_t i = e0 + threadIdx.x; i < e1; i += kCsrThreads) {
     const int32_t r = rows[i];
-    if (r >= 0 && r < n_node) atomicAdd(&s_h[r >> s1], 2u);
+    if (r < 0 || r >= n_node) continue;
+    const uint32_t s = sl.find((uint32_t)(r >> sl.shift));
+    if (!DIRECT || s != kNoSlot)
+      atomicAdd(&sl.cnt[s], 2u);
+    else
+      atomicAdd(&subcnt[r >> s2], 2u);
   }
   __syncthreads();
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) hist[t * nb + b] = s_h[b];
+  if constexpr (DIRECT) {
+    flush_counts(sl, subcnt);
+  } else {
+    for (int b = threadIdx.x; b < nb; b += kCsrThreads) hist[t * nb + b] = s_h[b];
+  }
 }
 
-template <typename V>
-__global__ __launch_bounds__(256) void k_pass1_csr(const int32_t* __restrict__ rows, const int32_t* __restrict__ cols,
-                                                 const V* __restrict__ vals, const V* __restrict__ res,
-                                                 const int64_t* __restrict__ nnz_dev, int64_t cap, int64_t n_node,
-                                                 int s1, int nb, const uint32_t* __restrict__ off1,
-                                                 uint16_t* __restrict__ orow, uint32_t* __restrict__ ocol,
-                                                 V* __restrict__ oval, uint32_t* __restrict__ emax) {
-  constexpr int NT = 256, PER = kCsrTile / NT;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const Pass1Smem<V, NT> sm(smem, 2 * kCsrTile, nb);
+static __global__ __launch_bounds__(kCsrThreads) void k_hist_csr(const int32_t* __restrict__ rows,
+                                                                 const int64_t* __restrict__ nnz_dev, int64_t cap,
+                                                                 int64_t n_node, int s1, int nb, int s2, int nsub,
+                                                                 int mode, const uint32_t* __restrict__ way,
+                                                                 uint32_t* __restrict__ hist,
+                                                                 uint32_t* __restrict__ subcnt) {
+  extern __shared__ uint32_t s_h[];  // as k_count
+  if (goes_direct(mode, way))
+    count_csr<true>(s_h, rows, nnz_dev, cap, n_node, s1, nb, s2, nsub, mode, hist, subcnt);
+  else
+    count_csr<false>(s_h, rows, nnz_dev, cap, n_node, s1, nb, s2, nsub, mode, hist, subcnt);
+}
+
+template <typename V, bool DIRECT>
+__device__ __forceinline__ void pass1_csr(unsigned char* smem, const int32_t* __restrict__ rows, const int32_t* __restrict__ cols,
+    const V* __restrict__ vals, const V* __restrict__ res, const int64_t* __restrict__ nnz_dev,
+    int64_t cap, int64_t n_node, const PairOut<V>& o, uint32_t* __restrict__ emax) {
+  constexpr int NT = kCsrThreads, PER = kCsrPer;
+  using SM = Pass1Smem<V, NT, DIRECT>;
+  const SM sm(smem, 2 * kCsrTile, o);
   const int64_t t = blockIdx.x;
-  for (int b = threadIdx.x; b < nb; b += NT) {
-    sm.cnt[b] = 0;
-    sm.base[b] = off1[t * nb + b];
-  }
+  sm.begin(o, t);
   if (threadIdx.x == 0) *sm.emax = 0;
   __syncthreads();
   const int64_t n = csr_entries(nnz_dev, cap);
@@ -855,40 +1293,67 @@ __global__ __launch_bounds__(256) void k_pass1_csr(const int32_t* __restrict__ r
     const int64_t i = e0 + u * NT + threadIdx.x;
     r[u] = i < n ? rows[i] : -1;
     if (r[u] >= n_node) r[u] = -1;
-    if (r[u] >= 0) q[u] = atomicAdd(&sm.cnt[r[u] >> s1], 2u);
+    if (r[u] < 0) continue;
+    const uint32_t s = sm.sl.find((uint32_t)(r[u] >> sm.sl.shift));
+    if constexpr (DIRECT)
+      q[u] = s == kNoSlot ? kNoSlot : (s << 16 | atomicAdd(&sm.sl.cnt[s], 2u));
+    else
+      q[u] = atomicAdd(&sm.sl.cnt[s], 2u);
   }
   __syncthreads();
-  const uint32_t n_items = block_scan_array(sm.cnt, nb, sm.scan);
+  const uint32_t n_items = block_scan_array(sm.sl.cnt, sm.sl.n, sm.scan);
+  uint32_t gb[SM::kPerLane];
+  sm.take_bases(o, n_items, gb);
   uint32_t em = 0;
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
     if (r[u] < 0) continue;
     const int64_t i = e0 + u * NT + threadIdx.x;
-    const uint32_t pos = sm.cnt[r[u] >> s1] + q[u];
-    const uint64_t key = (uint64_t)(uint32_t)r[u] << 32 | (uint32_t)cols[i];
-    const V h = vals[i];
+    const uint32_t col = (uint32_t)cols[i];
+    const uint32_t key2 = ((uint32_t)r[u] & ((1u << o.s2) - 1)) << o.colbits | col;
+    const V h = vals[i], x = res[i];
+    const uint32_t ep = (uint32_t)biased_exponent((double)h);  // |res| <= |h|
+    em = (ep > em && ep < 0x7FF) ? ep : em;
+    if (DIRECT && q[u] == kNoSlot) {
+      const uint32_t g = atomicAdd(&o.cursor[r[u] >> o.s2], 2u);
+      o.key2[g] = key2;
+      o.val2[g] = h;
+      o.key2[g + 1] = key2;
+      o.val2[g + 1] = x;
+      continue;
+    }
+    const uint32_t slot = sm.sl.slot(q[u], r[u]);
+    const uint32_t pos = sm.sl.cnt[slot] + sm.sl.place(q[u]);
+    const uint64_t key = DIRECT ? (uint64_t)slot << 32 | key2 : (uint64_t)(uint32_t)r[u] << 32 | col;
     sm.key[pos] = key;
     sm.val[pos] = h;
     sm.key[pos + 1] = key;
-    sm.val[pos + 1] = res[i];
-    const uint32_t ep = (uint32_t)biased_exponent((double)h);  // |res| <= |h|
-    em = (ep > em && ep < 0x7FF) ? ep : em;
+    sm.val[pos + 1] = x;
   }
   if (em) atomicMax(sm.emax, em);
+  sm.put_bases(gb);
   __syncthreads();
   if (threadIdx.x == 0 && *sm.emax) atomicMax(emax, *sm.emax);
-  pass1_write(sm, n_items, s1, NT, orow, ocol, oval);
+  pass1_write(sm, o, n_items);
+}
+
+template <typename V>
+__global__ __launch_bounds__(kCsrThreads) void k_pass1_csr(const int32_t* __restrict__ rows,
+                                                         const int32_t* __restrict__ cols,
+                                                         const V* __restrict__ vals, const V* __restrict__ res,
+                                                         const int64_t* __restrict__ nnz_dev, int64_t cap,
+                                                         int64_t n_node, const PairOut<V> o,
+                                                         uint32_t* __restrict__ emax) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  if (goes_direct(o.mode, o.way))
+    pass1_csr<V, true>(smem, rows, cols, vals, res, nnz_dev, cap, n_node, o, emax);
+  else
+    pass1_csr<V, false>(smem, rows, cols, vals, res, nnz_dev, cap, n_node, o, emax);
 }
 
 // ------------------------------------------------------------------------ pass 2
 // A bucket's pairs are cut into segments of SEG; segment ids run over all buckets
 // (segbase[b] is the first segment of bucket b, segbase[nb] their number).
-
-// seg2b[s] = bucket of segment s (one workgroup per bucket)
-__global__ __launch_bounds__(256) void k_seg_map(const uint32_t* __restrict__ segbase, uint32_t* __restrict__ seg2b) {
-  const uint32_t b = blockIdx.x;
-  for (uint32_t s = segbase[b] + threadIdx.x; s < segbase[b + 1]; s += blockDim.x) seg2b[s] = b;
-}
 
 // histogram of sub-buckets ((row >> s2) mod p2) per segment: hist2[s * p2 + j]
 // s[k] += 1 for each of N keys, one LDS atomic per run of equal consecutive keys (under a
@@ -914,8 +1379,10 @@ template <int SEG>
 __global__ __launch_bounds__(256) void k_hist2(const uint16_t* __restrict__ irow, const uint32_t* __restrict__ bstart,
                                                const uint32_t* __restrict__ segbase,
                                                const uint32_t* __restrict__ seg2b, int nb, int s2, int p2,
-                                               uint32_t* __restrict__ hist2) {
+                                               uint32_t* __restrict__ hist2, int mode,
+                                               const uint32_t* __restrict__ way) {
   extern __shared__ uint32_t s_h[];  // [p2]
+  if (goes_direct(mode, way)) return;
   const uint32_t sid = blockIdx.x;
   if (sid >= segbase[nb]) return;
   const uint32_t b = seg2b[sid], s = sid - segbase[b];
@@ -950,9 +1417,11 @@ __global__ __launch_bounds__(256) void k_hist2(const uint16_t* __restrict__ irow
 // hist2 over the bucket's segments (in place), then the sub-bucket starts
 // sbb[b * p2 + j] (sbb[nb * p2] = number of pairs).  A segment's run for sub-bucket j
 // starts at sbb[b * p2 + j] + hist2[s * p2 + j].
-__global__ __launch_bounds__(256) void k_colscan(uint32_t* __restrict__ hist2, const uint32_t* __restrict__ bstart,
+static __global__ __launch_bounds__(256) void k_colscan(uint32_t* __restrict__ hist2, const uint32_t* __restrict__ bstart,
                                                  const uint32_t* __restrict__ segbase, int nb, int p2,
-                                                 uint32_t* __restrict__ sbb) {
+                                                 uint32_t* __restrict__ sbb, int mode,
+                                                 const uint32_t* __restrict__ way) {
+  if (goes_direct(mode, way)) return;
   __shared__ uint32_t s_tot[1024];
   __shared__ uint32_t s_scan[8];
   const int b = blockIdx.x;
@@ -993,8 +1462,10 @@ __global__ __launch_bounds__(NT) void k_scatter2(const uint16_t* __restrict__ ir
                                                   const uint32_t* __restrict__ seg2b,
                                                   const uint32_t* __restrict__ off2, const uint32_t* __restrict__ sbb,
                                                   int nb, int s2, int p2, int colbits, uint32_t* __restrict__ okey,
-                                                  V* __restrict__ oval) {
+                                                  V* __restrict__ oval, int mode,
+                                                  const uint32_t* __restrict__ way) {
   extern __shared__ __align__(16) unsigned char smem[];
+  if (goes_direct(mode, way)) return;
   V* s_val = (V*)smem;                          // [SEG]
   uint32_t* s_key = (uint32_t*)(s_val + SEG);   // [SEG]
   uint16_t* s_sb = (uint16_t*)(s_key + SEG);    // [SEG] sub-bucket of staged pair
@@ -1053,10 +1524,10 @@ __global__ __launch_bounds__(NT) void k_scatter2(const uint16_t* __restrict__ ir
 }
 
 // The first kHeavyPar heavy sub-buckets of the list are split, and their first-level
-// digit ranges reduced, by many workgroups (k_heavy_rows, k_heavy_layout, k_heavy_hist,
-// k_heavy_starts, k_heavy_scatter, k_pass3_heavy_ranges); k_pass3_heavy_finish then
-// sums up each one's entries and k_final_heavy gathers them from the ranges.
-// k_pass3_heavy clears their tables and takes the other listed sub-buckets whole.
+// digit ranges reduced, by many workgroups (the phases of k_heavy: heavy_rows, heavy_layout, heavy_hist,
+// heavy_starts, heavy_scatter, heavy_bigleaf, heavy_ranges); heavy_finish then
+// sums up each one's entries and k_final gathers them from the ranges.
+// heavy_rest clears their tables and takes the other listed sub-buckets whole.
 // The first-level digits follow the rows: row r of a sub-bucket gets n_r digits (a
 // power of two, none for a row without pairs), each covering 2^(colbits) / n_r columns,
 // with n_r about kHvyShare times the row's share of the pairs, at most one digit per
@@ -1092,15 +1563,6 @@ struct HeavyTable {
   }
 };
 
-// table entry it of a listed sub-bucket: the row counts cleared
-__device__ __forceinline__ void heavy_table_init(uint32_t* hvy, uint32_t it) {
-  const HeavyTable t(hvy, it);
-  for (uint32_t r = threadIdx.x; r < (uint32_t)kHvyRows; r += blockDim.x) {
-    t.rcnt[r] = 0u;
-    t.rpair[r] = 0u;
-  }
-}
-
 // first-level digit of key k (row k >> colbits) from the layout in LDS
 __device__ __forceinline__ uint32_t heavy_digit(uint32_t k, int colbits, const uint32_t* s_rbase,
                                                 const uint32_t* s_rsh) {
@@ -1127,7 +1589,7 @@ __device__ __forceinline__ uint32_t slot_hash(uint32_t k) {
 // CSR order to tcol/tval[sbb[g] + f], each row's first entry (relative to the
 // sub-bucket) to rowoff, its total to usub[g].  A sub-bucket of more than 2^16 pairs
 // or more distinct entries than the table holds is appended to ov_list (count in
-// *ov_count) and left to k_pass3_heavy.
+// *ov_count) and left to k_heavy.
 // Sub-buckets run in their natural order: under a random numbering the lower-triangle
 // pairs of a row grow with its id, so an even interleave keeps the XCDs balanced.
 // With RES, each entry's residual (the exact sum minus its rounding) goes to tres too.
@@ -1171,7 +1633,7 @@ __global__ __launch_bounds__(256) void k_pass3(uint32_t* __restrict__ ikey, V* _
     s_hi[h] = 0ull;
   }
   for (int r = threadIdx.x; r < (1 << s2); r += NT) s_rc[r] = 0;
-  // more than 2^16 pairs could overflow the chunk sums: left to the heavy kernel
+  // more than 2^16 pairs could overflow the chunk sums: left to k_heavy
   if (threadIdx.x == 0) {
     s_over = (end - beg > (1u << 16)) ? 1u : 0u;
     s_nu = 0;
@@ -1224,7 +1686,7 @@ __global__ __launch_bounds__(256) void k_pass3(uint32_t* __restrict__ ikey, V* _
     }
   }
   __syncthreads();
-  if (s_over) {  // left to k_pass3_heavy
+  if (s_over) {  // left to k_heavy
     if (threadIdx.x == 0) ov_list[atomicAdd(ov_count, 1u)] = (uint32_t)g;
     return;
   }
@@ -1315,8 +1777,8 @@ __global__ __launch_bounds__(256) void k_pass3(uint32_t* __restrict__ ikey, V* _
 // A sub-bucket that overflows pass 3 (a node shared by very many elements: its row holds
 // more distinct entries than an LDS table, or more than 2^16 pairs) is split by key into
 // ranges of at most kLeafKeys keys, each summed into a direct-addressed LDS table.  The
-// first kHeavyPar listed are split by the whole device (k_heavy_*, the tables above);
-// each further one is reduced whole by one 1024-lane workgroup of k_pass3_heavy:
+// first kHeavyPar listed are split by the whole device (the tables above);
+// each further one is reduced whole by one 1024-lane workgroup of heavy_rest:
 //   - the key range [kmin, kmax] of the sub-bucket; a range wider than kLeafKeys is split
 //     into at most 2048 digit ranges of 2^shift keys (a histogram, its scan and a
 //     scatter into the other buffer, at the same place), twice at most for 31-bit keys;
@@ -1575,11 +2037,11 @@ __device__ uint32_t heavy_leaf(const HeavySmem& sm, const uint32_t* key, const V
 
 // Leaves of the split sub-buckets (first-level digit ranges no wider than a leaf) with
 // more than kBigLeafPairs pairs, such as the one holding a heavy node's diagonal, are
-// summed by several workgroups: k_heavy_starts lists up to kBigLeaves of them, each
-// workgroup of k_heavy_bigleaf sums one round (kRound pairs) of one of them into its LDS
+// summed by several workgroups: heavy_starts lists up to kBigLeaves of them, each
+// workgroup of heavy_bigleaf sums one round (kRound pairs) of one of them into its LDS
 // slots and adds the carried sums (lo, hi below 2^48, top) of its occupied slots into
 // the leaf's accumulator with 64-bit atomics (exact: a leaf of fewer than 2^31 pairs has
-// fewer than 2^16 rounds), and k_pass3_heavy_ranges carries the accumulated sums once
+// fewer than 2^16 rounds), and heavy_ranges carries the accumulated sums once
 // more and writes the leaf's entries.  Leaves beyond the list are summed as the others.
 constexpr int kBigLeaves = 8;
 constexpr uint32_t kBigLeafPairs = 2 * kRound;
@@ -1631,38 +2093,48 @@ __device__ uint32_t heavy_range(const HeavySmem& sm, uint32_t* ikey, V* ival, ui
   return U;
 }
 
-// The listed sub-buckets after the first kHeavyPar, one workgroup each; its first
-// kHeavyPar workgroups also clear the first kHeavyPar tables and the big-leaf count
-// (the pair buffers alias the output, so they carry no __restrict__)
-template <typename V, bool RES = false>
-__global__ __launch_bounds__(kHeavyThreads) void k_pass3_heavy(uint32_t* ikey, V* ival, uint32_t* akey, V* aval,
-                                                             const uint32_t* __restrict__ sbb, int s2, int colbits,
-                                                             int64_t n_node, const uint32_t* __restrict__ emax,
-                                                             V* __restrict__ tres, uint32_t* __restrict__ rowoff,
-                                                             uint32_t* __restrict__ usub,
-                                                             const uint32_t* __restrict__ ov_list,
-                                                             const uint32_t* __restrict__ ov_count,
-                                                             uint32_t* __restrict__ hvy) {
-  extern __shared__ __align__(16) unsigned char smem[];
+// What the phases of k_heavy share (the pair buffers alias the output, so nothing here
+// carries __restrict__).
+template <typename V>
+struct HeavyArgs {
+  uint32_t* ikey;  // the listed sub-buckets' pairs, then scratch
+  V* ival;
+  uint32_t* akey;  // the other pair buffer, then the output columns and values
+  V* aval;
+  V* tres;
+  const uint32_t* sbb;
+  int s2, colbits;
+  int64_t n_node;
+  int F;
+  uint32_t* rowoff;
+  uint32_t* usub;
+  const uint32_t* ov_list;
+  uint32_t n_over, npar;  // listed; of those, split by the whole device (the first npar)
+  uint32_t* hvy;
+};
+
+// The listed sub-buckets after the first npar, one workgroup each
+template <typename V, bool RES>
+__device__ void heavy_rest(unsigned char* smem, const HeavyArgs<V>& A, uint32_t blk, uint32_t nblk) {
   const HeavySmem sm(smem);
-  const uint32_t n_over = *ov_count;
-  // (launched with at least kHeavyPar workgroups)
-  if (blockIdx.x < n_over && blockIdx.x < (uint32_t)kHeavyPar) heavy_table_init(hvy, blockIdx.x);
-  if (blockIdx.x == 0 && threadIdx.x == 0 && n_over) BigLeaves(hvy).list[0] = 0u;
-  if ((uint32_t)kHeavyPar + blockIdx.x >= n_over) return;
+  const uint32_t n_over = A.n_over;
+  uint32_t *const ikey = A.ikey, *const akey = A.akey, *const rowoff = A.rowoff, *const usub = A.usub;
+  V *const ival = A.ival, *const aval = A.aval, *const tres = A.tres;
+  const uint32_t *const sbb = A.sbb, *const ov_list = A.ov_list;
+  const int s2 = A.s2, colbits = A.colbits, F = A.F;
+  if (A.npar + blk >= n_over) return;
   for (int h = threadIdx.x; h < kLeafKeys; h += kHeavyThreads) {
     sm.lo[h] = 0ull;
     sm.hi[h] = 0ll;
     sm.top[h] = 0ll;
   }
   if (threadIdx.x < kLeafKeys / 4) ((uint32_t*)sm.occ)[threadIdx.x] = 0u;
-  const int F = 1117 - (int)*emax;
   int32_t* const tcol = (int32_t*)akey;
-  for (uint32_t it = (uint32_t)kHeavyPar + blockIdx.x; it < n_over; it += gridDim.x) {
+  for (uint32_t it = A.npar + blk; it < n_over; it += nblk) {
     const int64_t g = ov_list[it];
     const uint32_t beg = sbb[g], end = sbb[g + 1];
     const int64_t r0 = g << s2;
-    const int R = (int)min((int64_t)1 << s2, n_node - r0);
+    const int R = (int)min((int64_t)1 << s2, A.n_node - r0);
     for (int r = threadIdx.x; r < 256; r += kHeavyThreads) sm.rowcnt[r] = 0u;
     // key range
     uint32_t mn = 0xFFFFFFFFu, mx = 0u;
@@ -1770,11 +2242,12 @@ __device__ __forceinline__ uint32_t heavy_chunk_owner(const uint32_t* s_c0, uint
 // Calls f(it, a, b) for each chunk [a, b) of this workgroup, it its sub-bucket's place
 // in the list.  f is called by all threads and may use barriers.
 template <typename Fn>
-__device__ __forceinline__ void heavy_chunks(const uint32_t* sbb, const uint32_t* ov_list, uint32_t npar, Fn f) {
+__device__ __forceinline__ void heavy_chunks(const uint32_t* sbb, const uint32_t* ov_list, uint32_t npar,
+                                             uint32_t blk, uint32_t nblk, Fn f) {
   __shared__ uint32_t s_beg[kHeavyPar], s_end[kHeavyPar], s_c0[kHeavyPar + 1];
   heavy_chunk_table(sbb, ov_list, npar, s_beg, s_end, s_c0);
   const uint32_t nch = s_c0[kHeavyPar];
-  for (uint32_t j = blockIdx.x; j < nch; j += gridDim.x) {
+  for (uint32_t j = blk; j < nch; j += nblk) {
     const uint32_t it = heavy_chunk_owner(s_c0, j);
     const uint32_t a = s_beg[it] + (j - s_c0[it]) * kSplitChunk;
     const uint32_t b = s_end[it] - a > kSplitChunk ? a + kSplitChunk : s_end[it];
@@ -1795,22 +2268,20 @@ __device__ __forceinline__ void heavy_count(const uint32_t* key, uint32_t a, uin
   });
 }
 
-// pairs of each row of the listed sub-buckets
-__global__ __launch_bounds__(kHeavyThreads) void k_heavy_rows(const uint32_t* __restrict__ ikey,
-                                                              const uint32_t* __restrict__ sbb, int colbits,
-                                                              const uint32_t* __restrict__ ov_list,
-                                                              const uint32_t* __restrict__ ov_count,
-                                                              uint32_t* __restrict__ hvy) {
-  __shared__ uint32_t s_rows[kHvyRows];
-  const uint32_t n_over = *ov_count;
-  const uint32_t npar = n_over < (uint32_t)kHeavyPar ? n_over : (uint32_t)kHeavyPar;
-  if (npar == 0) return;
-  heavy_chunks(sbb, ov_list, npar, [&](uint32_t it, uint32_t a, uint32_t b) {
+// Pairs of each row of the split sub-buckets; their digit counts cleared
+template <typename V>
+__device__ void heavy_rows(unsigned char* smem, const HeavyArgs<V>& A, uint32_t blk, uint32_t nblk) {
+  uint32_t* const s_rows = (uint32_t*)smem;  // [kHvyRows]
+  const int colbits = A.colbits;
+  for (uint32_t i = blk * kHeavyThreads + threadIdx.x; i < A.npar * (uint32_t)kHvyDigits; i += nblk * kHeavyThreads)
+    HeavyTable(A.hvy, i / kHvyDigits).hist[i % kHvyDigits] = 0u;
+  if (blk == 0 && threadIdx.x == 0) BigLeaves(A.hvy).list[0] = 0u;
+  heavy_chunks(A.sbb, A.ov_list, A.npar, blk, nblk, [&](uint32_t it, uint32_t a, uint32_t b) {
     for (int r = threadIdx.x; r < kHvyRows; r += kHeavyThreads) s_rows[r] = 0u;
     __syncthreads();
-    heavy_count(ikey, a, b, s_rows, [&](uint32_t k) { return k >> colbits; });
+    heavy_count(A.ikey, a, b, s_rows, [&](uint32_t k) { return k >> colbits; });
     __syncthreads();
-    const HeavyTable t(hvy, it);
+    const HeavyTable t(A.hvy, it);
     for (int r = threadIdx.x; r < kHvyRows; r += kHeavyThreads) {
       const uint32_t c = s_rows[r];
       if (c) atomicAdd(&t.rpair[r], c);
@@ -1819,21 +2290,13 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_rows(const uint32_t* __
   });
 }
 
-// one workgroup (kHvyRows threads) per listed sub-bucket: the digits of each row, the
-// digit counts cleared
-__global__ __launch_bounds__(kHvyRows) void k_heavy_layout(const uint32_t* __restrict__ sbb, int colbits,
-                                                           const uint32_t* __restrict__ ov_list,
-                                                           const uint32_t* __restrict__ ov_count,
-                                                           uint32_t* __restrict__ hvy) {
-  __shared__ uint32_t s_scan[kHvyRows / 64 + 1];
-  const uint32_t n_over = *ov_count;
-  const uint32_t it = blockIdx.x;
-  if (it >= n_over || it >= (uint32_t)kHeavyPar) return;
-  const HeavyTable t(hvy, it);
-  const uint32_t g = ov_list[it];
-  const uint64_t n = sbb[g + 1] - sbb[g];
+// The digits of each row of split sub-bucket it (of n pairs) from its rows' pair counts,
+// into LDS (s_rbase: kHvyRows + 1 words, s_rsh: kHvyRows, s_scan: kHeavyThreads / 64 + 1);
+// `store`: to the table too.  Ends with a barrier.
+__device__ __forceinline__ void heavy_layout(const HeavyTable& t, uint64_t n, int colbits, bool store,
+                                             uint32_t* s_rbase, uint32_t* s_rsh, uint32_t* s_scan) {
   const int r = threadIdx.x;
-  const uint32_t c = t.rpair[r];
+  const uint32_t c = r < kHvyRows ? t.rpair[r] : 0u;
   const int lg_max = colbits > 12 ? colbits - 12 : 0;  // digits no narrower than a leaf
   const int lg_min = colbits > 23 ? colbits - 23 : 0;  // nor wider than 2^23 keys
   int lg = 0;
@@ -1845,13 +2308,22 @@ __global__ __launch_bounds__(kHvyRows) void k_heavy_layout(const uint32_t* __res
   const uint32_t nr = c ? 1u << lg : 0u;
   uint32_t total;
   const uint32_t base = block_scan_u32(nr, s_scan, &total);
-  t.rbase[r] = base;
-  t.rsh[r] = (uint32_t)(colbits - lg);
-  if (r == 0) {
-    t.rbase[kHvyRows] = total;
-    t.meta[0] = total;
+  if (r < kHvyRows) {
+    s_rbase[r] = base;
+    s_rsh[r] = (uint32_t)(colbits - lg);
+    if (store) {
+      t.rbase[r] = base;
+      t.rsh[r] = (uint32_t)(colbits - lg);
+    }
   }
-  for (uint32_t d = threadIdx.x; d < total; d += kHvyRows) t.hist[d] = 0u;
+  if (r == 0) {
+    s_rbase[kHvyRows] = total;
+    if (store) {
+      t.rbase[kHvyRows] = total;
+      t.meta[0] = total;
+    }
+  }
+  __syncthreads();
 }
 
 // a sub-bucket's digit layout into LDS (s_rbase: kHvyRows + 1 words, s_rsh: kHvyRows)
@@ -1862,24 +2334,23 @@ __device__ __forceinline__ void heavy_load_layout(const HeavyTable& t, uint32_t*
   }
 }
 
-// pairs per first-level digit, summed over the chunks into the table's hist
-__global__ __launch_bounds__(kHeavyThreads) void k_heavy_hist(const uint32_t* __restrict__ ikey,
-                                                              const uint32_t* __restrict__ sbb, int colbits,
-                                                              const uint32_t* __restrict__ ov_list,
-                                                              const uint32_t* __restrict__ ov_count,
-                                                              uint32_t* __restrict__ hvy) {
-  __shared__ uint32_t s_hist[kHvyDigits];
-  __shared__ uint32_t s_rbase[kHvyRows + 1], s_rsh[kHvyRows];
-  const uint32_t n_over = *ov_count;
-  const uint32_t npar = n_over < (uint32_t)kHeavyPar ? n_over : (uint32_t)kHeavyPar;
-  if (npar == 0) return;
-  heavy_chunks(sbb, ov_list, npar, [&](uint32_t it, uint32_t a, uint32_t b) {
-    const HeavyTable t(hvy, it);
-    heavy_load_layout(t, s_rbase, s_rsh);
+// Pairs per first-level digit, summed over the chunks into the table's hist.  Every
+// workgroup works out the digit layout from the row counts (a scan of 256 words: less
+// than a launch of its own takes); the one with a sub-bucket's first chunk stores it.
+template <typename V>
+__device__ void heavy_hist(unsigned char* smem, const HeavyArgs<V>& A, uint32_t blk, uint32_t nblk) {
+  uint32_t* const s_hist = (uint32_t*)smem;        // [kHvyDigits]
+  uint32_t* const s_rbase = s_hist + kHvyDigits;   // [kHvyRows + 1]
+  uint32_t* const s_rsh = s_rbase + kHvyRows + 1;  // [kHvyRows]
+  uint32_t* const s_scan = s_rsh + kHvyRows;       // [kHeavyThreads / 64 + 1]
+  const int colbits = A.colbits;
+  heavy_chunks(A.sbb, A.ov_list, A.npar, blk, nblk, [&](uint32_t it, uint32_t a, uint32_t b) {
+    const HeavyTable t(A.hvy, it);
+    const uint32_t g = A.ov_list[it];
     for (int d = threadIdx.x; d < kHvyDigits; d += kHeavyThreads) s_hist[d] = 0u;
-    __syncthreads();
+    heavy_layout(t, A.sbb[g + 1] - A.sbb[g], colbits, a == A.sbb[g], s_rbase, s_rsh, s_scan);
     const uint32_t nd = s_rbase[kHvyRows];
-    heavy_count(ikey, a, b, s_hist, [&](uint32_t k) { return heavy_digit(k, colbits, s_rbase, s_rsh); });
+    heavy_count(A.ikey, a, b, s_hist, [&](uint32_t k) { return heavy_digit(k, colbits, s_rbase, s_rsh); });
     __syncthreads();
     for (uint32_t d = threadIdx.x; d < nd; d += kHeavyThreads) {
       const uint32_t c = s_hist[d];
@@ -1889,22 +2360,20 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_hist(const uint32_t* __
   });
 }
 
-// one workgroup per listed sub-bucket: the digit starts (absolute pair positions) from
-// the digit counts, which become the scatter's cursors; digit ranges no wider than a
-// leaf with more than kBigLeafPairs pairs are listed as big leaves
-__global__ __launch_bounds__(kHeavyThreads) void k_heavy_starts(const uint32_t* __restrict__ sbb, int colbits,
-                                                                const uint32_t* __restrict__ ov_list,
-                                                                const uint32_t* __restrict__ ov_count,
-                                                                uint32_t* __restrict__ hvy) {
-  __shared__ uint32_t s_off[kHvyDigits];
-  __shared__ uint32_t s_scan[kHeavyThreads / 64 + 1];
-  const uint32_t n_over = *ov_count;
-  const uint32_t it = blockIdx.x;
-  if (it >= n_over || it >= (uint32_t)kHeavyPar) return;
+// Per listed sub-bucket, the digit starts (absolute pair positions) from the
+// digit counts, which become the scatter's cursors; digit ranges no wider than a leaf with
+// more than kBigLeafPairs pairs are listed as big leaves
+template <typename V>
+__device__ void heavy_starts(unsigned char* smem, const HeavyArgs<V>& A, uint32_t it) {
+  uint32_t* const s_off = (uint32_t*)smem;      // [kHvyDigits]
+  uint32_t* const s_scan = s_off + kHvyDigits;  // [kHeavyThreads / 64 + 1]
+  if (it >= A.npar) return;
+  const int colbits = A.colbits;
+  uint32_t* const hvy = A.hvy;
   const HeavyTable t(hvy, it);
   const uint32_t nd = t.meta[0];
-  const uint32_t g = ov_list[it];
-  const uint32_t beg = sbb[g], end = sbb[g + 1];
+  const uint32_t g = A.ov_list[it];
+  const uint32_t beg = A.sbb[g], end = A.sbb[g + 1];
   for (uint32_t d = threadIdx.x; d < nd; d += kHeavyThreads) s_off[d] = t.hist[d];
   __syncthreads();
   block_scan_array(s_off, (int)nd, s_scan);  // (ends with a barrier)
@@ -1938,31 +2407,26 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_starts(const uint32_t* 
   if (threadIdx.x == 0) t.st[nd] = end;
 }
 
-// each chunk's pairs moved from (ikey, ival) to (akey, aval) in first-level digit order:
-// the chunk's digit counts taken again, a block of each digit reserved from the table's
-// cursors, then each pair placed in its digit's block
+// Each chunk's pairs moved from (ikey, ival) to (akey, aval) in first-level digit
+// order: the chunk's digit counts taken again, a block of each digit reserved from the
+// table's cursors, then each pair placed in its digit's block
 template <typename V>
-__global__ __launch_bounds__(kHeavyThreads) void k_heavy_scatter(const uint32_t* __restrict__ ikey,
-                                                                 const V* __restrict__ ival,
-                                                                 uint32_t* __restrict__ akey, V* __restrict__ aval,
-                                                                 const uint32_t* __restrict__ sbb, int colbits,
-                                                                 const uint32_t* __restrict__ ov_list,
-                                                                 const uint32_t* __restrict__ ov_count,
-                                                                 uint32_t* __restrict__ hvy) {
-  __shared__ uint32_t s_hist[kHvyDigits];
-  __shared__ uint32_t s_rbase[kHvyRows + 1], s_rsh[kHvyRows];
-  const uint32_t n_over = *ov_count;
-  const uint32_t npar = n_over < (uint32_t)kHeavyPar ? n_over : (uint32_t)kHeavyPar;
-  if (npar == 0) return;
+__device__ void heavy_scatter(unsigned char* smem, const HeavyArgs<V>& A, uint32_t blk, uint32_t nblk) {
+  uint32_t* const s_hist = (uint32_t*)smem;        // [kHvyDigits]
+  uint32_t* const s_rbase = s_hist + kHvyDigits;   // [kHvyRows + 1]
+  uint32_t* const s_rsh = s_rbase + kHvyRows + 1;  // [kHvyRows]
+  const int colbits = A.colbits;
+  uint32_t *const hvy = A.hvy, *const ikey = A.ikey, *const akey = A.akey;
+  V *const ival = A.ival, *const aval = A.aval;
   const int lane = threadIdx.x & 63;
-  {  // the big leaves' accumulators cleared (k_heavy_bigleaf adds into them next)
+  {  // the big leaves' accumulators cleared (the next phase adds into them)
     const BigLeaves big(hvy);
     uint32_t* const acc = big.list + kBigListWords;
     const size_t nw = (size_t)big.count() * kBigAccWords;
-    for (size_t w = (size_t)blockIdx.x * kHeavyThreads + threadIdx.x; w < nw; w += (size_t)gridDim.x * kHeavyThreads)
+    for (size_t w = (size_t)blk * kHeavyThreads + threadIdx.x; w < nw; w += (size_t)nblk * kHeavyThreads)
       acc[w] = 0u;
   }
-  heavy_chunks(sbb, ov_list, npar, [&](uint32_t it, uint32_t a, uint32_t b) {
+  heavy_chunks(A.sbb, A.ov_list, A.npar, blk, nblk, [&](uint32_t it, uint32_t a, uint32_t b) {
     const HeavyTable t(hvy, it);
     heavy_load_layout(t, s_rbase, s_rsh);
     for (int d = threadIdx.x; d < kHvyDigits; d += kHeavyThreads) s_hist[d] = 0u;
@@ -1997,17 +2461,13 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_scatter(const uint32_t*
   });
 }
 
-// the rounds of the listed big leaves, one per workgroup at a time, added into their
-// accumulators (each leaf's pairs in (akey, aval) [a, b), keys from k0)
+// The rounds of the listed big leaves, one per workgroup at a time, added into
+// their accumulators (each leaf's pairs in (akey, aval) [a, b), keys from k0)
 template <typename V>
-__global__ __launch_bounds__(kHeavyThreads) void k_heavy_bigleaf(const uint32_t* akey, const V* aval,
-                                                                 const uint32_t* __restrict__ emax,
-                                                                 const uint32_t* __restrict__ ov_count,
-                                                                 uint32_t* __restrict__ hvy) {
-  extern __shared__ __align__(16) unsigned char smem[];
+__device__ void heavy_bigleaf(unsigned char* smem, const HeavyArgs<V>& A, uint32_t blk, uint32_t nblk) {
   const HeavySmem sm(smem);
   __shared__ uint32_t s_p0[kBigLeaves + 1];
-  if (*ov_count == 0) return;
+  uint32_t* const hvy = A.hvy;
   const BigLeaves big(hvy);
   const uint32_t nbig = big.count();
   if (nbig == 0) return;
@@ -2026,14 +2486,13 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_bigleaf(const uint32_t*
   }
   if (threadIdx.x < kLeafKeys / 4) ((uint32_t*)sm.occ)[threadIdx.x] = 0u;
   __syncthreads();
-  const int F = 1117 - (int)*emax;
-  for (uint32_t p = blockIdx.x; p < s_p0[nbig]; p += gridDim.x) {
+  for (uint32_t p = blk; p < s_p0[nbig]; p += nblk) {
     uint32_t i = 0;
     while (i + 1 < nbig && s_p0[i + 1] <= p) ++i;
     const uint32_t* const q = big.rec(i);
     const uint32_t a = q[2] + (p - s_p0[i]) * kRound;
     const uint32_t b = q[3] - a > kRound ? a + kRound : q[3];
-    heavy_leaf_sum<V>(sm, akey, aval, a, b, q[4], F);
+    heavy_leaf_sum<V>(sm, A.akey, A.aval, a, b, q[4], A.F);
     unsigned long long* const glo = big.lo(i);
     unsigned long long* const ghi = big.hi(i);
     unsigned long long* const gtop = big.top(i);
@@ -2054,23 +2513,18 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_bigleaf(const uint32_t*
   }
 }
 
-// The first-level digit ranges of the first kHeavyPar listed sub-buckets, split by
-// k_heavy_scatter: range d0 of sub-bucket it is reduced by workgroup d0 mod gridDim.x,
-// its entries written from its own first pair's place (its pairs all read before;
-// other workgroups read other ranges), its entry count recorded in the table and added
-// to its row's.
-template <typename V, bool RES = false>
-__global__ __launch_bounds__(kHeavyThreads) void k_pass3_heavy_ranges(uint32_t* ikey, V* ival, uint32_t* akey,
-                                                                    V* aval, int colbits,
-                                                                    const uint32_t* __restrict__ emax,
-                                                                    V* __restrict__ tres,
-                                                                    const uint32_t* __restrict__ ov_count,
-                                                                    uint32_t* __restrict__ hvy) {
-  extern __shared__ __align__(16) unsigned char smem[];
+// The first-level digit ranges of the first kHeavyPar listed sub-buckets, split
+// by heavy_scatter: range d0 of sub-bucket it is reduced by workgroup d0 mod nblk, its
+// entries written from its own first pair's place (its pairs all read before; other
+// workgroups read other ranges), its entry count recorded in the table and added to its
+// row's.
+template <typename V, bool RES>
+__device__ void heavy_ranges(unsigned char* smem, const HeavyArgs<V>& A, uint32_t blk, uint32_t nblk) {
   const HeavySmem sm(smem);
-  const uint32_t n_over = *ov_count;
-  const uint32_t npar = n_over < (uint32_t)kHeavyPar ? n_over : (uint32_t)kHeavyPar;
-  if (npar == 0) return;
+  const uint32_t npar = A.npar;
+  const int colbits = A.colbits, F = A.F;
+  uint32_t *const hvy = A.hvy, *const ikey = A.ikey, *const akey = A.akey;
+  V *const ival = A.ival, *const aval = A.aval, *const tres = A.tres;
   for (int h = threadIdx.x; h < kLeafKeys; h += kHeavyThreads) {
     sm.lo[h] = 0ull;
     sm.hi[h] = 0ll;
@@ -2079,14 +2533,13 @@ __global__ __launch_bounds__(kHeavyThreads) void k_pass3_heavy_ranges(uint32_t* 
   if (threadIdx.x < kLeafKeys / 4) ((uint32_t*)sm.occ)[threadIdx.x] = 0u;
   for (int r = threadIdx.x; r < 256; r += kHeavyThreads) sm.rowcnt[r] = 0u;
   __syncthreads();
-  const int F = 1117 - (int)*emax;
   int32_t* const tcol = (int32_t*)akey;
   // the layout of the sub-bucket in hand, in the first of the two split-start arrays
   // (heavy_range uses the second)
   uint32_t* const s_rbase = sm.start;
   uint32_t* const s_rsh = sm.start + kHvyRows + 1;
   static_assert(2 * kHvyRows + 1 <= kDigits + 1, "the row layout fits one split-start array");
-  // the big leaves (summed by k_heavy_bigleaf): their sub-bucket and digit
+  // the big leaves (summed by heavy_bigleaf): their sub-bucket and digit
   __shared__ uint32_t s_big[2 * kBigLeaves];
   const BigLeaves big(hvy);
   const uint32_t nbig = big.count();
@@ -2099,7 +2552,7 @@ __global__ __launch_bounds__(kHeavyThreads) void k_pass3_heavy_ranges(uint32_t* 
     heavy_load_layout(t, s_rbase, s_rsh);
     __syncthreads();
     const uint32_t nd0 = s_rbase[kHvyRows];
-    for (uint32_t d0 = blockIdx.x; d0 < nd0; d0 += gridDim.x) {
+    for (uint32_t d0 = blk; d0 < nd0; d0 += nblk) {
       const uint32_t a = t.st[d0], b = t.st[d0 + 1];
       if (a == b) {  // (its count word still holds the scatter's cursor)
         if (threadIdx.x == 0) t.ucnt[d0] = 0u;
@@ -2160,30 +2613,27 @@ __device__ __forceinline__ uint32_t heavy_find(P off, uint32_t n, uint32_t f) {
 }
 
 constexpr uint32_t kFinalWave = 4096;  // entries one wavefront of k_final copies
+constexpr uint32_t kFinalHeavyGrid = 256;  // workgroups of k_final copying heavy sub-buckets
 
-// One workgroup per sub-bucket of the table: its ranges' entry counts replaced by their
-// offsets (k_final_heavy gathers the entries from the ranges through them), the row
-// offsets within the sub-bucket and its entry count.  A sub-bucket of at most
-// kFinalWave entries, which k_final copies as one run from its first pair's place, has
-// them moved there: each thread reads its entries, and writes them after a barrier.
-constexpr int kFinishThreads = 1024;
-template <typename V, bool RES = false>
-__global__ __launch_bounds__(kFinishThreads) void k_pass3_heavy_finish(uint32_t* akey, V* aval, V* tres,
-                                                                     const uint32_t* __restrict__ sbb, int s2,
-                                                                     int64_t n_node, uint32_t* __restrict__ rowoff,
-                                                                     uint32_t* __restrict__ usub,
-                                                                     const uint32_t* __restrict__ ov_list,
-                                                                     const uint32_t* __restrict__ ov_count,
-                                                                     uint32_t* __restrict__ hvy) {
-  __shared__ uint32_t s_off[kHvyDigits];
-  __shared__ uint32_t s_scan[kFinishThreads / 64 + 1];
-  const uint32_t n_over = *ov_count;
-  const uint32_t it = blockIdx.x;
-  if (it >= n_over || it >= (uint32_t)kHeavyPar) return;
-  const HeavyTable t(hvy, it);
+// Per sub-bucket of the table, its ranges' entry counts replaced by their
+// offsets (k_final gathers the entries from the ranges through them), the row offsets
+// within the sub-bucket and its entry count.  A sub-bucket of at most kFinalWave entries,
+// which k_final copies as one run from its first pair's place, has them moved there: each
+// thread reads its entries, and writes them after a barrier.
+constexpr int kFinishThreads = kHeavyThreads;
+template <typename V, bool RES>
+__device__ void heavy_finish(unsigned char* smem, const HeavyArgs<V>& A, uint32_t it) {
+  uint32_t* const s_off = (uint32_t*)smem;      // [kHvyDigits]
+  uint32_t* const s_scan = s_off + kHvyDigits;  // [kFinishThreads / 64 + 1]
+  if (it >= A.npar) return;
+  uint32_t *const akey = A.akey, *const rowoff = A.rowoff, *const usub = A.usub;
+  V *const aval = A.aval, *const tres = A.tres;
+  const int s2 = A.s2;
+  const int64_t n_node = A.n_node;
+  const HeavyTable t(A.hvy, it);
   const uint32_t nd0 = t.meta[0];
-  const int64_t g = ov_list[it];
-  const uint32_t beg = sbb[g];
+  const int64_t g = A.ov_list[it];
+  const uint32_t beg = A.sbb[g];
   for (uint32_t d = threadIdx.x; d < nd0; d += kFinishThreads) s_off[d] = t.ucnt[d];
   __syncthreads();
   const uint32_t U = block_scan_array(s_off, (int)nd0, s_scan);  // (ends with a barrier)
@@ -2242,63 +2692,101 @@ __global__ __launch_bounds__(kFinishThreads) void k_pass3_heavy_finish(uint32_t*
   if (threadIdx.x == 0) usub[g] = U;
 }
 
-// ------------------------------------------------------------------------- final
-// One wavefront per sub-bucket g: its entries copied to their final place ubase[g],
-// its rows' row_ptr = ubase[g] + local row offset.
-// GROUPED (running sums of a grouped build): also each entry's residual (tres -> res)
-// and its row (rows), the form in which the next group's pass reads them back.
-template <typename V, bool GROUPED = false>
-__global__ __launch_bounds__(256) void k_final(const uint32_t* __restrict__ sbb, const uint32_t* __restrict__ ubase,
-                                               const int32_t* __restrict__ tcol, const V* __restrict__ tval,
-                                               const V* __restrict__ tres, const uint32_t* __restrict__ rowoff,
-                                               int s2, int64_t n_node, int64_t nsub, int32_t* __restrict__ row_ptr,
-                                               int32_t* __restrict__ col_idx, V* __restrict__ vals,
-                                               V* __restrict__ res, int32_t* __restrict__ rows, int64_t cap,
-                                               uint32_t* __restrict__ status) {
-  const int lane = threadIdx.x & 63;
-  const int64_t g = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-  if (g >= nsub) return;
-  const int64_t nnz = ubase[nsub];
-  const uint32_t base = ubase[g], U = ubase[g + 1] - base;
-  const int64_t r0 = g << s2;
-  const int R = (int)min((int64_t)1 << s2, n_node - r0);
-  if (nnz <= cap && U <= kFinalWave) {  // (larger: a heavy sub-bucket, k_final_heavy)
-    const uint32_t src = sbb[g];
-    for (uint32_t f = lane; f < U; f += 64) {
-      col_idx[base + f] = tcol[src + f];
-      vals[base + f] = tval[src + f];
-      if constexpr (GROUPED) res[base + f] = tres[src + f];
+// The sub-buckets listed by pass 3, one kernel per phase; with none listed every workgroup
+// returns at once.  At most `par` of them are split by the whole device; a build of at most
+// 2^16 pairs has no pair to spare for that (par = 0): it launches the last phase alone,
+// whose workgroups take whole sub-buckets.  The phases are separate launches: one kernel
+// that hands their workgroups out as tickets in order, each phase waiting for the one
+// before, did not finish on a batch with two heavy rows.
+enum HeavyPhase { kHeavyRowsPhase, kHeavyHistPhase, kHeavyStartsPhase, kHeavyScatterPhase, kHeavyBigPhase,
+                  kHeavyRangesPhase, kHeavyFinishPhase };
+constexpr int64_t kHeavySplitPairs = 1 << 16;
+constexpr int kScanHere = 16384;  // sub-buckets whose entry counts the last phase scans itself
+
+__device__ __forceinline__ void scan_counts(uint32_t* usub, int n, uint32_t* ubase, int64_t* nnz,
+                                            uint32_t* s_scan) {
+  constexpr int PER = 4;
+  uint32_t carry = 0;
+  for (int b0 = 0; b0 < n; b0 += PER * (int)blockDim.x) {
+    const int b = b0 + PER * threadIdx.x;
+    uint32_t v[PER], sum = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      v[i] = b + i < n ? __hip_atomic_load(&usub[b + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+      sum += v[i];
     }
-    if constexpr (GROUPED) {
-      for (int r = lane; r < R; r += 64) {
-        const uint32_t k1 = r + 1 < R ? rowoff[r0 + r + 1] : U;
-        for (uint32_t k = rowoff[r0 + r]; k < k1; ++k) rows[base + k] = (int32_t)(r0 + r);
-      }
+    uint32_t total;
+    uint32_t off = carry + block_scan_u32(sum, s_scan, &total);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      if (b + i < n) ubase[b + i] = off;
+      off += v[i];
     }
-  } else if (nnz > cap && g == 0 && lane == 0) {
-    raise_flag(status, KB_F_CAPACITY);
+    carry += total;
   }
-  for (int r = lane; r < R; r += 64) row_ptr[r0 + r] = (int32_t)(base + rowoff[r0 + r]);
-  if (g == nsub - 1 && lane == 0) row_ptr[n_node] = (int32_t)nnz;
+  if (threadIdx.x == 0) {
+    ubase[n] = carry;
+    *nnz = carry;
+  }
 }
 
-// The entries of the sub-buckets k_final leaves (more than kFinalWave: only a heavy
-// sub-bucket, listed by pass 3, can hold more than a pass-3 table), copied by all the
-// workgroups of the grid in chunks of 1024: from the sub-bucket's first pair's place
-// on, or, for the first kHeavyPar listed, from the digit ranges that hold them (entry f
-// of the range d whose entry offset is the last at or below f, at the range's start
-// plus f minus that offset).  With GROUPED each entry's row is found by a binary search
-// of the sub-bucket's row offsets.
-template <typename V, bool GROUPED = false>
-__global__ __launch_bounds__(256) void k_final_heavy(const uint32_t* __restrict__ sbb, const uint32_t* __restrict__ ubase,
-                                                     const int32_t* __restrict__ tcol, const V* __restrict__ tval,
-                                                     const V* __restrict__ tres, const uint32_t* __restrict__ rowoff,
-                                                     int s2, int64_t n_node, int64_t nsub,
-                                                     const uint32_t* __restrict__ ov_list,
-                                                     const uint32_t* __restrict__ ov_count,
-                                                     const uint32_t* __restrict__ hvy,
-                                                     int32_t* __restrict__ col_idx, V* __restrict__ vals,
-                                                     V* __restrict__ res, int32_t* __restrict__ rows, int64_t cap) {
+// SCAN (the last launch): the entry counts of few sub-buckets (ubase not null) scanned too,
+// by the last workgroup to finish, or by the first if none is listed.
+template <typename V, bool RES, HeavyPhase PHASE, bool SCAN = false>
+__global__ __launch_bounds__(kHeavyThreads) void k_heavy(HeavyArgs<V> A, const uint32_t* __restrict__ emax,
+                                                       const uint32_t* __restrict__ n_over, uint32_t par,
+                                                       uint32_t* done, int nsub, uint32_t* ubase, int64_t* nnz) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  A.n_over = *n_over;
+  if (A.n_over == 0) {
+    if constexpr (SCAN)
+      if (ubase && blockIdx.x == 0) scan_counts(A.usub, nsub, ubase, nnz, (uint32_t*)smem);
+    return;
+  }
+  A.npar = A.n_over < par ? A.n_over : par;
+  A.F = 1117 - (int)*emax;
+  const uint32_t blk = blockIdx.x, nblk = gridDim.x;
+  if constexpr (PHASE == kHeavyRowsPhase) heavy_rows<V>(smem, A, blk, nblk);
+  if constexpr (PHASE == kHeavyHistPhase) heavy_hist<V>(smem, A, blk, nblk);
+  if constexpr (PHASE == kHeavyStartsPhase) heavy_starts<V>(smem, A, blk);
+  if constexpr (PHASE == kHeavyScatterPhase) heavy_scatter<V>(smem, A, blk, nblk);
+  if constexpr (PHASE == kHeavyBigPhase) heavy_bigleaf<V>(smem, A, blk, nblk);
+  if constexpr (PHASE == kHeavyRangesPhase) {
+    if (A.npar) heavy_ranges<V, RES>(smem, A, blk, nblk);
+    __syncthreads();
+    heavy_rest<V, RES>(smem, A, blk, nblk);
+  }
+  if constexpr (PHASE == kHeavyFinishPhase) heavy_finish<V, RES>(smem, A, blk);
+  if constexpr (SCAN) {
+    if (!ubase) return;
+    __shared__ uint32_t s_last;
+    __threadfence();  // this thread's counts before the arrival
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(done, 1u) == gridDim.x - 1 ? 1u : 0u;
+    __syncthreads();
+    if (!s_last) return;
+    __threadfence();
+    scan_counts(A.usub, nsub, ubase, nnz, (uint32_t*)smem);
+  }
+}
+
+// ------------------------------------------------------------------------- final
+// The entries of the sub-buckets that one wavefront does not copy (more than kFinalWave:
+// only a heavy sub-bucket, listed by pass 3, can hold more than a pass-3 table), copied
+// by nblk workgroups in chunks of 1024: from the sub-bucket's first pair's place on, or,
+// for the first `par` listed, from the digit ranges that hold them (entry f of the
+// range d whose entry offset is the last at or below f, at the range's start plus f minus
+// that offset).  With GROUPED each entry's row is found by a binary search of the
+// sub-bucket's row offsets.
+template <typename V, bool GROUPED>
+__device__ __forceinline__ void final_heavy(const uint32_t* __restrict__ sbb, const uint32_t* __restrict__ ubase,
+                                            const int32_t* __restrict__ tcol, const V* __restrict__ tval,
+                                            const V* __restrict__ tres, const uint32_t* __restrict__ rowoff, int s2,
+                                            int64_t n_node, int64_t nsub, const uint32_t* __restrict__ ov_list,
+                                            const uint32_t* __restrict__ ov_count, const uint32_t* __restrict__ hvy,
+                                            int32_t* __restrict__ col_idx, V* __restrict__ vals, V* __restrict__ res,
+                                            int32_t* __restrict__ rows, int64_t cap, uint32_t par, uint32_t blk,
+                                            uint32_t nblk) {
   __shared__ uint32_t s_off[kHvyDigits];  // entry offsets of the ranges
   const uint32_t n_over = *ov_count;
   if (n_over == 0 || (int64_t)ubase[nsub] > cap) return;
@@ -2307,7 +2795,7 @@ __global__ __launch_bounds__(256) void k_final_heavy(const uint32_t* __restrict_
     const uint32_t base = ubase[g], U = ubase[g + 1] - base;
     if (U <= kFinalWave) continue;
     const uint32_t beg = sbb[g];
-    const bool ranged = it < (uint32_t)kHeavyPar;
+    const bool ranged = it < par;
     const HeavyTable t(const_cast<uint32_t*>(hvy), ranged ? it : 0u);
     const uint32_t nd0 = ranged ? t.meta[0] : 0u;
     if (ranged) {
@@ -2317,7 +2805,7 @@ __global__ __launch_bounds__(256) void k_final_heavy(const uint32_t* __restrict_
     }
     const int64_t r0 = g << s2;
     const int R = (int)min((int64_t)1 << s2, n_node - r0);
-    for (uint32_t c = blockIdx.x * 1024u; c < U; c += gridDim.x * 1024u) {
+    for (uint32_t c = blk * 1024u; c < U; c += nblk * 1024u) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const uint32_t f = c + j * 256 + threadIdx.x;
@@ -2344,6 +2832,54 @@ __global__ __launch_bounds__(256) void k_final_heavy(const uint32_t* __restrict_
       }
     }
   }
+}
+
+// One wavefront per sub-bucket g: its entries copied to their final place ubase[g],
+// its rows' row_ptr = ubase[g] + local row offset.
+// GROUPED (running sums of a grouped build): also each entry's residual (tres -> res)
+// and its row (rows), the form in which the next group's pass reads them back.
+// The last kFinalHeavyGrid workgroups copy the larger sub-buckets (final_heavy).
+template <typename V, bool GROUPED = false>
+__global__ __launch_bounds__(256) void k_final(const uint32_t* __restrict__ sbb, const uint32_t* __restrict__ ubase,
+                                               const int32_t* __restrict__ tcol, const V* __restrict__ tval,
+                                               const V* __restrict__ tres, const uint32_t* __restrict__ rowoff,
+                                               int s2, int64_t n_node, int64_t nsub, int32_t* __restrict__ row_ptr,
+                                               int32_t* __restrict__ col_idx, V* __restrict__ vals,
+                                               V* __restrict__ res, int32_t* __restrict__ rows, int64_t cap,
+                                               uint32_t* __restrict__ status, const uint32_t* __restrict__ ov_list,
+                                               const uint32_t* __restrict__ ov_count,
+                                               const uint32_t* __restrict__ hvy, uint32_t par) {
+  const uint32_t n_wave = gridDim.x - kFinalHeavyGrid;
+  if (blockIdx.x >= n_wave) {
+    final_heavy<V, GROUPED>(sbb, ubase, tcol, tval, tres, rowoff, s2, n_node, nsub, ov_list, ov_count, hvy, col_idx,
+                            vals, res, rows, cap, par, blockIdx.x - n_wave, kFinalHeavyGrid);
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  const int64_t g = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
+  if (g >= nsub) return;
+  const int64_t nnz = ubase[nsub];
+  const uint32_t base = ubase[g], U = ubase[g + 1] - base;
+  const int64_t r0 = g << s2;
+  const int R = (int)min((int64_t)1 << s2, n_node - r0);
+  if (nnz <= cap && U <= kFinalWave) {  // (larger: a heavy sub-bucket, final_heavy)
+    const uint32_t src = sbb[g];
+    for (uint32_t f = lane; f < U; f += 64) {
+      col_idx[base + f] = tcol[src + f];
+      vals[base + f] = tval[src + f];
+      if constexpr (GROUPED) res[base + f] = tres[src + f];
+    }
+    if constexpr (GROUPED) {
+      for (int r = lane; r < R; r += 64) {
+        const uint32_t k1 = r + 1 < R ? rowoff[r0 + r + 1] : U;
+        for (uint32_t k = rowoff[r0 + r]; k < k1; ++k) rows[base + k] = (int32_t)(r0 + r);
+      }
+    }
+  } else if (nnz > cap && g == 0 && lane == 0) {
+    raise_flag(status, KB_F_CAPACITY);
+  }
+  for (int r = lane; r < R; r += 64) row_ptr[r0 + r] = (int32_t)(base + rowoff[r0 + r]);
+  if (g == nsub - 1 && lane == 0) row_ptr[n_node] = (int32_t)nnz;
 }
 
 }  // namespace kb

@@ -65,7 +65,7 @@ __device__ __forceinline__ void node_ranks(const int32_t (&E)[NEN], int (&r)[NEN
 // of element e is the global DOF dof*E[a]+i.  An id outside [0, n_node) maps to ids
 // outside [0, dof*n_node) (a negative one stays negative; distinct ids stay distinct
 // below 2^31/dof in magnitude), so the pipeline flags the element as the node ids would.
-__global__ __launch_bounds__(256) void k_dof_conn(const int32_t* __restrict__ conn, int64_t n, int dof,
+static __global__ __launch_bounds__(256) void k_dof_conn(const int32_t* __restrict__ conn, int64_t n, int dof,
                                                   int32_t* __restrict__ dconn) {
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
     const int64_t v = conn[t];
@@ -78,12 +78,12 @@ __global__ __launch_bounds__(256) void k_dof_conn(const int32_t* __restrict__ co
 }
 
 // ------------------------------------------------------------------------- fill
-__global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
+static __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
 }
 
-__global__ void k_init_status(uint32_t* __restrict__ status, int64_t* __restrict__ nnz) {
+static __global__ void k_init_status(uint32_t* __restrict__ status, int64_t* __restrict__ nnz) {
   if (threadIdx.x < KB_STATUS_WORDS) status[threadIdx.x] = 0u;
   if (threadIdx.x == 0 && nnz) *nnz = 0;
 }
@@ -116,8 +116,8 @@ __device__ __forceinline__ int32_t block_exclusive_scan(int32_t v, int32_t* smem
   return r;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_partials(const int32_t* __restrict__ in, int64_t n,
-                                                                int32_t* __restrict__ partials) {
+// sum of in[] over this workgroup's chunk of kScanChunk entries -> part[blockIdx.x]
+__device__ __forceinline__ void scan_chunk_sum(const int32_t* __restrict__ in, int64_t n, int32_t* __restrict__ part) {
   __shared__ int32_t sw[kScanThreads / 64 + 1];
   const int64_t base = (int64_t)blockIdx.x * kScanChunk + (int64_t)threadIdx.x * kScanItems;
   int32_t s = 0;
@@ -126,38 +126,20 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_partials(const int32_t* _
     if (base + i < n) s += in[base + i];
   int32_t total;
   block_exclusive_scan(s, sw, &total);
-  if (threadIdx.x == 0) partials[blockIdx.x] = total;
+  if (threadIdx.x == 0) part[blockIdx.x] = total;
 }
 
-// single block: exclusive scan of partials[0..nb) in place
-__global__ __launch_bounds__(kScanThreads) void k_scan_top(int32_t* __restrict__ partials, int64_t nb) {
+// out[0..n] = exclusive scan of in[0..n) (out[n] = total), this workgroup's chunk: the
+// chunk sums before it are added up here, so no kernel in between scans them.  also (in
+// itself, or null) gets out[0..n); total64 optional
+__device__ __forceinline__ void scan_chunk_down(const int32_t* in, int64_t n, const int32_t* __restrict__ part,
+                                                int32_t* __restrict__ out, int32_t* also,
+                                                int64_t* __restrict__ total64) {
   __shared__ int32_t sw[kScanThreads / 64 + 1];
-  int32_t carry = 0;
-  for (int64_t base = 0; base < nb; base += (int64_t)kScanThreads * kScanItems) {
-    const int64_t my = base + (int64_t)threadIdx.x * kScanItems;
-    int32_t v[kScanItems];
-    int32_t s = 0;
-#pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
-      v[i] = (my + i < nb) ? partials[my + i] : 0;
-      s += v[i];
-    }
-    int32_t total;
-    int32_t off = block_exclusive_scan(s, sw, &total) + carry;
-#pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
-      if (my + i < nb) partials[my + i] = off;
-      off += v[i];
-    }
-    carry += total;
-  }
-}
-
-// out[0..n] = exclusive scan of in[0..n) (out[n] = total); total64 optional
-__global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t* __restrict__ in, int64_t n,
-                                                            const int32_t* __restrict__ partials,
-                                                            int32_t* __restrict__ out, int64_t* __restrict__ total64) {
-  __shared__ int32_t sw[kScanThreads / 64 + 1];
+  int32_t before = 0;
+  for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kScanThreads) before += part[i];
+  int32_t prefix;
+  block_exclusive_scan(before, sw, &prefix);
   const int64_t base = (int64_t)blockIdx.x * kScanChunk + (int64_t)threadIdx.x * kScanItems;
   int32_t v[kScanItems];
   int32_t s = 0;
@@ -167,21 +149,35 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t* __res
     s += v[i];
   }
   int32_t total;
-  int32_t off = block_exclusive_scan(s, sw, &total) + partials[blockIdx.x];
+  int32_t off = block_exclusive_scan(s, sw, &total) + prefix;
 #pragma unroll
   for (int i = 0; i < kScanItems; ++i) {
-    if (base + i < n) out[base + i] = off;
+    if (base + i < n) {
+      out[base + i] = off;
+      if (also) also[base + i] = off;
+    }
     off += v[i];
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    const int32_t grand = partials[blockIdx.x] + total;
+  if ((int64_t)(blockIdx.x + 1) * kScanChunk >= n && threadIdx.x == 0) {
+    const int32_t grand = prefix + total;
     out[n] = grand;
     if (total64) *total64 = grand;
   }
 }
 
+static __global__ __launch_bounds__(kScanThreads) void k_scan_partials(const int32_t* __restrict__ in, int64_t n,
+                                                                int32_t* __restrict__ part) {
+  scan_chunk_sum(in, n, part);
+}
+
+static __global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t* __restrict__ in, int64_t n,
+                                                            const int32_t* __restrict__ part,
+                                                            int32_t* __restrict__ out, int64_t* __restrict__ total64) {
+  scan_chunk_down(in, n, part, out, nullptr, total64);
+}
+
 // n == 0: out[0] = 0
-__global__ void k_scan_empty(int32_t* __restrict__ out, int64_t* __restrict__ total64) {
+static __global__ void k_scan_empty(int32_t* __restrict__ out, int64_t* __restrict__ total64) {
   out[0] = 0;
   if (total64) *total64 = 0;
 }
@@ -224,11 +220,6 @@ struct NodesPadded {
     x[2] = v.z;
   }
 };
-
-__global__ void k_pad_coords(const double* __restrict__ c, int64_t n, double4* __restrict__ out) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    out[i] = make_double4(c[3 * i], c[3 * i + 1], c[3 * i + 2], 0.0);
-}
 
 // Coordinates of the element's nodes, gathered once into registers.
 template <int NEN, typename NODES>
@@ -347,17 +338,10 @@ __device__ __forceinline__ void element_values(const NODES& nodes, const double*
   if (!finite) *f |= KB_F_NONFINITE;
 }
 
-// A brick integrated by a lane pair (lanes 2i and 2i+1; h = lane & 1): lane h gathers
-// nodes 4h .. 4h+3, the coordinates relative to node 0 are exchanged by shuffles, each
-// lane integrates the four points of its half of the rule and the two halves of k are
-// added.  Both lanes of a pair must be active together; both end with the same k and
-// flags (the fallback is counted once, by h = 0).
-template <Prec P>
-__device__ __forceinline__ void element_values_pair(const NodesPadded& nodes, const double* __restrict__ coef,
-                                                    int64_t e, const int32_t (&E)[8], float tau, int h,
-                                                    typename PrecTraits<P>::V (&k)[36], uint32_t* f, uint32_t* fb) {
-  using V = typename PrecTraits<P>::V;
-  double xo[4][3];  // (a branch per half keeps every index into E a constant)
+// Lane h of a pair gathers nodes 4h .. 4h+3 of its brick (a branch per half keeps every
+// index into E a constant).
+__device__ __forceinline__ void gather_pair(const NodesPadded& nodes, const int32_t (&E)[8], int h,
+                                            double (&xo)[4][3]) {
   if (h) {
 #pragma unroll
     for (int a = 0; a < 4; ++a) nodes.get(E[4 + a], xo[a]);
@@ -365,6 +349,17 @@ __device__ __forceinline__ void element_values_pair(const NodesPadded& nodes, co
 #pragma unroll
     for (int a = 0; a < 4; ++a) nodes.get(E[a], xo[a]);
   }
+}
+
+// A brick of coefficient c integrated by a lane pair (lanes 2i and 2i+1; h = lane & 1)
+// from the nodes gather_pair brought: the coordinates relative to node 0 are exchanged by
+// shuffles, each lane integrates the four points of its half of the rule and the two
+// halves of k are added.  Both lanes of a pair must be active together; both end with the
+// same k and flags (the fallback is counted once, by h = 0).
+template <Prec P>
+__device__ __forceinline__ void element_values_pair(const double (&xo)[4][3], double c, float tau, int h,
+                                                    typename PrecTraits<P>::V (&k)[36], uint32_t* f, uint32_t* fb) {
+  using V = typename PrecTraits<P>::V;
   double X0[3];
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
@@ -381,7 +376,6 @@ __device__ __forceinline__ void element_values_pair(const NodesPadded& nodes, co
       Xd[a][j] = h ? other : mine;
       Xd[4 + a][j] = h ? mine : other;
     }
-  const double c = coef[e];
   bool ok;
   if constexpr (P == Prec::F64) {
     ok = hex_integrate_half<double, double, false>(Xd, k, 0.0, nullptr, h);
