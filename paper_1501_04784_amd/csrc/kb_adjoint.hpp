@@ -12,9 +12,15 @@
 //
 // Node gradients are sums over the elements at each node.  They are accumulated as the
 // same exact fixed-point integers as the assembly (scale from the largest exponent of
-// all element contributions; two 64-bit integer chunks per value, summed in LDS per
-// workgroup and then globally), so the result does not depend on the order of the
-// atomics: bitwise deterministic, exact while a node belongs to at most 2^16 elements.
+// all element contributions; two 64-bit integer chunks per value), so the result does not
+// depend on the order of the additions: bitwise deterministic, and exact.  The corners are partitioned by node bucket first, so each
+// bucket's sums are formed in one workgroup's LDS:
+//   k_adjoint_count   each corner's place within its bucket, and the bucket starts
+//   k_adjoint_elems   the gradients, one 32-byte record per corner at its place
+//   k_adjoint_reduce  a bucket's records summed, rounded once, written
+// Adding each workgroup's node sums to global accumulators instead (64-bit atomics: 27
+// G/s, and a node's six words from every workgroup that touches it) took 278 us of the
+// 64^3 bricks' 489 us.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -81,8 +87,197 @@ __device__ __forceinline__ void adjoint_point(const double (&G)[3][NEN], const d
       D[a][i] += f * (tr * G[i][a] - 2.0 * (P[i][0] * G[0][a] + P[i][1] * G[1][a] + P[i][2] * G[2][a]));
 }
 
-// Per element (one per lane): dL/dc_e into grad_coef, the nen x 3 coordinate
-// gradients into gel (element-major), the largest exponent of those into *emax.
+// ---- corners by node bucket (node >> bits) ------------------------------------------
+// at least 2^6 nodes a bucket, at most 2^10 (48 KB of LDS sums); about 512 buckets between
+constexpr int kAdjMinBits = 6, kAdjMaxBits = 10, kAdjBuckets = 512;
+constexpr int kAdjArray = 8192;           // buckets counted in an LDS array, else in the slot hash
+constexpr int kAdjPer = 4;                // elements per lane of k_adjoint_count
+constexpr uint32_t kAdjChunk = kRound;    // records per workgroup of k_adjoint_reduce at most (sums inside 64 bits)
+
+constexpr int kAdjAcc = 9;                // global words per node: low, high and top sums of x, y, z
+
+struct AdjointRecord {
+  double g[3];
+  uint64_t node;  // within its bucket
+};
+
+// head: [0] largest exponent, [1] workgroups done, [2] buckets of more than kAdjChunk
+// records, [3] workgroups they need beyond one each.  big: (bucket, first of those
+// workgroups, workgroups done) per such bucket.
+static __global__ __launch_bounds__(256) void k_adjoint_begin(uint32_t* __restrict__ status,
+                                                              uint32_t* __restrict__ head,
+                                                              uint32_t* __restrict__ cnt, int64_t nb) {
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < KB_STATUS_WORDS) status[threadIdx.x] = 0u;
+    if (threadIdx.x < 4) head[threadIdx.x] = 0u;
+  }
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nb; i += (int64_t)gridDim.x * blockDim.x)
+    cnt[i] = 0u;
+}
+
+// rel[e * NEN + a]: corner a's place within its node's bucket.  A workgroup counts its
+// elements' corners per bucket in LDS (one atomic per run of an element's corners in one
+// bucket), takes its places in each bucket with one global atomic, whose result is where
+// its corners start.  The last workgroup turns the counts into the bucket starts
+// start[0 .. nb] and lists the buckets of more than kAdjChunk corners.  An element that
+// fails its connectivity check has no places.
+template <int NEN>
+__global__ __launch_bounds__(256) void k_adjoint_count(const int32_t* __restrict__ conn, int64_t n_elem,
+                                                       int64_t n_node, int bits, int nb, uint32_t* cnt,
+                                                       uint32_t* __restrict__ start, uint32_t* __restrict__ rel,
+                                                       uint32_t* head, uint32_t* __restrict__ big) {
+  extern __shared__ uint32_t s_w[];  // counts, then bases (and keys of the hash)
+  const bool array = nb <= kAdjArray;
+  TileSlots<true> sl(s_w, s_w + kSlotsHash, array ? kDirect : kAsk, 0, 0, bits, nb);
+  sl.clear(blockDim.x);
+  __syncthreads();
+  const int64_t e0 = blockIdx.x * (int64_t)blockDim.x * kAdjPer;
+  uint32_t q[kAdjPer][NEN];
+  bool ok[kAdjPer];
+#pragma unroll
+  for (int u = 0; u < kAdjPer; ++u) {
+    const int64_t e = e0 + u * blockDim.x + threadIdx.x;
+    ok[u] = false;
+    if (e >= n_elem) continue;
+    int32_t E[NEN];
+    load_conn<NEN>(conn, e, E);
+    ok[u] = check_conn<NEN>(E, n_node) == 0;
+    if (!ok[u]) continue;
+    const int one[NEN] = {};  // (reserve_rows takes rank + 1 places a row: one each)
+    reserve_rows<NEN, 0>(sl, E, one, q[u]);
+#pragma unroll
+    for (int a = 0; a < NEN; ++a)  // no slot: the place taken at once
+      if (q[u][a] == kNoSlot) rel[e * NEN + a] = atomicAdd(&cnt[E[a] >> bits], 1u);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < sl.n; b += blockDim.x) {
+    const uint32_t c = sl.cnt[b];
+    if (c) sl.cnt[b] = atomicAdd(&cnt[sl.hash ? sl.key[b] : (uint32_t)b], c);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kAdjPer; ++u) {
+    const int64_t e = e0 + u * blockDim.x + threadIdx.x;
+    if (!ok[u]) continue;
+#pragma unroll
+    for (int a = 0; a < NEN; ++a)
+      if (q[u][a] != kNoSlot) rel[e * NEN + a] = sl.cnt[q[u][a] >> 16] + (q[u][a] & 0xFFFFu);
+  }
+  // bucket starts, and the buckets that need several workgroups
+  __shared__ uint32_t s_scan[8], s_last;
+  __threadfence();
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(&head[1], 1u) == gridDim.x - 1 ? 1u : 0u;
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  constexpr int PER = 4;
+  uint32_t carry = 0;
+  for (int b0 = 0; b0 < nb; b0 += PER * blockDim.x) {
+    const int b = b0 + PER * threadIdx.x;
+    uint32_t v[PER], sum = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      v[i] = b + i < nb ? __hip_atomic_load(&cnt[b + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+      sum += v[i];
+    }
+    uint32_t total;
+    uint32_t off = carry + block_scan_u32(sum, s_scan, &total);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      if (b + i < nb) start[b + i] = off;
+      off += v[i];
+      if (v[i] > kAdjChunk) {
+        uint32_t* const w = big + 3 * atomicAdd(&head[2], 1u);
+        w[0] = (uint32_t)(b + i);
+        w[1] = atomicAdd(&head[3], (v[i] - 1) / kAdjChunk);
+        w[2] = 0u;
+      }
+    }
+    carry += total;
+  }
+  if (threadIdx.x == 0) start[nb] = carry;
+}
+
+// The weights of an element's pairs as S (off-diagonal pairs at half weight).  All
+// off-diagonal positions are searched for in lockstep, one step of every search per
+// iteration, so the loads of a step are in flight together (one search after the other
+// waited for about 100 loads in a row: 195 us for the 64^3 bricks).  A diagonal entry
+// is the last of its row.  Returns KB_F_INDEX if an entry is missing (its weight is 0).
+template <int NEN>
+__device__ __forceinline__ uint32_t pair_weights(const int32_t* __restrict__ row_ptr,
+                                                 const int32_t* __restrict__ col_idx, int64_t nnz,
+                                                 const double* __restrict__ w, const int32_t (&E)[NEN],
+                                                 double (&S)[ElemTraits<NEN>::T]) {
+  constexpr int NP = NEN * (NEN - 1) / 2;
+  uint32_t f = 0;
+  if (nnz == 0) {
+#pragma unroll
+    for (int p = 0; p < ElemTraits<NEN>::T; ++p) S[p] = 0.0;
+    return KB_F_INDEX;
+  }
+  // each row's entries [lo, lo + n); n = 0 for a range outside [0, nnz)
+  uint32_t lo[NEN], n[NEN], longest = 0;
+#pragma unroll
+  for (int a = 0; a < NEN; ++a) {
+    const int64_t l = row_ptr[E[a]], h = row_ptr[E[a] + 1];
+    const bool ok = l >= 0 && h <= nnz && l < h;
+    lo[a] = ok ? (uint32_t)l : 0u;
+    n[a] = ok ? (uint32_t)(h - l) : 0u;
+    longest = n[a] > longest ? n[a] : longest;
+  }
+  uint32_t at[NP], len[NP];
+  bool none[NP];
+#pragma unroll
+  for (int a = 1; a < NEN; ++a)
+#pragma unroll
+    for (int b = 0; b < a; ++b) {
+      const int p = a * (a - 1) / 2 + b;
+      const bool up = E[a] > E[b];
+      at[p] = up ? lo[a] : lo[b];
+      len[p] = up ? n[a] : n[b];
+      none[p] = len[p] == 0;
+    }
+  // the last entry at or before the column, from `len` candidates
+  for (uint32_t m = longest; m > 1; m -= m >> 1) {
+    int32_t c[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) c[p] = col_idx[at[p] + (len[p] >> 1)];
+#pragma unroll
+    for (int a = 1; a < NEN; ++a)
+#pragma unroll
+      for (int b = 0; b < a; ++b) {
+        const int p = a * (a - 1) / 2 + b;
+        const uint32_t half = len[p] >> 1;
+        at[p] += c[p] <= (E[a] > E[b] ? E[b] : E[a]) ? half : 0u;
+        len[p] -= half;
+      }
+  }
+#pragma unroll
+  for (int a = 1; a < NEN; ++a)
+#pragma unroll
+    for (int b = 0; b < a; ++b) {
+      const int p = a * (a - 1) / 2 + b;
+      const bool found = !none[p] && col_idx[at[p]] == (E[a] > E[b] ? E[b] : E[a]);
+      const double v = w[at[p]];
+      S[lidx(a, b)] = found ? 0.5 * v : 0.0;
+      f |= found ? 0u : KB_F_INDEX;
+    }
+#pragma unroll
+  for (int a = 0; a < NEN; ++a) {
+    int64_t k = (int64_t)lo[a] + n[a] - 1;
+    if (n[a] == 0)
+      k = -1;
+    else if (col_idx[k] != E[a])  // (a pattern with columns past the diagonal)
+      k = csr_position(row_ptr, col_idx, nnz, E[a], E[a]);
+    S[lidx(a, a)] = k < 0 ? 0.0 : w[k];
+    f |= k < 0 ? KB_F_INDEX : 0u;
+  }
+  return f;
+}
+
+// Per element (one per lane): dL/dc_e into grad_coef, the nen x 3 coordinate gradients as
+// records at their corners' places, the largest exponent of those into head[0].
 template <int NEN>
 __global__ __launch_bounds__(128) void k_adjoint_elems(const int32_t* __restrict__ conn,
                                                        const double* __restrict__ coords,
@@ -90,35 +285,39 @@ __global__ __launch_bounds__(128) void k_adjoint_elems(const int32_t* __restrict
                                                        int64_t n_node, const int32_t* __restrict__ row_ptr,
                                                        const int32_t* __restrict__ col_idx, int64_t nnz,
                                                        const double* __restrict__ w,
-                                                       double* __restrict__ grad_coef, double* __restrict__ gel,
-                                                       uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+                                                       double* __restrict__ grad_coef, int bits,
+                                                       const uint32_t* __restrict__ start,
+                                                       const uint32_t* __restrict__ rel,
+                                                       AdjointRecord* __restrict__ rec,
+                                                       unsigned long long* __restrict__ acc,
+                                                       uint32_t* __restrict__ head, const uint32_t* __restrict__ big,
+                                                       uint32_t* __restrict__ status) {
   constexpr int T = ElemTraits<NEN>::T;
   __shared__ uint32_t s_emax;
   if (threadIdx.x == 0) s_emax = 0;
   __syncthreads();
+  // the global sums (kAdjAcc words a node) of the buckets that several workgroups reduce
+  for (uint32_t i = 0; i < head[2]; ++i) {
+    const int64_t n0 = (int64_t)big[3 * i] << bits;
+    const int64_t n1 = n0 + ((int64_t)1 << bits) < n_node ? n0 + ((int64_t)1 << bits) : n_node;
+    for (int64_t j = kAdjAcc * n0 + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < kAdjAcc * n1;
+         j += (int64_t)gridDim.x * blockDim.x)
+      acc[j] = 0ull;
+  }
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   uint32_t em = 0;
   if (e < n_elem) {
     int32_t E[NEN];
     load_conn<NEN>(conn, e, E);
     uint32_t f = check_conn<NEN>(E, n_node);
+    const bool placed = f == 0;
     double D[NEN][3];
 #pragma unroll
     for (int a = 0; a < NEN; ++a) D[a][0] = D[a][1] = D[a][2] = 0.0;
     double gc = 0.0;
     if (!f) {
-      // S from the weights of the element's pairs (off-diagonal pairs at half weight)
       double S[T];
-#pragma unroll
-      for (int a = 0; a < NEN; ++a)
-#pragma unroll
-        for (int b = 0; b <= a; ++b) {
-          const int32_t row = E[a] > E[b] ? E[a] : E[b], col = E[a] > E[b] ? E[b] : E[a];
-          const int64_t k = csr_position(row_ptr, col_idx, nnz, row, col);
-          if (k < 0) f |= KB_F_INDEX;
-          const double v = k < 0 ? 0.0 : w[k];
-          S[lidx(a, b)] = a == b ? v : 0.5 * v;
-        }
+      f |= pair_weights<NEN>(row_ptr, col_idx, nnz, w, E, S);
       double X[NEN][3];
       double X0[3] = {coords[(int64_t)E[0] * 3], coords[(int64_t)E[0] * 3 + 1], coords[(int64_t)E[0] * 3 + 2]};
 #pragma unroll
@@ -186,91 +385,106 @@ __global__ __launch_bounds__(128) void k_adjoint_elems(const int32_t* __restrict
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         const double v = D[a][j];
-        gel[(e * NEN + a) * 3 + j] = v;
         const uint32_t ep = (uint32_t)biased_exponent(v);
         em = (ep > em && ep < 0x7FF) ? ep : em;
       }
+    if (placed) {
+#pragma unroll
+      for (int a = 0; a < NEN; ++a)
+        rec[start[E[a] >> bits] + rel[e * NEN + a]] =
+            AdjointRecord{{D[a][0], D[a][1], D[a][2]}, (uint64_t)(E[a] & ((1 << bits) - 1))};
+    }
   }
   if (em) atomicMax(&s_emax, em);
   __syncthreads();
-  if (threadIdx.x == 0 && s_emax) atomicMax(emax, s_emax);
+  if (threadIdx.x == 0 && s_emax) atomicMax(&head[0], s_emax);
 }
 
-// Per workgroup, kScatEntries consecutive (element, corner) entries: their coordinate
-// gradients are summed per node in an LDS hash table (the same exact chunks, LDS
-// atomics), then each distinct node's sums are added once to its global fixed-point
-// accumulators acc[node][j] = (low chunk sum, high chunk sum).  Elements numbered with
-// locality share most of their nodes within a workgroup, so the global atomics (the
-// cost of this step) fall several fold; integer sums keep the result independent of
-// the order either way.
-constexpr int kScatEntries = 512, kScatSlots = 1024;  // at most half the slots in use
-
-template <int NEN>
-__global__ __launch_bounds__(256) void k_adjoint_scatter(const int32_t* __restrict__ conn, int64_t n_elem,
-                                                         int64_t n_node, const double* __restrict__ gel,
-                                                         const uint32_t* __restrict__ emax,
-                                                         unsigned long long* __restrict__ acc) {
-  __shared__ int32_t s_node[kScatSlots];
-  __shared__ unsigned long long s_acc[kScatSlots][6];
-  const int F = 1117 - (int)*emax;
-  for (int h = threadIdx.x; h < kScatSlots; h += blockDim.x) {
-    s_node[h] = -1;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) s_acc[h][c] = 0ull;
-  }
-  __syncthreads();
-  const int64_t n = n_elem * NEN;
-  const int64_t t0 = (int64_t)blockIdx.x * kScatEntries;
-  for (int64_t t = t0 + threadIdx.x; t < t0 + kScatEntries && t < n; t += blockDim.x) {
-    const int32_t node = conn[t];
-    if (node < 0 || node >= n_node) continue;  // its element was flagged and contributes zeros
-    uint32_t h = ((uint32_t)node * 2654435769u) >> (32 - 10);  // kScatSlots = 2^10
-    while (true) {  // at most kScatEntries keys in kScatSlots slots: a free slot exists
-      const int32_t k = s_node[h];
-      if (k == node) break;
-      if (k == -1) {
-        const int32_t prev = atomicCAS(&s_node[h], -1, node);
-        if (prev == -1 || prev == node) break;
+// A bucket's records summed per node in LDS and its nodes' gradients written: workgroup b
+// takes bucket b (its first kAdjChunk records).  Further records of a larger bucket (a
+// node of very many elements) go to workgroups nb, nb + 1, ...; all of that bucket's
+// workgroups then add their sums to global ones, and the last to finish writes them.
+constexpr int kAdjThreads = 1024;
+constexpr unsigned long long kMask48 = (1ull << 48) - 1;
+static __global__ __launch_bounds__(kAdjThreads) void k_adjoint_reduce(
+    const AdjointRecord* __restrict__ rec, const uint32_t* __restrict__ start, int64_t n_node, int bits, int nb,
+    const uint32_t* __restrict__ head, uint32_t* big, unsigned long long* acc, double* __restrict__ grad_coords) {
+  extern __shared__ unsigned long long s_acc[];  // [6][1 << bits]: low and high chunk sums of x, y, z
+  __shared__ uint32_t s_last;
+  const int N = 1 << bits, F = 1117 - (int)head[0];
+  int b = blockIdx.x;
+  uint32_t* entry = nullptr;  // the bucket's entry in the list of large ones
+  uint32_t chunk = 0;
+  const uint32_t n_big = head[2];
+  if (b >= nb) {
+    const uint32_t x = (uint32_t)(b - nb);
+    if (x >= head[3]) return;
+    for (uint32_t i = 0; i < n_big; ++i) {
+      const uint32_t g = big[3 * i], f0 = big[3 * i + 1], extra = (start[g + 1] - start[g] - 1) / kAdjChunk;
+      if (x >= f0 && x < f0 + extra) {
+        b = (int)g;
+        chunk = 1 + x - f0;
+        entry = big + 3 * i;
       }
-      h = (h + 1) & (kScatSlots - 1);
     }
+  } else {
+    for (uint32_t i = 0; i < n_big; ++i)
+      if (big[3 * i] == (uint32_t)b) entry = big + 3 * i;
+  }
+  for (int h = threadIdx.x; h < 6 * N; h += kAdjThreads) s_acc[h] = 0ull;
+  __syncthreads();
+  const uint32_t i0 = start[b] + chunk * kAdjChunk, end = start[b + 1];
+  const uint32_t i1 = end - i0 > kAdjChunk ? i0 + kAdjChunk : end;
+  for (uint32_t i = i0 + threadIdx.x; i < i1; i += kAdjThreads) {
+    const AdjointRecord r = rec[i];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       uint64_t c0;
       int64_t c1;
-      to_chunks(gel[t * 3 + j], F, c0, c1);
-      if (c0) atomicAdd(&s_acc[h][2 * j], (unsigned long long)c0);
-      if (c1) atomicAdd(&s_acc[h][2 * j + 1], (unsigned long long)c1);
+      to_chunks(r.g[j], F, c0, c1);
+      if (c0) atomicAdd(&s_acc[2 * j * N + (int)r.node], (unsigned long long)c0);
+      if (c1) atomicAdd(&s_acc[(2 * j + 1) * N + (int)r.node], (unsigned long long)c1);
     }
   }
   __syncthreads();
-  for (int h = threadIdx.x; h < kScatSlots; h += blockDim.x) {
-    const int32_t node = s_node[h];
-    if (node < 0) continue;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      const unsigned long long v = s_acc[h][c];
-      if (v) atomicAdd(&acc[(int64_t)node * 6 + c], v);
+  const int64_t n0 = (int64_t)b << bits;
+  const int nn = n_node - n0 < N ? (int)(n_node - n0) : N;
+  if (entry) {
+    // each pair of chunk sums carried into three words, so any number of workgroups adds up
+    for (int h = threadIdx.x; h < 3 * nn; h += kAdjThreads) {
+      const int j = h / nn, i = h - j * nn;
+      const unsigned long long lo = s_acc[2 * j * N + i];
+      const long long hi = (long long)s_acc[(2 * j + 1) * N + i] + (long long)(lo >> 48);
+      unsigned long long* const q = acc + (n0 + i) * kAdjAcc + 3 * j;
+      if (lo & kMask48) atomicAdd(&q[0], lo & kMask48);
+      if (hi) {
+        atomicAdd(&q[1], (unsigned long long)hi & kMask48);
+        atomicAdd(&q[2], (unsigned long long)(hi >> 48));
+      }
     }
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(&entry[2], 1u) == (end - start[b] - 1) / kAdjChunk ? 1u : 0u;
+    __syncthreads();
+    if (!s_last) return;
+    __threadfence();
+    for (int h = threadIdx.x; h < 3 * nn; h += kAdjThreads) {
+      uint64_t q[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        q[k] = __hip_atomic_load(&acc[n0 * kAdjAcc + 3 * (int64_t)h + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      q[1] += q[0] >> 48;  // (low and high sums: below 2^48 times 2^15 workgroups)
+      q[2] += q[1] >> 48;
+      grad_coords[3 * n0 + h] = from_fixed((q[0] & kMask48) | q[1] << 48, (q[1] & kMask48) >> 16 | q[2] << 32, F);
+    }
+    return;
   }
-}
-
-// Per node coordinate: the exact sum converted once (correct rounding) to FP64.
-__global__ __launch_bounds__(256) void k_adjoint_nodes(const unsigned long long* __restrict__ acc, int64_t n,
-                                                       const uint32_t* __restrict__ emax,
-                                                       double* __restrict__ grad_coords) {
-  const int F = 1117 - (int)*emax;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+  for (int h = threadIdx.x; h < 3 * nn; h += kAdjThreads) {
+    const int i = h / 3, j = h - 3 * i;
     uint64_t lo, hi;
-    join48(acc[2 * i], (int64_t)acc[2 * i + 1], lo, hi);
-    grad_coords[i] = from_fixed(lo, hi, F);
+    join48(s_acc[2 * j * N + i], (int64_t)s_acc[(2 * j + 1) * N + i], lo, hi);
+    grad_coords[3 * n0 + h] = from_fixed(lo, hi, F);
   }
-}
-
-// zero fill of 64-bit words (a kernel, so the sequence stays capturable in a graph)
-__global__ void k_fill_u64(unsigned long long* __restrict__ p, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0ull;
 }
 
 }  // namespace kb

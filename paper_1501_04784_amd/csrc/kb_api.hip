@@ -348,6 +348,79 @@ int check_mesh_ptrs(const kb_mesh* m, bool need_geometry) {
 
 }  // namespace
 
+// adjoint workspace: corner records and places, node accumulators (large buckets only),
+// bucket counts and starts, head words, the list of large buckets
+namespace {
+struct AdjointPlan {
+  int bits = kAdjMinBits;  // nodes per bucket: 2^bits
+  int64_t nb = 0, extra = 0;  // buckets; workgroups beyond one a bucket at most
+  size_t o_rec = 0, o_rel = 0, o_acc = 0, o_cnt = 0, o_start = 0, o_head = 0, o_big = 0, total = 0;
+};
+
+int make_adjoint_plan(const kb_mesh* m, AdjointPlan* p) {
+  if (!m) return KB_EINVAL;
+  if (m->elem != KB_HEX8 && m->elem != KB_TET4) return KB_EINVAL;
+  if (m->n_elem < 0 || m->n_node < 0 || m->op != KB_OP_STIFFNESS) return KB_EINVAL;
+  if (m->n_node >= (int64_t)INT32_MAX || m->n_elem > (int64_t)INT32_MAX / m->elem) return KB_ERANGE;
+  while (p->bits < kAdjMaxBits && div_up(m->n_node, (int64_t)1 << p->bits) > kAdjBuckets) ++p->bits;
+  p->nb = div_up(m->n_node, (int64_t)1 << p->bits);
+  const size_t nc = (size_t)m->elem * (size_t)m->n_elem;
+  p->extra = (int64_t)(nc / kAdjChunk);
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    size_t o = off;
+    off = align_up(off + (bytes > 0 ? bytes : 1));
+    return o;
+  };
+  p->o_rec = take(sizeof(AdjointRecord) * nc);
+  p->o_rel = take(4 * nc);
+  p->o_acc = take(p->extra ? 8 * kAdjAcc * (size_t)m->n_node : 0);
+  p->o_cnt = take(4 * (size_t)p->nb);
+  p->o_start = take(4 * ((size_t)p->nb + 1));
+  p->o_head = take(16);
+  p->o_big = take(12 * (size_t)p->extra);
+  p->total = off;
+  return KB_OK;
+}
+
+template <int NEN>
+int launch_adjoint(const AdjointPlan& p, const kb_mesh* m, const int32_t* row_ptr, const int32_t* col_idx,
+                   const double* w, int64_t nnz, unsigned char* ws, double* grad_coef, double* grad_coords,
+                   uint32_t* status, hipStream_t s) {
+  auto* rec = (AdjointRecord*)(ws + p.o_rec);
+  auto* rel = (uint32_t*)(ws + p.o_rel);
+  auto* acc = (unsigned long long*)(ws + p.o_acc);
+  auto* cnt = (uint32_t*)(ws + p.o_cnt);
+  auto* start = (uint32_t*)(ws + p.o_start);
+  auto* head = (uint32_t*)(ws + p.o_head);
+  auto* big = (uint32_t*)(ws + p.o_big);
+  const int64_t nel = m->n_elem, nn = m->n_node;
+  const int nb = (int)p.nb;
+  k_adjoint_begin<<<(unsigned)std::max<int64_t>(1, std::min<int64_t>(div_up(p.nb, 256), 1024)), 256, 0, s>>>(
+      status, head, cnt, p.nb);
+  KB_LAUNCH_CHECK();
+  // (also without elements or nodes: the bucket starts, the flags)
+  const size_t slots = 4 * (size_t)(nb <= kAdjArray ? std::max(nb, 1) : 2 * kSlotsHash);
+  k_adjoint_count<NEN><<<(unsigned)std::max<int64_t>(1, div_up(nel, 256 * kAdjPer)), 256, slots, s>>>(
+      m->conn, nel, nn, p.bits, nb, cnt, start, rel, head, big);
+  KB_LAUNCH_CHECK();
+  if (nel > 0) {
+    k_adjoint_elems<NEN><<<grid_for(nel, 128), 128, 0, s>>>(m->conn, m->coords, m->coef, nel, nn, row_ptr, col_idx,
+                                                            nnz, w, grad_coef, p.bits, start, rel, rec, acc, head,
+                                                            big, status);
+    KB_LAUNCH_CHECK();
+  }
+  if (nn > 0) {
+    const size_t lds = (size_t)48 << p.bits;
+    if (!set_lds(k_adjoint_reduce, lds)) return KB_EHIP;
+    k_adjoint_reduce<<<(unsigned)(p.nb + p.extra), kAdjThreads, lds, s>>>(rec, start, nn, p.bits, nb, head, big, acc,
+                                                                          grad_coords);
+    KB_LAUNCH_CHECK();
+  }
+  return KB_OK;
+}
+}  // namespace
+
 // Fixed scratch of kb_build_lower_csr_noalloc: one copy per device, resident until the
 // process ends.  Host code never uses the array's name as an address: the device address
 // is looked up once per device (hipGetSymbolAddress) and kept in scratch_ptr.
@@ -661,79 +734,27 @@ int kb_build_lower_csr_batched(const kb_batch* batch, int prec, const kb_tuning*
   return KB_OK;
 }
 
-// adjoint workspace: element gradients, node accumulators, one exponent word
-static int adjoint_layout(const kb_mesh* m, size_t* gel, size_t* acc, size_t* emax, size_t* total) {
-  if (!m) return KB_EINVAL;
-  if (m->elem != KB_HEX8 && m->elem != KB_TET4) return KB_EINVAL;
-  if (m->n_elem < 0 || m->n_node < 0 || m->op != KB_OP_STIFFNESS) return KB_EINVAL;
-  if (m->n_node >= (int64_t)INT32_MAX || m->n_elem > (int64_t)INT32_MAX / m->elem) return KB_ERANGE;
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    size_t o = off;
-    off = align_up(off + (bytes > 0 ? bytes : 1));
-    return o;
-  };
-  *gel = take(8 * 3 * (size_t)m->elem * (size_t)m->n_elem);
-  *acc = take(16 * 3 * (size_t)m->n_node);
-  *emax = take(4);
-  *total = off;
-  return KB_OK;
-}
-
 int kb_plan_adjoint(const kb_mesh* mesh, size_t* ws_bytes) {
-  size_t a, b, c, t;
-  KB_TRY(adjoint_layout(mesh, &a, &b, &c, &t));
-  if (ws_bytes) *ws_bytes = t;
+  AdjointPlan p;
+  KB_TRY(make_adjoint_plan(mesh, &p));
+  if (ws_bytes) *ws_bytes = p.total;
   return KB_OK;
 }
 
 int kb_adjoint_lower(const kb_mesh* mesh, const int32_t* row_ptr, const int32_t* col_idx, const double* w,
                      int64_t nnz, void* ws, size_t ws_bytes, double* grad_coef, double* grad_coords,
                      uint32_t* status_dev, void* stream) {
-  size_t o_gel, o_acc, o_emax, total;
-  KB_TRY(adjoint_layout(mesh, &o_gel, &o_acc, &o_emax, &total));
+  AdjointPlan p;
+  KB_TRY(make_adjoint_plan(mesh, &p));
   KB_TRY(check_mesh_ptrs(mesh, true));
   if (!status_dev || !ws) return KB_EINVAL;
-  if (ws_bytes < total) return KB_ENOSPC;
+  if (ws_bytes < p.total) return KB_ENOSPC;
   if (nnz < 0 || nnz >= (int64_t)INT32_MAX) return nnz < 0 ? KB_EINVAL : KB_ERANGE;
   if (mesh->n_elem > 0 && (!row_ptr || !grad_coef || (nnz > 0 && (!col_idx || !w)))) return KB_EINVAL;
   if (mesh->n_node > 0 && !grad_coords) return KB_EINVAL;
-  auto s = (hipStream_t)stream;
-  auto* wsb = (unsigned char*)ws;
-  auto* gel = (double*)(wsb + o_gel);
-  auto* acc = (unsigned long long*)(wsb + o_acc);
-  auto* emax = (uint32_t*)(wsb + o_emax);
-  const int64_t nel = mesh->n_elem, nn = mesh->n_node, nen = mesh->elem;
-  k_init_status<<<1, 64, 0, s>>>(status_dev, nullptr);
-  KB_LAUNCH_CHECK();
-  k_fill_i32<<<1, 64, 0, s>>>((int32_t*)emax, 1, 0);
-  KB_LAUNCH_CHECK();
-  if (nn > 0) {
-    k_fill_u64<<<(unsigned)std::min<int64_t>(div_up(6 * nn, 256), 65536), 256, 0, s>>>(acc, 6 * nn);
-    KB_LAUNCH_CHECK();
-  }
-  if (nel > 0) {
-    const unsigned ge = grid_for(nel, 128);
-    if (nen == 8)
-      k_adjoint_elems<8><<<ge, 128, 0, s>>>(mesh->conn, mesh->coords, mesh->coef, nel, nn, row_ptr, col_idx, nnz,
-                                            w, grad_coef, gel, emax, status_dev);
-    else
-      k_adjoint_elems<4><<<ge, 128, 0, s>>>(mesh->conn, mesh->coords, mesh->coef, nel, nn, row_ptr, col_idx, nnz,
-                                            w, grad_coef, gel, emax, status_dev);
-    KB_LAUNCH_CHECK();
-    const unsigned gs = (unsigned)div_up(nel * nen, kScatEntries);
-    if (nen == 8)
-      k_adjoint_scatter<8><<<gs, 256, 0, s>>>(mesh->conn, nel, nn, gel, emax, acc);
-    else
-      k_adjoint_scatter<4><<<gs, 256, 0, s>>>(mesh->conn, nel, nn, gel, emax, acc);
-    KB_LAUNCH_CHECK();
-  }
-  if (nn > 0) {
-    k_adjoint_nodes<<<(unsigned)std::min<int64_t>(div_up(3 * nn, 256), 65536), 256, 0, s>>>(acc, 3 * nn, emax,
-                                                                                            grad_coords);
-    KB_LAUNCH_CHECK();
-  }
-  return KB_OK;
+  auto* launch = mesh->elem == 8 ? launch_adjoint<8> : launch_adjoint<4>;
+  return launch(p, mesh, row_ptr, col_idx, w, nnz, (unsigned char*)ws, grad_coef, grad_coords, status_dev,
+                (hipStream_t)stream);
 }
 
 int kb_integrate_lower(const kb_mesh* mesh, int prec, const kb_tuning* tuning, void* vals, uint32_t* status_dev,
