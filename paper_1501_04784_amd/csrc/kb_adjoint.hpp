@@ -54,8 +54,8 @@ __device__ __forceinline__ int64_t csr_position(const int32_t* __restrict__ row_
 
 // one integration point: P = G S G^T from G (3 x NEN) and the lower triangle of S;
 // adds w tr(P) / det to *gc and c w / det^2 (tr(P) G_a - 2 P G_a) to D[a]
-template <int NEN>
-__device__ __forceinline__ void adjoint_point(const double (&G)[3][NEN], const double (&S)[ElemTraits<NEN>::T],
+template <int NEN, typename SMat>
+__device__ __forceinline__ void adjoint_point(const double (&G)[3][NEN], const SMat& S,
                                               double det, double w, double c, double* gc, double (&D)[NEN][3]) {
   // T = S G^T (NEN x 3), then P = G T (3 x 3)
   double P[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
@@ -95,6 +95,8 @@ constexpr int kAdjPer = 4;                // elements per lane of k_adjoint_coun
 constexpr uint32_t kAdjChunk = kRound;    // records per workgroup of k_adjoint_reduce at most (sums inside 64 bits)
 
 constexpr int kAdjAcc = 9;                // global words per node: low, high and top sums of x, y, z
+
+constexpr int kAdjElemThreads = 128;
 
 struct AdjointRecord {
   double g[3];
@@ -165,12 +167,10 @@ __global__ __launch_bounds__(256) void k_adjoint_count(const int32_t* __restrict
   }
   // bucket starts, and the buckets that need several workgroups
   __shared__ uint32_t s_scan[8], s_last;
-  __threadfence();
-  __syncthreads();
+  __syncthreads();  // (the additions to cnt have returned their results)
   if (threadIdx.x == 0) s_last = atomicAdd(&head[1], 1u) == gridDim.x - 1 ? 1u : 0u;
   __syncthreads();
   if (!s_last) return;
-  __threadfence();
   constexpr int PER = 4;
   uint32_t carry = 0;
   for (int b0 = 0; b0 < nb; b0 += PER * blockDim.x) {
@@ -204,11 +204,11 @@ __global__ __launch_bounds__(256) void k_adjoint_count(const int32_t* __restrict
 // iteration, so the loads of a step are in flight together (one search after the other
 // waited for about 100 loads in a row: 195 us for the 64^3 bricks).  A diagonal entry
 // is the last of its row.  Returns KB_F_INDEX if an entry is missing (its weight is 0).
-template <int NEN>
+template <int NEN, typename SMat>
 __device__ __forceinline__ uint32_t pair_weights(const int32_t* __restrict__ row_ptr,
                                                  const int32_t* __restrict__ col_idx, int64_t nnz,
                                                  const double* __restrict__ w, const int32_t (&E)[NEN],
-                                                 double (&S)[ElemTraits<NEN>::T]) {
+                                                 SMat& S) {
   constexpr int NP = NEN * (NEN - 1) / 2;
   uint32_t f = 0;
   if (nnz == 0) {
@@ -279,7 +279,7 @@ __device__ __forceinline__ uint32_t pair_weights(const int32_t* __restrict__ row
 // Per element (one per lane): dL/dc_e into grad_coef, the nen x 3 coordinate gradients as
 // records at their corners' places, the largest exponent of those into head[0].
 template <int NEN>
-__global__ __launch_bounds__(128) void k_adjoint_elems(const int32_t* __restrict__ conn,
+__global__ __launch_bounds__(kAdjElemThreads) void k_adjoint_elems(const int32_t* __restrict__ conn,
                                                        const double* __restrict__ coords,
                                                        const double* __restrict__ coef, int64_t n_elem,
                                                        int64_t n_node, const int32_t* __restrict__ row_ptr,
@@ -292,7 +292,6 @@ __global__ __launch_bounds__(128) void k_adjoint_elems(const int32_t* __restrict
                                                        unsigned long long* __restrict__ acc,
                                                        uint32_t* __restrict__ head, const uint32_t* __restrict__ big,
                                                        uint32_t* __restrict__ status) {
-  constexpr int T = ElemTraits<NEN>::T;
   __shared__ uint32_t s_emax;
   if (threadIdx.x == 0) s_emax = 0;
   __syncthreads();
@@ -316,7 +315,7 @@ __global__ __launch_bounds__(128) void k_adjoint_elems(const int32_t* __restrict
     for (int a = 0; a < NEN; ++a) D[a][0] = D[a][1] = D[a][2] = 0.0;
     double gc = 0.0;
     if (!f) {
-      double S[T];
+      double S[ElemTraits<NEN>::T];
       f |= pair_weights<NEN>(row_ptr, col_idx, nnz, w, E, S);
       double X[NEN][3];
       double X0[3] = {coords[(int64_t)E[0] * 3], coords[(int64_t)E[0] * 3 + 1], coords[(int64_t)E[0] * 3 + 2]};

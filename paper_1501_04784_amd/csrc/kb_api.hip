@@ -405,7 +405,7 @@ int launch_adjoint(const AdjointPlan& p, const kb_mesh* m, const int32_t* row_pt
       m->conn, nel, nn, p.bits, nb, cnt, start, rel, head, big);
   KB_LAUNCH_CHECK();
   if (nel > 0) {
-    k_adjoint_elems<NEN><<<grid_for(nel, 128), 128, 0, s>>>(m->conn, m->coords, m->coef, nel, nn, row_ptr, col_idx,
+    k_adjoint_elems<NEN><<<grid_for(nel, kAdjElemThreads), kAdjElemThreads, 0, s>>>(m->conn, m->coords, m->coef, nel, nn, row_ptr, col_idx,
                                                             nnz, w, grad_coef, p.bits, start, rel, rec, acc, head,
                                                             big, status);
     KB_LAUNCH_CHECK();

@@ -95,12 +95,13 @@ __device__ __forceinline__ uint32_t block_scan_array(T* a, int n, uint32_t* smem
 __device__ __forceinline__ void last_block_starts(uint32_t* cnt, int n, uint32_t* starts, uint32_t* done,
                                                   uint32_t blocks) {
   __shared__ uint32_t s_scan[8], s_last;
-  __threadfence();  // this thread's additions before the arrival
+  // this thread's additions done before the arrival (atomics on both sides: nothing else
+  // passes between the workgroups, so the L2 need not be written back by a fence)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) s_last = atomicAdd(done, 1u) == blocks - 1 ? 1u : 0u;
   __syncthreads();
   if (!s_last) return;
-  __threadfence();
   uint32_t carry = 0;
   for (int b0 = 0; b0 < n; b0 += blockDim.x) {
     const int b = b0 + threadIdx.x;
