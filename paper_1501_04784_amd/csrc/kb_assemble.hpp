@@ -679,25 +679,42 @@ struct Pass1Smem {
   }
 };
 
-// stage the pairs of local rows R0 .. R0+N-1: the r+1 pairs of row E[a] go contiguously
+// the packed lower triangle k as the values of pass1_stage
+template <typename V, int T>
+struct PackedValues {
+  const V (&k)[T];
+  __device__ __forceinline__ V operator()(int, int row, int b) const {
+    return row >= b ? k[lidx(row, b)] : k[lidx(b, row)];
+  }
+};
+
+// stage the pairs of local rows R0 .. R0+N-1 (values k(a, row, b) for row = R0 + a): the r+1 pairs of row E[a] go contiguously
 // into its slot's run (a row without a slot takes its places at once)
-template <int N, int R0, int NEN, typename V, int BLOCK, bool DIRECT>
+template <int N, int R0, int NEN, typename V, int BLOCK, bool DIRECT, typename Values>
 __device__ __forceinline__ void pass1_stage(const Pass1Smem<V, BLOCK, DIRECT>& sm, const PairOut<V>& o, const int32_t (&E)[NEN],
-                                            const uint32_t (&q)[N], const V (&k)[ElemTraits<NEN>::T]) {
+                                            const uint32_t (&q)[N], const Values& k) {
 #pragma unroll
   for (int a = 0; a < N; ++a) {
     const int row = R0 + a;
+    // (compared again here: kept from the ranks, the results of all rows' comparisons
+    // overflow the scalar registers)
+    int32_t F[NEN];
+#pragma unroll
+    for (int b = 0; b < NEN; ++b) {
+      F[b] = E[b];
+      asm volatile("" : "+v"(F[b]));
+    }
     const uint32_t rl = DIRECT ? ((uint32_t)E[row] & ((1u << o.s2) - 1)) << o.colbits : 0u;
     if (DIRECT && q[a] == kNoSlot) {
       uint32_t n = 0;
 #pragma unroll
-      for (int b = 0; b < NEN; ++b) n += E[b] <= E[row] ? 1u : 0u;
+      for (int b = 0; b < NEN; ++b) n += F[b] <= F[row] ? 1u : 0u;
       uint32_t g = atomicAdd(&o.cursor[E[row] >> o.s2], n);
 #pragma unroll
       for (int b = 0; b < NEN; ++b) {
-        if (E[b] <= E[row]) {
-          o.key2[g] = rl | (uint32_t)E[b];
-          o.val2[g] = row >= b ? k[lidx(row, b)] : k[lidx(b, row)];
+        if (F[b] <= F[row]) {
+          o.key2[g] = rl | (uint32_t)F[b];
+          o.val2[g] = k(a, row, b);
           ++g;
         }
       }
@@ -708,9 +725,9 @@ __device__ __forceinline__ void pass1_stage(const Pass1Smem<V, BLOCK, DIRECT>& s
     const uint64_t rk = (uint64_t)(DIRECT ? slot : (uint32_t)E[row]) << 32 | rl;
 #pragma unroll
     for (int b = 0; b < NEN; ++b) {
-      if (E[b] <= E[row]) {
-        sm.key[pos] = rk | (uint32_t)E[b];
-        sm.val[pos] = row >= b ? k[lidx(row, b)] : k[lidx(b, row)];
+      if (F[b] <= F[row]) {
+        sm.key[pos] = rk | (uint32_t)F[b];
+        sm.val[pos] = k(a, row, b);
         ++pos;
       }
     }
@@ -743,16 +760,27 @@ __device__ __forceinline__ void pass1_write(const Pass1Smem<V, BLOCK, DIRECT>& s
   }
 }
 
-// largest finite biased exponent of an element's values
+// largest finite biased exponent (as doubles) of an element's values: that of the largest
+// finite magnitude, compared as bits
 template <int T, typename V>
 __device__ __forceinline__ uint32_t values_emax(const V (&k)[T]) {
-  uint32_t m = 0;
+  if constexpr (sizeof(V) == 4) {
+    uint32_t m = 0;
 #pragma unroll
-  for (int p = 0; p < T; ++p) {
-    const uint32_t ep = (uint32_t)biased_exponent((double)k[p]);
-    m = (ep > m && ep < 0x7FF) ? ep : m;
+    for (int p = 0; p < T; ++p) {
+      const uint32_t b = __float_as_uint(k[p]) & 0x7FFFFFFFu;
+      m = (b > m && b < 0x7F800000u) ? b : m;
+    }
+    return (uint32_t)biased_exponent((double)__uint_as_float(m));
+  } else {
+    uint32_t m = 0;
+#pragma unroll
+    for (int p = 0; p < T; ++p) {
+      const uint32_t ep = (uint32_t)biased_exponent((double)k[p]);
+      m = (ep > m && ep < 0x7FF) ? ep : m;
+    }
+    return m;
   }
-  return m;
 }
 
 // element values from given per-element lower triangles (assembly-only path)
@@ -811,7 +839,7 @@ __device__ __forceinline__ void pass1_tile(unsigned char* smem, const int32_t (&
     else
       element_values_at<NEN, P, OP>(Xn, c_e, tau, k, &flags, &fb);
     atomicMax(sm.emax, values_emax<T>(k));
-    pass1_stage<NEN, 0>(sm, o, E, q, k);
+    pass1_stage<NEN, 0>(sm, o, E, q, PackedValues<V, T>{k});
   }
   if (flags) raise_flag(status, flags);
   if (fb) atomicAdd(&status[1], fb);
@@ -885,7 +913,7 @@ __device__ __forceinline__ void pass1_two(unsigned char* smem, const int32_t (&E
       element_values_at<NEN, P, OP>(Xn, c_e, tau, k, &flags, &fb);
       atomicMax(sm.emax, values_emax<T>(k));
     }
-    if (mine) pass1_stage<NEN, 0>(sm, o, E, q, k);
+    if (mine) pass1_stage<NEN, 0>(sm, o, E, q, PackedValues<V, T>{k});
     sm.put_bases(gb);
     __syncthreads();
     pass1_write(sm, o, n_items);
@@ -970,13 +998,14 @@ __device__ __forceinline__ void pass1_pair(unsigned char* smem, const int32_t (&
   sm.take_bases(o, n_items, gb);
   uint32_t flags = 0, fb = 0;
   if (valid) {
-    V k[T];
+    V k[4][8];
     element_values_pair<P>(xo, c_e, tau, h, k, &flags, &fb);
-    atomicMax(sm.emax, values_emax<T>(k));
+    const auto row_values = [&](int a, int, int b) { return k[a][b]; };
+    atomicMax(sm.emax, values_emax<32>((const V(&)[32])k));
     if (h)
-      pass1_stage<4, 4>(sm, o, E, q, k);
+      pass1_stage<4, 4>(sm, o, E, q, row_values);
     else
-      pass1_stage<4, 0>(sm, o, E, q, k);
+      pass1_stage<4, 0>(sm, o, E, q, row_values);
   }
   if (flags) raise_flag(status, flags);
   if (fb) atomicAdd(&status[1], fb);
@@ -1069,7 +1098,7 @@ __device__ __forceinline__ void pass1_tet(unsigned char* smem, const int32_t* __
         element_values_at<NEN, P, OP>(Xn, c_e, tau, k, &flags, &fb);
       const uint32_t me = values_emax<T>(k);
       em = me > em ? me : em;
-      pass1_stage<NEN, 0>(sm, o, E, q, k);
+      pass1_stage<NEN, 0>(sm, o, E, q, PackedValues<V, T>{k});
     }
     if (flags) raise_flag(status, flags);
     if (fb) atomicAdd(&status[1], fb);

@@ -269,7 +269,7 @@ __device__ __forceinline__ void element_values_at(const double (&Xn)[NEN][3], do
 #pragma unroll
   for (int p = 0; p < T; ++p) {
     k[p] = (V)(c * (double)k[p]);
-    finite = finite && isfinite((double)k[p]);
+    finite = finite && isfinite(k[p]);
   }
   if (!ok) *f |= KB_F_INVERTED;
   if (!finite) *f |= KB_F_NONFINITE;
@@ -352,58 +352,60 @@ __device__ __forceinline__ void gather_pair(const NodesPadded& nodes, const int3
 }
 
 // A brick of coefficient c integrated by a lane pair (lanes 2i and 2i+1; h = lane & 1)
-// from the nodes gather_pair brought: the coordinates relative to node 0 are exchanged by
-// shuffles, each lane integrates the four points of its half of the rule and the two
-// halves of k are added.  Both lanes of a pair must be active together; both end with the
-// same k and flags (the fallback is counted once, by h = 0).
+// from the nodes gather_pair brought: each lane forms its face's part of the mode
+// coefficients from the coordinates relative to node 0, in FP64; the parts are exchanged,
+// and each lane integrates the four points of its half of the rule.  Lane h ends with
+// rows 4h .. 4h+3, k[a][b] = k_(4h+a, b).  Both lanes of a pair must be active together.
+// A half with an ill-conditioned point takes the FP64 geometry (counted for h = 0).
 template <Prec P>
 __device__ __forceinline__ void element_values_pair(const double (&xo)[4][3], double c, float tau, int h,
-                                                    typename PrecTraits<P>::V (&k)[36], uint32_t* f, uint32_t* fb) {
+                                                    typename PrecTraits<P>::V (&k)[4][8], uint32_t* f, uint32_t* fb) {
   using V = typename PrecTraits<P>::V;
-  double X0[3];
+  const double sg = h ? 1.0 : -1.0;
+  double Cd[kModes][3];
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
-    const double other = __shfl_xor(xo[0][j], 1, 64);
-    X0[j] = h ? other : xo[0][j];
+    const double other = pair_other(xo[0][j]), x0 = h ? other : xo[0][j];
+    double own[4], o[4];
+    half_modes(xo[0][j] - x0, xo[1][j] - x0, xo[2][j] - x0, xo[3][j] - x0, own);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = pair_other(own[i]);
+    Cd[0][j] = own[1] + o[1];
+    Cd[1][j] = own[2] + o[2];
+    Cd[2][j] = sg * (own[0] - o[0]);  // (t = +1) - (t = -1)
+    Cd[3][j] = own[3] + o[3];
+    Cd[4][j] = sg * (own[2] - o[2]);
+    Cd[5][j] = sg * (own[1] - o[1]);
+    Cd[6][j] = sg * (own[3] - o[3]);
   }
-  double Xd[8][3];  // all eight nodes relative to node 0: own half and the partner's
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const double mine = xo[a][j] - X0[j];
-      const double other = __shfl_xor(mine, 1, 64);
-      Xd[a][j] = h ? other : mine;
-      Xd[4 + a][j] = h ? mine : other;
-    }
   bool ok;
+  V M[4][6];
   if constexpr (P == Prec::F64) {
-    ok = hex_integrate_half<double, double, false>(Xd, k, 0.0, nullptr, h);
+    ok = half_points<double, double, false>(Cd, M, 0.0, nullptr, h);
   } else {
-    float X[8][3];
+    float C[kModes][3];
 #pragma unroll
-    for (int a = 0; a < 8; ++a)
+    for (int m = 0; m < kModes; ++m)
 #pragma unroll
-      for (int j = 0; j < 3; ++j) X[a][j] = (float)Xd[a][j];
+      for (int j = 0; j < 3; ++j) C[m][j] = (float)Cd[m][j];
     bool need_fb = false;
-    ok = hex_integrate_half<float, float, P == Prec::F32FB>(X, k, tau, &need_fb, h);
+    ok = half_points<float, float, P == Prec::F32FB>(C, M, tau, &need_fb, h);
     if constexpr (P == Prec::F32FB) {
-      need_fb = need_fb || (__shfl_xor((int)need_fb, 1, 64) != 0);
-      if (need_fb) {  // the whole element, both halves, with FP64 geometry
-        ok = hex_integrate_half<double, float, false>(Xd, k, 0.0, nullptr, h);
+      if (need_fb) {  // this half's points with FP64 geometry
+        ok = half_points<double, float, false>(Cd, M, 0.0, nullptr, h);
         if (h == 0) *fb += 1;
       }
     }
   }
-#pragma unroll
-  for (int p = 0; p < 36; ++p) k[p] += __shfl_xor(k[p], 1, 64);
-  ok = ok && (__shfl_xor((int)ok, 1, 64) != 0);
+  half_matrix<V>(M, k, h);
   bool finite = true;
 #pragma unroll
-  for (int p = 0; p < 36; ++p) {
-    k[p] = (V)(c * (double)k[p]);
-    finite = finite && isfinite((double)k[p]);
-  }
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      k[a][b] = (V)(c * (double)k[a][b]);
+      finite = finite && isfinite(k[a][b]);
+    }
   if (!ok) *f |= KB_F_INVERTED;
   if (!finite) *f |= KB_F_NONFINITE;
 }
