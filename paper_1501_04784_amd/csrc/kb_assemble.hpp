@@ -956,79 +956,118 @@ __device__ __forceinline__ void pair_reserve_half(const TileSlots<DIRECT>& sl, c
   }
 }
 
+// The tiles of a persistent workgroup: XCD x owns one contiguous range of the tiles and its
+// workgroups walk it interleaved, so neighbouring runs meet in one L2.
+struct TileWalk {
+  int64_t t, hi, step;
+  __device__ __forceinline__ explicit TileWalk(int64_t ntiles) {
+    const int64_t G = gridDim.x, x = blockIdx.x % kXcds, w = blockIdx.x / kXcds;
+    step = G / kXcds + (x < G % kXcds ? 1 : 0);
+    const int64_t lo = x * (ntiles / kXcds) + min(x, ntiles % kXcds);
+    hi = lo + ntiles / kXcds + (x < ntiles % kXcds ? 1 : 0);
+    t = lo + w;
+  }
+};
+
 // Bricks, stiffness matrix: a lane pair per element (element_values_pair), BLOCK lanes
 // and BLOCK / 2 elements per tile.  Twice the waves of one lane per element for the same
 // staging LDS, and half the quadrature per lane; lane h counts and stages the pairs of
-// rows 4h .. 4h+3.
+// rows 4h .. 4h+3.  Persistent: the staging LDS leaves two workgroups per CU, so the next
+// tile's connectivity is loaded while the current one is integrated and its nodes are
+// gathered while the current one is written.
 template <Prec P, int BLOCK, bool DIRECT>
-__device__ __forceinline__ void pass1_pair(unsigned char* smem, const int32_t (&E)[8], const double4* __restrict__ coords4,
-    const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau,
-    const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
+__device__ __forceinline__ void pass1_pair(unsigned char* smem, const int32_t* __restrict__ conn,
+    const double4* __restrict__ coords4, const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau,
+    int64_t ntiles, const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
     uint32_t* __restrict__ status) {
   using V = typename PrecTraits<P>::V;
   using SM = Pass1Smem<V, BLOCK, DIRECT>;
   constexpr int NEN = 8, T = ElemTraits<NEN>::T, TE = BLOCK / 2;
   const SM sm(smem, TE * T, o);
-  const int64_t t = xcd_item(blockIdx.x, gridDim.x);
+  TileWalk walk(ntiles);
+  if (walk.t >= walk.hi) return;
   const int h = (int)(threadIdx.x & 1);
-  const int64_t e = t * TE + (threadIdx.x >> 1);
-  sm.begin(o, t);
   if (threadIdx.x == 0) *sm.emax = 0;
-  const bool valid = e < n_elem && check_conn<NEN>(E, n_node) == 0;
+  const auto fetch = [&](int64_t t, int32_t (&E)[NEN]) {
+    const int64_t e = t * TE + (threadIdx.x >> 1);
+    if (t >= walk.hi || e >= n_elem) return false;
+    load_conn<NEN>(conn, e, E);
+    return check_conn<NEN>(E, n_node) == 0;
+  };
+  int32_t E[NEN];
+  bool valid = fetch(walk.t, E);
   double xo[4][3];
   double c_e = 0.0;
   if (valid) {
     gather_pair(NodesPadded{coords4}, E, h, xo);
-    c_e = coef[e];
+    c_e = coef[walk.t * TE + (threadIdx.x >> 1)];
   }
-  __syncthreads();
-  // (a branch per half keeps every index into E and r a constant)
-  uint32_t q[4];
-  if (valid) {
-    int r[NEN];
-    node_ranks<NEN>(E, r);
-    if (h)
-      pair_reserve_half<4>(sm.sl, E, r, q);
-    else
-      pair_reserve_half<0>(sm.sl, E, r, q);
+  uint32_t em = 0;  // largest value exponent seen by this lane
+  while (true) {
+    sm.begin(o, walk.t);
+    __syncthreads();
+    // (a branch per half keeps every index into E and r a constant)
+    uint32_t q[4];
+    if (valid) {
+      int r[NEN];
+      node_ranks<NEN>(E, r);
+      if (h)
+        pair_reserve_half<4>(sm.sl, E, r, q);
+      else
+        pair_reserve_half<0>(sm.sl, E, r, q);
+    }
+    __syncthreads();
+    const uint32_t n_items = block_scan_array(sm.sl.cnt, sm.sl.n, sm.scan);
+    uint32_t gb[SM::kPerLane];
+    sm.take_bases(o, n_items, gb);
+    const int64_t tn = walk.t + walk.step;
+    int32_t En[NEN];
+    const bool vn = fetch(tn, En);
+    uint32_t flags = 0, fb = 0;
+    if (valid) {
+      V k[4][8];
+      element_values_pair<P>(xo, c_e, tau, h, k, &flags, &fb);
+      const auto row_values = [&](int a, int, int b) { return k[a][b]; };
+      const uint32_t me = values_emax<32>((const V(&)[32])k);
+      em = me > em ? me : em;
+      if (h)
+        pass1_stage<4, 4>(sm, o, E, q, row_values);
+      else
+        pass1_stage<4, 0>(sm, o, E, q, row_values);
+    }
+    if (flags) raise_flag(status, flags);
+    if (fb) atomicAdd(&status[1], fb);
+    sm.put_bases(gb);
+#pragma unroll
+    for (int a = 0; a < NEN; ++a) E[a] = En[a];
+    valid = vn;
+    if (valid) {
+      gather_pair(NodesPadded{coords4}, E, h, xo);
+      c_e = coef[tn * TE + (threadIdx.x >> 1)];
+    }
+    __syncthreads();
+    pass1_write(sm, o, n_items);
+    walk.t = tn;
+    if (tn >= walk.hi) break;
+    __syncthreads();
   }
-  __syncthreads();
-  const uint32_t n_items = block_scan_array(sm.sl.cnt, sm.sl.n, sm.scan);
-  uint32_t gb[SM::kPerLane];
-  sm.take_bases(o, n_items, gb);
-  uint32_t flags = 0, fb = 0;
-  if (valid) {
-    V k[4][8];
-    element_values_pair<P>(xo, c_e, tau, h, k, &flags, &fb);
-    const auto row_values = [&](int a, int, int b) { return k[a][b]; };
-    atomicMax(sm.emax, values_emax<32>((const V(&)[32])k));
-    if (h)
-      pass1_stage<4, 4>(sm, o, E, q, row_values);
-    else
-      pass1_stage<4, 0>(sm, o, E, q, row_values);
-  }
-  if (flags) raise_flag(status, flags);
-  if (fb) atomicAdd(&status[1], fb);
-  sm.put_bases(gb);
+  if (em) atomicMax(sm.emax, em);
   __syncthreads();
   if (threadIdx.x == 0 && *sm.emax) atomicMax(emax, *sm.emax);
-  pass1_write(sm, o, n_items);
 }
 
 template <Prec P, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_pass1_pair(const int32_t* __restrict__ conn,
                                                     const double4* __restrict__ coords4,
                                                     const double* __restrict__ coef, int64_t n_elem, int64_t n_node,
-                                                    float tau, const PairOut<typename PrecTraits<P>::V> o,
+                                                    float tau, int64_t ntiles,
+                                                    const PairOut<typename PrecTraits<P>::V> o,
                                                     uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char smem[];
-  int32_t E[8] = {};
-  const int64_t e = xcd_item(blockIdx.x, gridDim.x) * (BLOCK / 2) + (threadIdx.x >> 1);
-  if (e < n_elem) load_conn<8>(conn, e, E);  // under way while the branch waits for its word
   if (goes_direct(o.mode, o.way))
-    pass1_pair<P, BLOCK, true>(smem, E, coords4, coef, n_elem, n_node, tau, o, emax, status);
+    pass1_pair<P, BLOCK, true>(smem, conn, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
   else
-    pass1_pair<P, BLOCK, false>(smem, E, coords4, coef, n_elem, n_node, tau, o, emax, status);
+    pass1_pair<P, BLOCK, false>(smem, conn, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
 }
 
 // Tetrahedra: persistent workgroups.  XCD x owns one contiguous range of tiles and its

@@ -108,6 +108,14 @@ PairOut<V> pair_out(const Plan& p, unsigned char* ws) {
                     p.colbits};
 }
 
+// persistent workgroups of pass 1: those that fit on the device at once (LDS-bound), at
+// least one per XCD slot (b % 8) that owns tiles
+inline unsigned persistent_grid(const Plan& p, int threads) {
+  const int per_cu = std::max(1, (int)(163840 / std::max<size_t>(p.lds1, 1)));
+  return (unsigned)std::min<int64_t>(p.ntiles,
+                                     std::max<int64_t>(8, (int64_t)p.cus * std::min(per_cu, 2048 / threads)));
+}
+
 template <int NEN, Prec P, bool FROM_VALUES, int BLOCK, Op OP>
 int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsigned char* ws, uint32_t* status,
                        hipStream_t s) {
@@ -120,7 +128,8 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
     // (in FP64 the pair kernel sits at the register limit and was slower on 1M bricks)
     auto kern = k_pass1_pair<P, 2 * BLOCK>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<(unsigned)p.ntiles, 2 * BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, p.nel, p.nn, p.tau, o, emax, status);
+    kern<<<persistent_grid(p, 2 * BLOCK), 2 * BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, p.nel, p.nn, p.tau,
+                                                                  p.ntiles, o, emax, status);
     KB_LAUNCH_CHECK();
     return KB_OK;
   }
@@ -139,14 +148,10 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
     kern<<<(unsigned)p.ntiles, BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, (const V*)klow, p.nel, p.nn, p.tau, o,
                                                    emax, status);
   } else {
-    // tetrahedra: persistent, the workgroups that fit on the device at once (LDS-bound),
-    // at least one per XCD slot (b % 8) that owns tiles
+    // tetrahedra: persistent
     auto kern = k_pass1_tet<P, FROM_VALUES, BLOCK, OP>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    const int per_cu = std::max(1, (int)(163840 / std::max<size_t>(p.lds1, 1)));
-    const int64_t g1 =
-        std::min<int64_t>(p.ntiles, std::max<int64_t>(8, (int64_t)p.cus * std::min(per_cu, 2048 / BLOCK)));
-    kern<<<(unsigned)g1, BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, (const V*)klow, p.nel, p.nn, p.tau, p.ntiles,
+    kern<<<persistent_grid(p, BLOCK), BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, (const V*)klow, p.nel, p.nn, p.tau, p.ntiles,
                                              o, emax, status);
   }
   KB_LAUNCH_CHECK();
