@@ -148,12 +148,20 @@ int make_plan(const kb_mesh* m, int prec, const kb_tuning* tu, Plan* p, int dof 
   p->p2 = 1 << (p->s1 - p->s2);
   p->nb = (int)div_up(p->nn, (int64_t)1 << p->s1);
   p->nsub = (int64_t)p->nb * p->p2;
+  p->s2d = p->s2;
+  if (!sub_bits)
+    while (p->s2d < s2_max && (double)(2 << p->s2d) * u_row <= kDirectLoad * p->ht) ++p->s2d;
+  auto set_direct = [&](int s2d) {
+    p->s2d = s2d;
+    p->nsub_d = s2d == p->s2 ? p->nsub : div_up(p->nn, (int64_t)1 << s2d);
+  };
+  set_direct(p->s2d);
   // pass-1 tiles: pairs staged in LDS as (8-byte key, value).  Up to 8 rows: one
   // element per lane, `block` may pick the half-size tile (two workgroups per CU);
   // more rows (several DOFs per node): as many elements as keep the staged pairs near
   // 110 KB, on kWideThreads threads
   auto lds_of = [&](int tile, int mode) {
-    const size_t slots = 4 * PairOut<double>::slot_words(mode, p->nb, p->nsub);
+    const size_t slots = 4 * PairOut<double>::slot_words(mode, p->nb, p->nsub_d);
     if (p->nen <= 8)  // (scan words for up to two lanes per element)
       return (size_t)tile * p->te * (8 + p->vbytes) + slots + 4 * (2 * (size_t)tile / 64 + 2);
     return (size_t)tile * p->te * (8 + p->vbytes) + slots + 4 * (kWideThreads / 64 + 2) +
@@ -186,21 +194,26 @@ int make_plan(const kb_mesh* m, int prec, const kb_tuning* tu, Plan* p, int dof 
   // where pass 1 sends its pairs (kb_assemble.hpp): widths set by hand mean the two levels
   p->mode = kTwoLevel;
   if (p->nel > 0 && p->nb > 0 && !(tu && (tu->bucket_bits || tu->seg_pairs))) {
-    if (csr_cap == 0 && p->nsub <= kSlotsArray) {
+    const int s2d = p->s2d;
+    set_direct(p->s2);  // few sub-buckets: their number, not their size, keeps the device busy
+    if (csr_cap == 0 && p->nsub_d <= kSlotsArray) {
       int tile = p->tile;
       if (p->nen <= 8 && !tile_set && div_up(p->nel, tile) < kDirectTiles) tile = kSmallTile;
-      if (div_up(p->nel, tile) * p->nsub <= kDirectRuns && lds_of(tile, kDirect) <= 163840) {
+      if (div_up(p->nel, tile) * p->nsub_d <= kDirectRuns && lds_of(tile, kDirect) <= 163840) {
         p->mode = kDirect;
         p->tile = tile;
       }
     }
-    if (p->mode == kTwoLevel && lds_of(p->tile, kAsk) <= 163840) p->mode = kAsk;
+    if (p->mode == kTwoLevel) {
+      set_direct(s2d);
+      if (lds_of(p->tile, kAsk) <= 163840) p->mode = kAsk;
+    }
   }
   p->lds1 = lds_of(p->tile, p->mode);
   p->ntiles = div_up(p->nel, p->tile);
   p->ntiles_csr = div_up(csr_cap, kCsrTile);
   p->nhist = p->mode == kDirect ? 0 : (int64_t)p->nb * (p->ntiles + p->ntiles_csr);
-  p->lds_csr = 2 * (size_t)kCsrTile * (8 + p->vbytes) + 4 * PairOut<double>::slot_words(p->mode, p->nb, p->nsub) +
+  p->lds_csr = 2 * (size_t)kCsrTile * (8 + p->vbytes) + 4 * PairOut<double>::slot_words(p->mode, p->nb, p->nsub_d) +
                4 * (kCsrThreads / 64 + 2);
   if (csr_cap > 0 && p->lds_csr > 163840) return KB_EINVAL;
   if (tu && tu->seg_pairs)

@@ -278,6 +278,19 @@ __device__ __forceinline__ bool goes_direct(int mode, const uint32_t* __restrict
   return mode == kAsk ? *way != 0 : mode == kDirect;
 }
 
+// The sub-buckets of each way: rows per sub-bucket 2^s2[way] and their number, way 1 being
+// the direct one.  Rows of a mesh numbered with locality have much the same length, so the
+// direct way's sub-buckets may fill pass 3's table to kDirectLoad where the two-level
+// way's may not (under a random numbering the last rows are twice the average): 32 rows of
+// bricks instead of 16 (27M bricks FP64, pass 3 5.9 -> 4.9 ms; randomly numbered 1M bricks
+// 0.28 -> 0.33 ms).
+struct SubBuckets {
+  int s2[2], nsub[2];
+  int mode;
+  const uint32_t* way;
+  __device__ __forceinline__ int pick() const { return goes_direct(mode, way) ? 1 : 0; }
+};
+
 // The LDS counters of a tile: one per bucket (two levels), per sub-bucket of the mesh
 // (direct, array), or per sub-bucket that the tile touches (direct, hash: key[] holds the
 // sub-bucket of each slot).  The ways are separate code under one branch at the top of
@@ -1451,10 +1464,10 @@ __global__ __launch_bounds__(256) void k_hist2(const uint16_t* __restrict__ irow
                                                uint32_t* __restrict__ hist2, int mode,
                                                const uint32_t* __restrict__ way) {
   extern __shared__ uint32_t s_h[];  // [p2]
-  if (goes_direct(mode, way)) return;
   const uint32_t sid = blockIdx.x;
-  if (sid >= segbase[nb]) return;
-  const uint32_t b = seg2b[sid], s = sid - segbase[b];
+  const uint32_t n_seg = segbase[nb], b = seg2b[sid];
+  if (goes_direct(mode, way) || sid >= n_seg) return;  // (b is then not a bucket)
+  const uint32_t s = sid - segbase[b];
   for (int j = threadIdx.x; j < p2; j += blockDim.x) s_h[j] = 0;
   __syncthreads();
   const uint32_t be = bstart[b + 1];
@@ -1534,7 +1547,6 @@ __global__ __launch_bounds__(NT) void k_scatter2(const uint16_t* __restrict__ ir
                                                   V* __restrict__ oval, int mode,
                                                   const uint32_t* __restrict__ way) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if (goes_direct(mode, way)) return;
   V* s_val = (V*)smem;                          // [SEG]
   uint32_t* s_key = (uint32_t*)(s_val + SEG);   // [SEG]
   uint16_t* s_sb = (uint16_t*)(s_key + SEG);    // [SEG] sub-bucket of staged pair
@@ -1542,8 +1554,9 @@ __global__ __launch_bounds__(NT) void k_scatter2(const uint16_t* __restrict__ ir
   uint32_t* s_off = s_cnt + p2;                 // [p2] global offsets
   uint32_t* s_scan = s_off + p2;                // [NT/64 + 1]
   const uint32_t sid = (uint32_t)xcd_item(blockIdx.x, gridDim.x);
-  if (sid >= segbase[nb]) return;
-  const uint32_t b = seg2b[sid], s = sid - segbase[b];
+  const uint32_t n_seg = segbase[nb], b = seg2b[sid];
+  if (goes_direct(mode, way) || sid >= n_seg) return;  // (b is then not a bucket)
+  const uint32_t s = sid - segbase[b];
   for (int j = threadIdx.x; j < p2; j += blockDim.x) {
     s_cnt[j] = 0;
     s_off[j] = sbb[(int64_t)b * p2 + j] + off2[(int64_t)sid * p2 + j];
@@ -1662,9 +1675,13 @@ __device__ __forceinline__ uint32_t slot_hash(uint32_t k) {
 // Sub-buckets run in their natural order: under a random numbering the lower-triangle
 // pairs of a row grow with its id, so an even interleave keeps the XCDs balanced.
 // With RES, each entry's residual (the exact sum minus its rounding) goes to tres too.
+// (The grid has the two-level way's number of sub-buckets; where the direct way has fewer,
+// the other workgroups return: about 0.4 ns each, against 20% slower code if a workgroup
+// could take several in turn.)
 template <typename V, int HT, bool RES = false>
 __global__ __launch_bounds__(256) void k_pass3(uint32_t* __restrict__ ikey, V* __restrict__ ival,
-                                               const uint32_t* __restrict__ sbb, int s2, int colbits, int64_t n_node,
+                                               const uint32_t* __restrict__ sbb, const SubBuckets sub, int colbits,
+                                               int64_t n_node,
                                                const uint32_t* __restrict__ emax, int32_t* __restrict__ tcol,
                                                V* __restrict__ tval, V* __restrict__ tres,
                                                uint32_t* __restrict__ rowoff, uint32_t* __restrict__ usub,
@@ -1683,25 +1700,27 @@ __global__ __launch_bounds__(256) void k_pass3(uint32_t* __restrict__ ikey, V* _
   __shared__ uint32_t s_sep[kSepCols ? HT : 1];
   __shared__ uint32_t s_over, s_nu;
   extern __shared__ uint32_t s_rows[];  // 3 << s2 words: entries per row, row offsets, cursors
-  uint32_t* const s_rc = s_rows;
-  uint32_t* const s_ro = s_rows + (1 << s2);
-  uint32_t* const s_cur = s_rows + (2 << s2);
-  uint32_t* const s_lcol = kSepCols ? s_sep : (uint32_t*)s_hi;  // columns of the slots, grouped by row
-
   const int64_t g = blockIdx.x;
+  const bool either = g < sub.nsub[1];
+  if (!either && sub.pick()) return;  // (only the workgroups beyond the direct way's wait for its word here)
   const uint32_t beg = sbb[g], end = sbb[g + 1];
-  const int64_t r0 = g << s2;
-  const int64_t rr = n_node - r0;
-  const int R = rr <= 0 ? 0 : (rr < ((int64_t)1 << s2) ? (int)rr : (1 << s2));
-  const int F = 1117 - (int)*emax;
-  const uint32_t cmask = (1u << colbits) - 1;
-
+  uint32_t* const s_rc = s_rows;
   for (int h = threadIdx.x; h < HT; h += NT) {
     s_key[h] = kEmptyKey;
     s_lo[h] = 0ull;
     s_hi[h] = 0ull;
   }
-  for (int r = threadIdx.x; r < (1 << s2); r += NT) s_rc[r] = 0;
+  const int s2_max = sub.s2[0] > sub.s2[1] ? sub.s2[0] : sub.s2[1];
+  for (int r = threadIdx.x; r < (1 << s2_max); r += NT) s_rc[r] = 0;
+  const int s2 = sub.s2[either ? sub.pick() : 0];
+  uint32_t* const s_ro = s_rows + (1 << s2);
+  uint32_t* const s_cur = s_rows + (2 << s2);
+  uint32_t* const s_lcol = kSepCols ? s_sep : (uint32_t*)s_hi;  // columns of the slots, grouped by row
+  const int F = 1117 - (int)*emax;
+  const uint32_t cmask = (1u << colbits) - 1;
+  const int64_t r0 = g << s2;
+  const int64_t rr = n_node - r0;
+  const int R = rr <= 0 ? 0 : (rr < ((int64_t)1 << s2) ? (int)rr : (1 << s2));
   // more than 2^16 pairs could overflow the chunk sums: left to k_heavy
   if (threadIdx.x == 0) {
     s_over = (end - beg > (1u << 16)) ? 1u : 0u;
@@ -2172,7 +2191,8 @@ struct HeavyArgs {
   V* aval;
   V* tres;
   const uint32_t* sbb;
-  int s2, colbits;
+  SubBuckets sub;
+  int s2, colbits;  // (s2: the way taken)
   int64_t n_node;
   int F;
   uint32_t* rowoff;
@@ -2804,9 +2824,12 @@ __device__ __forceinline__ void scan_counts(uint32_t* usub, int n, uint32_t* uba
 template <typename V, bool RES, HeavyPhase PHASE, bool SCAN = false>
 __global__ __launch_bounds__(kHeavyThreads) void k_heavy(HeavyArgs<V> A, const uint32_t* __restrict__ emax,
                                                        const uint32_t* __restrict__ n_over, uint32_t par,
-                                                       uint32_t* done, int nsub, uint32_t* ubase, int64_t* nnz) {
+                                                       uint32_t* done, uint32_t* ubase, int64_t* nnz) {
   extern __shared__ __align__(16) unsigned char smem[];
   A.n_over = *n_over;
+  if (!SCAN && A.n_over == 0) return;
+  const int taken = A.sub.pick(), nsub = A.sub.nsub[taken];
+  A.s2 = A.sub.s2[taken];
   if (A.n_over == 0) {
     if constexpr (SCAN)
       if (ubase && blockIdx.x == 0) scan_counts(A.usub, nsub, ubase, nnz, (uint32_t*)smem);
@@ -2837,6 +2860,25 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy(HeavyArgs<V> A, const u
     __threadfence();
     scan_counts(A.usub, nsub, ubase, nnz, (uint32_t*)smem);
   }
+}
+
+// ------------------------------------------------------------------ many entry counts
+// ubase[0 .. nsub] = exclusive scan of usub over the sub-buckets of the way taken, in two
+// kernels (chunk sums, then each chunk with the sums before it)
+static __global__ __launch_bounds__(kScanThreads) void k_scan_partials(const int32_t* __restrict__ usub,
+                                                                       const SubBuckets sub,
+                                                                       int32_t* __restrict__ part) {
+  const int64_t n = sub.nsub[sub.pick()];
+  if ((int64_t)blockIdx.x * kScanChunk < n) scan_chunk_sum(usub, n, part);
+}
+
+static __global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t* __restrict__ usub,
+                                                                   const SubBuckets sub,
+                                                                   const int32_t* __restrict__ part,
+                                                                   int32_t* __restrict__ ubase,
+                                                                   int64_t* __restrict__ nnz) {
+  const int64_t n = sub.nsub[sub.pick()];
+  if ((int64_t)blockIdx.x * kScanChunk < n) scan_chunk_down(usub, n, part, ubase, nullptr, nnz);
 }
 
 // ------------------------------------------------------------------------- final
@@ -2912,22 +2954,24 @@ template <typename V, bool GROUPED = false>
 __global__ __launch_bounds__(256) void k_final(const uint32_t* __restrict__ sbb, const uint32_t* __restrict__ ubase,
                                                const int32_t* __restrict__ tcol, const V* __restrict__ tval,
                                                const V* __restrict__ tres, const uint32_t* __restrict__ rowoff,
-                                               int s2, int64_t n_node, int64_t nsub, int32_t* __restrict__ row_ptr,
+                                               const SubBuckets sub, int64_t n_node, int32_t* __restrict__ row_ptr,
                                                int32_t* __restrict__ col_idx, V* __restrict__ vals,
                                                V* __restrict__ res, int32_t* __restrict__ rows, int64_t cap,
                                                uint32_t* __restrict__ status, const uint32_t* __restrict__ ov_list,
                                                const uint32_t* __restrict__ ov_count,
                                                const uint32_t* __restrict__ hvy, uint32_t par) {
   const uint32_t n_wave = gridDim.x - kFinalHeavyGrid;
+  const int way = sub.pick(), s2 = sub.s2[way];
+  const int64_t nsub = sub.nsub[way];
   if (blockIdx.x >= n_wave) {
     final_heavy<V, GROUPED>(sbb, ubase, tcol, tval, tres, rowoff, s2, n_node, nsub, ov_list, ov_count, hvy, col_idx,
                             vals, res, rows, cap, par, blockIdx.x - n_wave, kFinalHeavyGrid);
     return;
   }
   const int lane = threadIdx.x & 63;
+  const int64_t nnz = ubase[nsub];
   const int64_t g = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
   if (g >= nsub) return;
-  const int64_t nnz = ubase[nsub];
   const uint32_t base = ubase[g], U = ubase[g + 1] - base;
   const int64_t r0 = g << s2;
   const int R = (int)min((int64_t)1 << s2, n_node - r0);

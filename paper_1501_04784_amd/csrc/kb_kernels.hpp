@@ -165,17 +165,6 @@ __device__ __forceinline__ void scan_chunk_down(const int32_t* in, int64_t n, co
   }
 }
 
-static __global__ __launch_bounds__(kScanThreads) void k_scan_partials(const int32_t* __restrict__ in, int64_t n,
-                                                                int32_t* __restrict__ part) {
-  scan_chunk_sum(in, n, part);
-}
-
-static __global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t* __restrict__ in, int64_t n,
-                                                            const int32_t* __restrict__ part,
-                                                            int32_t* __restrict__ out, int64_t* __restrict__ total64) {
-  scan_chunk_down(in, n, part, out, nullptr, total64);
-}
-
 // n == 0: out[0] = 0
 static __global__ void k_scan_empty(int32_t* __restrict__ out, int64_t* __restrict__ total64) {
   out[0] = 0;

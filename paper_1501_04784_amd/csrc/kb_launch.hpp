@@ -25,6 +25,7 @@ constexpr int kSeg = 4096, kSegLong = 8192, kMinRun = 16;
 constexpr int kSegThreads = 512;   // threads per pass-2 scatter workgroup
 constexpr int kTargetBuckets = 256;  // first-level buckets (pass-1 run length)
 constexpr double kSubEntries = 300;   // target distinct entries per sub-bucket
+constexpr double kDirectLoad = 0.46;  // of pass 3's table, at most, on the direct way
 constexpr int kHTMin = 512, kHTMax = 4096;
 // the direct way for small meshes: at most kDirectRuns runs (tiles x sub-buckets), each of
 // which may take a global atomic when counted and when written (about 27 G atomics/s: 20 us
@@ -48,13 +49,14 @@ struct Plan {
   size_t vbytes = 8;
   // assembly geometry
   int s1 = 0, s2 = 0, p2 = 1, nb = 0;  // bucket / sub-bucket shifts, sub-buckets per bucket, buckets
+  int s2d = 0;                         // sub-bucket shift of the direct way
   int colbits = 1;                     // bits of a column index
   int ht = 2048;                       // pass-3 hash slots
   int seg = kSeg;                      // pairs per pass-2 segment
   int tile = 0;                        // elements (= threads) per pass-1 workgroup
   int mode = kTwoLevel;                // where pass 1 sends its pairs
   int cus = 256;                       // compute units of the current device (launch time)
-  int64_t ntiles = 0, nsub = 0, nhist = 0, nseg_max = 0;
+  int64_t ntiles = 0, nsub = 0, nsub_d = 0, nhist = 0, nseg_max = 0;
   int64_t csr_cap = 0, ntiles_csr = 0;  // running sums read back as pairs (grouped builds)
   size_t lds1 = 0, lds2 = 0, lds_csr = 0;
   // workspace offsets
@@ -90,6 +92,14 @@ bool set_lds(K kernel, size_t bytes) {
          hipSuccess;
 }
 
+// (with as many sub-buckets either way, nothing has to know which was taken)
+inline SubBuckets sub_buckets(const Plan& p, unsigned char* ws) {
+  return SubBuckets{{p.s2, p.s2d},
+                    {(int)p.nsub, (int)p.nsub_d},
+                    p.nsub == p.nsub_d ? (int)kTwoLevel : p.mode,
+                    (const uint32_t*)(ws + p.o_head) + kHeadWay};
+}
+
 template <typename V>
 PairOut<V> pair_out(const Plan& p, unsigned char* ws) {
   return PairOut<V>{(uint16_t*)(ws + p.o_row1),
@@ -103,8 +113,8 @@ PairOut<V> pair_out(const Plan& p, unsigned char* ws) {
                     p.mode,
                     p.s1,
                     p.nb,
-                    p.s2,
-                    (int)p.nsub,
+                    p.s2d,
+                    (int)p.nsub_d,
                     p.colbits};
 }
 
@@ -238,22 +248,22 @@ int launch_pass3(const Plan& p, unsigned char* ws, V* tres, int64_t* nnz_dev, hi
       default: return k_pass3<V, 4096, RES>;
     }
   }();
-  k3<<<(unsigned)p.nsub, 256, (size_t)12 << p.s2, s>>>(key2, val2, sbb, p.s2, p.colbits, p.nn, head, tcol, tval, tres,
-                                                       rowoff, usub, ov_list, head + 1);
+  const SubBuckets sub = sub_buckets(p, ws);
+  k3<<<(unsigned)p.nsub, 256, (size_t)12 << std::max(p.s2, p.s2d), s>>>(
+      key2, val2, sbb, sub, p.colbits, p.nn, head, tcol, tval, tres, rowoff, usub, ov_list, head + 1);
   KB_LAUNCH_CHECK();
-  const HeavyArgs<V> A{key2, val2, (uint32_t*)tcol, tval, tres, sbb, p.s2, p.colbits, p.nn, 0, rowoff, usub, ov_list,
+  const HeavyArgs<V> A{key2, val2, (uint32_t*)tcol, tval, tres, sbb, sub, p.s2, p.colbits, p.nn, 0, rowoff, usub, ov_list,
                        0, 0, (uint32_t*)(ws + p.o_hvy)};
   uint32_t* const ubase = p.nsub <= kScanHere ? (uint32_t*)(ws + p.o_ubase) : nullptr;
   const unsigned cus = (unsigned)std::max(1, p.cus);
   auto phase = [&](auto kern, unsigned grid, size_t lds) {
     if (!set_lds(kern, lds)) return (int)KB_EHIP;
-    kern<<<grid, kHeavyThreads, lds, s>>>(A, head, head + 1, heavy_par(p), head + 2, (int)p.nsub,
-                                          ubase, nnz_dev);
+    kern<<<grid, kHeavyThreads, lds, s>>>(A, head, head + 1, heavy_par(p), head + 2, ubase, nnz_dev);
     return hipGetLastError() == hipSuccess ? (int)KB_OK : (int)KB_EHIP;
   };
   constexpr size_t kTabLds = 4 * (size_t)(kHvyDigits + 2 * kHvyRows + 1 + kHeavyThreads / 64 + 1);
   if (!heavy_par(p))
-    return phase(k_heavy<V, RES, kHeavyRangesPhase, true>, (unsigned)std::min<int64_t>(p.nsub, cus),
+    return phase(k_heavy<V, RES, kHeavyRangesPhase, true>, (unsigned)std::min<int64_t>(std::max<int64_t>(p.nsub, 1), cus),
                  HeavySmem::bytes());
   KB_TRY(phase(k_heavy<V, RES, kHeavyRowsPhase>, 2 * cus, kTabLds));
   KB_TRY(phase(k_heavy<V, RES, kHeavyHistPhase>, 2 * cus, kTabLds));
@@ -316,11 +326,12 @@ int assemble_tail(const Plan& p, unsigned char* ws, int32_t* row_ptr, int32_t* c
   }
   KB_TRY(ev.rec(KB_STAGE_COMPRESS));
   if (p.nsub > 0) {
+    const SubBuckets sub = sub_buckets(p, ws);
     if (p.nsub > kScanHere) {
       const unsigned g = grid_for(p.nsub, kScanChunk);
-      k_scan_partials<<<g, kScanThreads, 0, s>>>(usub, p.nsub, part);
+      k_scan_partials<<<g, kScanThreads, 0, s>>>(usub, sub, part);
       KB_LAUNCH_CHECK();
-      k_scan_down<<<g, kScanThreads, 0, s>>>(usub, p.nsub, part, (int32_t*)ubase, nnz_dev);
+      k_scan_down<<<g, kScanThreads, 0, s>>>(usub, sub, part, (int32_t*)ubase, nnz_dev);
       KB_LAUNCH_CHECK();
     }
     const unsigned gf = (unsigned)div_up(p.nsub, 4) + kFinalHeavyGrid;
@@ -331,10 +342,10 @@ int assemble_tail(const Plan& p, unsigned char* ws, int32_t* row_ptr, int32_t* c
     auto* hvy = (const uint32_t*)(ws + p.o_hvy);
     const uint32_t par = heavy_par(p);
     if (cr)
-      k_final<V, true><<<gf, 256, 0, s>>>(sbb, ubase, tcol, tval, tres, rowoff, p.s2, p.nn, p.nsub, row_ptr, col_idx,
+      k_final<V, true><<<gf, 256, 0, s>>>(sbb, ubase, tcol, tval, tres, rowoff, sub, p.nn, row_ptr, col_idx,
                                           vals, (V*)cr->res_out, cr->rows_out, cap, status, ov_list, head + 1, hvy, par);
     else
-      k_final<V><<<gf, 256, 0, s>>>(sbb, ubase, tcol, tval, nullptr, rowoff, p.s2, p.nn, p.nsub, row_ptr, col_idx,
+      k_final<V><<<gf, 256, 0, s>>>(sbb, ubase, tcol, tval, nullptr, rowoff, sub, p.nn, row_ptr, col_idx,
                                     vals, nullptr, nullptr, cap, status, ov_list, head + 1, hvy, par);
     KB_LAUNCH_CHECK();
   } else {
@@ -371,42 +382,42 @@ int build_impl(const Plan& p, const kb_mesh* m, const void* klow, unsigned char*
     const bool pad = p.ntiles > 0 && p.nb > 0 && !klow && p.nn > 0;
     auto* hvy = (uint32_t*)(ws + p.o_hvy);
     const int64_t n = std::max<int64_t>(
-        {pad ? p.nn : 0, p.mode != kTwoLevel ? p.nsub : 0, (int64_t)2 * kHvyRows * std::max(1u, heavy_par(p))});
+        {pad ? p.nn : 0, p.mode != kTwoLevel ? p.nsub_d : 0, (int64_t)2 * kHvyRows * std::max(1u, heavy_par(p))});
     k_begin<NEN><<<(unsigned)(kSamples + std::min<int64_t>(div_up(n, 256), 8192)), 256, 0, s>>>(
-        m->conn, p.nel, p.nn, p.tile, p.ntiles, p.s2, p.mode, first ? status : nullptr, first ? nnz_dev : nullptr,
-        head, subcnt, p.nsub, m->coords, pad ? (double4*)(ws + p.o_coords4) : nullptr, hvy + kHvyDigits * 2 + 1,
+        m->conn, p.nel, p.nn, p.tile, p.ntiles, p.s2d, p.mode, first ? status : nullptr, first ? nnz_dev : nullptr,
+        head, subcnt, p.nsub_d, m->coords, pad ? (double4*)(ws + p.o_coords4) : nullptr, hvy + kHvyDigits * 2 + 1,
         (int)heavy_par(p), kHvyWords, 2 * kHvyRows);
     KB_LAUNCH_CHECK();
   }
 
   KB_TRY(ev.rec(KB_STAGE_COUNT));
   // LDS words of the counting kernels' slots
-  const size_t slots = p.mode == kDirect ? (size_t)p.nsub
+  const size_t slots = p.mode == kDirect ? (size_t)p.nsub_d
                        : p.mode == kAsk  ? std::max<size_t>(2 * kSlotsHash, (size_t)p.nb)
                                          : (size_t)std::max(p.nb, 1);
   if (p.ntiles > 0) {
     // with no nodes every element has an index error: flagged, nothing counted
     k_count<NEN><<<(unsigned)p.ntiles, 256, 4 * slots, s>>>(m->conn, p.nel, p.nn, p.tile, p.nb > 0 ? p.s1 : 30, p.nb,
-                                                            p.s2, (int)p.nsub, p.mode, head, hist, subcnt, sbb, status);
+                                                            p.s2d, (int)p.nsub_d, p.mode, head, hist, subcnt, sbb, status);
     KB_LAUNCH_CHECK();
   }
   if (ntc > 0) {
-    k_hist_csr<<<(unsigned)ntc, kCsrThreads, 4 * slots, s>>>(cr->rows, cr->nnz, p.csr_cap, p.nn, p.s1, p.nb, p.s2,
-                                                             (int)p.nsub, p.mode, way, hist + p.ntiles * p.nb,
+    k_hist_csr<<<(unsigned)ntc, kCsrThreads, 4 * slots, s>>>(cr->rows, cr->nnz, p.csr_cap, p.nn, p.s1, p.nb, p.s2d,
+                                                             (int)p.nsub_d, p.mode, way, hist + p.ntiles * p.nb,
                                                              subcnt);
     KB_LAUNCH_CHECK();
   }
   KB_TRY(ev.rec(KB_STAGE_OFFSETS));
   if (p.nb > 0 && p.mode != kDirect) {
-    const int64_t nchunk = div_up(nt_all, kColChunk), nsc = p.mode == kAsk ? div_up(p.nsub, kScanChunk) : 0;
+    const int64_t nchunk = div_up(nt_all, kColChunk), nsc = p.mode == kAsk ? div_up(p.nsub_d, kScanChunk) : 0;
     const int64_t gc = nchunk * div_up(p.nb, 256);
     if (std::max(gc, nsc) > 0) {
       k_offsets_sums<<<(unsigned)std::max(gc, nsc), kScanThreads, 0, s>>>(hist, nt_all, p.nb, nchunk, csum, subcnt,
-                                                                         p.nsub, part, p.mode, way);
+                                                                         p.nsub_d, part, p.mode, way);
       KB_LAUNCH_CHECK();
     }
     k_offsets_scan<<<(unsigned)std::max<int64_t>(p.nb, nsc), kScanThreads, 0, s>>>(csum, nchunk, p.nb, tot, subcnt,
-                                                                                  p.nsub, part, sbb, p.mode, way);
+                                                                                  p.nsub_d, part, sbb, p.mode, way);
     KB_LAUNCH_CHECK();
     k_bucket_starts<<<1, 1024, 0, s>>>(tot, p.nb, p.seg, bstart, segbase, p.mode, way);
     KB_LAUNCH_CHECK();
