@@ -260,14 +260,14 @@ int make_plan(const kb_mesh* m, int prec, const kb_tuning* tu, Plan* p, int dof 
 template <int NEN>
 int dispatch_build(const Plan& p, const kb_mesh* m, const void* klow, unsigned char* ws, int32_t* row_ptr,
                    int32_t* col_idx, void* vals, int64_t cap, int64_t* nnz_dev, uint32_t* status, Events& ev,
-                   hipStream_t s, const Carry* cr = nullptr) {
+                   hipStream_t s, const Carry* cr = nullptr, const BatchRows* br = nullptr) {
   switch (p.prec) {
     case KB_FP64:
-      return build_impl<NEN, Prec::F64>(p, m, klow, ws, row_ptr, col_idx, vals, cap, nnz_dev, status, ev, s, cr);
+      return build_impl<NEN, Prec::F64>(p, m, klow, ws, row_ptr, col_idx, vals, cap, nnz_dev, status, ev, s, cr, br);
     case KB_FP32:
-      return build_impl<NEN, Prec::F32>(p, m, klow, ws, row_ptr, col_idx, vals, cap, nnz_dev, status, ev, s, cr);
+      return build_impl<NEN, Prec::F32>(p, m, klow, ws, row_ptr, col_idx, vals, cap, nnz_dev, status, ev, s, cr, br);
     default:
-      return build_impl<NEN, Prec::F32FB>(p, m, klow, ws, row_ptr, col_idx, vals, cap, nnz_dev, status, ev, s, cr);
+      return build_impl<NEN, Prec::F32FB>(p, m, klow, ws, row_ptr, col_idx, vals, cap, nnz_dev, status, ev, s, cr, br);
   }
 }
 
@@ -329,11 +329,10 @@ int batch_as_mesh(const kb_batch* b, kb_mesh* m) {
   return KB_OK;
 }
 
-// batch workspace: the pipeline's, then the shifted connectivity, the batch CSR row
-// pointers and one flag word
+// batch workspace: the pipeline's, then the shifted connectivity and one flag word
 struct BatchPlan {
   Plan p;
-  size_t o_gconn = 0, o_uptr = 0, o_flags = 0, total = 0;
+  size_t o_gconn = 0, o_flags = 0, total = 0;
 };
 
 int make_batch_plan(const kb_batch* b, int prec, const kb_tuning* tu, BatchPlan* bp) {
@@ -347,7 +346,6 @@ int make_batch_plan(const kb_batch* b, int prec, const kb_tuning* tu, BatchPlan*
     return o;
   };
   bp->o_gconn = take(4 * (size_t)bp->p.nen * (size_t)bp->p.nel);
-  bp->o_uptr = take(4 * ((size_t)bp->p.nn + 1));
   bp->o_flags = take(4);
   bp->total = off;
   return KB_OK;
@@ -710,7 +708,6 @@ int kb_build_lower_csr_batched(const kb_batch* batch, int prec, const kb_tuning*
   auto* w = (unsigned char*)ws;
   auto s = (hipStream_t)stream;
   auto* gconn = (int32_t*)(w + bp.o_gconn);
-  auto* uptr = (int32_t*)(w + bp.o_uptr);
   auto* flags = (uint32_t*)(w + bp.o_flags);
   const int64_t nm = batch->n_mesh;
   k_fill_i32<<<1, 64, 0, s>>>((int32_t*)flags, 1, 0);
@@ -726,24 +723,17 @@ int kb_build_lower_csr_batched(const kb_batch* batch, int prec, const kb_tuning*
     KB_LAUNCH_CHECK();
     m.conn = gconn;
   }
-  // the batch's matrix: union CSR row pointers into the workspace, entries in place;
-  // nnz_off[n_mesh] receives the total
+  // the batch's matrix, written mesh by mesh; nnz_off[n_mesh] receives the total
   Events ev{tuning ? tuning->stage_events : nullptr, s};
+  const BatchRows br{batch->node_off, nm, flags};
   if (p.nen == 8)
-    KB_TRY(dispatch_build<8>(p, &m, nullptr, w, uptr, col_idx, vals, cap, nnz_off + nm, status_dev, ev, s));
+    KB_TRY(dispatch_build<8>(p, &m, nullptr, w, row_ptr, col_idx, vals, cap, nnz_off + nm, status_dev, ev, s, nullptr, &br));
   else
-    KB_TRY(dispatch_build<4>(p, &m, nullptr, w, uptr, col_idx, vals, cap, nnz_off + nm, status_dev, ev, s));
-  if (nm > 0) {
-    // (also with no nodes: failed offsets zero all n_node + n_mesh row pointers)
-    k_batch_rows<<<(unsigned)std::min<int64_t>(div_up(p.nn + nm, 256), 65536), 256, 0, s>>>(
-        uptr, batch->node_off, nm, p.nn, cap, flags, col_idx, row_ptr);
-    KB_LAUNCH_CHECK();
-    k_batch_meshes<<<grid_for(nm, 256), 256, 0, s>>>(uptr, batch->node_off, nm, flags, row_ptr, nnz_off, status_dev);
-    KB_LAUNCH_CHECK();
-  } else {
-    k_batch_meshes<<<1, 64, 0, s>>>(uptr, batch->node_off, nm, flags, row_ptr, nnz_off, status_dev);
-    KB_LAUNCH_CHECK();
-  }
+    KB_TRY(dispatch_build<4>(p, &m, nullptr, w, row_ptr, col_idx, vals, cap, nnz_off + nm, status_dev, ev, s, nullptr, &br));
+  k_batch_meshes<<<grid_for(std::max<int64_t>(nm, 1), 256), 256, 0, s>>>(
+      (const uint32_t*)(w + p.o_ubase), (const uint32_t*)(w + p.o_rowoff), sub_buckets(p, w), p.nn, batch->node_off,
+      nm, flags, row_ptr, nnz_off, status_dev);
+  KB_LAUNCH_CHECK();
   return KB_OK;
 }
 

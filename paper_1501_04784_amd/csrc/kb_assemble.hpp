@@ -2882,6 +2882,33 @@ static __global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t
 }
 
 // ------------------------------------------------------------------------- final
+// A batch of meshes built as one block-diagonal matrix (kb_batch.hpp): each mesh's rows
+// and columns are written in its own numbering.  node_off null: one mesh.
+struct BatchRows {
+  const int64_t* node_off;  // [n_mesh + 1]
+  int64_t n_mesh;
+  const uint32_t* flags;    // set: the offsets failed their check and are not read
+};
+
+// the last mesh m with node_off[m] <= i, by a whole wave: 64 candidates at a time
+__device__ __forceinline__ int64_t wave_owner(const int64_t* __restrict__ off, int64_t n, int64_t i) {
+  const int lane = threadIdx.x & 63;
+  int64_t lo = 0;
+  while (n > 1) {
+    const int64_t step = (n + 63) / 64, at = lo + lane * step;
+    const int k = __popcll(__ballot(lane * step < n && off[at] <= i)) - 1;  // (off[lo] <= i)
+    lo += k * step;
+    n = n - k * step < step ? n - k * step : step;
+  }
+  return lo;
+}
+
+// position of node i's first entry in the union matrix (i = n_node: the number of entries)
+__device__ __forceinline__ int64_t row_start(const uint32_t* __restrict__ ubase, const uint32_t* __restrict__ rowoff,
+                                             int s2, int64_t n_node, int64_t nsub, int64_t i) {
+  return i >= n_node ? (int64_t)ubase[nsub] : (int64_t)ubase[i >> s2] + rowoff[i];
+}
+
 // The entries of the sub-buckets that one wavefront does not copy (more than kFinalWave:
 // only a heavy sub-bucket, listed by pass 3, can hold more than a pass-3 table), copied
 // by nblk workgroups in chunks of 1024: from the sub-bucket's first pair's place on, or,
@@ -2889,15 +2916,15 @@ static __global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t
 // range d whose entry offset is the last at or below f, at the range's start plus f minus
 // that offset).  With GROUPED each entry's row is found by a binary search of the
 // sub-bucket's row offsets.
-template <typename V, bool GROUPED>
+template <typename V, bool GROUPED, bool BATCH>
 __device__ __forceinline__ void final_heavy(const uint32_t* __restrict__ sbb, const uint32_t* __restrict__ ubase,
                                             const int32_t* __restrict__ tcol, const V* __restrict__ tval,
                                             const V* __restrict__ tres, const uint32_t* __restrict__ rowoff, int s2,
                                             int64_t n_node, int64_t nsub, const uint32_t* __restrict__ ov_list,
                                             const uint32_t* __restrict__ ov_count, const uint32_t* __restrict__ hvy,
                                             int32_t* __restrict__ col_idx, V* __restrict__ vals, V* __restrict__ res,
-                                            int32_t* __restrict__ rows, int64_t cap, uint32_t par, uint32_t blk,
-                                            uint32_t nblk) {
+                                            int32_t* __restrict__ rows, int64_t cap, const BatchRows& batch,
+                                            uint32_t par, uint32_t blk, uint32_t nblk) {
   __shared__ uint32_t s_off[kHvyDigits];  // entry offsets of the ranges
   const uint32_t n_over = *ov_count;
   if (n_over == 0 || (int64_t)ubase[nsub] > cap) return;
@@ -2926,10 +2953,9 @@ __device__ __forceinline__ void final_heavy(const uint32_t* __restrict__ sbb, co
           const uint32_t d = heavy_find(s_off, nd0, f);
           src = t.st[d] + (f - s_off[d]);
         }
-        col_idx[base + f] = tcol[src];
+        int32_t col = tcol[src];
         vals[base + f] = tval[src];
-        if constexpr (GROUPED) {
-          res[base + f] = tres[src];
+        if constexpr (GROUPED || BATCH) {
           int lo = 0, hi = R - 1;  // last row whose first entry is at or before f
           while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -2938,8 +2964,20 @@ __device__ __forceinline__ void final_heavy(const uint32_t* __restrict__ sbb, co
             else
               hi = mid - 1;
           }
-          rows[base + f] = (int32_t)(r0 + lo);
+          if constexpr (GROUPED) {
+            res[base + f] = tres[src];
+            rows[base + f] = (int32_t)(r0 + lo);
+          } else {  // the row's mesh: the last with node_off <= row
+            int64_t m = 0, n = batch.n_mesh;
+            while (n > 1) {
+              const int64_t half = n >> 1;
+              if (batch.node_off[m + half] <= r0 + lo) m += half;
+              n -= half;
+            }
+            col -= (int32_t)batch.node_off[m];
+          }
         }
+        col_idx[base + f] = col;
       }
     }
   }
@@ -2949,8 +2987,10 @@ __device__ __forceinline__ void final_heavy(const uint32_t* __restrict__ sbb, co
 // its rows' row_ptr = ubase[g] + local row offset.
 // GROUPED (running sums of a grouped build): also each entry's residual (tres -> res)
 // and its row (rows), the form in which the next group's pass reads them back.
+// BATCH: columns and row pointers of each mesh in its own numbering, as they are copied (a
+// second pass over the columns took 0.96 of the 256-brick batch's 7.3 ms).
 // The last kFinalHeavyGrid workgroups copy the larger sub-buckets (final_heavy).
-template <typename V, bool GROUPED = false>
+template <typename V, bool GROUPED = false, bool BATCH = false>
 __global__ __launch_bounds__(256) void k_final(const uint32_t* __restrict__ sbb, const uint32_t* __restrict__ ubase,
                                                const int32_t* __restrict__ tcol, const V* __restrict__ tval,
                                                const V* __restrict__ tres, const uint32_t* __restrict__ rowoff,
@@ -2959,13 +2999,19 @@ __global__ __launch_bounds__(256) void k_final(const uint32_t* __restrict__ sbb,
                                                V* __restrict__ res, int32_t* __restrict__ rows, int64_t cap,
                                                uint32_t* __restrict__ status, const uint32_t* __restrict__ ov_list,
                                                const uint32_t* __restrict__ ov_count,
-                                               const uint32_t* __restrict__ hvy, uint32_t par) {
+                                               const uint32_t* __restrict__ hvy, uint32_t par, const BatchRows batch) {
   const uint32_t n_wave = gridDim.x - kFinalHeavyGrid;
   const int way = sub.pick(), s2 = sub.s2[way];
   const int64_t nsub = sub.nsub[way];
+  if (BATCH && *batch.flags) {  // no element was kept: empty rows for every mesh
+    const int64_t n = n_node + batch.n_mesh;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+      row_ptr[i] = 0;
+    return;
+  }
   if (blockIdx.x >= n_wave) {
-    final_heavy<V, GROUPED>(sbb, ubase, tcol, tval, tres, rowoff, s2, n_node, nsub, ov_list, ov_count, hvy, col_idx,
-                            vals, res, rows, cap, par, blockIdx.x - n_wave, kFinalHeavyGrid);
+    final_heavy<V, GROUPED, BATCH>(sbb, ubase, tcol, tval, tres, rowoff, s2, n_node, nsub, ov_list, ov_count, hvy, col_idx,
+                            vals, res, rows, cap, batch, par, blockIdx.x - n_wave, kFinalHeavyGrid);
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -2975,6 +3021,29 @@ __global__ __launch_bounds__(256) void k_final(const uint32_t* __restrict__ sbb,
   const uint32_t base = ubase[g], U = ubase[g + 1] - base;
   const int64_t r0 = g << s2;
   const int R = (int)min((int64_t)1 << s2, n_node - r0);
+  if constexpr (BATCH) {
+    if (nnz > cap && g == 0 && lane == 0) raise_flag(status, KB_F_CAPACITY);
+    if (R <= 0) return;
+    const uint32_t src = sbb[g];
+    const bool copy = nnz <= cap && U <= kFinalWave;  // (larger: a heavy sub-bucket, final_heavy)
+    // the sub-bucket's rows mesh by mesh
+    int64_t m = wave_owner(batch.node_off, batch.n_mesh, r0);
+    for (int64_t a = r0; a < r0 + R; ++m) {
+      const int64_t n0 = batch.node_off[m], n1 = batch.node_off[m + 1];
+      const int64_t b = n1 < r0 + R ? n1 : r0 + R;
+      if (b <= a) continue;  // (a mesh without nodes)
+      const uint32_t f0 = rowoff[a], f1 = b < r0 + R ? rowoff[b] : U;
+      if (copy)
+        for (uint32_t f = f0 + lane; f < f1; f += 64) {
+          col_idx[base + f] = tcol[src + f] - (int32_t)n0;
+          vals[base + f] = tval[src + f];
+        }
+      const int64_t first = row_start(ubase, rowoff, s2, n_node, nsub, n0);
+      for (int64_t r = a + lane; r < b; r += 64) row_ptr[r + m] = (int32_t)(base + rowoff[r] - first);
+      a = b;
+    }
+    return;
+  }
   if (nnz <= cap && U <= kFinalWave) {  // (larger: a heavy sub-bucket, final_heavy)
     const uint32_t src = sbb[g];
     for (uint32_t f = lane; f < U; f += 64) {

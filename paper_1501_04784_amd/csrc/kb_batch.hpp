@@ -4,12 +4,13 @@
 // [node_off[m], node_off[m+1]), connectivity in mesh-local node ids).  Shifting each
 // mesh's ids by node_off[m] gives one mesh whose K is block diagonal (no element spans
 // two meshes), so one pass of the ordinary pipeline builds every mesh's matrix at once;
-// its CSR lists the meshes' rows in order.  Each mesh's own CSR is then that block with
-// its row pointers rebased to 0 and its columns shifted back to local ids.
+// its CSR lists the meshes' rows in order.  Each mesh's own CSR is that block with its row
+// pointers rebased to 0 and its columns shifted back to local ids, as k_final writes it.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kb_assemble.hpp"
 #include "kb_kernels.hpp"
 #include "kbuild.h"
 
@@ -69,51 +70,35 @@ __global__ __launch_bounds__(256) void k_batch_conn(const int32_t* __restrict__ 
   }
 }
 
-// One thread per node i of the batch (mesh m): its row in mesh m's own CSR.  row_ptr of
-// mesh m occupies out_ptr[node_off[m] + m .. node_off[m+1] + m]; columns become local.
-// Columns are rewritten only when the union CSR was written (nnz <= cap).  Offsets that
-// failed their check (*flags set) say nothing trustworthy about where a mesh's rows
-// go: then every one of the n_node + n_mesh row pointers is written as 0 instead (no
-// element was kept, so the union CSR is empty) and node_off is not read.
-__global__ __launch_bounds__(256) void k_batch_rows(const int32_t* __restrict__ uptr, const int64_t* __restrict__ node_off,
-                                                    int64_t n_mesh, int64_t n_node, int64_t cap,
-                                                    const uint32_t* __restrict__ flags,
-                                                    int32_t* __restrict__ col_idx, int32_t* __restrict__ out_ptr) {
-  if (*flags) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_node + n_mesh;
-         i += (int64_t)gridDim.x * blockDim.x)
-      out_ptr[i] = 0;
-    return;
-  }
-  const int64_t nnz = uptr[n_node];
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_node;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t m = owner_of(node_off, n_mesh, i);
-    const int64_t base = node_off[m];
-    out_ptr[i + m] = uptr[i] - uptr[base];
-    if (nnz <= cap)
-      for (int32_t k = uptr[i]; k < uptr[i + 1]; ++k) col_idx[k] -= (int32_t)base;
-  }
-}
-
-// One thread per mesh: its closing row pointer and its first entry in col_idx / vals;
-// nnz_off[n_mesh] already holds the batch total.  Folds the offset-check flags into the
-// status word.  With failed offsets (*flags set) node_off is not read: every mesh gets
-// the empty range nnz_off[m] = 0 (k_batch_rows has zeroed the row pointers).
-__global__ void k_batch_meshes(const int32_t* __restrict__ uptr, const int64_t* __restrict__ node_off,
-                               int64_t n_mesh, const uint32_t* __restrict__ flags, int32_t* __restrict__ out_ptr,
-                               int64_t* __restrict__ nnz_off, uint32_t* __restrict__ status) {
+// One thread per mesh: its closing row pointer and its first entry in col_idx / vals (its
+// other row pointers and its columns come from k_final, in the mesh's own numbering);
+// nnz_off[n_mesh] already holds the batch total.  row_ptr of mesh m occupies
+// out_ptr[node_off[m] + m .. node_off[m+1] + m].  Folds the offset-check flags into the
+// status word.  With failed offsets (*flags set) node_off is not read: every mesh gets the
+// empty range nnz_off[m] = 0, and all row pointers are zeroed (here where the batch has no
+// node at all).
+static __global__ void k_batch_meshes(const uint32_t* __restrict__ ubase, const uint32_t* __restrict__ rowoff,
+                                      const SubBuckets sub, int64_t n_node, const int64_t* __restrict__ node_off,
+                                      int64_t n_mesh, const uint32_t* __restrict__ flags,
+                                      int32_t* __restrict__ out_ptr, int64_t* __restrict__ nnz_off,
+                                      uint32_t* __restrict__ status) {
   const int64_t m = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const uint32_t bad = *flags;
   if (m == 0 && bad) atomicOr(status, bad);
   if (m >= n_mesh) return;
   if (bad) {
     nnz_off[m] = 0;
+    if (n_node == 0) out_ptr[m] = 0;
     return;
   }
   const int64_t b = node_off[m], e = node_off[m + 1];
-  out_ptr[e + m] = uptr[e] - uptr[b];
-  nnz_off[m] = uptr[b];
+  const int way = sub.pick();
+  const int64_t nsub = sub.nsub[way];
+  const auto start = [&](int64_t i) {
+    return n_node == 0 ? (int64_t)0 : row_start(ubase, rowoff, sub.s2[way], n_node, nsub, i);
+  };
+  out_ptr[e + m] = (int32_t)(start(e) - start(b));
+  nnz_off[m] = start(b);
 }
 
 }  // namespace kb

@@ -165,9 +165,9 @@ __device__ __forceinline__ void scan_chunk_down(const int32_t* in, int64_t n, co
   }
 }
 
-// n == 0: out[0] = 0
+// n == 0: out[0] = 0 (optional)
 static __global__ void k_scan_empty(int32_t* __restrict__ out, int64_t* __restrict__ total64) {
-  out[0] = 0;
+  if (out) out[0] = 0;
   if (total64) *total64 = 0;
 }
 

@@ -276,7 +276,7 @@ int launch_pass3(const Plan& p, unsigned char* ws, V* tres, int64_t* nnz_dev, hi
 
 template <typename V>
 int assemble_tail(const Plan& p, unsigned char* ws, int32_t* row_ptr, int32_t* col_idx, V* vals, int64_t cap,
-                  int64_t* nnz_dev, uint32_t* status, Events& ev, hipStream_t s, const Carry* cr) {
+                  int64_t* nnz_dev, uint32_t* status, Events& ev, hipStream_t s, const Carry* cr, const BatchRows* br) {
   auto* bstart = (uint32_t*)(ws + p.o_bstart);
   auto* segbase = (uint32_t*)(ws + p.o_segbase);
   auto* hist2 = (uint32_t*)(ws + p.o_hist2);
@@ -341,15 +341,19 @@ int assemble_tail(const Plan& p, unsigned char* ws, int32_t* row_ptr, int32_t* c
     auto* ov_list = (const uint32_t*)(ws + p.o_ovl);
     auto* hvy = (const uint32_t*)(ws + p.o_hvy);
     const uint32_t par = heavy_par(p);
-    if (cr)
+    if (br)
+      k_final<V, false, true><<<gf, 256, 0, s>>>(sbb, ubase, tcol, tval, nullptr, rowoff, sub, p.nn, row_ptr, col_idx,
+                                                 vals, nullptr, nullptr, cap, status, ov_list, head + 1, hvy, par, *br);
+    else if (cr)
       k_final<V, true><<<gf, 256, 0, s>>>(sbb, ubase, tcol, tval, tres, rowoff, sub, p.nn, row_ptr, col_idx,
-                                          vals, (V*)cr->res_out, cr->rows_out, cap, status, ov_list, head + 1, hvy, par);
+                                          vals, (V*)cr->res_out, cr->rows_out, cap, status, ov_list, head + 1, hvy, par,
+                                          BatchRows{});
     else
       k_final<V><<<gf, 256, 0, s>>>(sbb, ubase, tcol, tval, nullptr, rowoff, sub, p.nn, row_ptr, col_idx,
-                                    vals, nullptr, nullptr, cap, status, ov_list, head + 1, hvy, par);
+                                    vals, nullptr, nullptr, cap, status, ov_list, head + 1, hvy, par, BatchRows{});
     KB_LAUNCH_CHECK();
   } else {
-    k_scan_empty<<<1, 1, 0, s>>>(row_ptr, nnz_dev);
+    k_scan_empty<<<1, 1, 0, s>>>(br ? nullptr : row_ptr, nnz_dev);
     KB_LAUNCH_CHECK();
   }
   KB_TRY(ev.rec(KB_N_STAGES));
@@ -359,7 +363,7 @@ int assemble_tail(const Plan& p, unsigned char* ws, int32_t* row_ptr, int32_t* c
 template <int NEN, Prec P>
 int build_impl(const Plan& p, const kb_mesh* m, const void* klow, unsigned char* ws, int32_t* row_ptr,
                int32_t* col_idx, void* vals, int64_t cap, int64_t* nnz_dev, uint32_t* status, Events& ev,
-               hipStream_t s, const Carry* cr = nullptr) {
+               hipStream_t s, const Carry* cr = nullptr, const BatchRows* br = nullptr) {
   using V = typename PrecTraits<P>::V;
   auto* hist = (uint32_t*)(ws + p.o_hist);
   auto* csum = (uint32_t*)(ws + p.o_csum);
@@ -447,7 +451,7 @@ int build_impl(const Plan& p, const kb_mesh* m, const void* klow, unsigned char*
                                                                  (const V*)cr->res, cr->nnz, p.csr_cap, p.nn, o, head);
     KB_LAUNCH_CHECK();
   }
-  return assemble_tail<V>(p, ws, row_ptr, col_idx, (V*)vals, cap, nnz_dev, status, ev, s, cr);
+  return assemble_tail<V>(p, ws, row_ptr, col_idx, (V*)vals, cap, nnz_dev, status, ev, s, cr, br);
 }
 
 template <int NEN, Prec P>
@@ -474,7 +478,7 @@ int integrate_impl(const Plan& p, const kb_mesh* m, void* vals, uint32_t* status
 // the instantiations of one precision
 #define KB_BUILD_INSTANCE(X, NEN, P)                                                                                 \
   X template int build_impl<NEN, P>(const Plan&, const kb_mesh*, const void*, unsigned char*, int32_t*, int32_t*, void*, \
-                                    int64_t, int64_t*, uint32_t*, Events&, hipStream_t, const Carry*);
+                                    int64_t, int64_t*, uint32_t*, Events&, hipStream_t, const Carry*, const BatchRows*);
 #define KB_INSTANCES(X, P)                                                                                         \
   KB_BUILD_INSTANCE(X, 4, P)                                                                                       \
   KB_BUILD_INSTANCE(X, 8, P)                                                                                       \
