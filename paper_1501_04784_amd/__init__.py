@@ -209,13 +209,16 @@ class Builder:
 
     def result(self, check: bool = True, allow_flags: int = 0) -> LowerCSR:
         """Synchronise and return the (trimmed) CSR; raise on data errors if ``check``."""
-        torch.cuda.current_stream().synchronize()
-        nnz = int(self.nnz_dev.item())
-        st = self.status.clone()
+        # the entry count and the status words in one copy to the host, which waits for the
+        # build (a synchronisation, two one-word copies and a clone took 30 us more)
+        words = torch.cat((self.nnz_dev.view(torch.int32), self.status))
+        host = words.cpu()
+        nnz = int(host[:2].view(torch.int64).item())
+        st = words[2:]
         res = LowerCSR(self.row_ptr, self.col_idx[:nnz] if nnz <= self.cap else self.col_idx[:0],
                        self.vals[:nnz] if nnz <= self.cap else self.vals[:0], nnz, st)
         if check:
-            _raise_on_flags(res.flags, allow_flags)
+            _raise_on_flags(int(host[2].item()) & 0xFFFFFFFF, allow_flags)
         return res
 
 
@@ -450,9 +453,10 @@ class AdjointBuilder:
 
     def result(self, check: bool = True, allow_flags: int = 0):
         """Synchronise and return (dL/dc, dL/dX); raise on data errors if ``check``."""
-        torch.cuda.current_stream().synchronize()
-        if check:
+        if check:  # (reading the status word waits for the kernels)
             _raise_on_flags(int(self.status[0].item()) & 0xFFFFFFFF, allow_flags)
+        else:
+            torch.cuda.current_stream().synchronize()
         return self.grad_coef, self.grad_coords
 
 
