@@ -453,23 +453,23 @@ __device__ __forceinline__ void flush_counts(const TileSlots<true>& sl, uint32_t
 // invalid elements contribute nothing.  With kDirect the last workgroup to finish turns
 // the counts into the sub-bucket starts sbb[0 .. nsub] and, in place, the write cursors.
 // With kAsk the samples decide, and the first workgroup tells the kernels after this one.
+// A workgroup counts `per` tiles; direct, where no tile has a histogram of its own, as one
+// (the slots are cleared and flushed once: 27M bricks 638 -> 516 us).
 template <int NEN, bool DIRECT>
-__device__ __forceinline__ void count_tile(uint32_t* s_h, const int32_t* __restrict__ conn, int64_t n_elem,
-                                           int64_t n_node, int te, int s1, int nb, int s2, int nsub, int mode,
-                                           uint32_t* __restrict__ hist, uint32_t* __restrict__ subcnt,
-                                           uint32_t* __restrict__ status) {
-  const TileSlots<DIRECT> sl(s_h, s_h + kSlotsHash, mode, s1, nb, s2, nsub);
-  const int64_t t = blockIdx.x;
-  sl.clear(blockDim.x);
-  __syncthreads();
-  const int64_t e0 = t * te, e1 = (e0 + te < n_elem) ? e0 + te : n_elem;
-  uint32_t flags = 0;
-  for (int64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
+__device__ __forceinline__ void count_elements(const TileSlots<DIRECT>& sl, const int32_t* __restrict__ conn,
+                                               int64_t e0, int64_t e1, int64_t n_node, uint32_t* __restrict__ subcnt,
+                                               uint32_t* flags) {
+  int32_t En[NEN];
+  int64_t e = e0 + threadIdx.x;
+  if (e < e1) load_conn<NEN>(conn, e, En);
+  for (; e < e1; e += blockDim.x) {
     int32_t E[NEN];
-    load_conn<NEN>(conn, e, E);
+#pragma unroll
+    for (int a = 0; a < NEN; ++a) E[a] = En[a];
+    if (e + blockDim.x < e1) load_conn<NEN>(conn, e + blockDim.x, En);
     const uint32_t f = check_conn<NEN>(E, n_node);
     if (f) {
-      flags |= f;
+      *flags |= f;
       continue;
     }
     int r[NEN];
@@ -479,32 +479,95 @@ __device__ __forceinline__ void count_tile(uint32_t* s_h, const int32_t* __restr
     if constexpr (DIRECT) {
 #pragma unroll
       for (int a = 0; a < NEN; ++a)
-        if (q[a] == kNoSlot) atomicAdd(&subcnt[E[a] >> s2], (uint32_t)(r[a] + 1));
+        if (q[a] == kNoSlot) atomicAdd(&subcnt[E[a] >> sl.shift], (uint32_t)(r[a] + 1));
+    }
+  }
+}
+
+// Elements of more than 8 rows come in tiles of a few dozen: a lane takes one row of an
+// element (1M bricks of 3 components, 31 elements a tile: 501 -> 436 us).  s_E: LDS for te
+// elements' ids, then a word each (its errors).
+template <int NEN, bool DIRECT>
+__device__ __forceinline__ void count_rows(const TileSlots<DIRECT>& sl, uint32_t* s_E, const int32_t* __restrict__ conn,
+                                           int64_t e0, int64_t e1, int te, int64_t n_node,
+                                           uint32_t* __restrict__ subcnt, uint32_t* flags) {
+  uint32_t* s_bad = s_E + te * NEN;
+  for (; e0 < e1; e0 += te) {
+    const int ne = (int)(e1 - e0 < te ? e1 - e0 : te), n = ne * NEN;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) s_E[i] = (uint32_t)conn[e0 * NEN + i];
+    for (int i = threadIdx.x; i < ne; i += blockDim.x) s_bad[i] = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+      const int el = i / NEN, a = i - el * NEN;
+      const int32_t Ea = (int32_t)s_E[i];
+      uint32_t f = Ea < 0 || Ea >= n_node ? KB_F_INDEX : 0u;
+#pragma unroll
+      for (int b = 0; b < NEN; ++b) f |= b != a && (int32_t)s_E[el * NEN + b] == Ea ? KB_F_REPEAT : 0u;
+      if (f) atomicOr(&s_bad[el], f);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+      const int el = i / NEN;
+      if (s_bad[el]) {
+        *flags |= s_bad[el];
+        continue;
+      }
+      const int32_t Ea = (int32_t)s_E[i];
+      uint32_t r = 0;
+#pragma unroll
+      for (int b = 0; b < NEN; ++b) r += (int32_t)s_E[el * NEN + b] < Ea ? 1u : 0u;
+      const uint32_t s = sl.find((uint32_t)(Ea >> sl.shift));
+      if (DIRECT && s == kNoSlot)
+        atomicAdd(&subcnt[Ea >> sl.shift], r + 1);
+      else
+        atomicAdd(&sl.cnt[s], r + 1);
+    }
+    __syncthreads();
+  }
+}
+
+template <int NEN, bool DIRECT>
+__device__ __forceinline__ void count_tiles(uint32_t* s_h, const int32_t* __restrict__ conn, int64_t n_elem,
+                                            int64_t n_node, int te, int64_t ntiles, int per, int slot_words, int s1, int nb,
+                                            int s2, int nsub, int mode, uint32_t* __restrict__ hist,
+                                            uint32_t* __restrict__ subcnt, uint32_t* __restrict__ status) {
+  const TileSlots<DIRECT> sl(s_h, s_h + kSlotsHash, mode, s1, nb, s2, nsub);
+  const int64_t t0 = (int64_t)blockIdx.x * per, t1 = t0 + per < ntiles ? t0 + per : ntiles;
+  uint32_t flags = 0;
+  for (int64_t t = t0; t < t1; ++t) {
+    sl.clear(blockDim.x);
+    __syncthreads();
+    const int64_t e0 = t * te, n = DIRECT ? (t1 - t0) * te : te, e1 = e0 + n < n_elem ? e0 + n : n_elem;
+    if constexpr (NEN > 8)
+      count_rows<NEN>(sl, s_h + slot_words, conn, e0, e1, te, n_node, subcnt, &flags);
+    else
+      count_elements<NEN>(sl, conn, e0, e1, n_node, subcnt, &flags);
+    __syncthreads();
+    if constexpr (DIRECT) {
+      flush_counts(sl, subcnt);
+      break;
+    } else {
+      for (int b = threadIdx.x; b < nb; b += blockDim.x) hist[t * nb + b] = s_h[b];
+      // (a lane clears the counters that it has written out)
     }
   }
   if (flags) raise_flag(status, flags);
-  __syncthreads();
-  if constexpr (DIRECT) {
-    flush_counts(sl, subcnt);
-  } else {
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) hist[t * nb + b] = s_h[b];
-  }
 }
 
 template <int NEN>
 __global__ __launch_bounds__(256) void k_count(const int32_t* __restrict__ conn, int64_t n_elem, int64_t n_node,
-                                               int te, int s1, int nb, int s2, int nsub, int mode,
-                                               uint32_t* head, uint32_t* __restrict__ hist,
+                                               int te, int64_t ntiles, int per, int slot_words, int s1, int nb, int s2,
+                                               int nsub, int mode, uint32_t* head, uint32_t* __restrict__ hist,
                                                uint32_t* __restrict__ subcnt, uint32_t* __restrict__ sbb,
                                                uint32_t* __restrict__ status) {
   extern __shared__ uint32_t s_h[];  // the slots' counters, then (hash) their keys
   const bool direct = mode == kAsk ? votes_direct(head + kHeadVotes) : mode == kDirect;
   if (mode == kAsk && blockIdx.x == 0 && threadIdx.x == 0) head[kHeadWay] = direct ? 1u : 0u;
   if (direct) {
-    count_tile<NEN, true>(s_h, conn, n_elem, n_node, te, s1, nb, s2, nsub, mode, hist, subcnt, status);
+    count_tiles<NEN, true>(s_h, conn, n_elem, n_node, te, ntiles, per, slot_words, s1, nb, s2, nsub, mode, hist, subcnt, status);
     if (mode == kDirect) last_block_starts(subcnt, nsub, sbb, &head[3], gridDim.x);
   } else {
-    count_tile<NEN, false>(s_h, conn, n_elem, n_node, te, s1, nb, s2, nsub, mode, hist, subcnt, status);
+    count_tiles<NEN, false>(s_h, conn, n_elem, n_node, te, ntiles, per, slot_words, s1, nb, s2, nsub, mode, hist, subcnt, status);
   }
 }
 
@@ -747,29 +810,45 @@ __device__ __forceinline__ void pass1_stage(const Pass1Smem<V, BLOCK, DIRECT>& s
   }
 }
 
-// write the staged pairs: index i lies in slot b, local start cnt[b]
+// write the staged pairs: index i lies in slot b, local start cnt[b].  kWriteBatch pairs of
+// a lane are under way together: each takes two dependent reads of LDS, and few waves share
+// a CU here (pass 1 of 27M bricks FP64 6.60 -> 6.50 ms, of 1M bricks FP32 260 -> 255 us).
+constexpr int kWriteBatch = 4;
 template <typename V, int BLOCK, bool DIRECT>
 __device__ __forceinline__ void pass1_write(const Pass1Smem<V, BLOCK, DIRECT>& sm, const PairOut<V>& o,
                                             uint32_t n_items) {
-  constexpr int nthreads = BLOCK;
-  if constexpr (DIRECT) {
-    for (uint32_t i = threadIdx.x; i < n_items; i += nthreads) {
-      const uint64_t key = sm.key[i];
-      const uint32_t b = (uint32_t)(key >> 32);
-      const uint32_t g = sm.base[b] + (i - sm.sl.cnt[b]);
+  const auto put = [&](uint32_t g, uint64_t key, V v) {
+    if constexpr (DIRECT) {
       o.key2[g] = (uint32_t)key;
-      o.val2[g] = sm.val[i];
+    } else {
+      o.row1[g] = (uint16_t)((uint32_t)(key >> 32) & ((1u << o.s1) - 1));  // row within its bucket
+      o.col1[g] = (uint32_t)key;
     }
-    return;
+    (DIRECT ? o.val2 : o.val1)[g] = v;
+  };
+  const auto slot = [&](uint64_t key) { return (uint32_t)(key >> 32) >> (DIRECT ? 0 : o.s1); };
+  uint32_t i = threadIdx.x;
+  for (; i + (kWriteBatch - 1) * BLOCK < n_items; i += kWriteBatch * BLOCK) {
+    uint64_t key[kWriteBatch];
+    V v[kWriteBatch];
+    uint32_t g[kWriteBatch];
+#pragma unroll
+    for (int u = 0; u < kWriteBatch; ++u) {
+      key[u] = sm.key[i + u * BLOCK];
+      v[u] = sm.val[i + u * BLOCK];
+    }
+#pragma unroll
+    for (int u = 0; u < kWriteBatch; ++u) {
+      const uint32_t b = slot(key[u]);
+      g[u] = sm.base[b] + (i + u * BLOCK - sm.sl.cnt[b]);
+    }
+#pragma unroll
+    for (int u = 0; u < kWriteBatch; ++u) put(g[u], key[u], v[u]);
   }
-  for (uint32_t i = threadIdx.x; i < n_items; i += nthreads) {
+  for (; i < n_items; i += BLOCK) {
     const uint64_t key = sm.key[i];
-    const uint32_t row = (uint32_t)(key >> 32);
-    const int b = (int)(row >> o.s1);
-    const uint32_t g = sm.base[b] + (i - sm.sl.cnt[b]);
-    o.row1[g] = (uint16_t)(row & ((1u << o.s1) - 1));  // row within its bucket
-    o.col1[g] = (uint32_t)key;
-    o.val1[g] = sm.val[i];
+    const uint32_t b = slot(key);
+    put(sm.base[b] + (i - sm.sl.cnt[b]), key, sm.val[i]);
   }
 }
 
@@ -879,61 +958,115 @@ __global__ __launch_bounds__(BLOCK) void k_pass1(const int32_t* __restrict__ con
     pass1_tile<NEN, P, FROM_VALUES, BLOCK, OP, false>(smem, E, coords4, coef, klow, n_elem, n_node, tau, o, emax, status);
 }
 
-// Bricks in FP64 from coordinates (one element per lane at the register limit): two
-// tiles per workgroup of 2 BLOCK lanes, so that each SIMD holds two waves while the
-// elements are gathered and integrated.  The two tiles are then counted, staged and
-// written one after the other through the one staging area (BLOCK elements' pairs).
-// Workgroup w takes tiles 2w and 2w + 1, XCD-contiguously as k_pass1.
+// The tiles of a persistent workgroup: XCD x owns one contiguous range of the tiles and its
+// workgroups walk it interleaved, so neighbouring runs meet in one L2.
+struct TileWalk {
+  int64_t t, hi, step;
+  __device__ __forceinline__ explicit TileWalk(int64_t ntiles) {
+    const int64_t G = gridDim.x, x = blockIdx.x % kXcds, w = blockIdx.x / kXcds;
+    step = G / kXcds + (x < G % kXcds ? 1 : 0);
+    const int64_t lo = x * (ntiles / kXcds) + min(x, ntiles % kXcds);
+    hi = lo + ntiles / kXcds + (x < ntiles % kXcds ? 1 : 0);
+    t = lo + w;
+  }
+};
+
+// coordinates that are not read again: a later conditional gather otherwise keeps them in
+// registers as the value of the lanes that do not gather
+template <int N>
+__device__ __forceinline__ void forget(double (&x)[N][3]) {
+#pragma unroll
+  for (int a = 0; a < N; ++a)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) asm volatile("" : "=v"(x[a][c]));
+}
+
+// Bricks in FP64 from coordinates (an element per lane): two tiles per workgroup of 2 BLOCK
+// lanes, so that each SIMD holds two waves while the elements are gathered and integrated.
+// The two tiles are then counted, staged and written one after the other through the one
+// staging area (BLOCK elements' pairs, which fill the CU's LDS).  Persistent: with one
+// workgroup on a CU nothing else covers its start and its gathers, so the next two tiles'
+// connectivity is loaded while these are integrated and their nodes are gathered while the
+// last one is written (27M bricks: 6.5 -> 5.5 ms).
 template <int NEN, Prec P, int BLOCK, Op OP, bool DIRECT>
-__device__ __forceinline__ void pass1_two(unsigned char* smem, const int32_t (&E)[NEN], const double4* __restrict__ coords4,
-    const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau, int64_t ntiles,
-    const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
+__device__ __forceinline__ void pass1_two(unsigned char* smem, const int32_t* __restrict__ conn,
+    const double4* __restrict__ coords4, const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau,
+    int64_t ntiles, const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
     uint32_t* __restrict__ status) {
   using V = typename PrecTraits<P>::V;
   using SM = Pass1Smem<V, 2 * BLOCK, DIRECT>;
   constexpr int T = ElemTraits<NEN>::T;
   const SM sm(smem, BLOCK * T, o);
-  const int64_t w = xcd_item(blockIdx.x, gridDim.x);
+  TileWalk walk((ntiles + 1) / 2);  // pairs of tiles
+  if (walk.t >= walk.hi) return;
   const int half = threadIdx.x >= BLOCK ? 1 : 0;
-  const int64_t e = (2 * w + half) * BLOCK + (threadIdx.x - half * BLOCK);
   if (threadIdx.x == 0) *sm.emax = 0;
-  const bool valid = e < n_elem && check_conn<NEN>(E, n_node) == 0;
+  const auto fetch = [&](int64_t w, int32_t (&E)[NEN]) {
+    const int64_t e = w * (2 * BLOCK) + threadIdx.x;
+    if (w >= walk.hi || e >= n_elem) return false;
+    load_conn<NEN>(conn, e, E);
+    return check_conn<NEN>(E, n_node) == 0;
+  };
+  int32_t E[NEN];
+  bool valid = fetch(walk.t, E);
   double Xn[NEN][3];
   double c_e = 0.0;
   if (valid) {
     gather_nodes<NEN>(NodesPadded{coords4}, E, Xn);
-    c_e = coef[e];
+    c_e = coef[walk.t * (2 * BLOCK) + threadIdx.x];
   }
-  uint32_t flags = 0, fb = 0;
-  V k[T];
-  for (int h = 0; h < 2; ++h) {
-    const int64_t t = 2 * w + h;
-    if (t >= ntiles) break;
-    sm.begin(o, t);
-    __syncthreads();
-    uint32_t q[NEN];
-    const bool mine = valid && half == h;
-    if (mine) {
-      int r[NEN];
-      node_ranks<NEN>(E, r);
-      reserve_rows<NEN, 0>(sm.sl, E, r, q);
-    }
-    __syncthreads();
-    const uint32_t n_items = block_scan_array(sm.sl.cnt, sm.sl.n, sm.scan);
-    uint32_t gb[SM::kPerLane];
-    sm.take_bases(o, n_items, gb);
-    if (h == 0 && valid) {  // both tiles' elements (the first tile's counts hide the gathers)
+  uint32_t em = 0;  // largest value exponent seen by this lane
+  while (true) {
+    const int64_t w = walk.t;
+    uint32_t flags = 0, fb = 0;
+    V k[T];
+    if (valid) {  // both tiles' elements
       element_values_at<NEN, P, OP>(Xn, c_e, tau, k, &flags, &fb);
-      atomicMax(sm.emax, values_emax<T>(k));
+      const uint32_t me = values_emax<T>(k);
+      em = me > em ? me : em;
     }
-    if (mine) pass1_stage<NEN, 0>(sm, o, E, q, PackedValues<V, T>{k});
-    sm.put_bases(gb);
+    if (flags) raise_flag(status, flags);
+    if (fb) atomicAdd(&status[1], fb);
+    int32_t En[NEN];
+    const bool vn = fetch(w + walk.step, En);
+    uint32_t n_items;
+    for (int h = 0;; ++h) {
+      sm.begin(o, 2 * w + h);
+      __syncthreads();
+      uint32_t q[NEN];
+      const bool mine = valid && half == h;
+      if (mine) {
+        int r[NEN];
+        node_ranks<NEN>(E, r);
+        reserve_rows<NEN, 0>(sm.sl, E, r, q);
+      }
+      __syncthreads();
+      n_items = block_scan_array(sm.sl.cnt, sm.sl.n, sm.scan);
+      uint32_t gb[SM::kPerLane];
+      sm.take_bases(o, n_items, gb);
+      if (mine) pass1_stage<NEN, 0>(sm, o, E, q, PackedValues<V, T>{k});
+      sm.put_bases(gb);
+      if (h == 1 || 2 * w + 1 >= ntiles) break;
+      __syncthreads();
+      pass1_write(sm, o, n_items);
+      __syncthreads();  // the staging area is reused by the next tile
+    }
+#pragma unroll
+    for (int a = 0; a < NEN; ++a) E[a] = En[a];
+    valid = vn;
+    forget(Xn);
+    if (valid) {
+      gather_nodes<NEN>(NodesPadded{coords4}, E, Xn);
+      c_e = coef[(w + walk.step) * (2 * BLOCK) + threadIdx.x];
+    }
     __syncthreads();
     pass1_write(sm, o, n_items);
-    __syncthreads();  // the staging area is reused by the next tile
+    walk.t = w + walk.step;
+    if (walk.t >= walk.hi) break;
+    __syncthreads();
   }
-  if (flags) raise_flag(status, flags);
-  if (fb) atomicAdd(&status[1], fb);
+  if (em) atomicMax(sm.emax, em);
+  __syncthreads();
   if (threadIdx.x == 0 && *sm.emax) atomicMax(emax, *sm.emax);
 }
 
@@ -945,13 +1078,10 @@ __global__ __launch_bounds__(2 * BLOCK) void k_pass1_two(const int32_t* __restri
                                                        const PairOut<typename PrecTraits<P>::V> o,
                                                        uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char smem[];
-  int32_t E[NEN] = {};
-  const int64_t e = xcd_item(blockIdx.x, gridDim.x) * (2 * BLOCK) + threadIdx.x;
-  if (e < n_elem) load_conn<NEN>(conn, e, E);  // under way while the branch waits for its word
   if (goes_direct(o.mode, o.way))
-    pass1_two<NEN, P, BLOCK, OP, true>(smem, E, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_two<NEN, P, BLOCK, OP, true>(smem, conn, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
   else
-    pass1_two<NEN, P, BLOCK, OP, false>(smem, E, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_two<NEN, P, BLOCK, OP, false>(smem, conn, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
 }
 
 // offsets of the lane's four rows R0 .. R0+3 in their slots (two levels: per-row atomics
@@ -968,19 +1098,6 @@ __device__ __forceinline__ void pair_reserve_half(const TileSlots<DIRECT>& sl, c
     }
   }
 }
-
-// The tiles of a persistent workgroup: XCD x owns one contiguous range of the tiles and its
-// workgroups walk it interleaved, so neighbouring runs meet in one L2.
-struct TileWalk {
-  int64_t t, hi, step;
-  __device__ __forceinline__ explicit TileWalk(int64_t ntiles) {
-    const int64_t G = gridDim.x, x = blockIdx.x % kXcds, w = blockIdx.x / kXcds;
-    step = G / kXcds + (x < G % kXcds ? 1 : 0);
-    const int64_t lo = x * (ntiles / kXcds) + min(x, ntiles % kXcds);
-    hi = lo + ntiles / kXcds + (x < ntiles % kXcds ? 1 : 0);
-    t = lo + w;
-  }
-};
 
 // Bricks, stiffness matrix: a lane pair per element (element_values_pair), BLOCK lanes
 // and BLOCK / 2 elements per tile.  Twice the waves of one lane per element for the same
@@ -1054,6 +1171,7 @@ __device__ __forceinline__ void pass1_pair(unsigned char* smem, const int32_t* _
 #pragma unroll
     for (int a = 0; a < NEN; ++a) E[a] = En[a];
     valid = vn;
+    forget(xo);
     if (valid) {
       gather_pair(NodesPadded{coords4}, E, h, xo);
       c_e = coef[tn * TE + (threadIdx.x >> 1)];

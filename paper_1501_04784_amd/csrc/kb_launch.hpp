@@ -33,6 +33,10 @@ constexpr int kHTMin = 512, kHTMax = 4096;
 // compute unit one
 constexpr int64_t kDirectRuns = 1 << 19;
 constexpr int64_t kDirectTiles = 256;
+// elements that a workgroup of k_count takes (in whole tiles), as long as kCountGroups
+// workgroups per CU are left
+constexpr int64_t kCountElems = 1024;
+constexpr int64_t kCountGroups = 16;
 constexpr int kSmallTile = 64;
 constexpr double kHalfTileRatio = 16;   // pairs per tile x bucket histogram entry
 constexpr size_t kWideStage = 112640;  // staged pair bytes per pass-1 tile, elements of > 8 rows
@@ -120,9 +124,9 @@ PairOut<V> pair_out(const Plan& p, unsigned char* ws) {
 
 // persistent workgroups of pass 1: those that fit on the device at once (LDS-bound), at
 // least one per XCD slot (b % 8) that owns tiles
-inline unsigned persistent_grid(const Plan& p, int threads) {
+inline unsigned persistent_grid(const Plan& p, int threads, int64_t ntiles) {
   const int per_cu = std::max(1, (int)(163840 / std::max<size_t>(p.lds1, 1)));
-  return (unsigned)std::min<int64_t>(p.ntiles,
+  return (unsigned)std::min<int64_t>(ntiles,
                                      std::max<int64_t>(8, (int64_t)p.cus * std::min(per_cu, 2048 / threads)));
 }
 
@@ -138,7 +142,7 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
     // (in FP64 the pair kernel sits at the register limit and was slower on 1M bricks)
     auto kern = k_pass1_pair<P, 2 * BLOCK>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<persistent_grid(p, 2 * BLOCK), 2 * BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, p.nel, p.nn, p.tau,
+    kern<<<persistent_grid(p, 2 * BLOCK, p.ntiles), 2 * BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, p.nel, p.nn, p.tau,
                                                                   p.ntiles, o, emax, status);
     KB_LAUNCH_CHECK();
     return KB_OK;
@@ -147,8 +151,8 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
     // bricks in FP64: two tiles per workgroup (two waves per SIMD while integrating)
     auto kern = k_pass1_two<NEN, P, BLOCK, OP>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<(unsigned)div_up(p.ntiles, 2), 2 * BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, p.nel, p.nn, p.tau,
-                                                                  p.ntiles, o, emax, status);
+    kern<<<persistent_grid(p, 2 * BLOCK, div_up(p.ntiles, 2)), 2 * BLOCK, p.lds1, s>>>(
+        m->conn, coords4, m->coef, p.nel, p.nn, p.tau, p.ntiles, o, emax, status);
     KB_LAUNCH_CHECK();
     return KB_OK;
   }
@@ -161,7 +165,7 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
     // tetrahedra: persistent
     auto kern = k_pass1_tet<P, FROM_VALUES, BLOCK, OP>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<persistent_grid(p, BLOCK), BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, (const V*)klow, p.nel, p.nn, p.tau, p.ntiles,
+    kern<<<persistent_grid(p, BLOCK, p.ntiles), BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, (const V*)klow, p.nel, p.nn, p.tau, p.ntiles,
                                              o, emax, status);
   }
   KB_LAUNCH_CHECK();
@@ -401,8 +405,12 @@ int build_impl(const Plan& p, const kb_mesh* m, const void* klow, unsigned char*
                                          : (size_t)std::max(p.nb, 1);
   if (p.ntiles > 0) {
     // with no nodes every element has an index error: flagged, nothing counted
-    k_count<NEN><<<(unsigned)p.ntiles, 256, 4 * slots, s>>>(m->conn, p.nel, p.nn, p.tile, p.nb > 0 ? p.s1 : 30, p.nb,
-                                                            p.s2d, (int)p.nsub_d, p.mode, head, hist, subcnt, sbb, status);
+    const int per = (int)std::max<int64_t>(
+        1, std::min<int64_t>(kCountElems / p.tile, p.ntiles / (kCountGroups * (int64_t)p.cus)));
+    const size_t ids = NEN > 8 ? (size_t)p.tile * (NEN + 1) : 0;
+    k_count<NEN><<<(unsigned)div_up(p.ntiles, per), 256, 4 * (slots + ids), s>>>(
+        m->conn, p.nel, p.nn, p.tile, p.ntiles, per, (int)slots, p.nb > 0 ? p.s1 : 30, p.nb, p.s2d, (int)p.nsub_d, p.mode, head, hist,
+        subcnt, sbb, status);
     KB_LAUNCH_CHECK();
   }
   if (ntc > 0) {
