@@ -1886,7 +1886,8 @@ __global__ __launch_bounds__(256) void k_pass3(uint32_t* __restrict__ ikey, V* _
         uint64_t c0;
         int64_t c1;
         to_chunks(vv[u], F, c0, c1);
-        atomicAdd(&s_lo[h], (unsigned long long)c0);
+        // (a float within 2^23 of the largest is a multiple of 2^48: 20.25M tets, 671 -> 655 us)
+        if (sizeof(V) == 8 || c0) atomicAdd(&s_lo[h], (unsigned long long)c0);
         atomicAdd(&s_hi[h], (unsigned long long)c1);
       }
     }
@@ -1963,6 +1964,7 @@ __global__ __launch_bounds__(256) void k_pass3(uint32_t* __restrict__ ikey, V* _
     const uint32_t row = k >> colbits, col = k & cmask;
     const uint32_t ro = s_ro[row], nr = s_rc[row];
     uint32_t rank = 0;
+#pragma unroll 4
     for (uint32_t q = 0; q < nr; ++q) rank += (s_lcol[ro + q] < col) ? 1u : 0u;
     const uint32_t pos = ro + rank;
     tcol[beg + pos] = (int32_t)col;
