@@ -368,20 +368,24 @@ __device__ __forceinline__ void reserve_rows(const TileSlots<DIRECT>& sl, const 
 }
 
 // ---------------------------------------------------------------------- begin, count
+__device__ __forceinline__ double4 padded(const double* __restrict__ coords, int64_t i) {
+  return make_double4(coords[3 * i], coords[3 * i + 1], coords[3 * i + 2], 0.0);
+}
+
 // First kernel of a build.  Workgroups 0 .. kSamples-1: workgroup 0 clears the status (if
 // not null), the entry count and the head words; with kAsk, workgroup i samples the tile at
 // i / kSamples of the elements.  The others clear n_zero words at every stride-th word of
-// zero (n_tab times: the row counts of the heavy sub-buckets' tables), and the sub-bucket counters and copy the coordinates into
-// 32-byte records (out4 null: none).
+// zero (n_tab times: the row counts of the heavy sub-buckets' tables), and the sub-bucket counters,
+// and pad the coordinates of the first n_pad nodes (k_count).
 template <int NEN>
 __global__ __launch_bounds__(256) void k_begin(const int32_t* __restrict__ conn, int64_t n_elem, int64_t n_node,
                                                int tile, int64_t ntiles, int s2, int mode,
                                                uint32_t* __restrict__ status, int64_t* __restrict__ nnz,
                                                uint32_t* __restrict__ head, uint32_t* __restrict__ subcnt,
                                                int64_t nsub, const double* __restrict__ coords,
-                                               double4* __restrict__ out4, uint32_t* __restrict__ zero, int n_tab,
-                                               int stride, int n_zero) {
-  constexpr int kSet = 2048;
+                                               double4* __restrict__ coords4, int64_t n_pad,
+                                               uint32_t* __restrict__ zero, int n_tab, int stride, int n_zero) {
+  constexpr int kSet = NEN == 4 ? 8192 : 4096;  // twice the sub-buckets of a random tile
   __shared__ uint32_t s_set[kSet];
   __shared__ uint32_t s_runs, s_pairs;
   if (blockIdx.x >= kSamples) {
@@ -390,9 +394,7 @@ __global__ __launch_bounds__(256) void k_begin(const int32_t* __restrict__ conn,
     for (int64_t i = i0; i < (int64_t)n_tab * n_zero; i += step) zero[i / n_zero * stride + i % n_zero] = 0u;
     if (mode != kTwoLevel)
       for (int64_t i = i0; i < nsub; i += step) subcnt[i] = 0u;
-    if (out4)
-      for (int64_t i = i0; i < n_node; i += step)
-        out4[i] = make_double4(coords[3 * i], coords[3 * i + 1], coords[3 * i + 2], 0.0);
+    for (int64_t i = i0; i < n_pad; i += step) coords4[i] = padded(coords, i);
     return;
   }
   if (blockIdx.x == 0) {
@@ -410,10 +412,8 @@ __global__ __launch_bounds__(256) void k_begin(const int32_t* __restrict__ conn,
   const int64_t t = ntiles * blockIdx.x / kSamples;
   const int64_t e0 = t * tile, e1 = e0 + tile < n_elem ? e0 + tile : n_elem;
   uint32_t runs = 0, pairs = 0;
-  for (int64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
-    int32_t E[NEN];
-    load_conn<NEN>(conn, e, E);
-    if (check_conn<NEN>(E, n_node)) continue;
+  const auto add = [&](const int32_t (&E)[NEN]) {
+    if (check_conn<NEN>(E, n_node)) return;
     pairs += NEN * (NEN + 1) / 2;
 #pragma unroll
     for (int a = 0; a < NEN; ++a) {
@@ -423,13 +423,26 @@ __global__ __launch_bounds__(256) void k_begin(const int32_t* __restrict__ conn,
       int p = 0;
 #pragma unroll 1
       for (; p < 16; ++p) {
-        const uint32_t k = atomicCAS(&s_set[h], kEmptyKey, x);
-        if (k == kEmptyKey) ++runs;
+        uint32_t k = __hip_atomic_load(&s_set[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (k == kEmptyKey) {
+          k = atomicCAS(&s_set[h], kEmptyKey, x);
+          if (k == kEmptyKey) ++runs;
+        }
         if (k == kEmptyKey || k == x) break;
         h = (h + 1) & (kSet - 1);
       }
       if (p == 16) ++runs;  // a full set: no locality
     }
+  };
+  constexpr int kAhead = NEN > 8 ? 1 : 4;  // elements of a lane loaded together
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += kAhead * blockDim.x) {
+    int32_t E[kAhead][NEN];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (e + u * blockDim.x < e1) load_conn<NEN>(conn, e + u * blockDim.x, E[u]);
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (e + u * blockDim.x < e1) add(E[u]);
   }
   if (runs) atomicAdd(&s_runs, runs);
   if (pairs) atomicAdd(&s_pairs, pairs);
@@ -528,11 +541,11 @@ __device__ __forceinline__ void count_rows(const TileSlots<DIRECT>& sl, uint32_t
 
 template <int NEN, bool DIRECT>
 __device__ __forceinline__ void count_tiles(uint32_t* s_h, const int32_t* __restrict__ conn, int64_t n_elem,
-                                            int64_t n_node, int te, int64_t ntiles, int per, int slot_words, int s1, int nb,
-                                            int s2, int nsub, int mode, uint32_t* __restrict__ hist,
+                                            int64_t n_node, int te, int64_t ntiles, uint32_t n_pad, int per, int slot_words,
+                                            int s1, int nb, int s2, int nsub, int mode, uint32_t* __restrict__ hist,
                                             uint32_t* __restrict__ subcnt, uint32_t* __restrict__ status) {
   const TileSlots<DIRECT> sl(s_h, s_h + kSlotsHash, mode, s1, nb, s2, nsub);
-  const int64_t t0 = (int64_t)blockIdx.x * per, t1 = t0 + per < ntiles ? t0 + per : ntiles;
+  const int64_t t0 = (int64_t)(blockIdx.x - n_pad) * per, t1 = t0 + per < ntiles ? t0 + per : ntiles;
   uint32_t flags = 0;
   for (int64_t t = t0; t < t1; ++t) {
     sl.clear(blockDim.x);
@@ -554,20 +567,34 @@ __device__ __forceinline__ void count_tiles(uint32_t* s_h, const int32_t* __rest
   if (flags) raise_flag(status, flags);
 }
 
+// Under a random numbering pass 1 gathers its coordinates from 32-byte records, each in one
+// cache line: the first n_pad workgroups copy those of the nodes from pad0 on.  The direct
+// way gathers the 24-byte records as given, whose lines its tiles share, and saves the copy
+// (27M bricks: 0.31 of 13.6 ms); the nodes before pad0 are copied beside the sampling, which
+// takes as long, before the way is known.
 template <int NEN>
 __global__ __launch_bounds__(256) void k_count(const int32_t* __restrict__ conn, int64_t n_elem, int64_t n_node,
                                                int te, int64_t ntiles, int per, int slot_words, int s1, int nb, int s2,
                                                int nsub, int mode, uint32_t* head, uint32_t* __restrict__ hist,
                                                uint32_t* __restrict__ subcnt, uint32_t* __restrict__ sbb,
-                                               uint32_t* __restrict__ status) {
+                                               uint32_t* __restrict__ status, uint32_t n_pad,
+                                               const double* __restrict__ coords, double4* __restrict__ coords4,
+                                               int64_t pad0) {
   extern __shared__ uint32_t s_h[];  // the slots' counters, then (hash) their keys
   const bool direct = mode == kAsk ? votes_direct(head + kHeadVotes) : mode == kDirect;
-  if (mode == kAsk && blockIdx.x == 0 && threadIdx.x == 0) head[kHeadWay] = direct ? 1u : 0u;
+  if (mode == kAsk && blockIdx.x == n_pad && threadIdx.x == 0) head[kHeadWay] = direct ? 1u : 0u;
+  if (blockIdx.x < n_pad) {
+    if (direct) return;
+    const int64_t step = (int64_t)n_pad * blockDim.x;
+    for (int64_t i = pad0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_node; i += step)
+      coords4[i] = padded(coords, i);
+    return;
+  }
   if (direct) {
-    count_tiles<NEN, true>(s_h, conn, n_elem, n_node, te, ntiles, per, slot_words, s1, nb, s2, nsub, mode, hist, subcnt, status);
+    count_tiles<NEN, true>(s_h, conn, n_elem, n_node, te, ntiles, n_pad, per, slot_words, s1, nb, s2, nsub, mode, hist, subcnt, status);
     if (mode == kDirect) last_block_starts(subcnt, nsub, sbb, &head[3], gridDim.x);
   } else {
-    count_tiles<NEN, false>(s_h, conn, n_elem, n_node, te, ntiles, per, slot_words, s1, nb, s2, nsub, mode, hist, subcnt, status);
+    count_tiles<NEN, false>(s_h, conn, n_elem, n_node, te, ntiles, n_pad, per, slot_words, s1, nb, s2, nsub, mode, hist, subcnt, status);
   }
 }
 
@@ -887,11 +914,15 @@ __device__ __forceinline__ void read_values(const V* __restrict__ klow, int64_t 
   if (!finite) *flags |= KB_F_NONFINITE;
 }
 
+// where pass 1 gathers its coordinates (k_count)
+template <bool DIRECT>
+using PassNodes = std::conditional_t<DIRECT, NodesXYZ, NodesPadded>;
+
 // Bricks: one tile per workgroup; tiles are assigned XCD-contiguously, so the runs that
 // neighbouring tiles write side by side meet in one L2.  OP: the integrand (unless the
 // values are given).
 template <int NEN, Prec P, bool FROM_VALUES, int BLOCK, Op OP, bool DIRECT>
-__device__ __forceinline__ void pass1_tile(unsigned char* smem, const int32_t (&E)[NEN], const double4* __restrict__ coords4,
+__device__ __forceinline__ void pass1_tile(unsigned char* smem, const int32_t (&E)[NEN], const PassNodes<DIRECT> nodes,
     const double* __restrict__ coef, const typename PrecTraits<P>::V* __restrict__ klow,
     int64_t n_elem, int64_t n_node, float tau, const PairOut<typename PrecTraits<P>::V>& o,
     uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
@@ -908,7 +939,7 @@ __device__ __forceinline__ void pass1_tile(unsigned char* smem, const int32_t (&
   double c_e = 0.0;
   if constexpr (!FROM_VALUES) {
     if (valid) {
-      gather_nodes<NEN>(NodesPadded{coords4}, E, Xn);
+      gather_nodes<NEN>(nodes, E, Xn);
       c_e = coef[e];
     }
   }
@@ -942,7 +973,8 @@ __device__ __forceinline__ void pass1_tile(unsigned char* smem, const int32_t (&
 }
 
 template <int NEN, Prec P, bool FROM_VALUES, int BLOCK, Op OP = Op::Stiffness>
-__global__ __launch_bounds__(BLOCK) void k_pass1(const int32_t* __restrict__ conn, const double4* __restrict__ coords4,
+__global__ __launch_bounds__(BLOCK) void k_pass1(const int32_t* __restrict__ conn, const double* __restrict__ coords,
+                                               const double4* __restrict__ coords4,
                                                const double* __restrict__ coef,
                                                const typename PrecTraits<P>::V* __restrict__ klow, int64_t n_elem,
                                                int64_t n_node, float tau,
@@ -953,9 +985,9 @@ __global__ __launch_bounds__(BLOCK) void k_pass1(const int32_t* __restrict__ con
   const int64_t e = xcd_item(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
   if (e < n_elem) load_conn<NEN>(conn, e, E);  // under way while the branch waits for its word
   if (goes_direct(o.mode, o.way))
-    pass1_tile<NEN, P, FROM_VALUES, BLOCK, OP, true>(smem, E, coords4, coef, klow, n_elem, n_node, tau, o, emax, status);
+    pass1_tile<NEN, P, FROM_VALUES, BLOCK, OP, true>(smem, E, NodesXYZ{coords}, coef, klow, n_elem, n_node, tau, o, emax, status);
   else
-    pass1_tile<NEN, P, FROM_VALUES, BLOCK, OP, false>(smem, E, coords4, coef, klow, n_elem, n_node, tau, o, emax, status);
+    pass1_tile<NEN, P, FROM_VALUES, BLOCK, OP, false>(smem, E, NodesPadded{coords4}, coef, klow, n_elem, n_node, tau, o, emax, status);
 }
 
 // The tiles of a persistent workgroup: XCD x owns one contiguous range of the tiles and its
@@ -990,7 +1022,7 @@ __device__ __forceinline__ void forget(double (&x)[N][3]) {
 // last one is written (27M bricks: 6.5 -> 5.5 ms).
 template <int NEN, Prec P, int BLOCK, Op OP, bool DIRECT>
 __device__ __forceinline__ void pass1_two(unsigned char* smem, const int32_t* __restrict__ conn,
-    const double4* __restrict__ coords4, const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau,
+    const PassNodes<DIRECT> nodes, const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau,
     int64_t ntiles, const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
     uint32_t* __restrict__ status) {
   using V = typename PrecTraits<P>::V;
@@ -1012,7 +1044,7 @@ __device__ __forceinline__ void pass1_two(unsigned char* smem, const int32_t* __
   double Xn[NEN][3];
   double c_e = 0.0;
   if (valid) {
-    gather_nodes<NEN>(NodesPadded{coords4}, E, Xn);
+    gather_nodes<NEN>(nodes, E, Xn);
     c_e = coef[walk.t * (2 * BLOCK) + threadIdx.x];
   }
   uint32_t em = 0;  // largest value exponent seen by this lane
@@ -1056,7 +1088,7 @@ __device__ __forceinline__ void pass1_two(unsigned char* smem, const int32_t* __
     valid = vn;
     forget(Xn);
     if (valid) {
-      gather_nodes<NEN>(NodesPadded{coords4}, E, Xn);
+      gather_nodes<NEN>(nodes, E, Xn);
       c_e = coef[(w + walk.step) * (2 * BLOCK) + threadIdx.x];
     }
     __syncthreads();
@@ -1072,6 +1104,7 @@ __device__ __forceinline__ void pass1_two(unsigned char* smem, const int32_t* __
 
 template <int NEN, Prec P, int BLOCK, Op OP = Op::Stiffness>
 __global__ __launch_bounds__(2 * BLOCK) void k_pass1_two(const int32_t* __restrict__ conn,
+                                                       const double* __restrict__ coords,
                                                        const double4* __restrict__ coords4,
                                                        const double* __restrict__ coef, int64_t n_elem, int64_t n_node,
                                                        float tau, int64_t ntiles,
@@ -1079,9 +1112,9 @@ __global__ __launch_bounds__(2 * BLOCK) void k_pass1_two(const int32_t* __restri
                                                        uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (goes_direct(o.mode, o.way))
-    pass1_two<NEN, P, BLOCK, OP, true>(smem, conn, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_two<NEN, P, BLOCK, OP, true>(smem, conn, NodesXYZ{coords}, coef, n_elem, n_node, tau, ntiles, o, emax, status);
   else
-    pass1_two<NEN, P, BLOCK, OP, false>(smem, conn, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_two<NEN, P, BLOCK, OP, false>(smem, conn, NodesPadded{coords4}, coef, n_elem, n_node, tau, ntiles, o, emax, status);
 }
 
 // offsets of the lane's four rows R0 .. R0+3 in their slots (two levels: per-row atomics
@@ -1107,7 +1140,7 @@ __device__ __forceinline__ void pair_reserve_half(const TileSlots<DIRECT>& sl, c
 // gathered while the current one is written.
 template <Prec P, int BLOCK, bool DIRECT>
 __device__ __forceinline__ void pass1_pair(unsigned char* smem, const int32_t* __restrict__ conn,
-    const double4* __restrict__ coords4, const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau,
+    const PassNodes<DIRECT> nodes, const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau,
     int64_t ntiles, const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
     uint32_t* __restrict__ status) {
   using V = typename PrecTraits<P>::V;
@@ -1129,7 +1162,7 @@ __device__ __forceinline__ void pass1_pair(unsigned char* smem, const int32_t* _
   double xo[4][3];
   double c_e = 0.0;
   if (valid) {
-    gather_pair(NodesPadded{coords4}, E, h, xo);
+    gather_pair(nodes, E, h, xo);
     c_e = coef[walk.t * TE + (threadIdx.x >> 1)];
   }
   uint32_t em = 0;  // largest value exponent seen by this lane
@@ -1173,7 +1206,7 @@ __device__ __forceinline__ void pass1_pair(unsigned char* smem, const int32_t* _
     valid = vn;
     forget(xo);
     if (valid) {
-      gather_pair(NodesPadded{coords4}, E, h, xo);
+      gather_pair(nodes, E, h, xo);
       c_e = coef[tn * TE + (threadIdx.x >> 1)];
     }
     __syncthreads();
@@ -1189,6 +1222,7 @@ __device__ __forceinline__ void pass1_pair(unsigned char* smem, const int32_t* _
 
 template <Prec P, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_pass1_pair(const int32_t* __restrict__ conn,
+                                                    const double* __restrict__ coords,
                                                     const double4* __restrict__ coords4,
                                                     const double* __restrict__ coef, int64_t n_elem, int64_t n_node,
                                                     float tau, int64_t ntiles,
@@ -1196,9 +1230,9 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_pair(const int32_t* __restrict_
                                                     uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (goes_direct(o.mode, o.way))
-    pass1_pair<P, BLOCK, true>(smem, conn, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_pair<P, BLOCK, true>(smem, conn, NodesXYZ{coords}, coef, n_elem, n_node, tau, ntiles, o, emax, status);
   else
-    pass1_pair<P, BLOCK, false>(smem, conn, coords4, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_pair<P, BLOCK, false>(smem, conn, NodesPadded{coords4}, coef, n_elem, n_node, tau, ntiles, o, emax, status);
 }
 
 // Tetrahedra: persistent workgroups.  XCD x owns one contiguous range of tiles and its
@@ -1206,7 +1240,7 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_pair(const int32_t* __restrict_
 // tile's connectivity is loaded while the current tile is integrated, and its node
 // coordinates while the current tile is written.
 template <Prec P, bool FROM_VALUES, int BLOCK, Op OP, bool DIRECT>
-__device__ __forceinline__ void pass1_tet(unsigned char* smem, const int32_t* __restrict__ conn, const double4* __restrict__ coords4,
+__device__ __forceinline__ void pass1_tet(unsigned char* smem, const int32_t* __restrict__ conn, const PassNodes<DIRECT> nodes,
     const double* __restrict__ coef, const typename PrecTraits<P>::V* __restrict__ klow,
     int64_t n_elem, int64_t n_node, float tau, int64_t ntiles,
     const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
@@ -1237,7 +1271,7 @@ __device__ __forceinline__ void pass1_tet(unsigned char* smem, const int32_t* __
   double c_e = 0.0;
   if constexpr (!FROM_VALUES) {
     if (valid) {
-      gather_nodes<NEN>(NodesPadded{coords4}, E, Xn);
+      gather_nodes<NEN>(nodes, E, Xn);
       c_e = coef[t * BLOCK + threadIdx.x];
     }
   }
@@ -1278,7 +1312,7 @@ __device__ __forceinline__ void pass1_tet(unsigned char* smem, const int32_t* __
     valid = vn;
     if constexpr (!FROM_VALUES) {
       if (valid) {
-        gather_nodes<NEN>(NodesPadded{coords4}, E, Xn);
+        gather_nodes<NEN>(nodes, E, Xn);
         c_e = coef[tn * BLOCK + threadIdx.x];
       }
     }
@@ -1295,6 +1329,7 @@ __device__ __forceinline__ void pass1_tet(unsigned char* smem, const int32_t* __
 
 template <Prec P, bool FROM_VALUES, int BLOCK, Op OP = Op::Stiffness>
 __global__ __launch_bounds__(BLOCK) void k_pass1_tet(const int32_t* __restrict__ conn,
+                                                   const double* __restrict__ coords,
                                                    const double4* __restrict__ coords4,
                                                    const double* __restrict__ coef,
                                                    const typename PrecTraits<P>::V* __restrict__ klow, int64_t n_elem,
@@ -1303,9 +1338,9 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_tet(const int32_t* __restrict__
                                                    uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (goes_direct(o.mode, o.way))
-    pass1_tet<P, FROM_VALUES, BLOCK, OP, true>(smem, conn, coords4, coef, klow, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_tet<P, FROM_VALUES, BLOCK, OP, true>(smem, conn, NodesXYZ{coords}, coef, klow, n_elem, n_node, tau, ntiles, o, emax, status);
   else
-    pass1_tet<P, FROM_VALUES, BLOCK, OP, false>(smem, conn, coords4, coef, klow, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_tet<P, FROM_VALUES, BLOCK, OP, false>(smem, conn, NodesPadded{coords4}, coef, klow, n_elem, n_node, tau, ntiles, o, emax, status);
 }
 
 // Elements of more than eight rows (nodes with several degrees of freedom), values

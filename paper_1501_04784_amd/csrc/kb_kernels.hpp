@@ -329,8 +329,8 @@ __device__ __forceinline__ void element_values(const NODES& nodes, const double*
 
 // Lane h of a pair gathers nodes 4h .. 4h+3 of its brick (a branch per half keeps every
 // index into E a constant).
-__device__ __forceinline__ void gather_pair(const NodesPadded& nodes, const int32_t (&E)[8], int h,
-                                            double (&xo)[4][3]) {
+template <typename NODES>
+__device__ __forceinline__ void gather_pair(const NODES& nodes, const int32_t (&E)[8], int h, double (&xo)[4][3]) {
   if (h) {
 #pragma unroll
     for (int a = 0; a < 4; ++a) nodes.get(E[4 + a], xo[a]);

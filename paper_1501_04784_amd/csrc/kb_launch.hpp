@@ -37,6 +37,8 @@ constexpr int64_t kDirectTiles = 256;
 // workgroups per CU are left
 constexpr int64_t kCountElems = 1024;
 constexpr int64_t kCountGroups = 16;
+constexpr int64_t kPadGroups = 16;  // workgroups per CU that pad the coordinates beside it
+constexpr int64_t kPadFirst = 1 << 20;  // nodes padded beside the sampling
 constexpr int kSmallTile = 64;
 constexpr double kHalfTileRatio = 16;   // pairs per tile x bucket histogram entry
 constexpr size_t kWideStage = 112640;  // staged pair bytes per pass-1 tile, elements of > 8 rows
@@ -142,7 +144,7 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
     // (in FP64 the pair kernel sits at the register limit and was slower on 1M bricks)
     auto kern = k_pass1_pair<P, 2 * BLOCK>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<persistent_grid(p, 2 * BLOCK, p.ntiles), 2 * BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, p.nel, p.nn, p.tau,
+    kern<<<persistent_grid(p, 2 * BLOCK, p.ntiles), 2 * BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef, p.nel, p.nn, p.tau,
                                                                   p.ntiles, o, emax, status);
     KB_LAUNCH_CHECK();
     return KB_OK;
@@ -152,20 +154,20 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
     auto kern = k_pass1_two<NEN, P, BLOCK, OP>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
     kern<<<persistent_grid(p, 2 * BLOCK, div_up(p.ntiles, 2)), 2 * BLOCK, p.lds1, s>>>(
-        m->conn, coords4, m->coef, p.nel, p.nn, p.tau, p.ntiles, o, emax, status);
+        m->conn, m->coords, coords4, m->coef, p.nel, p.nn, p.tau, p.ntiles, o, emax, status);
     KB_LAUNCH_CHECK();
     return KB_OK;
   }
   if constexpr (NEN == 8) {
     auto kern = k_pass1<NEN, P, FROM_VALUES, BLOCK, OP>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<(unsigned)p.ntiles, BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, (const V*)klow, p.nel, p.nn, p.tau, o,
+    kern<<<(unsigned)p.ntiles, BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef, (const V*)klow, p.nel, p.nn, p.tau, o,
                                                    emax, status);
   } else {
     // tetrahedra: persistent
     auto kern = k_pass1_tet<P, FROM_VALUES, BLOCK, OP>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<persistent_grid(p, BLOCK, p.ntiles), BLOCK, p.lds1, s>>>(m->conn, coords4, m->coef, (const V*)klow, p.nel, p.nn, p.tau, p.ntiles,
+    kern<<<persistent_grid(p, BLOCK, p.ntiles), BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef, (const V*)klow, p.nel, p.nn, p.tau, p.ntiles,
                                              o, emax, status);
   }
   KB_LAUNCH_CHECK();
@@ -384,17 +386,19 @@ int build_impl(const Plan& p, const kb_mesh* m, const void* klow, unsigned char*
   // tiles of running sums read back (grouped builds) follow the element tiles
   const int64_t ntc = (cr && cr->nnz && p.nb > 0) ? p.ntiles_csr : 0;
   const int64_t nt_all = p.ntiles + ntc;
+  // coordinates padded: the first of them by k_begin, the others by k_count
+  const int64_t n_pad = p.ntiles > 0 && p.mode != kDirect && p.nb > 0 && !klow ? p.nn : 0;
+  const int64_t pad0 = std::min<int64_t>(n_pad, kPadFirst);
   KB_TRY(ev.rec(KB_STAGE_INIT));
   {
     const bool first = !cr || cr->first;
-    const bool pad = p.ntiles > 0 && p.nb > 0 && !klow && p.nn > 0;
     auto* hvy = (uint32_t*)(ws + p.o_hvy);
     const int64_t n = std::max<int64_t>(
-        {pad ? p.nn : 0, p.mode != kTwoLevel ? p.nsub_d : 0, (int64_t)2 * kHvyRows * std::max(1u, heavy_par(p))});
+        {pad0, p.mode != kTwoLevel ? p.nsub_d : 0, (int64_t)2 * kHvyRows * std::max(1u, heavy_par(p))});
     k_begin<NEN><<<(unsigned)(kSamples + std::min<int64_t>(div_up(n, 256), 8192)), 256, 0, s>>>(
         m->conn, p.nel, p.nn, p.tile, p.ntiles, p.s2d, p.mode, first ? status : nullptr, first ? nnz_dev : nullptr,
-        head, subcnt, p.nsub_d, m->coords, pad ? (double4*)(ws + p.o_coords4) : nullptr, hvy + kHvyDigits * 2 + 1,
-        (int)heavy_par(p), kHvyWords, 2 * kHvyRows);
+        head, subcnt, p.nsub_d, m->coords, (double4*)(ws + p.o_coords4), pad0,
+        hvy + kHvyDigits * 2 + 1, (int)heavy_par(p), kHvyWords, 2 * kHvyRows);
     KB_LAUNCH_CHECK();
   }
 
@@ -408,9 +412,11 @@ int build_impl(const Plan& p, const kb_mesh* m, const void* klow, unsigned char*
     const int per = (int)std::max<int64_t>(
         1, std::min<int64_t>(kCountElems / p.tile, p.ntiles / (kCountGroups * (int64_t)p.cus)));
     const size_t ids = NEN > 8 ? (size_t)p.tile * (NEN + 1) : 0;
-    k_count<NEN><<<(unsigned)div_up(p.ntiles, per), 256, 4 * (slots + ids), s>>>(
-        m->conn, p.nel, p.nn, p.tile, p.ntiles, per, (int)slots, p.nb > 0 ? p.s1 : 30, p.nb, p.s2d, (int)p.nsub_d, p.mode, head, hist,
-        subcnt, sbb, status);
+    const int64_t n_count = div_up(p.ntiles, per);
+    const int64_t pad_groups = std::min<int64_t>(div_up(n_pad - pad0, 256), kPadGroups * (int64_t)p.cus);
+    k_count<NEN><<<(unsigned)(pad_groups + n_count), 256, 4 * (slots + ids), s>>>(
+        m->conn, p.nel, p.nn, p.tile, p.ntiles, per, (int)slots, p.nb > 0 ? p.s1 : 30, p.nb, p.s2d, (int)p.nsub_d,
+        p.mode, head, hist, subcnt, sbb, status, (uint32_t)pad_groups, m->coords, (double4*)(ws + p.o_coords4), pad0);
     KB_LAUNCH_CHECK();
   }
   if (ntc > 0) {
