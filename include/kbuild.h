@@ -93,10 +93,10 @@ extern "C" {
 
 /* stages recorded into kb_tuning.stage_events (KB_N_STAGES + 1 events) */
 #define KB_N_STAGES 8
-#define KB_STAGE_INIT 0       /* clear status                                              */
+#define KB_STAGE_INIT 0       /* clear status and counters, sample the numbering           */
 #define KB_STAGE_COUNT 1      /* validate connectivity, pairs per row bucket per tile       */
-#define KB_STAGE_OFFSETS 2    /* scan: each tile's write offset in each bucket; coordinates
-                                 copied into padded 32-byte records                        */
+#define KB_STAGE_OFFSETS 2    /* scan: each tile's write offset in each bucket, or the
+                                 places of the sub-buckets                                 */
 #define KB_STAGE_INTEGRATE 3  /* integrate (or read given values), partition by bucket     */
 #define KB_STAGE_HISTOGRAM 4  /* sub-bucket histogram per segment of a bucket, offsets      */
 #define KB_STAGE_PARTITION 5  /* partition each bucket into sub-buckets                     */
@@ -344,8 +344,8 @@ int kb_build_lower_csr_batched(const kb_batch* batch, int prec, const kb_tuning*
  * nnz is the number of entries of col_idx and w: no entry outside [0, nnz) is read,
  * and a row whose pointers fall outside it counts as missing from the pattern.
  * All arithmetic is FP64 whatever precision built K.  Node gradients are summed exactly
- * (fixed-point integers), so the output is bitwise deterministic; exact while no node
- * belongs to more than 65,536 elements.  A node pair of an element that is missing
+ * (fixed-point integers), so the output is bitwise deterministic, whatever a node's
+ * valence.  A node pair of an element that is missing
  * from the pattern sets KB_F_INDEX (its weight is taken as 0); elements with index
  * errors contribute nothing.  An element whose Jacobian determinant is not > 0 at some
  * integration point sets KB_F_INVERTED; one whose gradients are not finite (degenerate

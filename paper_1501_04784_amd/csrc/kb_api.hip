@@ -346,6 +346,7 @@ int make_batch_plan(const kb_batch* b, int prec, const kb_tuning* tu, BatchPlan*
     return o;
   };
   bp->o_gconn = take(4 * (size_t)bp->p.nen * (size_t)bp->p.nel);
+  take(4 * ((size_t)bp->p.nn + 1));  // not used: the size stays that of plans which stored the union's row pointers
   bp->o_flags = take(4);
   bp->total = off;
   return KB_OK;
