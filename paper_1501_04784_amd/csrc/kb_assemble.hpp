@@ -248,7 +248,11 @@ __device__ __forceinline__ V fixed_residual(uint64_t lo, uint64_t hi, int F, V h
 //     kDirectRuns runs in all): one LDS counter per sub-bucket;
 //   - kAsk: elements and nodes numbered with locality.  k_begin counts the sub-buckets
 //     that kSamples evenly spaced tiles touch, and every kernel after it takes the direct
-//     way if the sampled runs average at least kDirectRun pairs.  An LDS hash of
+//     way if the sampled runs average at least kDirectRun pairs.  A sample is the first
+//     256 elements of a tile: in grid order their runs have 115 pairs and more, and under
+//     a random numbering of the nodes a run is a node, about 30 at most (there the longest
+//     rows would overfill the direct way's tables: 95,000 tets in grid order with random
+//     nodes, pass 3 15 us on two levels and 117 direct).  An LDS hash of
 //     kSlotsHash slots then maps a tile's sub-buckets to counters; a row whose sub-bucket
 //     finds no slot takes its places one by one.
 // The sums are exact, so both ways give the same matrix bit for bit.
@@ -385,7 +389,7 @@ __global__ __launch_bounds__(256) void k_begin(const int32_t* __restrict__ conn,
                                                int64_t nsub, const double* __restrict__ coords,
                                                double4* __restrict__ coords4, int64_t n_pad,
                                                uint32_t* __restrict__ zero, int n_tab, int stride, int n_zero) {
-  constexpr int kSet = NEN == 4 ? 8192 : 4096;  // twice the sub-buckets of a random tile
+  constexpr int kSet = 4096;  // twice the sub-buckets of a random sample of bricks
   __shared__ uint32_t s_set[kSet];
   __shared__ uint32_t s_runs, s_pairs;
   if (blockIdx.x >= kSamples) {
@@ -412,8 +416,10 @@ __global__ __launch_bounds__(256) void k_begin(const int32_t* __restrict__ conn,
   const int64_t t = ntiles * blockIdx.x / kSamples;
   const int64_t e0 = t * tile, e1 = e0 + tile < n_elem ? e0 + tile : n_elem;
   uint32_t runs = 0, pairs = 0;
-  const auto add = [&](const int32_t (&E)[NEN]) {
-    if (check_conn<NEN>(E, n_node)) return;
+  const int64_t e = e0 + threadIdx.x;
+  int32_t E[NEN];
+  if (e < e1) load_conn<NEN>(conn, e, E);
+  if (e < e1 && check_conn<NEN>(E, n_node) == 0) {
     pairs += NEN * (NEN + 1) / 2;
 #pragma unroll
     for (int a = 0; a < NEN; ++a) {
@@ -433,16 +439,6 @@ __global__ __launch_bounds__(256) void k_begin(const int32_t* __restrict__ conn,
       }
       if (p == 16) ++runs;  // a full set: no locality
     }
-  };
-  constexpr int kAhead = NEN > 8 ? 1 : 4;  // elements of a lane loaded together
-  for (int64_t e = e0 + threadIdx.x; e < e1; e += kAhead * blockDim.x) {
-    int32_t E[kAhead][NEN];
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u)
-      if (e + u * blockDim.x < e1) load_conn<NEN>(conn, e + u * blockDim.x, E[u]);
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u)
-      if (e + u * blockDim.x < e1) add(E[u]);
   }
   if (runs) atomicAdd(&s_runs, runs);
   if (pairs) atomicAdd(&s_pairs, pairs);
