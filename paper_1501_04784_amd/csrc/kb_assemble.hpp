@@ -1454,7 +1454,7 @@ __global__ __launch_bounds__(kWideThreads) void k_pass1_wide(const int32_t* __re
 // elements' pairs.  Tiles of kCsrTile entries follow the element tiles.  The entries
 // are read only if they were written (nnz <= cap); rows outside [0, n_node) are skipped
 // (both kernels apply the same test, so counts and writes agree).
-constexpr int kCsrTile = 2048;
+constexpr int kCsrTile = 1792;  // three workgroups per CU beside the hash's slots (2048: two; grouped 20M tets 295 us, 1792: 239)
 
 __device__ __forceinline__ int64_t csr_entries(const int64_t* nnz_dev, int64_t cap) {
   const int64_t n = *nnz_dev;
