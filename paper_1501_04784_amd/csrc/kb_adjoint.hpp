@@ -13,8 +13,8 @@
 // Node gradients are sums over the elements at each node.  They are accumulated as the
 // same exact fixed-point integers as the assembly (scale from the largest exponent of
 // all element contributions; two 64-bit integer chunks per value), so the result does not
-// depend on the order of the additions: bitwise deterministic, and exact.  The corners are partitioned by node bucket first, so each
-// bucket's sums are formed in one workgroup's LDS:
+// depend on the order of the additions: bitwise deterministic, and exact.  The corners are
+// partitioned by node bucket first, so each bucket's sums are formed in one workgroup's LDS:
 //   k_adjoint_count   each corner's place within its bucket, and the bucket starts
 //   k_adjoint_elems   the gradients, one 32-byte record per corner at its place
 //   k_adjoint_reduce  a bucket's records summed, rounded once, written

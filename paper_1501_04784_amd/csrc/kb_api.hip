@@ -417,7 +417,8 @@ int launch_adjoint(const AdjointPlan& p, const kb_mesh* m, const int32_t* row_pt
       m->conn, nel, nn, p.bits, nb, cnt, start, rel, head, big);
   KB_LAUNCH_CHECK();
   if (nel > 0) {
-    k_adjoint_elems<NEN><<<grid_for(nel, kAdjElemThreads), kAdjElemThreads, 0, s>>>(m->conn, m->coords, m->coef, nel, nn, row_ptr, col_idx,
+    k_adjoint_elems<NEN><<<grid_for(nel, kAdjElemThreads), kAdjElemThreads, 0, s>>>(m->conn, m->coords, m->coef, nel,
+        nn, row_ptr, col_idx,
                                                             nnz, w, grad_coef, p.bits, start, rel, rec, acc, head,
                                                             big, status);
     KB_LAUNCH_CHECK();
@@ -637,7 +638,8 @@ static int grouped_pass(const GroupPlan& gp, const kb_mesh* mesh, int64_t g, con
   cr.rows_out = out.rows;
   const Carry* crp = gp.n_groups > 1 ? &cr : nullptr;
   Events& e = g == gp.n_groups - 1 ? ev : none;
-  if (p.nen == 8) return dispatch_build<8>(p, &mg, nullptr, w, out.rp, out.col, out.val, cap, out.nnz, status_dev, e, s, crp);
+  if (p.nen == 8) return dispatch_build<8>(p, &mg, nullptr, w, out.rp, out.col, out.val, cap, out.nnz, status_dev, e,
+      s, crp);
   return dispatch_build<4>(p, &mg, nullptr, w, out.rp, out.col, out.val, cap, out.nnz, status_dev, e, s, crp);
 }
 
@@ -728,9 +730,11 @@ int kb_build_lower_csr_batched(const kb_batch* batch, int prec, const kb_tuning*
   Events ev{tuning ? tuning->stage_events : nullptr, s};
   const BatchRows br{batch->node_off, nm, flags};
   if (p.nen == 8)
-    KB_TRY(dispatch_build<8>(p, &m, nullptr, w, row_ptr, col_idx, vals, cap, nnz_off + nm, status_dev, ev, s, nullptr, &br));
+    KB_TRY(dispatch_build<8>(p, &m, nullptr, w, row_ptr, col_idx, vals, cap, nnz_off + nm, status_dev, ev, s, nullptr,
+        &br));
   else
-    KB_TRY(dispatch_build<4>(p, &m, nullptr, w, row_ptr, col_idx, vals, cap, nnz_off + nm, status_dev, ev, s, nullptr, &br));
+    KB_TRY(dispatch_build<4>(p, &m, nullptr, w, row_ptr, col_idx, vals, cap, nnz_off + nm, status_dev, ev, s, nullptr,
+        &br));
   k_batch_meshes<<<grid_for(std::max<int64_t>(nm, 1), 256), 256, 0, s>>>(
       (const uint32_t*)(w + p.o_ubase), (const uint32_t*)(w + p.o_rowoff), sub_buckets(p, w), p.nn, batch->node_off,
       nm, flags, row_ptr, nnz_off, status_dev);

@@ -537,7 +537,8 @@ __device__ __forceinline__ void count_rows(const TileSlots<DIRECT>& sl, uint32_t
 
 template <int NEN, bool DIRECT>
 __device__ __forceinline__ void count_tiles(uint32_t* s_h, const int32_t* __restrict__ conn, int64_t n_elem,
-                                            int64_t n_node, int te, int64_t ntiles, uint32_t n_pad, int per, int slot_words,
+                                            int64_t n_node, int te, int64_t ntiles, uint32_t n_pad, int per,
+                                                int slot_words,
                                             int s1, int nb, int s2, int nsub, int mode, uint32_t* __restrict__ hist,
                                             uint32_t* __restrict__ subcnt, uint32_t* __restrict__ status) {
   const TileSlots<DIRECT> sl(s_h, s_h + kSlotsHash, mode, s1, nb, s2, nsub);
@@ -587,10 +588,12 @@ __global__ __launch_bounds__(256) void k_count(const int32_t* __restrict__ conn,
     return;
   }
   if (direct) {
-    count_tiles<NEN, true>(s_h, conn, n_elem, n_node, te, ntiles, n_pad, per, slot_words, s1, nb, s2, nsub, mode, hist, subcnt, status);
+    count_tiles<NEN, true>(s_h, conn, n_elem, n_node, te, ntiles, n_pad, per, slot_words, s1, nb, s2, nsub, mode,
+        hist, subcnt, status);
     if (mode == kDirect) last_block_starts(subcnt, nsub, sbb, &head[3], gridDim.x);
   } else {
-    count_tiles<NEN, false>(s_h, conn, n_elem, n_node, te, ntiles, n_pad, per, slot_words, s1, nb, s2, nsub, mode, hist, subcnt, status);
+    count_tiles<NEN, false>(s_h, conn, n_elem, n_node, te, ntiles, n_pad, per, slot_words, s1, nb, s2, nsub, mode,
+        hist, subcnt, status);
   }
 }
 
@@ -626,7 +629,8 @@ static __global__ __launch_bounds__(kScanThreads) void k_offsets_sums(const uint
 
 // one workgroup per bucket b: exclusive scan of csum[.][b] over the chunks, in place; the
 // bucket's total to tot[b].  Direct: one workgroup per chunk of subcnt.
-static __global__ __launch_bounds__(kScanThreads) void k_offsets_scan(uint32_t* __restrict__ csum, int64_t nchunk, int nb,
+static __global__ __launch_bounds__(kScanThreads) void k_offsets_scan(uint32_t* __restrict__ csum, int64_t nchunk,
+    int nb,
                                                                uint32_t* __restrict__ tot, uint32_t* subcnt,
                                                                int64_t nsub, const int32_t* __restrict__ part,
                                                                uint32_t* __restrict__ sbb, int mode,
@@ -679,7 +683,8 @@ static __global__ __launch_bounds__(1024) void k_bucket_starts(const uint32_t* _
 
 // counts of chunk c turned into offsets in place (grid as k_offsets_sums); the nb
 // workgroups after those write seg2b[s] = bucket of segment s
-static __global__ __launch_bounds__(256) void k_offsets_down(uint32_t* __restrict__ hist, const uint32_t* __restrict__ csum,
+static __global__ __launch_bounds__(256) void k_offsets_down(uint32_t* __restrict__ hist,
+    const uint32_t* __restrict__ csum,
                                                       const uint32_t* __restrict__ bstart, int64_t ntiles, int nb,
                                                       int64_t nchunk, const uint32_t* __restrict__ segbase,
                                                       uint32_t* __restrict__ seg2b, int mode,
@@ -787,10 +792,12 @@ struct PackedValues {
   }
 };
 
-// stage the pairs of local rows R0 .. R0+N-1 (values k(a, row, b) for row = R0 + a): the r+1 pairs of row E[a] go contiguously
-// into its slot's run (a row without a slot takes its places at once)
+// stage the pairs of local rows R0 .. R0+N-1 (values k(a, row, b) for row = R0 + a): the r+1
+// pairs of row E[a] go contiguously into its slot's run (a row without a slot takes its
+// places at once)
 template <int N, int R0, int NEN, typename V, int BLOCK, bool DIRECT, typename Values>
-__device__ __forceinline__ void pass1_stage(const Pass1Smem<V, BLOCK, DIRECT>& sm, const PairOut<V>& o, const int32_t (&E)[NEN],
+__device__ __forceinline__ void pass1_stage(const Pass1Smem<V, BLOCK, DIRECT>& sm, const PairOut<V>& o,
+    const int32_t (&E)[NEN],
                                             const uint32_t (&q)[N], const Values& k) {
 #pragma unroll
   for (int a = 0; a < N; ++a) {
@@ -981,9 +988,11 @@ __global__ __launch_bounds__(BLOCK) void k_pass1(const int32_t* __restrict__ con
   const int64_t e = xcd_item(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
   if (e < n_elem) load_conn<NEN>(conn, e, E);  // under way while the branch waits for its word
   if (goes_direct(o.mode, o.way))
-    pass1_tile<NEN, P, FROM_VALUES, BLOCK, OP, true>(smem, E, NodesXYZ{coords}, coef, klow, n_elem, n_node, tau, o, emax, status);
+    pass1_tile<NEN, P, FROM_VALUES, BLOCK, OP, true>(smem, E, NodesXYZ{coords}, coef, klow, n_elem, n_node, tau, o,
+        emax, status);
   else
-    pass1_tile<NEN, P, FROM_VALUES, BLOCK, OP, false>(smem, E, NodesPadded{coords4}, coef, klow, n_elem, n_node, tau, o, emax, status);
+    pass1_tile<NEN, P, FROM_VALUES, BLOCK, OP, false>(smem, E, NodesPadded{coords4}, coef, klow, n_elem, n_node, tau,
+        o, emax, status);
 }
 
 // The tiles of a persistent workgroup: XCD x owns one contiguous range of the tiles and its
@@ -1108,9 +1117,11 @@ __global__ __launch_bounds__(2 * BLOCK) void k_pass1_two(const int32_t* __restri
                                                        uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (goes_direct(o.mode, o.way))
-    pass1_two<NEN, P, BLOCK, OP, true>(smem, conn, NodesXYZ{coords}, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_two<NEN, P, BLOCK, OP, true>(smem, conn, NodesXYZ{coords}, coef, n_elem, n_node, tau, ntiles, o, emax,
+        status);
   else
-    pass1_two<NEN, P, BLOCK, OP, false>(smem, conn, NodesPadded{coords4}, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_two<NEN, P, BLOCK, OP, false>(smem, conn, NodesPadded{coords4}, coef, n_elem, n_node, tau, ntiles, o, emax,
+        status);
 }
 
 // offsets of the lane's four rows R0 .. R0+3 in their slots (two levels: per-row atomics
@@ -1236,7 +1247,8 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_pair(const int32_t* __restrict_
 // tile's connectivity is loaded while the current tile is integrated, and its node
 // coordinates while the current tile is written.
 template <Prec P, bool FROM_VALUES, int BLOCK, Op OP, bool DIRECT>
-__device__ __forceinline__ void pass1_tet(unsigned char* smem, const int32_t* __restrict__ conn, const PassNodes<DIRECT> nodes,
+__device__ __forceinline__ void pass1_tet(unsigned char* smem, const int32_t* __restrict__ conn,
+    const PassNodes<DIRECT> nodes,
     const double* __restrict__ coef, const typename PrecTraits<P>::V* __restrict__ klow,
     int64_t n_elem, int64_t n_node, float tau, int64_t ntiles,
     const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
@@ -1334,9 +1346,11 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_tet(const int32_t* __restrict__
                                                    uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (goes_direct(o.mode, o.way))
-    pass1_tet<P, FROM_VALUES, BLOCK, OP, true>(smem, conn, NodesXYZ{coords}, coef, klow, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_tet<P, FROM_VALUES, BLOCK, OP, true>(smem, conn, NodesXYZ{coords}, coef, klow, n_elem, n_node, tau, ntiles,
+        o, emax, status);
   else
-    pass1_tet<P, FROM_VALUES, BLOCK, OP, false>(smem, conn, NodesPadded{coords4}, coef, klow, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_tet<P, FROM_VALUES, BLOCK, OP, false>(smem, conn, NodesPadded{coords4}, coef, klow, n_elem, n_node, tau,
+        ntiles, o, emax, status);
 }
 
 // Elements of more than eight rows (nodes with several degrees of freedom), values
@@ -1351,7 +1365,8 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_tet(const int32_t* __restrict__
 constexpr int kWideThreads = 1024;  // threads per wide pass-1 workgroup (one per CU: LDS)
 
 template <int NEN, typename V, bool DIRECT>
-__device__ __forceinline__ void pass1_wide(unsigned char* smem, const int32_t* __restrict__ conn, const V* __restrict__ klow, int64_t n_elem, int64_t n_node,
+__device__ __forceinline__ void pass1_wide(unsigned char* smem, const int32_t* __restrict__ conn,
+    const V* __restrict__ klow, int64_t n_elem, int64_t n_node,
     int te, const PairOut<V>& o, uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   constexpr int T = ElemTraits<NEN>::T, NT = kWideThreads;
   using SM = Pass1Smem<V, NT, DIRECT>;
@@ -1437,7 +1452,8 @@ __device__ __forceinline__ void pass1_wide(unsigned char* smem, const int32_t* _
 }
 
 template <int NEN, typename V>
-__global__ __launch_bounds__(kWideThreads) void k_pass1_wide(const int32_t* __restrict__ conn, const V* __restrict__ klow,
+__global__ __launch_bounds__(kWideThreads) void k_pass1_wide(const int32_t* __restrict__ conn,
+    const V* __restrict__ klow,
                                                   int64_t n_elem, int64_t n_node, int te, const PairOut<V> o,
                                                   uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1454,7 +1470,8 @@ __global__ __launch_bounds__(kWideThreads) void k_pass1_wide(const int32_t* __re
 // elements' pairs.  Tiles of kCsrTile entries follow the element tiles.  The entries
 // are read only if they were written (nnz <= cap); rows outside [0, n_node) are skipped
 // (both kernels apply the same test, so counts and writes agree).
-constexpr int kCsrTile = 1792;  // three workgroups per CU beside the hash's slots (2048: two; grouped 20M tets 295 us, 1792: 239)
+// three workgroups per CU beside the hash's slots (2048: two; grouped 20M tets 295 us, 1792: 239)
+constexpr int kCsrTile = 1792;
 
 __device__ __forceinline__ int64_t csr_entries(const int64_t* nnz_dev, int64_t cap) {
   const int64_t n = *nnz_dev;
@@ -1505,7 +1522,8 @@ static __global__ __launch_bounds__(kCsrThreads) void k_hist_csr(const int32_t* 
 }
 
 template <typename V, bool DIRECT>
-__device__ __forceinline__ void pass1_csr(unsigned char* smem, const int32_t* __restrict__ rows, const int32_t* __restrict__ cols,
+__device__ __forceinline__ void pass1_csr(unsigned char* smem, const int32_t* __restrict__ rows,
+    const int32_t* __restrict__ cols,
     const V* __restrict__ vals, const V* __restrict__ res, const int64_t* __restrict__ nnz_dev,
     int64_t cap, int64_t n_node, const PairOut<V>& o, uint32_t* __restrict__ emax) {
   constexpr int NT = kCsrThreads, PER = kCsrPer;
@@ -1648,7 +1666,8 @@ __global__ __launch_bounds__(256) void k_hist2(const uint16_t* __restrict__ irow
 // hist2 over the bucket's segments (in place), then the sub-bucket starts
 // sbb[b * p2 + j] (sbb[nb * p2] = number of pairs).  A segment's run for sub-bucket j
 // starts at sbb[b * p2 + j] + hist2[s * p2 + j].
-static __global__ __launch_bounds__(256) void k_colscan(uint32_t* __restrict__ hist2, const uint32_t* __restrict__ bstart,
+static __global__ __launch_bounds__(256) void k_colscan(uint32_t* __restrict__ hist2,
+    const uint32_t* __restrict__ bstart,
                                                  const uint32_t* __restrict__ segbase, int nb, int p2,
                                                  uint32_t* __restrict__ sbb, int mode,
                                                  const uint32_t* __restrict__ way) {
@@ -3161,7 +3180,8 @@ __global__ __launch_bounds__(256) void k_final(const uint32_t* __restrict__ sbb,
     return;
   }
   if (blockIdx.x >= n_wave) {
-    final_heavy<V, GROUPED, BATCH>(sbb, ubase, tcol, tval, tres, rowoff, s2, n_node, nsub, ov_list, ov_count, hvy, col_idx,
+    final_heavy<V, GROUPED, BATCH>(sbb, ubase, tcol, tval, tres, rowoff, s2, n_node, nsub, ov_list, ov_count, hvy,
+        col_idx,
                             vals, res, rows, cap, batch, par, blockIdx.x - n_wave, kFinalHeavyGrid);
     return;
   }

@@ -239,7 +239,8 @@ __device__ __forceinline__ void walsh4(T x0, T x1, T x2, T x3, T& one, T& a, T& 
 
 // ---- brick, one precision for geometry (GT) and one for M / accumulation (AT) ----------
 // X[a][j] = x_j(node a) - x_j(node 0) for a = 1..7 (X[0] = 0).  k[36]: lower triangle of
-// the element integral (without c).  Returns false if some det is not > 0.  If CHECK, *need_fb is set when a point's Jacobian is ill-conditioned.
+// the element integral (without c).  Returns false if some det is not > 0.  If CHECK, *need_fb is
+// set when a point's Jacobian is ill-conditioned.
 template <typename GT, typename AT, bool CHECK>
 __device__ __forceinline__ bool hex_integrate(const GT (&X)[8][3], AT (&k)[36], GT tau, bool* need_fb) {
   GT C[kModes][3];

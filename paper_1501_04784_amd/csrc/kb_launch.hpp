@@ -66,9 +66,9 @@ struct Plan {
   int64_t csr_cap = 0, ntiles_csr = 0;  // running sums read back as pairs (grouped builds)
   size_t lds1 = 0, lds2 = 0, lds_csr = 0;
   // workspace offsets
-  size_t o_coords4 = 0, o_hist = 0, o_csum = 0, o_tot = 0, o_part = 0, o_bstart = 0, o_segbase = 0, o_hist2 = 0, o_seg2b = 0, o_head = 0,
-         o_dconn = 0, o_ovl = 0, o_hvy = 0, o_tres = 0, o_row1 = 0, o_col1 = 0, o_val1 = 0, o_key2 = 0, o_val2 = 0, o_sbb = 0, o_rowoff = 0, o_usub = 0, o_ubase = 0,
-         total = 0;
+  size_t o_coords4 = 0, o_hist = 0, o_csum = 0, o_tot = 0, o_part = 0, o_bstart = 0, o_segbase = 0, o_hist2 = 0,
+         o_seg2b = 0, o_head = 0, o_dconn = 0, o_ovl = 0, o_hvy = 0, o_tres = 0, o_row1 = 0, o_col1 = 0, o_val1 = 0,
+         o_key2 = 0, o_val2 = 0, o_sbb = 0, o_rowoff = 0, o_usub = 0, o_ubase = 0, total = 0;
 };
 
 struct Events {
@@ -144,7 +144,8 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
     // (in FP64 the pair kernel sits at the register limit and was slower on 1M bricks)
     auto kern = k_pass1_pair<P, 2 * BLOCK>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<persistent_grid(p, 2 * BLOCK, p.ntiles), 2 * BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef, p.nel, p.nn, p.tau,
+    kern<<<persistent_grid(p, 2 * BLOCK, p.ntiles), 2 * BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef,
+        p.nel, p.nn, p.tau,
                                                                   p.ntiles, o, emax, status);
     KB_LAUNCH_CHECK();
     return KB_OK;
@@ -161,13 +162,15 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
   if constexpr (NEN == 8) {
     auto kern = k_pass1<NEN, P, FROM_VALUES, BLOCK, OP>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<(unsigned)p.ntiles, BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef, (const V*)klow, p.nel, p.nn, p.tau, o,
+    kern<<<(unsigned)p.ntiles, BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef, (const V*)klow, p.nel, p.nn,
+        p.tau, o,
                                                    emax, status);
   } else {
     // tetrahedra: persistent
     auto kern = k_pass1_tet<P, FROM_VALUES, BLOCK, OP>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<persistent_grid(p, BLOCK, p.ntiles), BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef, (const V*)klow, p.nel, p.nn, p.tau, p.ntiles,
+    kern<<<persistent_grid(p, BLOCK, p.ntiles), BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef,
+        (const V*)klow, p.nel, p.nn, p.tau, p.ntiles,
                                              o, emax, status);
   }
   KB_LAUNCH_CHECK();
@@ -258,7 +261,8 @@ int launch_pass3(const Plan& p, unsigned char* ws, V* tres, int64_t* nnz_dev, hi
   k3<<<(unsigned)p.nsub, 256, (size_t)12 << std::max(p.s2, p.s2d), s>>>(
       key2, val2, sbb, sub, p.colbits, p.nn, head, tcol, tval, tres, rowoff, usub, ov_list, head + 1);
   KB_LAUNCH_CHECK();
-  const HeavyArgs<V> A{key2, val2, (uint32_t*)tcol, tval, tres, sbb, sub, p.s2, p.colbits, p.nn, 0, rowoff, usub, ov_list,
+  const HeavyArgs<V> A{key2, val2, (uint32_t*)tcol, tval, tres, sbb, sub, p.s2, p.colbits, p.nn, 0, rowoff, usub,
+      ov_list,
                        0, 0, (uint32_t*)(ws + p.o_hvy)};
   uint32_t* const ubase = p.nsub <= kScanHere ? (uint32_t*)(ws + p.o_ubase) : nullptr;
   const unsigned cus = (unsigned)std::max(1, p.cus);
@@ -269,7 +273,8 @@ int launch_pass3(const Plan& p, unsigned char* ws, V* tres, int64_t* nnz_dev, hi
   };
   constexpr size_t kTabLds = 4 * (size_t)(kHvyDigits + 2 * kHvyRows + 1 + kHeavyThreads / 64 + 1);
   if (!heavy_par(p))
-    return phase(k_heavy<V, RES, kHeavyRangesPhase, true>, (unsigned)std::min<int64_t>(std::max<int64_t>(p.nsub, 1), cus),
+    return phase(k_heavy<V, RES, kHeavyRangesPhase, true>, (unsigned)std::min<int64_t>(std::max<int64_t>(p.nsub, 1),
+        cus),
                  HeavySmem::bytes());
   KB_TRY(phase(k_heavy<V, RES, kHeavyRowsPhase>, 2 * cus, kTabLds));
   KB_TRY(phase(k_heavy<V, RES, kHeavyHistPhase>, 2 * cus, kTabLds));
