@@ -277,9 +277,21 @@ __device__ __forceinline__ bool votes_direct(const uint32_t* __restrict__ votes)
   return runs * kDirectRun <= pairs;
 }
 
-// *way: written by k_count
+// elements in random order too: runs of a few pairs (8 nodes of a brick: 4.5; in grid order
+// with random nodes 9)
+__device__ __forceinline__ bool votes_scattered(const uint32_t* __restrict__ votes) {
+  uint64_t runs = 0, pairs = 0;
+#pragma unroll
+  for (int i = 0; i < kSamples; ++i) {
+    runs += votes[2 * i];
+    pairs += votes[2 * i + 1];
+  }
+  return runs * 6 > pairs;
+}
+
+// *way: written by k_count (1: direct, 2: two levels, elements in random order)
 __device__ __forceinline__ bool goes_direct(int mode, const uint32_t* __restrict__ way) {
-  return mode == kAsk ? *way != 0 : mode == kDirect;
+  return mode == kAsk ? *way == 1 : mode == kDirect;
 }
 
 // The sub-buckets of each way: rows per sub-bucket 2^s2[way] and their number, way 1 being
@@ -579,7 +591,7 @@ __global__ __launch_bounds__(256) void k_count(const int32_t* __restrict__ conn,
                                                int64_t pad0) {
   extern __shared__ uint32_t s_h[];  // the slots' counters, then (hash) their keys
   const bool direct = mode == kAsk ? votes_direct(head + kHeadVotes) : mode == kDirect;
-  if (mode == kAsk && blockIdx.x == n_pad && threadIdx.x == 0) head[kHeadWay] = direct ? 1u : 0u;
+  if (mode == kAsk && blockIdx.x == n_pad && threadIdx.x == 0) head[kHeadWay] = direct ? 1u : votes_scattered(head + kHeadVotes) ? 2u : 0u;
   if (blockIdx.x < n_pad) {
     if (direct) return;
     const int64_t step = (int64_t)n_pad * blockDim.x;
@@ -996,11 +1008,18 @@ __global__ __launch_bounds__(BLOCK) void k_pass1(const int32_t* __restrict__ con
 }
 
 // The tiles of a persistent workgroup: XCD x owns one contiguous range of the tiles and its
-// workgroups walk it interleaved, so neighbouring runs meet in one L2.
+// G workgroups walk it interleaved, so neighbouring runs meet in one L2.  They drift apart,
+// though, and where runs are a few pairs long (many buckets, elements in random order) the
+// lines that neighbouring tiles share are then written in parts: such a mesh takes a
+// workgroup per tile, in the order of dispatch (17.9M bricks FP32, all random: pass 1 10.3 ->
+// 9.7 ms; with elements in grid order the walk is the faster one, 7.4 -> 7.0 ms).
+__device__ __forceinline__ uint32_t walkers(int mode, const uint32_t* __restrict__ way, uint32_t persist) {
+  return mode == kAsk && *way == 2 ? gridDim.x : persist;
+}
 struct TileWalk {
   int64_t t, hi, step;
-  __device__ __forceinline__ explicit TileWalk(int64_t ntiles) {
-    const int64_t G = gridDim.x, x = blockIdx.x % kXcds, w = blockIdx.x / kXcds;
+  __device__ __forceinline__ TileWalk(int64_t ntiles, int64_t G) {
+    const int64_t x = blockIdx.x % kXcds, w = blockIdx.x / kXcds;
     step = G / kXcds + (x < G % kXcds ? 1 : 0);
     const int64_t lo = x * (ntiles / kXcds) + min(x, ntiles % kXcds);
     hi = lo + ntiles / kXcds + (x < ntiles % kXcds ? 1 : 0);
@@ -1028,13 +1047,13 @@ __device__ __forceinline__ void forget(double (&x)[N][3]) {
 template <int NEN, Prec P, int BLOCK, Op OP, bool DIRECT>
 __device__ __forceinline__ void pass1_two(unsigned char* smem, const int32_t* __restrict__ conn,
     const PassNodes<DIRECT> nodes, const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau,
-    int64_t ntiles, const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
+    int64_t ntiles, int64_t G, const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
     uint32_t* __restrict__ status) {
   using V = typename PrecTraits<P>::V;
   using SM = Pass1Smem<V, 2 * BLOCK, DIRECT>;
   constexpr int T = ElemTraits<NEN>::T;
   const SM sm(smem, BLOCK * T, o);
-  TileWalk walk((ntiles + 1) / 2);  // pairs of tiles
+  TileWalk walk((ntiles + 1) / 2, G);  // pairs of tiles
   if (walk.t >= walk.hi) return;
   const int half = threadIdx.x >= BLOCK ? 1 : 0;
   if (threadIdx.x == 0) *sm.emax = 0;
@@ -1114,13 +1133,16 @@ __global__ __launch_bounds__(2 * BLOCK) void k_pass1_two(const int32_t* __restri
                                                        const double* __restrict__ coef, int64_t n_elem, int64_t n_node,
                                                        float tau, int64_t ntiles,
                                                        const PairOut<typename PrecTraits<P>::V> o,
-                                                       uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+                                                       uint32_t* __restrict__ emax, uint32_t* __restrict__ status,
+                                                           uint32_t persist) {
   extern __shared__ __align__(16) unsigned char smem[];
+  const uint32_t G = walkers(o.mode, o.way, persist);
+  if (blockIdx.x >= G) return;
   if (goes_direct(o.mode, o.way))
-    pass1_two<NEN, P, BLOCK, OP, true>(smem, conn, NodesXYZ{coords}, coef, n_elem, n_node, tau, ntiles, o, emax,
+    pass1_two<NEN, P, BLOCK, OP, true>(smem, conn, NodesXYZ{coords}, coef, n_elem, n_node, tau, ntiles, G, o, emax,
         status);
   else
-    pass1_two<NEN, P, BLOCK, OP, false>(smem, conn, NodesPadded{coords4}, coef, n_elem, n_node, tau, ntiles, o, emax,
+    pass1_two<NEN, P, BLOCK, OP, false>(smem, conn, NodesPadded{coords4}, coef, n_elem, n_node, tau, ntiles, G, o, emax,
         status);
 }
 
@@ -1148,13 +1170,13 @@ __device__ __forceinline__ void pair_reserve_half(const TileSlots<DIRECT>& sl, c
 template <Prec P, int BLOCK, bool DIRECT>
 __device__ __forceinline__ void pass1_pair(unsigned char* smem, const int32_t* __restrict__ conn,
     const PassNodes<DIRECT> nodes, const double* __restrict__ coef, int64_t n_elem, int64_t n_node, float tau,
-    int64_t ntiles, const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
+    int64_t ntiles, int64_t G, const PairOut<typename PrecTraits<P>::V>& o, uint32_t* __restrict__ emax,
     uint32_t* __restrict__ status) {
   using V = typename PrecTraits<P>::V;
   using SM = Pass1Smem<V, BLOCK, DIRECT>;
   constexpr int NEN = 8, T = ElemTraits<NEN>::T, TE = BLOCK / 2;
   const SM sm(smem, TE * T, o);
-  TileWalk walk(ntiles);
+  TileWalk walk(ntiles, G);
   if (walk.t >= walk.hi) return;
   const int h = (int)(threadIdx.x & 1);
   if (threadIdx.x == 0) *sm.emax = 0;
@@ -1234,12 +1256,16 @@ __global__ __launch_bounds__(BLOCK) void k_pass1_pair(const int32_t* __restrict_
                                                     const double* __restrict__ coef, int64_t n_elem, int64_t n_node,
                                                     float tau, int64_t ntiles,
                                                     const PairOut<typename PrecTraits<P>::V> o,
-                                                    uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
+                                                    uint32_t* __restrict__ emax, uint32_t* __restrict__ status,
+                                                        uint32_t persist) {
   extern __shared__ __align__(16) unsigned char smem[];
+  const uint32_t G = walkers(o.mode, o.way, persist);
+  if (blockIdx.x >= G) return;
   if (goes_direct(o.mode, o.way))
-    pass1_pair<P, BLOCK, true>(smem, conn, NodesXYZ{coords}, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_pair<P, BLOCK, true>(smem, conn, NodesXYZ{coords}, coef, n_elem, n_node, tau, ntiles, G, o, emax, status);
   else
-    pass1_pair<P, BLOCK, false>(smem, conn, NodesPadded{coords4}, coef, n_elem, n_node, tau, ntiles, o, emax, status);
+    pass1_pair<P, BLOCK, false>(smem, conn, NodesPadded{coords4}, coef, n_elem, n_node, tau, ntiles, G, o, emax,
+        status);
 }
 
 // Tetrahedra: persistent workgroups.  XCD x owns one contiguous range of tiles and its

@@ -132,6 +132,12 @@ inline unsigned persistent_grid(const Plan& p, int threads, int64_t ntiles) {
                                      std::max<int64_t>(8, (int64_t)p.cus * std::min(per_cu, 2048 / threads)));
 }
 
+// their grid where a workgroup per tile may be the better choice (TileWalk): the others
+// return, about 0.4 ns each, so only with so many buckets that a random tile's runs are short
+inline unsigned walk_grid(const Plan& p, unsigned persist, int64_t ntiles) {
+  return p.mode == kAsk && p.nb > 2 * kTargetBuckets ? (unsigned)std::max<int64_t>(persist, ntiles) : persist;
+}
+
 template <int NEN, Prec P, bool FROM_VALUES, int BLOCK, Op OP>
 int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsigned char* ws, uint32_t* status,
                        hipStream_t s) {
@@ -144,9 +150,9 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
     // (in FP64 the pair kernel sits at the register limit and was slower on 1M bricks)
     auto kern = k_pass1_pair<P, 2 * BLOCK>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<persistent_grid(p, 2 * BLOCK, p.ntiles), 2 * BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef,
-        p.nel, p.nn, p.tau,
-                                                                  p.ntiles, o, emax, status);
+    const unsigned persist = persistent_grid(p, 2 * BLOCK, p.ntiles);
+    kern<<<walk_grid(p, persist, p.ntiles), 2 * BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef, p.nel, p.nn,
+                                                                    p.tau, p.ntiles, o, emax, status, persist);
     KB_LAUNCH_CHECK();
     return KB_OK;
   }
@@ -154,8 +160,10 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
     // bricks in FP64: two tiles per workgroup (two waves per SIMD while integrating)
     auto kern = k_pass1_two<NEN, P, BLOCK, OP>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
-    kern<<<persistent_grid(p, 2 * BLOCK, div_up(p.ntiles, 2)), 2 * BLOCK, p.lds1, s>>>(
-        m->conn, m->coords, coords4, m->coef, p.nel, p.nn, p.tau, p.ntiles, o, emax, status);
+    const int64_t n2 = div_up(p.ntiles, 2);
+    const unsigned persist = persistent_grid(p, 2 * BLOCK, n2);
+    kern<<<walk_grid(p, persist, n2), 2 * BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef, p.nel, p.nn, p.tau,
+                                                              p.ntiles, o, emax, status, persist);
     KB_LAUNCH_CHECK();
     return KB_OK;
   }
