@@ -854,7 +854,9 @@ __device__ __forceinline__ void pass1_stage(const Pass1Smem<V, BLOCK, DIRECT>& s
 
 // write the staged pairs: index i lies in slot b, local start cnt[b].  kWriteBatch pairs of
 // a lane are under way together: each takes two dependent reads of LDS, and few waves share
-// a CU here (pass 1 of 27M bricks FP64 6.60 -> 6.50 ms, of 1M bricks FP32 260 -> 255 us).
+// a CU here (pass 1 of 27M bricks FP64 6.60 -> 6.50 ms).  Direct only: the short runs of the
+// two-level way then lose the order in which they share lines (17.9M bricks FP32, all
+// random: 8.8 -> 9.7 ms).
 constexpr int kWriteBatch = 4;
 template <typename V, int BLOCK, bool DIRECT>
 __device__ __forceinline__ void pass1_write(const Pass1Smem<V, BLOCK, DIRECT>& sm, const PairOut<V>& o,
@@ -870,7 +872,7 @@ __device__ __forceinline__ void pass1_write(const Pass1Smem<V, BLOCK, DIRECT>& s
   };
   const auto slot = [&](uint64_t key) { return (uint32_t)(key >> 32) >> (DIRECT ? 0 : o.s1); };
   uint32_t i = threadIdx.x;
-  for (; i + (kWriteBatch - 1) * BLOCK < n_items; i += kWriteBatch * BLOCK) {
+  for (; DIRECT && i + (kWriteBatch - 1) * BLOCK < n_items; i += kWriteBatch * BLOCK) {
     uint64_t key[kWriteBatch];
     V v[kWriteBatch];
     uint32_t g[kWriteBatch];
@@ -1012,7 +1014,7 @@ __global__ __launch_bounds__(BLOCK) void k_pass1(const int32_t* __restrict__ con
 // though, and where runs are a few pairs long (many buckets, elements in random order) the
 // lines that neighbouring tiles share are then written in parts: such a mesh takes a
 // workgroup per tile, in the order of dispatch (17.9M bricks FP32, all random: pass 1 10.3 ->
-// 9.7 ms; with elements in grid order the walk is the faster one, 7.4 -> 7.0 ms).
+// 9.7 ms; with elements in grid order the walk is the faster one, 7.4 -> 6.5 ms).
 __device__ __forceinline__ uint32_t walkers(int mode, const uint32_t* __restrict__ way, uint32_t persist) {
   return mode == kAsk && *way == 2 ? gridDim.x : persist;
 }
