@@ -299,13 +299,13 @@ __device__ __forceinline__ bool hex_integrate(const GT (&X)[8][3], AT (&k)[36], 
   return ok;
 }
 
-// value of the other lane of a pair (lanes 2i and 2i + 1)
-__device__ __forceinline__ float pair_other(float x) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false));  // quad_perm [1 0 3 2]
+// value of the other lane of a pair (lanes 2i and 2i + 1), both active
+__device__ __forceinline__ int pair_other(int x) {
+  return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, false);  // quad_perm [1 0 3 2]
 }
+__device__ __forceinline__ float pair_other(float x) { return __int_as_float(pair_other(__float_as_int(x))); }
 __device__ __forceinline__ double pair_other(double x) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), 0xB1, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), 0xB1, 0xF, 0xF, false);
+  const int lo = pair_other(__double2loint(x)), hi = pair_other(__double2hiint(x));
   return __hiloint2double(hi, lo);
 }
 

@@ -345,7 +345,7 @@ __device__ __forceinline__ void gather_pair(const NODES& nodes, const int32_t (&
 // coefficients from the coordinates relative to node 0, in FP64; the parts are exchanged,
 // and each lane integrates the four points of its half of the rule.  Lane h ends with
 // rows 4h .. 4h+3, k[a][b] = k_(4h+a, b).  Both lanes of a pair must be active together.
-// A half with an ill-conditioned point takes the FP64 geometry (counted for h = 0).
+// An ill-conditioned point in either half gives the element FP64 geometry (counted by h = 0).
 template <Prec P>
 __device__ __forceinline__ void element_values_pair(const double (&xo)[4][3], double c, float tau, int h,
                                                     typename PrecTraits<P>::V (&k)[4][8], uint32_t* f, uint32_t* fb) {
@@ -380,7 +380,8 @@ __device__ __forceinline__ void element_values_pair(const double (&xo)[4][3], do
     bool need_fb = false;
     ok = half_points<float, float, P == Prec::F32FB>(C, M, tau, &need_fb, h);
     if constexpr (P == Prec::F32FB) {
-      if (need_fb) {  // this half's points with FP64 geometry
+      const int other = pair_other((int)need_fb);  // (outside any branch: both lanes take part)
+      if (need_fb || other) {  // the element: both halves with FP64 geometry
         ok = half_points<double, float, false>(Cd, M, 0.0, nullptr, h);
         if (h == 0) *fb += 1;
       }
