@@ -93,11 +93,13 @@ __device__ __forceinline__ bool ill_conditioned(const T (&J)[3][3], const T (&A)
 // (+-g): J takes 8 additions an entry for all points together, and
 //   k_mn = sum_q dphi_m^T M(q) dphi_n
 // needs only the Walsh sums of M's six entries over the eight points.  About 1200
-// operations a brick against 2400 with G^T G formed corner by corner at every point; no
-// sum is longer or has larger terms, and rigid translation drops out exactly.
-// J is 8 times the Jacobian (the 1/8 of the shape functions left out), so M would be 8 times
-// and the corner values of k 512 times too large: kModalScale, a power of two, in 1 / det.
-constexpr double kModalScale = 1.0 / 512.0;
+// operations a brick against 2400 with G^T G formed corner by corner at every point, and
+// rigid translation drops out exactly.
+// The 1/8 of the shape functions is in the mode coefficients, so that J is the Jacobian and
+// its determinant and 1 / det span FP32's range as they do corner by corner (with J 8 times
+// the Jacobian a brick of side 1.8e12 had det = infinity and k = 0); the 1/64 of k's two
+// gradients is in its entries in modes (kModalScale).  Both are powers of two.
+constexpr double kModalScale = 1.0 / 64.0;
 constexpr int kModes = 7;
 
 // d phi_m / d xi_i as a set of coordinates multiplied together (bits: r 1, s 2, t 4), or -1
@@ -116,15 +118,15 @@ __host__ __device__ constexpr double gauss_power(int d) {
   return d == 0 ? 1.0 : d == 1 ? kGauss2 : d == 2 ? 1.0 / 3.0 : d == 3 ? kGauss2 / 3.0 : 1.0 / 9.0;
 }
 
-// mode coefficients (times 8) of a field with values x[8] at the corners: C[7], modes r s
-// t rs st tr rst.  half_modes: of the four corners of one face t = const (sum, r, s, rs).
+// mode coefficients of a field with values x[8] at the corners: C[7], modes r s t rs st tr
+// rst.  half_modes: the part of the four corners of one face t = const (sum, r, s, rs).
 template <typename T>
 __device__ __forceinline__ void half_modes(T x0, T x1, T x2, T x3, T (&h)[4]) {
   const T p0 = x1 + x0, m0 = x1 - x0, p1 = x2 + x3, m1 = x2 - x3;
-  h[0] = p0 + p1;
-  h[1] = m0 + m1;
-  h[2] = p1 - p0;
-  h[3] = m1 - m0;
+  h[0] = T(0.125) * (p0 + p1);
+  h[1] = T(0.125) * (m0 + m1);
+  h[2] = T(0.125) * (p1 - p0);
+  h[3] = T(0.125) * (m1 - m0);
 }
 template <typename T>
 __device__ __forceinline__ void corner_modes(const T (&X)[8][3], T (&C)[kModes][3]) {
@@ -143,7 +145,7 @@ __device__ __forceinline__ void corner_modes(const T (&X)[8][3], T (&C)[kModes][
   }
 }
 
-// kModalScale A^T A / det of one point (A = adj J, geometry GT; M in AT); returns det > 0,
+// A^T A / det of one point (A = adj J, geometry GT; M in AT); returns det > 0,
 // and sets *need_fb for an ill-conditioned J if CHECK
 template <typename GT, typename AT, bool CHECK>
 __device__ __forceinline__ bool point_metric(const GT (&J)[3][3], GT tau, bool* need_fb, AT (&M)[6]) {
@@ -152,7 +154,7 @@ __device__ __forceinline__ bool point_metric(const GT (&J)[3][3], GT tau, bool* 
   if (CHECK) {
     if (ill_conditioned(J, A, det, tau)) *need_fb = true;
   }
-  const AT f = AT(GT(kModalScale) / det);
+  const AT f = AT(GT(1) / det);
   AT B[3][3];  // f A: the scale of 1 / length, so that no product leaves the range of AT
 #pragma unroll
   for (int i = 0; i < 3; ++i)
@@ -188,8 +190,7 @@ __device__ __forceinline__ void modal_entry(const AT (&W)[6][8], AT (&K)[kModes]
   constexpr int m = MN / kModes, n = MN % kModes;
   if constexpr (n <= m) {
     constexpr int d = mode_degree(m) + mode_degree(n);
-    AT s = modal_sum<m, n, mode_term(m, n, 0)>(W);
-    if constexpr (d > 0) s *= AT(gauss_power(d));
+    const AT s = AT(kModalScale * gauss_power(d)) * modal_sum<m, n, mode_term(m, n, 0)>(W);
     K[m][n] = s;
     K[n][m] = s;
   }

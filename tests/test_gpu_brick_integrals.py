@@ -1,5 +1,5 @@
 """Brick integrals where the lanes that share a brick, the build and the integrals alone can
-differ: elements ill-conditioned at one end only."""
+differ: elements ill-conditioned at one end only, sides near the ends of FP32's range."""
 import numpy as np
 import pytest
 import torch
@@ -52,3 +52,19 @@ def test_fallback_counts_elements():
     _, status = kb.integrate_lower(*mesh, 8, prec="fp32fb64", tuning=tuning)
     assert int(status[1]) == 3 * n
     assert kb.build_lower_csr(*mesh, 8, prec="fp32fb64", tuning=tuning).n_fallback == 3 * n
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp32fb64"])
+@pytest.mark.parametrize("side", [1e-12, 1e12, 5e12])
+def test_sides_near_the_ends_of_fp32(side, prec):
+    """The determinant of a brick goes with the cube of its side, which FP32 holds for sides
+    from about 5e-13 to 8e12: there the integrals are those of the unit brick times the side."""
+    x = np.random.default_rng(1).uniform(-0.1, 0.1, (1000, 8, 3)) + (SIGNS * 0.5 + 0.5)
+    conn, unit, coef = alone(x)
+    ref, _ = kb.integrate_lower(conn, unit, coef, 8, prec="fp64")
+    print(f"[fp32 range] {side:g} {prec}", flush=True)
+    got, _ = kb.integrate_lower(conn, unit * side, coef, 8, prec=prec)
+    k = kb.build_lower_csr(conn, unit * side, coef, 8, prec=prec)
+    for vals in (got, k.vals.reshape(-1, 36)):  # (a row's columns ascend: the packed order)
+        err = (vals.double() / side - ref).abs().max().item() / ref.max().item()
+        assert err < 2e-6  # some dozen roundings to 24 bits
