@@ -239,13 +239,11 @@ __device__ __forceinline__ void walsh4(T x0, T x1, T x2, T x3, T& one, T& a, T& 
 }
 
 // ---- brick, one precision for geometry (GT) and one for M / accumulation (AT) ----------
-// X[a][j] = x_j(node a) - x_j(node 0) for a = 1..7 (X[0] = 0).  k[36]: lower triangle of
-// the element integral (without c).  Returns false if some det is not > 0.  If CHECK, *need_fb is
-// set when a point's Jacobian is ill-conditioned.
+// C: mode coefficients of the node coordinates (corner_modes).  k[36]: lower triangle of
+// the element integral (without c).  Returns false if some det is not > 0.  If CHECK,
+// *need_fb is set when a point's Jacobian is ill-conditioned.
 template <typename GT, typename AT, bool CHECK>
-__device__ __forceinline__ bool hex_integrate(const GT (&X)[8][3], AT (&k)[36], GT tau, bool* need_fb) {
-  GT C[kModes][3];
-  corner_modes(X, C);
+__device__ __forceinline__ bool hex_integrate(const GT (&C)[kModes][3], AT (&k)[36], GT tau, bool* need_fb) {
   bool ok = true;
   AT W[6][8];
 #pragma unroll
@@ -493,6 +491,8 @@ struct ElemTraits {
 // the element integrand: stiffness (Eq. 7-9) or consistent mass
 enum class Op { Stiffness = 0, Mass = 1 };
 
+// from the node coordinates relative to node 0 (the stiffness of bricks: hex_integrate)
+
 template <int NEN, typename GT, typename AT, bool CHECK, Op OP = Op::Stiffness>
 __device__ __forceinline__ bool integrate(const GT (&X)[NEN][3], AT (&k)[ElemTraits<NEN>::T], GT tau, bool* need_fb) {
   if constexpr (OP == Op::Mass) {
@@ -501,10 +501,8 @@ __device__ __forceinline__ bool integrate(const GT (&X)[NEN][3], AT (&k)[ElemTra
     else
       return tet_mass<GT, AT, CHECK>(X, k, tau, need_fb);
   } else {
-    if constexpr (NEN == 8)
-      return hex_integrate<GT, AT, CHECK>(X, k, tau, need_fb);
-    else
-      return tet_integrate<GT, AT, CHECK>(X, k, tau, need_fb);
+    static_assert(NEN == 4, "bricks: hex_integrate, from their modes");
+    return tet_integrate<GT, AT, CHECK>(X, k, tau, need_fb);
   }
 }
 

@@ -217,43 +217,72 @@ __device__ __forceinline__ void gather_nodes(const NODES& nodes, const int32_t (
   for (int a = 0; a < NEN; ++a) nodes.get(E[a], Xn[a]);
 }
 
-// Integrate one element from its gathered node coordinates Xn and coefficient c into k
-// (value type V, c applied).  Adds flag bits to *f and counts a fallback in *fb.
-template <int NEN, Prec P, Op OP = Op::Stiffness>
-__device__ __forceinline__ void element_values_at(const double (&Xn)[NEN][3], double c, float tau,
+// An element's integrals (without c); relative(X) fills in its node coordinates relative to
+// node 0.  What the Jacobian of a brick's stiffness is made of is formed in FP64 whatever
+// the precision, as in element_values_pair, and rounded once (from corner differences rounded
+// to FP32 the integrals of bricks ten times as long as wide were off by 1.18e-7 rms, not
+// 0.98e-7).  With FP32 geometry an ill-conditioned element is integrated again with its
+// Jacobian, determinant and adjugate in FP64 and counted in *fb.  Returns false if some
+// determinant is not > 0.
+template <int NEN, Prec P, Op OP, typename Fn>
+__device__ __forceinline__ bool element_integrals(const Fn& relative, float tau,
+                                                  typename PrecTraits<P>::V (&k)[ElemTraits<NEN>::T], uint32_t* fb) {
+  constexpr bool kModal = NEN == 8 && OP == Op::Stiffness;
+  constexpr int N = kModal ? kModes : NEN;
+  const auto geometry = [&](double (&G)[N][3]) {
+    if constexpr (kModal) {
+      double X[NEN][3];
+      relative(X);
+      corner_modes(X, G);
+    } else {
+      relative(G);
+    }
+  };
+  const auto wide = [&] {
+    using V = typename PrecTraits<P>::V;
+    double G[N][3];
+    geometry(G);
+    if constexpr (kModal)
+      return hex_integrate<double, V, false>(G, k, 0.0, nullptr);
+    else
+      return integrate<NEN, double, V, false, OP>(G, k, 0.0, nullptr);
+  };
+  if constexpr (P == Prec::F64) {
+    return wide();
+  } else {
+    float F[N][3];
+    {
+      double G[N][3];
+      geometry(G);
+#pragma unroll
+      for (int a = 0; a < N; ++a)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) F[a][j] = (float)G[a][j];
+    }
+    bool need_fb = false, ok;
+    if constexpr (kModal)
+      ok = hex_integrate<float, float, P == Prec::F32FB>(F, k, tau, &need_fb);
+    else
+      ok = integrate<NEN, float, float, P == Prec::F32FB, OP>(F, k, tau, &need_fb);
+    if constexpr (P == Prec::F32FB) {
+      if (need_fb) {
+        ok = wide();
+        *fb += 1;
+      }
+    }
+    return ok;
+  }
+}
+
+// Integrate one element of coefficient c into k (value type V, c applied).  Adds flag bits to
+// *f and counts a fallback in *fb.
+template <int NEN, Prec P, Op OP, typename Fn>
+__device__ __forceinline__ void element_values_of(const Fn& relative, double c, float tau,
                                                   typename PrecTraits<P>::V (&k)[ElemTraits<NEN>::T], uint32_t* f,
                                                   uint32_t* fb) {
   constexpr int T = ElemTraits<NEN>::T;
   using V = typename PrecTraits<P>::V;
-  bool ok;
-  if constexpr (P == Prec::F64) {
-    double X[NEN][3];
-#pragma unroll
-    for (int a = 0; a < NEN; ++a)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) X[a][j] = a ? Xn[a][j] - Xn[0][j] : 0.0;
-    ok = integrate<NEN, double, double, false, OP>(X, k, 0.0, nullptr);
-  } else {
-    float X[NEN][3];
-#pragma unroll
-    for (int a = 0; a < NEN; ++a)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) X[a][j] = a ? (float)(Xn[a][j] - Xn[0][j]) : 0.f;
-    bool need_fb = false;
-    ok = integrate<NEN, float, float, P == Prec::F32FB, OP>(X, k, tau, &need_fb);
-    if constexpr (P == Prec::F32FB) {
-      if (need_fb) {
-        // Jacobian, determinant and adjugate in FP64 for this element
-        double Xd[NEN][3];
-#pragma unroll
-        for (int a = 0; a < NEN; ++a)
-#pragma unroll
-          for (int j = 0; j < 3; ++j) Xd[a][j] = a ? Xn[a][j] - Xn[0][j] : 0.0;
-        ok = integrate<NEN, double, float, false, OP>(Xd, k, 0.0, nullptr);
-        *fb += 1;
-      }
-    }
-  }
+  const bool ok = element_integrals<NEN, P, OP>(relative, tau, k, fb);
   bool finite = true;
 #pragma unroll
   for (int p = 0; p < T; ++p) {
@@ -264,67 +293,40 @@ __device__ __forceinline__ void element_values_at(const double (&Xn)[NEN][3], do
   if (!finite) *f |= KB_F_NONFINITE;
 }
 
-// Gather and integrate element e.  E must be valid.  Each node's offset from node 0 is
-// formed as soon as it arrives, so at most two nodes' FP64 coordinates are live.
+// from its gathered node coordinates Xn
+template <int NEN, Prec P, Op OP = Op::Stiffness>
+__device__ __forceinline__ void element_values_at(const double (&Xn)[NEN][3], double c, float tau,
+                                                  typename PrecTraits<P>::V (&k)[ElemTraits<NEN>::T], uint32_t* f,
+                                                  uint32_t* fb) {
+  const auto relative = [&](double (&X)[NEN][3]) {
+#pragma unroll
+    for (int a = 0; a < NEN; ++a)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) X[a][j] = a ? Xn[a][j] - Xn[0][j] : 0.0;
+  };
+  element_values_of<NEN, P, OP>(relative, c, tau, k, f, fb);
+}
+
+// gathering its nodes (again for a fallback, which needs fewer registers than to keep them).
+// E must be valid.
 template <int NEN, Prec P, typename NODES, Op OP = Op::Stiffness>
 __device__ __forceinline__ void element_values(const NODES& nodes, const double* __restrict__ coef, int64_t e,
                                                const int32_t (&E)[NEN], float tau,
                                                typename PrecTraits<P>::V (&k)[ElemTraits<NEN>::T], uint32_t* f,
                                                uint32_t* fb) {
-  constexpr int T = ElemTraits<NEN>::T;
-  using V = typename PrecTraits<P>::V;
   double X0[3];
   nodes.get(E[0], X0);
   const double c = coef[e];
-  bool ok;
-  if constexpr (P == Prec::F64) {
-    double X[NEN][3];
+  const auto relative = [&](double (&X)[NEN][3]) {
     X[0][0] = X[0][1] = X[0][2] = 0.0;
 #pragma unroll
     for (int a = 1; a < NEN; ++a) {
-      double xa[3];
-      nodes.get(E[a], xa);
+      nodes.get(E[a], X[a]);
 #pragma unroll
-      for (int j = 0; j < 3; ++j) X[a][j] = xa[j] - X0[j];
+      for (int j = 0; j < 3; ++j) X[a][j] -= X0[j];
     }
-    ok = integrate<NEN, double, double, false, OP>(X, k, 0.0, nullptr);
-  } else {
-    float X[NEN][3];
-    X[0][0] = X[0][1] = X[0][2] = 0.f;
-#pragma unroll
-    for (int a = 1; a < NEN; ++a) {
-      double xa[3];
-      nodes.get(E[a], xa);
-#pragma unroll
-      for (int j = 0; j < 3; ++j) X[a][j] = (float)(xa[j] - X0[j]);
-    }
-    bool need_fb = false;
-    ok = integrate<NEN, float, float, P == Prec::F32FB, OP>(X, k, tau, &need_fb);
-    if constexpr (P == Prec::F32FB) {
-      if (need_fb) {
-        // Jacobian, determinant and adjugate in FP64 for this element (nodes re-read)
-        double Xd[NEN][3];
-        Xd[0][0] = Xd[0][1] = Xd[0][2] = 0.0;
-#pragma unroll
-        for (int a = 1; a < NEN; ++a) {
-          double xa[3];
-          nodes.get(E[a], xa);
-#pragma unroll
-          for (int j = 0; j < 3; ++j) Xd[a][j] = xa[j] - X0[j];
-        }
-        ok = integrate<NEN, double, float, false, OP>(Xd, k, 0.0, nullptr);
-        *fb += 1;
-      }
-    }
-  }
-  bool finite = true;
-#pragma unroll
-  for (int p = 0; p < T; ++p) {
-    k[p] = (V)(c * (double)k[p]);
-    finite = finite && isfinite((double)k[p]);
-  }
-  if (!ok) *f |= KB_F_INVERTED;
-  if (!finite) *f |= KB_F_NONFINITE;
+  };
+  element_values_of<NEN, P, OP>(relative, c, tau, k, f, fb);
 }
 
 // Lane h of a pair gathers nodes 4h .. 4h+3 of its brick (a branch per half keeps every

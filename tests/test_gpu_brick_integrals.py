@@ -1,5 +1,6 @@
 """Brick integrals where the lanes that share a brick, the build and the integrals alone can
-differ: elements ill-conditioned at one end only, sides near the ends of FP32's range."""
+differ: elements ill-conditioned at one end only, sides near the ends of FP32's range,
+long elements in FP32."""
 import numpy as np
 import pytest
 import torch
@@ -68,3 +69,20 @@ def test_sides_near_the_ends_of_fp32(side, prec):
     for vals in (got, k.vals.reshape(-1, 36)):  # (a row's columns ascend: the packed order)
         err = (vals.double() / side - ref).abs().max().item() / ref.max().item()
         assert err < 2e-6  # some dozen roundings to 24 bits
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp32fb64"])
+def test_integrals_alone_as_accurate_as_the_build(prec):
+    """Long distorted bricks in FP32: both form what the Jacobian is made of in FP64 from
+    the coordinates, so the integrals alone are no further off than the matrix."""
+    c = (SIGNS * 0.5 + 0.5) * (1, 1, 10)
+    x = c + np.random.default_rng(2).uniform(-0.25, 0.25, (20000, 8, 3))
+    mesh = alone(x)
+    ref, _ = kb.integrate_lower(*mesh, 8, prec="fp64")
+    print(f"[fp32 integrals] {prec}", flush=True)
+    tuning = kb.Tuning(fb_tau=1e6)  # (FP32 geometry throughout)
+    got, _ = kb.integrate_lower(*mesh, 8, prec=prec, tuning=tuning)
+    k = kb.build_lower_csr(*mesh, 8, prec=prec, tuning=tuning)
+    rms = [(((v.double() - ref).norm(dim=1) / ref.norm(dim=1)) ** 2).mean().sqrt().item()
+           for v in (got, k.vals.reshape(-1, 36))]
+    assert rms[0] < 1.05 * rms[1], rms  # (20,000 elements: the rms is good to about 1%)
