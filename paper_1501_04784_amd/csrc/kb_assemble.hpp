@@ -263,7 +263,8 @@ constexpr uint32_t kDirectRun = 32;
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 
 // head words of a build: [0] largest exponent, [1] heavy sub-buckets, [2] and [3]
-// workgroups done (k_heavy, k_count), then the way taken (kAsk) and the samples
+// workgroups done (k_heavy, k_count), [4] sub-buckets listed for k_pass3_parts, then the way
+// taken (kAsk) and the samples
 constexpr int kHeadWay = 15, kHeadVotes = 16, kHeadWords = 64;
 
 // the way sampled: votes[2 i], votes[2 i + 1] are the sub-buckets and the pairs of tile i
@@ -1866,141 +1867,131 @@ __device__ __forceinline__ uint32_t slot_hash(uint32_t k) {
 // One workgroup per sub-bucket g (rows [g << s2, ...)).  Writes its unique entries in
 // CSR order to tcol/tval[sbb[g] + f], each row's first entry (relative to the
 // sub-bucket) to rowoff, its total to usub[g].  A sub-bucket of more than 2^16 pairs
-// or more distinct entries than the table holds is appended to ov_list (count in
-// *ov_count) and left to k_heavy.
+// or more distinct entries than the table holds is appended to list (count in *count) and
+// left to k_heavy or, if the direct way's sub-buckets are wider, to k_pass3_parts.
 // Sub-buckets run in their natural order: under a random numbering the lower-triangle
 // pairs of a row grow with its id, so an even interleave keeps the XCDs balanced.
 // With RES, each entry's residual (the exact sum minus its rounding) goes to tres too.
 // (The grid has the two-level way's number of sub-buckets; where the direct way has fewer,
 // the other workgroups return: about 0.4 ns each, against 20% slower code if a workgroup
 // could take several in turn.)
-template <typename V, int HT, bool RES = false>
-__global__ __launch_bounds__(256) void k_pass3(uint32_t* __restrict__ ikey, V* __restrict__ ival,
-                                               const uint32_t* __restrict__ sbb, const SubBuckets sub, int colbits,
-                                               int64_t n_node,
-                                               const uint32_t* __restrict__ emax, int32_t* __restrict__ tcol,
-                                               V* __restrict__ tval, V* __restrict__ tres,
-                                               uint32_t* __restrict__ rowoff, uint32_t* __restrict__ usub,
-                                               uint32_t* __restrict__ ov_list, uint32_t* __restrict__ ov_count) {
-  constexpr int NT = 256, PER = 8;
-  // once summed, each slot's value (and residual) is kept in place of its low chunk sum,
-  // which frees the high chunk sums for the columns grouped by row (one array fewer); a
-  // double with its double residual needs both words.  The per-row arrays are sized by
-  // the sub-bucket's rows at launch and the columns are grouped by row through cursors
-  // (no per-slot index within the row): 22.4 KB at 1024 slots, seven workgroups per CU
-  constexpr bool kSepCols = RES && sizeof(V) == 8;
-  __shared__ uint32_t s_key[HT];
-  __shared__ unsigned long long s_lo[HT];  // sum of low 48-bit chunks, then value (+ residual)
-  __shared__ unsigned long long s_hi[HT];  // sum of signed high chunks, then the columns
-  __shared__ uint16_t s_slot[HT];  // occupied slots, in insertion order
-  __shared__ uint32_t s_sep[kSepCols ? HT : 1];
-  __shared__ uint32_t s_over, s_nu;
-  extern __shared__ uint32_t s_rows[];  // 3 << s2 words: entries per row, row offsets, cursors
-  const int64_t g = blockIdx.x;
-  const bool either = g < sub.nsub[1];
-  if (!either && sub.pick()) return;  // (only the workgroups beyond the direct way's wait for its word here)
-  const uint32_t beg = sbb[g], end = sbb[g + 1];
-  uint32_t* const s_rc = s_rows;
-  for (int h = threadIdx.x; h < HT; h += NT) {
-    s_key[h] = kEmptyKey;
-    s_lo[h] = 0ull;
-    s_hi[h] = 0ull;
-  }
-  const int s2_max = sub.s2[0] > sub.s2[1] ? sub.s2[0] : sub.s2[1];
-  for (int r = threadIdx.x; r < (1 << s2_max); r += NT) s_rc[r] = 0;
-  const int s2 = sub.s2[either ? sub.pick() : 0];
-  uint32_t* const s_ro = s_rows + (1 << s2);
-  uint32_t* const s_cur = s_rows + (2 << s2);
-  uint32_t* const s_lcol = kSepCols ? s_sep : (uint32_t*)s_hi;  // columns of the slots, grouped by row
-  const int F = 1117 - (int)*emax;
-  const uint32_t cmask = (1u << colbits) - 1;
-  const int64_t r0 = g << s2;
-  const int64_t rr = n_node - r0;
-  const int R = rr <= 0 ? 0 : (rr < ((int64_t)1 << s2) ? (int)rr : (1 << s2));
-  // more than 2^16 pairs could overflow the chunk sums: left to k_heavy
-  if (threadIdx.x == 0) {
-    s_over = (end - beg > (1u << 16)) ? 1u : 0u;
-    s_nu = 0;
-  }
-  __syncthreads();
-  // stream the pairs into the table: PER loads per lane in flight (indices clamped into
-  // the range; the empty asm keeps the compiler from sinking a load into the branch
-  // that first uses it)
-  if (!s_over) {
-    // (offsets from the sub-bucket's first pair: below 2^16 here)
-    const uint32_t n = end - beg;
-    const uint32_t* const kp = ikey + beg;
-    const V* const vp = ival + beg;
-    for (uint32_t j0 = 0; j0 < n; j0 += PER * NT) {
-      uint32_t kk[PER];
-      V vv[PER];
-#pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        const uint32_t j = j0 + u * NT + threadIdx.x;
-        const uint32_t jc = (j < n ? j : 0u) & 0xffffu;
-        kk[u] = kp[jc];
-        vv[u] = vp[jc];
-      }
-#pragma unroll
-      for (int u = 0; u < PER; ++u) asm volatile("" : "+v"(kk[u]), "+v"(vv[u]));
-#pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        if (j0 + u * NT + threadIdx.x >= n) continue;
-        const uint32_t key = kk[u];
-        // one compare-and-swap per probe: it returns the empty marker when this lane
-        // took the slot, the key when the entry was there already, else another key
-        uint32_t h = slot_hash<HT>(key);
-        uint32_t k = atomicCAS(&s_key[h], kEmptyKey, key);
-        int probes = 0;
-#pragma unroll 1
-        while (k != kEmptyKey && k != key && ++probes < HT) {
-          h = (h + 1) & (HT - 1);
-          k = atomicCAS(&s_key[h], kEmptyKey, key);
-        }
-        if (k != kEmptyKey && k != key) {  // the table is full
-          s_over = 1;
-          continue;
-        }
-        uint64_t c0;
-        int64_t c1;
-        to_chunks(vv[u], F, c0, c1);
-        // (a float within 2^23 of the largest is a multiple of 2^48: 20.25M tets, 671 -> 655 us)
-        if (sizeof(V) == 8 || c0) atomicAdd(&s_lo[h], (unsigned long long)c0);
-        atomicAdd(&s_hi[h], (unsigned long long)c1);
-      }
+constexpr int kPass3Threads = 256;
+
+// a workgroup's table and the arrays that order its entries.  Once summed, each slot's value
+// (and residual) is kept in place of its low chunk sum, which frees the high chunk sums for
+// the columns grouped by row (one array fewer); a double with its double residual needs both
+// words.  The per-row arrays are sized by the sub-bucket's rows at launch and the columns are
+// grouped by row through cursors (no per-slot index within the row): 22.4 KB at 1024 slots,
+// seven workgroups per CU
+template <typename V, int HT, bool RES>
+struct Pass3Smem {
+  static constexpr bool kSepCols = RES && sizeof(V) == 8;
+  uint32_t* key;
+  unsigned long long* lo;  // sum of low 48-bit chunks, then value (+ residual)
+  unsigned long long* hi;  // sum of signed high chunks, then the columns
+  uint16_t* slot;          // occupied slots, in insertion order
+  uint32_t* lcol;          // columns of the slots, grouped by row
+  uint32_t *rc, *ro, *cur;  // [1 << s2] entries per row, row offsets, cursors
+  uint32_t *over, *nu;     // the table is full; occupied slots
+  __device__ __forceinline__ void clear(int rows) const {
+    for (int h = threadIdx.x; h < HT; h += kPass3Threads) {
+      key[h] = kEmptyKey;
+      lo[h] = 0ull;
+      hi[h] = 0ull;
     }
+    for (int r = threadIdx.x; r < rows; r += kPass3Threads) rc[r] = 0;
   }
-  __syncthreads();
-  if (s_over) {  // left to k_heavy
-    if (threadIdx.x == 0) ov_list[atomicAdd(ov_count, 1u)] = (uint32_t)g;
-    return;
+};
+
+// Stream n <= 2^16 pairs into the table: PER loads per lane in flight (indices clamped into
+// the range; the empty asm keeps the compiler from sinking a load into the branch that first
+// uses it).  A key that finds no slot sets *over, which ends the stream, and empties the table,
+// whose sums are then not used: each further pair probing a full table to its end took 0.5 ms
+// for 2000 pairs (a limit on the probes short of that costs the pairs of every other table:
+// 20.25M tets 3.98 -> 4.01 ms).
+// PART: only the pairs whose key >> part_shift is part.
+template <bool PART, typename V, int HT, bool RES>
+__device__ __forceinline__ void pass3_insert(const Pass3Smem<V, HT, RES>& sm, const uint32_t* kp, const V* vp,
+                                             uint32_t n, int F, uint32_t part, int part_shift) {
+  constexpr int NT = kPass3Threads, PER = 8;
+  for (uint32_t j0 = 0; j0 < n; j0 += PER * NT) {
+    uint32_t kk[PER];
+    V vv[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const uint32_t j = j0 + u * NT + threadIdx.x;
+      const uint32_t jc = (j < n ? j : 0u) & 0xffffu;
+      kk[u] = kp[jc];
+      vv[u] = vp[jc];
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) asm volatile("" : "+v"(kk[u]), "+v"(vv[u]));
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      if (j0 + u * NT + threadIdx.x >= n) continue;
+      const uint32_t key = kk[u];
+      if (PART && key >> part_shift != part) continue;
+      // one compare-and-swap per probe: it returns the empty marker when this lane
+      // took the slot, the key when the entry was there already, else another key
+      uint32_t h = slot_hash<HT>(key);
+      uint32_t k = atomicCAS(&sm.key[h], kEmptyKey, key);
+      int probes = 0;
+#pragma unroll 1
+      while (k != kEmptyKey && k != key && ++probes < HT) {
+        h = (h + 1) & (HT - 1);
+        k = atomicCAS(&sm.key[h], kEmptyKey, key);
+      }
+      if (k != kEmptyKey && k != key) {
+        *sm.over = 1;
+#pragma unroll 1
+        for (int i = 0; i < HT; ++i) sm.key[i] = kEmptyKey;
+        continue;
+      }
+      uint64_t c0;
+      int64_t c1;
+      to_chunks(vv[u], F, c0, c1);
+      // (a float within 2^23 of the largest is a multiple of 2^48: 20.25M tets, 671 -> 655 us)
+      if (sizeof(V) == 8 || c0) atomicAdd(&sm.lo[h], (unsigned long long)c0);
+      atomicAdd(&sm.hi[h], (unsigned long long)c1);
+    }
+    if (j0 + PER * NT < n && __hip_atomic_load(sm.over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
   }
+}
+
+// The table's entries rounded, ordered by (row, col) and written from tcol / tval / tres
+// [0, ...) on, and the first entries of rows [row_lo, row_hi), counted from u0, to rowoff
+template <typename V, int HT, bool RES>
+__device__ __forceinline__ void pass3_emit(const Pass3Smem<V, HT, RES>& sm, int F, int colbits, int s2, uint32_t u0,
+                                           int row_lo, int row_hi, int32_t* tcol, V* tval, V* tres,
+                                           uint32_t* rowoff) {
+  constexpr int NT = kPass3Threads;
+  const uint32_t cmask = (1u << colbits) - 1;
   // list the occupied slots and count the entries of each row (once per entry here
   // rather than on the insertion path of every pair)
   for (int h = threadIdx.x; h < HT; h += NT) {
-    const uint32_t k = s_key[h];
+    const uint32_t k = sm.key[h];
     if (k != kEmptyKey) {
-      s_slot[atomicAdd(&s_nu, 1u)] = (uint16_t)h;
-      atomicAdd(&s_rc[k >> colbits], 1u);
+      sm.slot[atomicAdd(sm.nu, 1u)] = (uint16_t)h;
+      atomicAdd(&sm.rc[k >> colbits], 1u);
     }
   }
   __syncthreads();
   // order the U entries by (row, col): the row counts scanned by one
   // wave while the others round each sum to its value, the entries grouped by row, then
   // ranked by column within their row
-  const uint32_t U = s_nu;
+  const uint32_t U = *sm.nu;
   const int RB = 1 << s2;  // rows of a full sub-bucket (<= 256)
   for (uint32_t f = threadIdx.x < 64 ? U : threadIdx.x - 64; f < U; f += NT - 64) {
-    const uint32_t h = s_slot[f];
+    const uint32_t h = sm.slot[f];
     uint64_t lo, hi;
-    join48(s_lo[h], (int64_t)s_hi[h], lo, hi);
+    join48(sm.lo[h], (int64_t)sm.hi[h], lo, hi);
     const V hv = from_fixed_as<V>(lo, hi, F);
     if constexpr (sizeof(V) == 8) {
-      s_lo[h] = (unsigned long long)__double_as_longlong((double)hv);
-      if constexpr (RES) s_hi[h] = (unsigned long long)__double_as_longlong((double)fixed_residual<V>(lo, hi, F, hv));
+      sm.lo[h] = (unsigned long long)__double_as_longlong((double)hv);
+      if constexpr (RES) sm.hi[h] = (unsigned long long)__double_as_longlong((double)fixed_residual<V>(lo, hi, F, hv));
     } else {
       const uint32_t rv = RES ? __float_as_uint((float)fixed_residual<V>(lo, hi, F, hv)) : 0u;
-      s_lo[h] = ((unsigned long long)rv << 32) | __float_as_uint((float)hv);
+      sm.lo[h] = ((unsigned long long)rv << 32) | __float_as_uint((float)hv);
     }
   }
   if (threadIdx.x < 64) {
@@ -2009,7 +2000,7 @@ __global__ __launch_bounds__(256) void k_pass3(uint32_t* __restrict__ ikey, V* _
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int r = lane * 4 + k;
-      v[k] = r < RB ? s_rc[r] : 0u;
+      v[k] = r < RB ? sm.rc[r] : 0u;
       sum += v[k];
     }
     uint32_t x = sum;
@@ -2023,40 +2014,145 @@ __global__ __launch_bounds__(256) void k_pass3(uint32_t* __restrict__ ikey, V* _
     for (int k = 0; k < 4; ++k) {
       const int r = lane * 4 + k;
       if (r < RB) {
-        s_ro[r] = run;
-        s_cur[r] = run;
+        sm.ro[r] = run;
+        sm.cur[r] = run;
       }
       run += v[k];
     }
   }
   __syncthreads();
   for (uint32_t f = threadIdx.x; f < U; f += NT) {
-    const uint32_t h = s_slot[f];
-    const uint32_t k = s_key[h];
-    s_lcol[atomicAdd(&s_cur[k >> colbits], 1u)] = k & cmask;
+    const uint32_t h = sm.slot[f];
+    const uint32_t k = sm.key[h];
+    sm.lcol[atomicAdd(&sm.cur[k >> colbits], 1u)] = k & cmask;
   }
   __syncthreads();
   for (uint32_t f = threadIdx.x; f < U; f += NT) {
-    const uint32_t h = s_slot[f];
-    const uint32_t k = s_key[h];
+    const uint32_t h = sm.slot[f];
+    const uint32_t k = sm.key[h];
     const uint32_t row = k >> colbits, col = k & cmask;
-    const uint32_t ro = s_ro[row], nr = s_rc[row];
+    const uint32_t ro = sm.ro[row], nr = sm.rc[row];
     uint32_t rank = 0;
 #pragma unroll 4
-    for (uint32_t q = 0; q < nr; ++q) rank += (s_lcol[ro + q] < col) ? 1u : 0u;
+    for (uint32_t q = 0; q < nr; ++q) rank += (sm.lcol[ro + q] < col) ? 1u : 0u;
     const uint32_t pos = ro + rank;
-    tcol[beg + pos] = (int32_t)col;
-    const unsigned long long w = s_lo[h];
+    tcol[pos] = (int32_t)col;
+    const unsigned long long w = sm.lo[h];
     if constexpr (sizeof(V) == 8) {
-      tval[beg + pos] = (V)__longlong_as_double((long long)w);
-      if constexpr (RES) tres[beg + pos] = (V)__longlong_as_double((long long)s_hi[h]);
+      tval[pos] = (V)__longlong_as_double((long long)w);
+      if constexpr (RES) tres[pos] = (V)__longlong_as_double((long long)sm.hi[h]);
     } else {
-      tval[beg + pos] = (V)__uint_as_float((uint32_t)w);
-      if constexpr (RES) tres[beg + pos] = (V)__uint_as_float((uint32_t)(w >> 32));
+      tval[pos] = (V)__uint_as_float((uint32_t)w);
+      if constexpr (RES) tres[pos] = (V)__uint_as_float((uint32_t)(w >> 32));
     }
   }
-  for (int r = threadIdx.x; r < R; r += NT) rowoff[r0 + r] = s_ro[r];
-  if (threadIdx.x == 0) usub[g] = U;
+  for (int r = row_lo + threadIdx.x; r < row_hi; r += NT) rowoff[r] = u0 + sm.ro[r];
+}
+
+template <typename V, int HT, bool RES = false>
+__global__ __launch_bounds__(kPass3Threads) void k_pass3(uint32_t* __restrict__ ikey, V* __restrict__ ival,
+                                               const uint32_t* __restrict__ sbb, const SubBuckets sub, int colbits,
+                                               int64_t n_node,
+                                               const uint32_t* __restrict__ emax, int32_t* __restrict__ tcol,
+                                               V* __restrict__ tval, V* __restrict__ tres,
+                                               uint32_t* __restrict__ rowoff, uint32_t* __restrict__ usub,
+                                               uint32_t* __restrict__ list, uint32_t* __restrict__ count) {
+  using SM = Pass3Smem<V, HT, RES>;
+  __shared__ uint32_t s_key[HT];
+  __shared__ unsigned long long s_lo[HT];
+  __shared__ unsigned long long s_hi[HT];
+  __shared__ uint16_t s_slot[HT];
+  __shared__ uint32_t s_sep[SM::kSepCols ? HT : 1];
+  __shared__ uint32_t s_over, s_nu;
+  extern __shared__ uint32_t s_rows[];  // 3 << s2 words
+  const int64_t g = blockIdx.x;
+  const bool either = g < sub.nsub[1];
+  if (!either && sub.pick()) return;  // (only the workgroups beyond the direct way's wait for its word here)
+  const uint32_t beg = sbb[g], end = sbb[g + 1];
+  SM sm{s_key, s_lo, s_hi, s_slot, SM::kSepCols ? s_sep : (uint32_t*)s_hi, s_rows, nullptr, nullptr, &s_over, &s_nu};
+  sm.clear(1 << (sub.s2[0] > sub.s2[1] ? sub.s2[0] : sub.s2[1]));
+  const int s2 = sub.s2[either ? sub.pick() : 0];
+  sm.ro = s_rows + (1 << s2);
+  sm.cur = s_rows + (2 << s2);
+  const int F = 1117 - (int)*emax;
+  const int64_t r0 = g << s2;
+  const int64_t rr = n_node - r0;
+  const int R = rr <= 0 ? 0 : (rr < ((int64_t)1 << s2) ? (int)rr : (1 << s2));
+  // more than 2^16 pairs could overflow the chunk sums: left to k_heavy
+  if (threadIdx.x == 0) {
+    s_over = (end - beg > (1u << 16)) ? 1u : 0u;
+    s_nu = 0;
+  }
+  __syncthreads();
+  if (!s_over) pass3_insert<false>(sm, ikey + beg, ival + beg, end - beg, F, 0u, 0);
+  __syncthreads();
+  if (s_over) {
+    if (threadIdx.x == 0) list[atomicAdd(count, 1u)] = (uint32_t)g;
+    return;
+  }
+  pass3_emit(sm, F, colbits, s2, 0u, 0, R, tcol + beg, tval + beg, RES ? tres + beg : nullptr, rowoff + r0);
+  if (threadIdx.x == 0) usub[g] = s_nu;
+}
+
+// The sub-buckets that k_pass3 listed, if the direct way's are the wider ones.  Those are
+// sized for the mesh's average row: one whose rows are longer (rows of unlike length in
+// ranges of ids) is reduced here in parts of the two-level way's width, each with the whole
+// table; its pairs are read once per part.  What does not fit its table goes to ov_list,
+// for k_heavy (a workgroup of which takes some 0.5 ms: a mesh of 216,000 bricks that share no
+// node, all of it listed, took 128 ms).  In k_pass3 itself the parts made every sub-bucket
+// slower (scalar registers: 27M bricks 13.3 -> 13.7 ms); the launch takes 3 us when nothing
+// is listed.
+constexpr int kPartsGroups = 7;   // workgroups per CU
+template <typename V, int HT, bool RES = false>
+__global__ __launch_bounds__(kPass3Threads) void k_pass3_parts(
+    uint32_t* __restrict__ ikey, V* __restrict__ ival, const uint32_t* __restrict__ sbb, const SubBuckets sub,
+    int colbits, int64_t n_node, const uint32_t* __restrict__ emax, int32_t* __restrict__ tcol, V* __restrict__ tval,
+    V* __restrict__ tres, uint32_t* __restrict__ rowoff, uint32_t* __restrict__ usub,
+    const uint32_t* __restrict__ list, const uint32_t* __restrict__ count, uint32_t* __restrict__ ov_list,
+    uint32_t* __restrict__ ov_count) {
+  using SM = Pass3Smem<V, HT, RES>;
+  __shared__ uint32_t s_key[HT];
+  __shared__ unsigned long long s_lo[HT];
+  __shared__ unsigned long long s_hi[HT];
+  __shared__ uint16_t s_slot[HT];
+  __shared__ uint32_t s_sep[SM::kSepCols ? HT : 1];
+  __shared__ uint32_t s_over, s_nu;
+  extern __shared__ uint32_t s_rows[];  // 3 << s2 words
+  const uint32_t n_list = *count;
+  if (blockIdx.x >= n_list) return;
+  const int s2 = sub.s2[sub.pick()], s2p = s2 < sub.s2[0] ? s2 : sub.s2[0], np = 1 << (s2 - s2p);
+  const SM sm{s_key,  s_lo, s_hi, s_slot, SM::kSepCols ? s_sep : (uint32_t*)s_hi, s_rows, s_rows + (1 << s2),
+              s_rows + (2 << s2), &s_over, &s_nu};
+  const int F = 1117 - (int)*emax;
+  for (uint32_t i = blockIdx.x; i < n_list; i += gridDim.x) {
+    const int64_t g = list[i], r0 = g << s2;
+    const uint32_t beg = sbb[g], end = sbb[g + 1];
+    const int R = (int)min((int64_t)1 << s2, n_node - r0);
+    uint32_t U = 0;
+    int p = end - beg > (1u << 16) ? np + 1 : 0;  // (as k_pass3)
+    for (; p < np; ++p) {
+      __syncthreads();  // (the entries before are written)
+      sm.clear(1 << s2);
+      if (threadIdx.x == 0) {
+        s_over = 0u;
+        s_nu = 0;
+      }
+      __syncthreads();
+      pass3_insert<true>(sm, ikey + beg, ival + beg, end - beg, F, (uint32_t)p, colbits + s2p);
+      __syncthreads();
+      if (s_over) break;
+      const int lo = p << s2p, hi = lo + (1 << s2p) < R ? lo + (1 << s2p) : R;
+      pass3_emit(sm, F, colbits, s2, U, lo, hi, tcol + beg + U, tval + beg + U, RES ? tres + beg + U : nullptr,
+                 rowoff + r0);
+      U += s_nu;
+    }
+    if (threadIdx.x == 0) {
+      if (p == np)
+        usub[g] = U;
+      else
+        ov_list[atomicAdd(ov_count, 1u)] = (uint32_t)g;
+    }
+  }
 }
 
 // ------------------------------------------------------------ heavy sub-buckets

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "kb_assemble.hpp"
 #include "kb_kernels.hpp"
@@ -244,7 +245,7 @@ struct Carry {
 // heavy sub-buckets that the whole device may split
 inline uint32_t heavy_par(const Plan& p) { return p.T > kHeavySplitPairs ? (uint32_t)kHeavyPar : 0u; }
 
-// pass 3, then the sub-buckets it could not hold (k_heavy, which returns at once when there
+// pass 3, then the sub-buckets it could not hold (in parts; k_heavy, which returns at once when there
 // are none; its last launch scans the entry counts of few sub-buckets into ubase and nnz)
 template <typename V, bool RES>
 int launch_pass3(const Plan& p, unsigned char* ws, V* tres, int64_t* nnz_dev, hipStream_t s) {
@@ -257,18 +258,31 @@ int launch_pass3(const Plan& p, unsigned char* ws, V* tres, int64_t* nnz_dev, hi
   auto* rowoff = (uint32_t*)(ws + p.o_rowoff);
   auto* usub = (uint32_t*)(ws + p.o_usub);
   auto* ov_list = (uint32_t*)(ws + p.o_ovl);
-  auto k3 = [&] {
-    switch (p.ht) {
-      case 512: return k_pass3<V, 512, RES>;
-      case 1024: return k_pass3<V, 1024, RES>;
-      case 2048: return k_pass3<V, 2048, RES>;
-      default: return k_pass3<V, 4096, RES>;
-    }
-  }();
   const SubBuckets sub = sub_buckets(p, ws);
-  k3<<<(unsigned)p.nsub, 256, (size_t)12 << std::max(p.s2, p.s2d), s>>>(
-      key2, val2, sbb, sub, p.colbits, p.nn, head, tcol, tval, tres, rowoff, usub, ov_list, head + 1);
-  KB_LAUNCH_CHECK();
+  const size_t lds3 = (size_t)12 << std::max(p.s2, p.s2d);
+  const bool parts = p.mode == kAsk && p.s2d > p.s2;
+  // (the list of k_pass3_parts lies where the scan of the entry counts goes later)
+  auto* list = parts ? (uint32_t*)(ws + p.o_ubase) : ov_list;
+  uint32_t* const count = head + (parts ? 4 : 1);
+  const auto reduce = [&](auto slots) {
+    constexpr int HT = decltype(slots)::value;
+    k_pass3<V, HT, RES><<<(unsigned)p.nsub, kPass3Threads, lds3, s>>>(
+        key2, val2, sbb, sub, p.colbits, p.nn, head, tcol, tval, tres, rowoff, usub, list, count);
+    KB_LAUNCH_CHECK();
+    if (parts) {
+      k_pass3_parts<V, HT, RES><<<(unsigned)std::min<int64_t>(p.nsub, (int64_t)kPartsGroups * std::max(1, p.cus)),
+                                  kPass3Threads, lds3, s>>>(key2, val2, sbb, sub, p.colbits, p.nn, head, tcol, tval,
+                                                            tres, rowoff, usub, list, count, ov_list, head + 1);
+      KB_LAUNCH_CHECK();
+    }
+    return (int)KB_OK;
+  };
+  switch (p.ht) {
+    case 512: KB_TRY(reduce(std::integral_constant<int, 512>{})); break;
+    case 1024: KB_TRY(reduce(std::integral_constant<int, 1024>{})); break;
+    case 2048: KB_TRY(reduce(std::integral_constant<int, 2048>{})); break;
+    default: KB_TRY(reduce(std::integral_constant<int, 4096>{}));
+  }
   const HeavyArgs<V> A{key2, val2, (uint32_t*)tcol, tval, tres, sbb, sub, p.s2, p.colbits, p.nn, 0, rowoff, usub,
       ov_list,
                        0, 0, (uint32_t*)(ws + p.o_hvy)};
