@@ -1819,27 +1819,27 @@ constexpr int kHeavyPar = 64;
 constexpr int kHvyDigits = 4096;  // first-level digits at most
 constexpr uint32_t kHvyShare = 3584;
 constexpr int kHvyRows = 256;  // rows of a sub-bucket at most
-constexpr int kHvyWords = (kHvyDigits + 1) + kHvyDigits + 3 * kHvyRows + (kHvyRows + 1) + 4;
+constexpr int kHvyWords = (kHvyDigits + 1) + kHvyDigits + 2 * kHvyRows + (kHvyRows + 1) + 4;
 struct HeavyTable {
   uint32_t* st;     // [kHvyDigits + 1] digit starts (absolute pair positions)
   uint32_t* hist;   // [kHvyDigits] pairs of each digit, then the scatter's cursors
   uint32_t* ucnt;   // the same words once the scatter is done: the entries of each digit
                     // range (every range writes its own), then their offsets
-  uint32_t* rcnt;   // [kHvyRows] entries of each row
   uint32_t* rpair;  // [kHvyRows] pairs of each row
   uint32_t* rsh;    // [kHvyRows] column shift of each row's digits
   uint32_t* rbase;  // [kHvyRows + 1] first digit of each row; rbase[kHvyRows] = digits
-  uint32_t* meta;   // [4] digits
+  uint32_t* meta;   // [4] digits; workgroups of the sub-bucket's team done (heavy_team)
   __device__ HeavyTable(uint32_t* hvy, uint32_t it) {
     st = hvy + (size_t)it * kHvyWords;
     hist = st + kHvyDigits + 1;
     ucnt = hist;
-    rcnt = hist + kHvyDigits;
-    rpair = rcnt + kHvyRows;
+    rpair = hist + kHvyDigits;
     rsh = rpair + kHvyRows;
     rbase = rsh + kHvyRows;
     meta = rbase + kHvyRows + 1;
   }
+  // words that k_begin clears, per table: rpair; for the teams meta[1]
+  static constexpr int kRpairAt = 2 * kHvyDigits + 1, kTeamAt = kHvyWords - 3;
 };
 
 // first-level digit of key k (row k >> colbits) from the layout in LDS
@@ -2301,11 +2301,12 @@ __device__ __forceinline__ void heavy_normalise(const HeavySmem& sm) {
 // 2^48 unsigned, below 2^47 in magnitude signed) stay inside 64 bits
 constexpr uint32_t kRound = 65532;
 
-// the exact sums of the leaf's pairs [a, b) (keys in [kmin, kmin + kLeafKeys)) into the
-// LDS slots, carried after every round (lo, hi below 2^48; occ set)
-template <typename V>
+// the exact sums of the leaf's pairs [a, b) (keys in [kmin, kmin + kLeafKeys); PICK: of those
+// with keys in [kmin, kmin + w), w <= kLeafKeys) into the LDS slots, carried after every round
+// (lo, hi below 2^48; occ set)
+template <typename V, bool PICK = false>
 __device__ void heavy_leaf_sum(const HeavySmem& sm, const uint32_t* key, const V* val, uint32_t a, uint32_t b,
-                               uint32_t kmin, int F) {
+                               uint32_t kmin, int F, uint32_t w = kLeafKeys) {
   const int lane = threadIdx.x & 63;
   // the wave's kept slot: once a slot has been hot (held by more than one lane), the
   // lanes that meet it again while it is the wave's first lane's slot add its chunks to
@@ -2333,6 +2334,7 @@ __device__ void heavy_leaf_sum(const HeavySmem& sm, const uint32_t* key, const V
     };
     heavy_stream<true>(key, val, r, re, [&](uint32_t k, V v, bool ok) {
       const uint32_t h = k - kmin;
+      if constexpr (PICK) ok = ok && h < w;
       uint64_t c0;
       int64_t c1;
       to_chunks(v, F, c0, c1);
@@ -2673,13 +2675,13 @@ __device__ void heavy_rows(unsigned char* smem, const HeavyArgs<V>& A, uint32_t 
   });
 }
 
-// The digits of each row of split sub-bucket it (of n pairs) from its rows' pair counts,
+// The digits of each row of a split sub-bucket (of n pairs) from its rows' pair counts,
 // into LDS (s_rbase: kHvyRows + 1 words, s_rsh: kHvyRows, s_scan: kHeavyThreads / 64 + 1);
 // `store`: to the table too.  Ends with a barrier.
-__device__ __forceinline__ void heavy_layout(const HeavyTable& t, uint64_t n, int colbits, bool store,
-                                             uint32_t* s_rbase, uint32_t* s_rsh, uint32_t* s_scan) {
+__device__ __forceinline__ void heavy_layout(const HeavyTable& t, const uint32_t* rpair, uint64_t n, int colbits,
+                                             bool store, uint32_t* s_rbase, uint32_t* s_rsh, uint32_t* s_scan) {
   const int r = threadIdx.x;
-  const uint32_t c = r < kHvyRows ? t.rpair[r] : 0u;
+  const uint32_t c = r < kHvyRows ? rpair[r] : 0u;
   const int lg_max = colbits > 12 ? colbits - 12 : 0;  // digits no narrower than a leaf
   const int lg_min = colbits > 23 ? colbits - 23 : 0;  // nor wider than 2^23 keys
   int lg = 0;
@@ -2731,7 +2733,7 @@ __device__ void heavy_hist(unsigned char* smem, const HeavyArgs<V>& A, uint32_t 
     const HeavyTable t(A.hvy, it);
     const uint32_t g = A.ov_list[it];
     for (int d = threadIdx.x; d < kHvyDigits; d += kHeavyThreads) s_hist[d] = 0u;
-    heavy_layout(t, A.sbb[g + 1] - A.sbb[g], colbits, a == A.sbb[g], s_rbase, s_rsh, s_scan);
+    heavy_layout(t, t.rpair, A.sbb[g + 1] - A.sbb[g], colbits, a == A.sbb[g], s_rbase, s_rsh, s_scan);
     const uint32_t nd = s_rbase[kHvyRows];
     heavy_count(A.ikey, a, b, s_hist, [&](uint32_t k) { return heavy_digit(k, colbits, s_rbase, s_rsh); });
     __syncthreads();
@@ -2741,6 +2743,18 @@ __device__ void heavy_hist(unsigned char* smem, const HeavyArgs<V>& A, uint32_t 
     }
     __syncthreads();
   });
+}
+
+// the row of digit d: the last r with rbase[r] <= d
+__device__ __forceinline__ uint32_t heavy_row(const uint32_t* rbase, uint32_t d) {
+  uint32_t r = 0, n = kHvyRows;
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {  // kHvyRows = 2^8 candidates
+    const uint32_t half = n >> 1;
+    if (rbase[r + half] <= d) r += half;
+    n -= half;
+  }
+  return r;
 }
 
 // Per listed sub-bucket, the digit starts (absolute pair positions) from the
@@ -2766,13 +2780,7 @@ __device__ void heavy_starts(unsigned char* smem, const HeavyArgs<V>& A, uint32_
     t.st[d] = a;
     t.hist[d] = a;
     if (b - a > kBigLeafPairs) {
-      // the row of digit d: the last r with rbase[r] <= d (rare: read from the table)
-      uint32_t r = 0, n = kHvyRows;
-      for (int s = 0; s < 8; ++s) {
-        const uint32_t half = n >> 1;
-        if (t.rbase[r + half] <= d) r += half;
-        n -= half;
-      }
+      const uint32_t r = heavy_row(t.rbase, d);  // (rare: read from the table)
       const uint32_t sh = t.rsh[r];
       if ((1u << sh) <= (uint32_t)kLeafKeys) {
         const uint32_t i = atomicAdd(big.list, 1u);
@@ -2899,8 +2907,7 @@ __device__ void heavy_bigleaf(unsigned char* smem, const HeavyArgs<V>& A, uint32
 // The first-level digit ranges of the first kHeavyPar listed sub-buckets, split
 // by heavy_scatter: range d0 of sub-bucket it is reduced by workgroup d0 mod nblk, its
 // entries written from its own first pair's place (its pairs all read before; other
-// workgroups read other ranges), its entry count recorded in the table and added to its
-// row's.
+// workgroups read other ranges), its entry count recorded in the table.
 template <typename V, bool RES>
 __device__ void heavy_ranges(unsigned char* smem, const HeavyArgs<V>& A, uint32_t blk, uint32_t nblk) {
   const HeavySmem sm(smem);
@@ -2941,13 +2948,7 @@ __device__ void heavy_ranges(unsigned char* smem, const HeavyArgs<V>& A, uint32_
         if (threadIdx.x == 0) t.ucnt[d0] = 0u;
         continue;
       }
-      uint32_t r = 0, n = kHvyRows;  // the row of digit d0: the last r with s_rbase[r] <= d0
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {  // kHvyRows = 2^8 candidates
-        const uint32_t half = n >> 1;
-        if (s_rbase[r + half] <= d0) r += half;
-        n -= half;
-      }
+      const uint32_t r = heavy_row(s_rbase, d0);
       const uint32_t sh = s_rsh[r];
       const uint32_t k0 = (r << colbits) + ((d0 - s_rbase[r]) << sh);
       uint32_t bi = nbig;
@@ -2974,10 +2975,7 @@ __device__ void heavy_ranges(unsigned char* smem, const HeavyArgs<V>& A, uint32_
         U = heavy_range<V, RES>(sm, ikey, ival, akey, aval, a, b, k0, 1u << sh, F, colbits, tcol + a, aval + a,
                                 RES ? tres + a : nullptr, 0);
       }
-      if (threadIdx.x == 0) {
-        t.ucnt[d0] = U;
-        atomicAdd(&t.rcnt[r], U);
-      }
+      if (threadIdx.x == 0) t.ucnt[d0] = U;
     }
     __syncthreads();  // (the next layout overwrites this one)
   }
@@ -3046,43 +3044,106 @@ __device__ void heavy_finish(unsigned char* smem, const HeavyArgs<V>& A, uint32_
       if constexpr (RES) tres[beg + f] = e[j];
     }
   }
-  // row offsets within the sub-bucket from the entries per row
+  // a row's entries start where its first digit's do
   const int64_t r0 = g << s2;
   const int R = (int)min((int64_t)1 << s2, n_node - r0);
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    uint32_t v[4], sum = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int r = lane * 4 + k;
-      v[k] = r < R ? t.rcnt[r] : 0u;
-      sum += v[k];
-    }
-    uint32_t x = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(x, d, 64);
-      if (lane >= d) x += y;
-    }
-    uint32_t run = x - sum;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int r = lane * 4 + k;
-      if (r < R) rowoff[r0 + r] = run;
-      run += v[k];
-    }
+  for (int r = threadIdx.x; r < R; r += kFinishThreads) {
+    const uint32_t d = t.rbase[r];
+    rowoff[r0 + r] = d < nd0 ? s_off[d] : U;
   }
   if (threadIdx.x == 0) usub[g] = U;
 }
 
+// A build of at most kHeavySplitPairs pairs, in the one launch that it makes: each of the first
+// kHeavyPar listed sub-buckets is reduced by a team of workgroups, with no workgroup waiting
+// for another.  Every member works out the digit layout and the digits' pair counts itself
+// (two reads of at most 2^16 keys); a digit's member then sums it straight from the
+// unpartitioned pairs, keeping those of the digit, and writes its entries where the digit's
+// pairs would start.  The last member to finish turns the entry counts into offsets
+// (heavy_finish).  One workgroup for a whole sub-bucket (heavy_rest) took 5 us for each of the
+// 264 or more leaves of a fan's: 500 tetrahedra around a node 0.78 ms in all, ten fans of 650
+// 1.7 ms.
+template <typename V, bool RES>
+__device__ void heavy_team(unsigned char* smem, const HeavyArgs<V>& A, uint32_t blk, uint32_t nblk) {
+  const HeavySmem sm(smem);
+  // (the words of heavy_split, which a team does not use)
+  uint32_t* const s_start = sm.hist;                    // [kHvyDigits + 1] pairs before each digit
+  uint32_t* const s_rbase = s_start + kHvyDigits + 1;   // [kHvyRows + 1]
+  uint32_t* const s_rsh = s_rbase + kHvyRows + 1;       // [kHvyRows]
+  uint32_t* const s_rows = s_rsh + kHvyRows;            // [kHvyRows]
+  static_assert(kHvyDigits + 1 + 3 * kHvyRows + 1 <= kDigits + 2 * (kDigits + 1), "a team's words fit");
+  __shared__ uint32_t s_last;
+  const uint32_t team = nblk / A.npar, it = blk % A.npar, member = blk / A.npar;
+  if (member >= team) return;
+  const int colbits = A.colbits;
+  const uint32_t g = A.ov_list[it], beg = A.sbb[g], end = A.sbb[g + 1];
+  const HeavyTable t(A.hvy, it);
+  for (int h = threadIdx.x; h < kLeafKeys; h += kHeavyThreads) {
+    sm.lo[h] = 0ull;
+    sm.hi[h] = 0ll;
+    sm.top[h] = 0ll;
+  }
+  if (threadIdx.x < kLeafKeys / 4) ((uint32_t*)sm.occ)[threadIdx.x] = 0u;
+  for (int d = threadIdx.x; d <= kHvyDigits; d += kHeavyThreads) s_start[d] = 0u;
+  if (threadIdx.x < kHvyRows) s_rows[threadIdx.x] = 0u;
+  __syncthreads();
+  heavy_count(A.ikey, beg, end, s_rows, [&](uint32_t k) { return k >> colbits; });
+  __syncthreads();
+  heavy_layout(t, s_rows, end - beg, colbits, member == 0, s_rbase, s_rsh, sm.scan);
+  const uint32_t nd = s_rbase[kHvyRows];
+  heavy_count(A.ikey, beg, end, s_start, [&](uint32_t k) { return heavy_digit(k, colbits, s_rbase, s_rsh); });
+  __syncthreads();
+  block_scan_array(s_start, (int)nd + 1, sm.scan);  // (ends with a barrier)
+  if (member == 0)
+    for (uint32_t d = threadIdx.x; d <= nd; d += kHeavyThreads) t.st[d] = beg + s_start[d];
+  int32_t* const tcol = (int32_t*)A.akey;
+  for (uint32_t d = member; d < nd; d += team) {
+    const uint32_t a = beg + s_start[d];
+    uint32_t U = 0;
+    if (s_start[d + 1] > s_start[d]) {
+      const uint32_t r = heavy_row(s_rbase, d), sh = s_rsh[r], w = 1u << sh;
+      const uint32_t k0 = (r << colbits) + ((d - s_rbase[r]) << sh);
+      // leaves of the digit (one, unless the mesh has very many nodes), from its keys found next
+      for (uint32_t at = 0; at < w;) {
+        if (w > (uint32_t)kLeafKeys) {
+          uint32_t mn = w;
+          heavy_stream<false>(A.ikey, A.ival, beg, end, [&](uint32_t k, V, bool ok) {
+            const uint32_t x = k - k0;
+            mn = ok && x >= at && x < mn ? x : mn;
+          });
+          if (threadIdx.x == 0) sm.misc[0] = w;
+          __syncthreads();
+          if (mn < w) atomicMin(&sm.misc[0], mn);
+          __syncthreads();
+          at = sm.misc[0];
+          __syncthreads();
+          if (at >= w) break;
+        }
+        const uint32_t n = w - at < (uint32_t)kLeafKeys ? w - at : (uint32_t)kLeafKeys;
+        heavy_leaf_sum<V, true>(sm, A.ikey, A.ival, beg, end, k0 + at, A.F, n);
+        U += heavy_leaf_emit<V, RES>(sm, k0 + at, A.F, colbits, tcol + a, A.aval + a, RES ? A.tres + a : nullptr, U);
+        at += n;
+      }
+    }
+    if (threadIdx.x == 0) t.ucnt[d] = U;
+  }
+  __threadfence();  // this thread's entries and counts before the arrival
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(&t.meta[1], 1u) == team - 1 ? 1u : 0u;
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  heavy_finish<V, RES>(smem, A, it);
+}
+
 // The sub-buckets listed by pass 3, one kernel per phase; with none listed every workgroup
 // returns at once.  At most `par` of them are split by the whole device; a build of at most
-// 2^16 pairs has no pair to spare for that (par = 0): it launches the last phase alone,
-// whose workgroups take whole sub-buckets.  The phases are separate launches: one kernel
+// 2^16 pairs launches one phase alone, whose workgroups form teams (heavy_team).  The others'
+// phases are separate launches: one kernel
 // that hands their workgroups out as tickets in order, each phase waiting for the one
 // before, did not finish on a batch with two heavy rows.
 enum HeavyPhase { kHeavyRowsPhase, kHeavyHistPhase, kHeavyStartsPhase, kHeavyScatterPhase, kHeavyBigPhase,
-                  kHeavyRangesPhase, kHeavyFinishPhase };
+                  kHeavyRangesPhase, kHeavyFinishPhase, kHeavyTeamPhase };
 constexpr int64_t kHeavySplitPairs = 1 << 16;
 constexpr int kScanHere = 16384;  // sub-buckets whose entry counts the last phase scans itself
 
@@ -3138,11 +3199,16 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy(HeavyArgs<V> A, const u
   if constexpr (PHASE == kHeavyScatterPhase) heavy_scatter<V>(smem, A, blk, nblk);
   if constexpr (PHASE == kHeavyBigPhase) heavy_bigleaf<V>(smem, A, blk, nblk);
   if constexpr (PHASE == kHeavyRangesPhase) {
-    if (A.npar) heavy_ranges<V, RES>(smem, A, blk, nblk);
+    heavy_ranges<V, RES>(smem, A, blk, nblk);
     __syncthreads();
     heavy_rest<V, RES>(smem, A, blk, nblk);
   }
   if constexpr (PHASE == kHeavyFinishPhase) heavy_finish<V, RES>(smem, A, blk);
+  if constexpr (PHASE == kHeavyTeamPhase) {
+    heavy_team<V, RES>(smem, A, blk, nblk);
+    __syncthreads();
+    heavy_rest<V, RES>(smem, A, blk, nblk);
+  }
   if constexpr (SCAN) {
     if (!ubase) return;
     __shared__ uint32_t s_last;

@@ -242,8 +242,8 @@ struct Carry {
   int32_t* rows_out = nullptr;
 };
 
-// heavy sub-buckets that the whole device may split
-inline uint32_t heavy_par(const Plan& p) { return p.T > kHeavySplitPairs ? (uint32_t)kHeavyPar : 0u; }
+// a build so small that its heavy sub-buckets are reduced by teams of one launch
+inline bool heavy_teams(const Plan& p) { return p.T <= kHeavySplitPairs; }
 
 // pass 3, then the sub-buckets it could not hold (in parts; k_heavy, which returns at once when there
 // are none; its last launch scans the entry counts of few sub-buckets into ubase and nnz)
@@ -290,14 +290,13 @@ int launch_pass3(const Plan& p, unsigned char* ws, V* tres, int64_t* nnz_dev, hi
   const unsigned cus = (unsigned)std::max(1, p.cus);
   auto phase = [&](auto kern, unsigned grid, size_t lds) {
     if (!set_lds(kern, lds)) return (int)KB_EHIP;
-    kern<<<grid, kHeavyThreads, lds, s>>>(A, head, head + 1, heavy_par(p), head + 2, ubase, nnz_dev);
+    kern<<<grid, kHeavyThreads, lds, s>>>(A, head, head + 1, (uint32_t)kHeavyPar, head + 2, ubase, nnz_dev);
     return hipGetLastError() == hipSuccess ? (int)KB_OK : (int)KB_EHIP;
   };
   constexpr size_t kTabLds = 4 * (size_t)(kHvyDigits + 2 * kHvyRows + 1 + kHeavyThreads / 64 + 1);
-  if (!heavy_par(p))
-    return phase(k_heavy<V, RES, kHeavyRangesPhase, true>, (unsigned)std::min<int64_t>(std::max<int64_t>(p.nsub, 1),
-        cus),
-                 HeavySmem::bytes());
+  if (heavy_teams(p))  // (at least a workgroup for each of the sub-buckets that a team may take)
+    return phase(k_heavy<V, RES, kHeavyTeamPhase, true>,
+                 std::max<unsigned>(kHeavyPar, (unsigned)std::min<int64_t>(p.nsub, cus)), HeavySmem::bytes());
   KB_TRY(phase(k_heavy<V, RES, kHeavyRowsPhase>, 2 * cus, kTabLds));
   KB_TRY(phase(k_heavy<V, RES, kHeavyHistPhase>, 2 * cus, kTabLds));
   KB_TRY(phase(k_heavy<V, RES, kHeavyStartsPhase>, kHeavyPar, kTabLds));
@@ -373,7 +372,7 @@ int assemble_tail(const Plan& p, unsigned char* ws, int32_t* row_ptr, int32_t* c
     auto* rowoff = (const uint32_t*)(ws + p.o_rowoff);
     auto* ov_list = (const uint32_t*)(ws + p.o_ovl);
     auto* hvy = (const uint32_t*)(ws + p.o_hvy);
-    const uint32_t par = heavy_par(p);
+    const uint32_t par = kHeavyPar;
     if (br)
       k_final<V, false, true><<<gf, 256, 0, s>>>(sbb, ubase, tcol, tval, nullptr, rowoff, sub, p.nn, row_ptr, col_idx,
                                                  vals, nullptr, nullptr, cap, status, ov_list, head + 1, hvy, par, *br);
@@ -420,12 +419,12 @@ int build_impl(const Plan& p, const kb_mesh* m, const void* klow, unsigned char*
   {
     const bool first = !cr || cr->first;
     auto* hvy = (uint32_t*)(ws + p.o_hvy);
-    const int64_t n = std::max<int64_t>(
-        {pad0, p.mode != kTwoLevel ? p.nsub_d : 0, (int64_t)2 * kHvyRows * std::max(1u, heavy_par(p))});
+    const int n_zero = heavy_teams(p) ? 1 : kHvyRows;
+    const int64_t n = std::max<int64_t>({pad0, p.mode != kTwoLevel ? p.nsub_d : 0, (int64_t)n_zero * kHeavyPar});
     k_begin<NEN><<<(unsigned)(kSamples + std::min<int64_t>(div_up(n, 256), 8192)), 256, 0, s>>>(
         m->conn, p.nel, p.nn, p.tile, p.ntiles, p.s2d, p.mode, first ? status : nullptr, first ? nnz_dev : nullptr,
         head, subcnt, p.nsub_d, m->coords, (double4*)(ws + p.o_coords4), pad0,
-        hvy + kHvyDigits * 2 + 1, (int)heavy_par(p), kHvyWords, 2 * kHvyRows);
+        hvy + (heavy_teams(p) ? HeavyTable::kTeamAt : HeavyTable::kRpairAt), kHeavyPar, kHvyWords, n_zero);
     KB_LAUNCH_CHECK();
   }
 
