@@ -369,7 +369,7 @@ int check_mesh_ptrs(const kb_mesh* m, bool need_geometry) {
 
 }  // namespace
 
-// adjoint workspace: corner records and places, node accumulators (large buckets only),
+// adjoint workspace: corner records and places, the large buckets' node accumulators,
 // bucket counts and starts, head words, the list of large buckets
 namespace {
 struct AdjointPlan {
@@ -395,7 +395,7 @@ int make_adjoint_plan(const kb_mesh* m, AdjointPlan* p) {
   };
   p->o_rec = take(sizeof(AdjointRecord) * nc);
   p->o_rel = take(4 * nc);
-  p->o_acc = take(p->extra ? 8 * kAdjAcc * (size_t)m->n_node : 0);
+  p->o_acc = take(8 * kAdjAcc * ((size_t)std::min(p->extra, p->nb) << p->bits));
   p->o_cnt = take(4 * (size_t)p->nb);
   p->o_start = take(4 * ((size_t)p->nb + 1));
   p->o_head = take(16);
