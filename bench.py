@@ -46,12 +46,12 @@ WORKLOADS = {
 }
 
 
-def algorithmic_bytes(elem: int, n_elem: int, n_node: int, nnz: int, prec: str) -> dict:
+def algorithmic_bytes(elem: int, n_elem: int, n_node: int, nnz: int, prec: str, direct: bool = False) -> dict:
     """Compulsory HBM bytes of each stage and of the whole path (per launch).
 
     Per stage: its inputs read once and its outputs written once, in the formats the
     stages exchange: (16-bit row within its bucket, col, value) after pass 1, (packed key,
-    value) after pass 2.
+    value) after pass 2; with ``direct`` the latter after pass 1, and no pass 2.
     For the path: E, c and C read once (coordinates once per node), the lower values
     written once and read once, CSR written once.
     """
@@ -70,6 +70,8 @@ def algorithmic_bytes(elem: int, n_elem: int, n_node: int, nnz: int, prec: str) 
         "reduce": (4 + vb) * T + (4 + vb) * nnz + 4 * n_node,     # pairs in; unique entries, row counts out
         "compress": 2 * (4 + vb) * nnz + 8 * n_node,              # unique entries in, CSR out
     }
+    if direct:
+        b.update(integrate=conn + coef + coords + (4 + vb) * T, histogram=0, partition=0)
     # the path as a whole: E, c, C in once, lower values once out and in, CSR out
     b["path"] = conn + coef + coords + 2 * vb * T + (4 + vb) * nnz + 4 * (n_node + 1)
     return b
@@ -92,14 +94,18 @@ def source_digest() -> str:
     return h.hexdigest()
 
 
-def pass1_kernel(elem: int, prec: str, op: str) -> str:
+#: elements of the tile that small meshes take so that every compute unit has one
+SMALL_TILE = 64
+
+
+def pass1_kernel(elem: int, prec: str, op: str, tile: int = 0) -> str:
     """The pass-1 kernel a build from coordinates launches: tets in the persistent tet
-    kernel; bricks in FP64 two tiles per workgroup, in FP32 a lane pair per element for the
-    stiffness matrix, else one lane per element."""
+    kernel; bricks in FP64 two tiles per workgroup (one of the small tiles), in FP32 a lane
+    pair per element for the stiffness matrix, else one lane per element."""
     if elem == 4:
         return "k_pass1_tet"
     if prec == "fp64":
-        return "k_pass1_two"
+        return "k_pass1" if tile == SMALL_TILE else "k_pass1_two"
     return "k_pass1_pair" if op == "stiffness" else "k_pass1"
 
 
@@ -208,9 +214,24 @@ def time_builds(kb, torch, mesh_dev, m, prec, steps, warmup, stage_events=True, 
         for e in evs:
             e.close()
     res = result()
+    way = None if groups > 1 else partition_way(kb, b, m, prec, tuning, op)
     if isinstance(res, list):  # a batch: totals over its meshes
         res = BatchTotals(sum(r.nnz for r in res), res[0].n_fallback if res else 0)
-    return ms, wall / steps * 1e3, stages, res
+    return ms, wall / steps * 1e3, stages, res, way
+
+
+def partition_way(kb, b, m, prec, tuning, op="stiffness"):
+    """(whether the last build of ``b`` sent its pairs straight to the sub-buckets, elements of
+    a pass-1 tile)."""
+    import ctypes
+
+    way, tile, at = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_size_t()
+    mesh, tu = kb._mesh(m.elem, m.n_elem, m.n_node, op=op), (tuning or kb.Tuning()).to_c()
+    kb._check(kb._lib.lib().kb_plan_way(ctypes.byref(mesh), kb._prec(prec), ctypes.byref(tu), ctypes.byref(way),
+                                        ctypes.byref(tile), ctypes.byref(at)), "kb_plan_way")
+    if way.value == kb._lib.KB_WAY_SAMPLED:  # the device decided
+        return bytes(b.ws[at.value:at.value + 4].tolist()) == (1).to_bytes(4, sys.byteorder), tile.value
+    return way.value == kb._lib.KB_WAY_DIRECT, tile.value
 
 
 def time_adjoint(kb, torch, mesh_dev, m, steps, warmup):
@@ -508,9 +529,10 @@ def main():
         tune = {"tuning": entry["tuning"], "source": entry["source"], "key": entry["key"],
                 "search_s": time.perf_counter() - t0, "candidates_timed": entry.get("candidates_timed")}
         print(f"[bench] tuning ({entry['source']}): {tuning}", file=sys.stderr, flush=True)
-    ms, wall_ms, stages, res = time_builds(kb, torch, mesh_dev, m, prec, args.steps, args.warmup,
-                                           stage_events=not args.profile_steps, tuning=tuning, op=args.op,
-                                           groups=groups)
+    ms, wall_ms, stages, res, way = time_builds(kb, torch, mesh_dev, m, prec, args.steps, args.warmup,
+                                                stage_events=not args.profile_steps, tuning=tuning, op=args.op,
+                                                groups=groups)
+    direct, tile = way or (False, 0)
     nnz = res.nnz
     print(f"[bench] {prec}: {ms:.3f} ms/step, nnz {nnz}, fallback elements {res.n_fallback}", file=sys.stderr,
           flush=True)
@@ -520,11 +542,7 @@ def main():
     n_fallback = res.n_fallback
     del res
     value = m.n_elem / (ms * 1e-3)
-    ab = algorithmic_bytes(m.elem, m.n_elem, m.n_node, nnz, prec)
-    if stages and ab["partition"] > 2e6 * HBM_PEAK_GBS * stages["partition"]:
-        # faster than its bytes can move: pass 1 wrote to the sub-buckets (key, value), and the
-        # partition's kernels returned at once
-        ab.update(integrate=ab["integrate"] - 2 * m.n_elem * m.elem * (m.elem + 1) // 2, histogram=0, partition=0)
+    ab = algorithmic_bytes(m.elem, m.n_elem, m.n_node, nnz, prec, direct)
     out = {
         "metric": METRIC, "value": value, "unit": "elements/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "scaling": "weak",
@@ -535,7 +553,7 @@ def main():
                    "fp64_fallback_elements": n_fallback, "parallelism": "single GPU",
                    "tuning": {"block": tuning.block, "bucket_bits": tuning.bucket_bits, "sub_bits": tuning.sub_bits,
                               "seg_pairs": tuning.seg_pairs, "table_slots": tuning.table_slots},
-                   "groups": groups if groups > 1 else 1},
+                   "groups": groups if groups > 1 else 1, "direct": direct},
         "path_hbm_frac": ab["path"] / (ms * 1e-3) / (HBM_PEAK_GBS * 1e9),
     }
     if stages and groups > 1:
@@ -546,7 +564,7 @@ def main():
         dom = max(SINGLE_KERNEL_STAGES, key=lambda k: stages[k])
         kernel = SINGLE_KERNEL_STAGES[dom]
         if dom == "integrate":
-            kernel = pass1_kernel(m.elem, prec, args.op)
+            kernel = pass1_kernel(m.elem, prec, args.op, tile)
         elif dom == "reduce" and args.workload == "fan":
             # its heavy row adds the heavy-path kernels to the stage
             kernel = "k_pass3 + heavy path (k_heavy)"
@@ -565,7 +583,7 @@ def main():
                                  if stages.get(k, 0) > 0}
     if tune is not None:
         # the built-in tuning on the same batch, for comparison with the tuned value
-        msd, _, _, _ = time_builds(kb, torch, mesh_dev, m, prec, args.steps, args.warmup, stage_events=False)
+        msd, _, _, _, _ = time_builds(kb, torch, mesh_dev, m, prec, args.steps, args.warmup, stage_events=False)
         tune["default_ms_per_step"] = msd
         tune["default_value"] = m.n_elem / (msd * 1e-3)
         tune["speedup_vs_default"] = msd / ms
@@ -579,7 +597,7 @@ def main():
             out["copy_ceiling"]["dominant_kernel_frac"] = out["roofline"]["achieved"] / cc["GBps"]
         print(f"[bench] device copy {cc['GBps']:.0f} GB/s", file=sys.stderr, flush=True)
     if not args.no_fp64 and prec != "fp64":
-        ms64, _, st64, r64 = time_builds(kb, torch, mesh_dev, m, "fp64", max(3, args.steps // 2), 2,
+        ms64, _, st64, r64, _ = time_builds(kb, torch, mesh_dev, m, "fp64", max(3, args.steps // 2), 2,
                                          stage_events=False, tuning=kb.Tuning(bucket_bits=args.bucket_bits,
                                                                               sub_bits=args.sub_bits), op=args.op,
                                          groups=groups)

@@ -160,6 +160,19 @@ typedef struct {
 int kb_plan(const kb_mesh* mesh, int prec, const kb_tuning* tuning, size_t* ws_bytes, int64_t* n_triplets);
 
 /*
+ * For measurements: how a build of this mesh shape partitions its pairs (host only; the result
+ * is the same).  *way: KB_WAY_BUCKETS, in two levels (the stages histogram and partition);
+ * KB_WAY_DIRECT, straight to the sub-buckets (those stages have nothing to do); or
+ * KB_WAY_SAMPLED, decided on the device from a sample of the elements: the uint32 at byte
+ * *way_at of the workspace is then 1 after a build that went direct.  *tile: elements that a
+ * workgroup of pass 1 takes at a time.  Errors as kb_plan.
+ */
+#define KB_WAY_BUCKETS 0
+#define KB_WAY_DIRECT 1
+#define KB_WAY_SAMPLED 2
+int kb_plan_way(const kb_mesh* mesh, int prec, const kb_tuning* tuning, int32_t* way, int32_t* tile, size_t* way_at);
+
+/*
  * Full construction (Alg. 1 with the integration of Alg. 2): integrate the lower
  * triangle of every element matrix and assemble lower-triangular CSR K.
  *   ws        device workspace of ws_bytes >= kb_plan's figure (contents scratch)

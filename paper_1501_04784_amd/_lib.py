@@ -9,6 +9,7 @@ LIB_PATH = os.path.join(HERE, "libkbuild.so")
 
 KB_HEX8, KB_TET4 = 8, 4
 KB_OP_STIFFNESS, KB_OP_MASS = 0, 1
+KB_WAY_BUCKETS, KB_WAY_DIRECT, KB_WAY_SAMPLED = 0, 1, 2
 KB_FP64, KB_FP32, KB_FP32_FB64 = 0, 1, 2
 KB_OK, KB_EINVAL, KB_ERANGE, KB_ENOSPC, KB_EHIP = 0, -1, -2, -3, -4
 KB_STATUS_WORDS = 4
@@ -18,8 +19,8 @@ KB_SCRATCH_BYTES = 64 << 20  # fixed workspace of kb_build_lower_csr_noalloc
 STAGE_NAMES = ("init", "count", "offsets", "integrate", "histogram", "partition", "reduce", "compress")
 
 # every function declared in include/kbuild.h
-EXPORTS = ("kb_plan", "kb_build_lower_csr", "kb_build_lower_csr_noalloc", "kb_integrate_lower", "kb_assemble_lower_csr", "kb_plan_dof",
-           "kb_assemble_lower_csr_dof", "kb_plan_grouped", "kb_build_lower_csr_grouped",
+EXPORTS = ("kb_plan", "kb_plan_way", "kb_build_lower_csr", "kb_build_lower_csr_noalloc", "kb_integrate_lower",
+           "kb_assemble_lower_csr", "kb_plan_dof", "kb_assemble_lower_csr_dof", "kb_plan_grouped", "kb_build_lower_csr_grouped",
            "kb_build_lower_csr_group_pass", "kb_plan_batched", "kb_build_lower_csr_batched", "kb_plan_adjoint",
            "kb_adjoint_lower", "kb_status_string", "kb_version")
 
@@ -78,6 +79,9 @@ def lib():
         PM, PT = ctypes.POINTER(KbMesh), ctypes.POINTER(KbTuning)
         L.kb_plan.argtypes = [PM, i32, PT, ctypes.POINTER(sz), ctypes.POINTER(i64)]
         L.kb_plan.restype = i32
+        L.kb_plan_way.argtypes = [PM, i32, PT, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32),
+                                  ctypes.POINTER(sz)]
+        L.kb_plan_way.restype = i32
         L.kb_build_lower_csr.argtypes = [PM, i32, PT, p, sz, p, p, p, i64, p, p, p]
         L.kb_build_lower_csr.restype = i32
         L.kb_build_lower_csr_noalloc.argtypes = [PM, i32, PT, p, p, p, i64, p, p, p]

@@ -492,6 +492,17 @@ int kb_plan(const kb_mesh* mesh, int prec, const kb_tuning* tuning, size_t* ws_b
   return KB_OK;
 }
 
+static_assert(kTwoLevel == KB_WAY_BUCKETS && kDirect == KB_WAY_DIRECT && kAsk == KB_WAY_SAMPLED, "as in the header");
+
+int kb_plan_way(const kb_mesh* mesh, int prec, const kb_tuning* tuning, int32_t* way, int32_t* tile, size_t* way_at) {
+  Plan p;
+  KB_TRY(make_plan(mesh, prec, tuning, &p));
+  if (way) *way = p.mode;
+  if (tile) *tile = p.tile;
+  if (way_at) *way_at = p.o_head + 4 * kHeadWay;
+  return KB_OK;
+}
+
 // use_scratch: the library's fixed scratch array is the workspace (ws, ws_bytes ignored);
 // every host check comes before the device is touched
 static int build_common(const kb_mesh* mesh, int prec, const kb_tuning* tuning, const void* klow, void* ws,
