@@ -20,8 +20,8 @@ STAGE_NAMES = ("init", "count", "offsets", "integrate", "histogram", "partition"
 
 # every function declared in include/kbuild.h
 EXPORTS = ("kb_plan", "kb_plan_way", "kb_build_lower_csr", "kb_build_lower_csr_noalloc", "kb_integrate_lower",
-           "kb_assemble_lower_csr", "kb_plan_dof", "kb_assemble_lower_csr_dof", "kb_plan_grouped", "kb_build_lower_csr_grouped",
-           "kb_build_lower_csr_group_pass", "kb_plan_batched", "kb_build_lower_csr_batched", "kb_plan_adjoint",
+           "kb_assemble_lower_csr", "kb_plan_dof", "kb_assemble_lower_csr_dof", "kb_plan_grouped",
+           "kb_build_lower_csr_grouped", "kb_build_lower_csr_group_pass", "kb_plan_batched", "kb_build_lower_csr_batched", "kb_plan_adjoint",
            "kb_adjoint_lower", "kb_status_string", "kb_version")
 
 

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void k_adjoint_count(const int32_t* __restrict
   }
   // bucket starts, and the buckets that need several workgroups
   __shared__ uint32_t s_scan[8], s_last;
-  __syncthreads();  // (the additions to cnt have returned their results)
+  __syncthreads();  // (the additions to cnt have returned their results: last_block_starts)
   if (threadIdx.x == 0) s_last = atomicAdd(&head[1], 1u) == gridDim.x - 1 ? 1u : 0u;
   __syncthreads();
   if (!s_last) return;

@@ -355,7 +355,8 @@ int make_batch_plan(const kb_batch* b, int prec, const kb_tuning* tu, BatchPlan*
     return o;
   };
   bp->o_gconn = take(4 * (size_t)bp->p.nen * (size_t)bp->p.nel);
-  take(4 * ((size_t)bp->p.nn + 1));  // not used: the size stays that of plans which stored the union's row pointers
+  // (not used, once the union's row pointers: the plan is at least this much above a mesh's)
+  take(4 * ((size_t)bp->p.nn + 1));
   bp->o_flags = take(4);
   bp->total = off;
   return KB_OK;
@@ -426,10 +427,9 @@ int launch_adjoint(const AdjointPlan& p, const kb_mesh* m, const int32_t* row_pt
       m->conn, nel, nn, p.bits, nb, cnt, start, rel, head, big);
   KB_LAUNCH_CHECK();
   if (nel > 0) {
-    k_adjoint_elems<NEN><<<grid_for(nel, kAdjElemThreads), kAdjElemThreads, 0, s>>>(m->conn, m->coords, m->coef, nel,
-        nn, row_ptr, col_idx,
-                                                            nnz, w, grad_coef, p.bits, start, rel, rec, acc, head,
-                                                            big, status);
+    k_adjoint_elems<NEN><<<grid_for(nel, kAdjElemThreads), kAdjElemThreads, 0, s>>>(
+        m->conn, m->coords, m->coef, nel, nn, row_ptr, col_idx, nnz, w, grad_coef, p.bits, start, rel, rec, acc, head,
+        big, status);
     KB_LAUNCH_CHECK();
   }
   if (nn > 0) {
@@ -658,8 +658,8 @@ static int grouped_pass(const GroupPlan& gp, const kb_mesh* mesh, int64_t g, con
   cr.rows_out = out.rows;
   const Carry* crp = gp.n_groups > 1 ? &cr : nullptr;
   Events& e = g == gp.n_groups - 1 ? ev : none;
-  if (p.nen == 8) return dispatch_build<8>(p, &mg, nullptr, w, out.rp, out.col, out.val, cap, out.nnz, status_dev, e,
-      s, crp);
+  if (p.nen == 8)
+    return dispatch_build<8>(p, &mg, nullptr, w, out.rp, out.col, out.val, cap, out.nnz, status_dev, e, s, crp);
   return dispatch_build<4>(p, &mg, nullptr, w, out.rp, out.col, out.val, cap, out.nnz, status_dev, e, s, crp);
 }
 
@@ -751,10 +751,10 @@ int kb_build_lower_csr_batched(const kb_batch* batch, int prec, const kb_tuning*
   const BatchRows br{batch->node_off, nm, flags};
   if (p.nen == 8)
     KB_TRY(dispatch_build<8>(p, &m, nullptr, w, row_ptr, col_idx, vals, cap, nnz_off + nm, status_dev, ev, s, nullptr,
-        &br));
+                             &br));
   else
     KB_TRY(dispatch_build<4>(p, &m, nullptr, w, row_ptr, col_idx, vals, cap, nnz_off + nm, status_dev, ev, s, nullptr,
-        &br));
+                             &br));
   k_batch_meshes<<<grid_for(std::max<int64_t>(nm, 1), 256), 256, 0, s>>>(
       (const uint32_t*)(w + p.o_ubase), (const uint32_t*)(w + p.o_rowoff), sub_buckets(p, w), p.nn, batch->node_off,
       nm, flags, row_ptr, nnz_off, status_dev);

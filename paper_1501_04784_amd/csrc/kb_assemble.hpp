@@ -95,8 +95,11 @@ __device__ __forceinline__ uint32_t block_scan_array(T* a, int n, uint32_t* smem
 __device__ __forceinline__ void last_block_starts(uint32_t* cnt, int n, uint32_t* starts, uint32_t* done,
                                                   uint32_t blocks) {
   __shared__ uint32_t s_scan[8], s_last;
-  // this thread's additions done before the arrival (atomics on both sides: nothing else
-  // passes between the workgroups, so the L2 need not be written back by a fence)
+  // This thread's additions done before the arrival.  Nothing but atomics passes between the
+  // workgroups, so the wait stands for a release fence, which would write back the L2.  That is
+  // particular to gfx9, not a release of the HIP memory model: there s_waitcnt vmcnt(0) also
+  // waits for atomics that return nothing, which by then are done where every XCD sees them, as
+  // the agent-scope loads below do (later families count such atomics apart, in vscnt).
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) s_last = atomicAdd(done, 1u) == blocks - 1 ? 1u : 0u;
@@ -156,24 +159,18 @@ __device__ __forceinline__ void to_fixed(double v, int F, uint64_t& lo, uint64_t
   }
 }
 
-// q (two's complement 128-bit, |q| < 2^95) as c0 + c1 * 2^48 with c0 in [0, 2^48)
-// and c1 signed: sums of up to 2^16 such terms fit in one unsigned / signed 64-bit
-// word each, so they can be accumulated without carries (and in any order).
-__device__ __forceinline__ void split48(uint64_t lo, uint64_t hi, uint64_t& c0, int64_t& c1) {
-  c0 = lo & ((1ull << 48) - 1);
-  c1 = (int64_t)((lo >> 48) | (hi << 16));
-}
-
-// split48 chunks of trunc(v * 2^F) for a double or float value (non-finite: zero),
-// formed in FP64 arithmetic, where every step is exact: v 2^F only moves the exponent
+// A double or float value's q = trunc(v * 2^F) (non-finite: zero; |q| < 2^95) as chunks
+// c0 + c1 * 2^48 with c0 in [0, 2^48) and c1 signed: sums of up to 2^16 such terms fit in one
+// unsigned / signed 64-bit word each, so they can be accumulated without carries (and in any
+// order).  Formed in FP64 arithmetic, where every step is exact: v 2^F only moves the exponent
 // (|q| < 2^95; a result below 2^-1022 truncates to 0 either way), trunc and floor give
 // integers, and c1 = floor(q / 2^48), c0 = q - c1 2^48 in [0, 2^48) are multiples of
 // q's last bit below 2^53 of it.  Each integer then becomes a 64-bit word by an exact
 // FP64 addition: c0 + 2^52 and c1 + 1.5 2^52 (|c1| < 2^47) lie in [2^52, 2^53), where
 // the spacing is 1, so their bit patterns are those of the constants plus the integer
 // (two's complement for a negative c1), and the constants' low 32 bits are zero: one
-// 32-bit subtraction from the high word leaves the integer.  The same integers as
-// split48 of to_fixed's q, without forming the 128-bit integer and without branches.
+// 32-bit subtraction from the high word leaves the integer: the same as from to_fixed's
+// q, without forming the 128-bit integer and without branches.
 __device__ __forceinline__ void to_chunks(double v, int F, uint64_t& c0, int64_t& c1) {
   const double d = isfinite(v) ? v : 0.0;
   const double q = trunc(ldexp(d, F));
@@ -551,9 +548,9 @@ __device__ __forceinline__ void count_rows(const TileSlots<DIRECT>& sl, uint32_t
 template <int NEN, bool DIRECT>
 __device__ __forceinline__ void count_tiles(uint32_t* s_h, const int32_t* __restrict__ conn, int64_t n_elem,
                                             int64_t n_node, int te, int64_t ntiles, uint32_t n_pad, int per,
-                                                int slot_words,
-                                            int s1, int nb, int s2, int nsub, int mode, uint32_t* __restrict__ hist,
-                                            uint32_t* __restrict__ subcnt, uint32_t* __restrict__ status) {
+                                                int slot_words, int s1, int nb, int s2, int nsub, int mode,
+                                            uint32_t* __restrict__ hist, uint32_t* __restrict__ subcnt,
+                                            uint32_t* __restrict__ status) {
   const TileSlots<DIRECT> sl(s_h, s_h + kSlotsHash, mode, s1, nb, s2, nsub);
   const int64_t t0 = (int64_t)(blockIdx.x - n_pad) * per, t1 = t0 + per < ntiles ? t0 + per : ntiles;
   uint32_t flags = 0;
@@ -592,7 +589,8 @@ __global__ __launch_bounds__(256) void k_count(const int32_t* __restrict__ conn,
                                                int64_t pad0) {
   extern __shared__ uint32_t s_h[];  // the slots' counters, then (hash) their keys
   const bool direct = mode == kAsk ? votes_direct(head + kHeadVotes) : mode == kDirect;
-  if (mode == kAsk && blockIdx.x == n_pad && threadIdx.x == 0) head[kHeadWay] = direct ? 1u : votes_scattered(head + kHeadVotes) ? 2u : 0u;
+  if (mode == kAsk && blockIdx.x == n_pad && threadIdx.x == 0)
+    head[kHeadWay] = direct ? 1u : votes_scattered(head + kHeadVotes) ? 2u : 0u;
   if (blockIdx.x < n_pad) {
     if (direct) return;
     const int64_t step = (int64_t)n_pad * blockDim.x;
@@ -643,8 +641,7 @@ static __global__ __launch_bounds__(kScanThreads) void k_offsets_sums(const uint
 // one workgroup per bucket b: exclusive scan of csum[.][b] over the chunks, in place; the
 // bucket's total to tot[b].  Direct: one workgroup per chunk of subcnt.
 static __global__ __launch_bounds__(kScanThreads) void k_offsets_scan(uint32_t* __restrict__ csum, int64_t nchunk,
-    int nb,
-                                                               uint32_t* __restrict__ tot, uint32_t* subcnt,
+                                                               int nb, uint32_t* __restrict__ tot, uint32_t* subcnt,
                                                                int64_t nsub, const int32_t* __restrict__ part,
                                                                uint32_t* __restrict__ sbb, int mode,
                                                                const uint32_t* __restrict__ way) {
@@ -697,7 +694,7 @@ static __global__ __launch_bounds__(1024) void k_bucket_starts(const uint32_t* _
 // counts of chunk c turned into offsets in place (grid as k_offsets_sums); the nb
 // workgroups after those write seg2b[s] = bucket of segment s
 static __global__ __launch_bounds__(256) void k_offsets_down(uint32_t* __restrict__ hist,
-    const uint32_t* __restrict__ csum,
+                                                      const uint32_t* __restrict__ csum,
                                                       const uint32_t* __restrict__ bstart, int64_t ntiles, int nb,
                                                       int64_t nchunk, const uint32_t* __restrict__ segbase,
                                                       uint32_t* __restrict__ seg2b, int mode,
@@ -810,8 +807,7 @@ struct PackedValues {
 // places at once)
 template <int N, int R0, int NEN, typename V, int BLOCK, bool DIRECT, typename Values>
 __device__ __forceinline__ void pass1_stage(const Pass1Smem<V, BLOCK, DIRECT>& sm, const PairOut<V>& o,
-    const int32_t (&E)[NEN],
-                                            const uint32_t (&q)[N], const Values& k) {
+                                            const int32_t (&E)[NEN], const uint32_t (&q)[N], const Values& k) {
 #pragma unroll
   for (int a = 0; a < N; ++a) {
     const int row = R0 + a;
@@ -1137,7 +1133,7 @@ __global__ __launch_bounds__(2 * BLOCK) void k_pass1_two(const int32_t* __restri
                                                        float tau, int64_t ntiles,
                                                        const PairOut<typename PrecTraits<P>::V> o,
                                                        uint32_t* __restrict__ emax, uint32_t* __restrict__ status,
-                                                           uint32_t persist) {
+                                                       uint32_t persist) {
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t G = walkers(o.mode, o.way, persist);
   if (blockIdx.x >= G) return;
@@ -1482,7 +1478,7 @@ __device__ __forceinline__ void pass1_wide(unsigned char* smem, const int32_t* _
 
 template <int NEN, typename V>
 __global__ __launch_bounds__(kWideThreads) void k_pass1_wide(const int32_t* __restrict__ conn,
-    const V* __restrict__ klow,
+                                                  const V* __restrict__ klow,
                                                   int64_t n_elem, int64_t n_node, int te, const PairOut<V> o,
                                                   uint32_t* __restrict__ emax, uint32_t* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1696,7 +1692,7 @@ __global__ __launch_bounds__(256) void k_hist2(const uint16_t* __restrict__ irow
 // sbb[b * p2 + j] (sbb[nb * p2] = number of pairs).  A segment's run for sub-bucket j
 // starts at sbb[b * p2 + j] + hist2[s * p2 + j].
 static __global__ __launch_bounds__(256) void k_colscan(uint32_t* __restrict__ hist2,
-    const uint32_t* __restrict__ bstart,
+                                                 const uint32_t* __restrict__ bstart,
                                                  const uint32_t* __restrict__ segbase, int nb, int p2,
                                                  uint32_t* __restrict__ sbb, int mode,
                                                  const uint32_t* __restrict__ way) {
@@ -3371,8 +3367,7 @@ __global__ __launch_bounds__(256) void k_final(const uint32_t* __restrict__ sbb,
   }
   if (blockIdx.x >= n_wave) {
     final_heavy<V, GROUPED, BATCH>(sbb, ubase, tcol, tval, tres, rowoff, s2, n_node, nsub, ov_list, ov_count, hvy,
-        col_idx,
-                            vals, res, rows, cap, batch, par, blockIdx.x - n_wave, kFinalHeavyGrid);
+                                   col_idx, vals, res, rows, cap, batch, par, blockIdx.x - n_wave, kFinalHeavyGrid);
     return;
   }
   const int lane = threadIdx.x & 63;

@@ -49,7 +49,7 @@ __global__ void k_batch_check(const int64_t* __restrict__ elem_off, const int64_
 // element can be placed in a mesh: every id becomes -1.
 template <int NEN>
 __global__ __launch_bounds__(256) void k_batch_conn(const int32_t* __restrict__ conn,
-    const int64_t* __restrict__ elem_off,
+                                                    const int64_t* __restrict__ elem_off,
                                                     const int64_t* __restrict__ node_off, int64_t n_mesh,
                                                     int64_t n_elem, const uint32_t* __restrict__ flags,
                                                     int32_t* __restrict__ gconn) {

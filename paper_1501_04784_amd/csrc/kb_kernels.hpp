@@ -351,6 +351,7 @@ __device__ __forceinline__ void gather_pair(const NODES& nodes, const int32_t (&
 template <Prec P>
 __device__ __forceinline__ void element_values_pair(const double (&xo)[4][3], double c, float tau, int h,
                                                     typename PrecTraits<P>::V (&k)[4][8], uint32_t* f, uint32_t* fb) {
+  static_assert(P != Prec::F64, "one lane per brick in FP64 (k_pass1_two)");
   using V = typename PrecTraits<P>::V;
   const double sg = h ? 1.0 : -1.0;
   double Cd[kModes][3];
@@ -369,24 +370,19 @@ __device__ __forceinline__ void element_values_pair(const double (&xo)[4][3], do
     Cd[5][j] = sg * (own[1] - o[1]);
     Cd[6][j] = sg * (own[3] - o[3]);
   }
-  bool ok;
+  float C[kModes][3];
+#pragma unroll
+  for (int m = 0; m < kModes; ++m)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) C[m][j] = (float)Cd[m][j];
   V M[4][6];
-  if constexpr (P == Prec::F64) {
-    ok = half_points<double, double, false>(Cd, M, 0.0, nullptr, h);
-  } else {
-    float C[kModes][3];
-#pragma unroll
-    for (int m = 0; m < kModes; ++m)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) C[m][j] = (float)Cd[m][j];
-    bool need_fb = false;
-    ok = half_points<float, float, P == Prec::F32FB>(C, M, tau, &need_fb, h);
-    if constexpr (P == Prec::F32FB) {
-      const int other = pair_other((int)need_fb);  // (outside any branch: both lanes take part)
-      if (need_fb || other) {  // the element: both halves with FP64 geometry
-        ok = half_points<double, float, false>(Cd, M, 0.0, nullptr, h);
-        if (h == 0) *fb += 1;
-      }
+  bool need_fb = false;
+  bool ok = half_points<float, float, P == Prec::F32FB>(C, M, tau, &need_fb, h);
+  if constexpr (P == Prec::F32FB) {
+    const int other = pair_other((int)need_fb);  // (outside any branch: both lanes take part)
+    if (need_fb || other) {  // the element: both halves with FP64 geometry
+      ok = half_points<double, float, false>(Cd, M, 0.0, nullptr, h);
+      if (h == 0) *fb += 1;
     }
   }
   half_matrix<V>(M, k, h);
@@ -429,19 +425,5 @@ __global__ __launch_bounds__(256) void k_integrate_store(const int32_t* __restri
   if (f) raise_flag(status, f);
   if (fb) atomicAdd(&status[1], fb);
 }
-
-// ------------------------------------------------------------------- row reduce
-template <typename V>
-struct Bits;
-template <>
-struct Bits<double> {
-  using U = uint64_t;
-  __device__ static U get(double v) { return (U)__double_as_longlong(v); }
-};
-template <>
-struct Bits<float> {
-  using U = uint32_t;
-  __device__ static U get(float v) { return __float_as_uint(v); }
-};
 
 }  // namespace kb

@@ -172,15 +172,14 @@ int launch_pass1_block(const Plan& p, const kb_mesh* m, const void* klow, unsign
     auto kern = k_pass1<NEN, P, FROM_VALUES, BLOCK, OP>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
     kern<<<(unsigned)p.ntiles, BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef, (const V*)klow, p.nel, p.nn,
-        p.tau, o,
-                                                   emax, status);
+                                                   p.tau, o, emax, status);
   } else {
     // tetrahedra: persistent
     auto kern = k_pass1_tet<P, FROM_VALUES, BLOCK, OP>;
     if (!set_lds(kern, p.lds1)) return KB_EHIP;
     kern<<<persistent_grid(p, BLOCK, p.ntiles), BLOCK, p.lds1, s>>>(m->conn, m->coords, coords4, m->coef,
-        (const V*)klow, p.nel, p.nn, p.tau, p.ntiles,
-                                             o, emax, status);
+                                                                    (const V*)klow, p.nel, p.nn, p.tau, p.ntiles, o,
+                                                                    emax, status);
   }
   KB_LAUNCH_CHECK();
   return KB_OK;
@@ -284,8 +283,7 @@ int launch_pass3(const Plan& p, unsigned char* ws, V* tres, int64_t* nnz_dev, hi
     default: KB_TRY(reduce(std::integral_constant<int, 4096>{}));
   }
   const HeavyArgs<V> A{key2, val2, (uint32_t*)tcol, tval, tres, sbb, sub, p.s2, p.colbits, p.nn, 0, rowoff, usub,
-      ov_list,
-                       0, 0, (uint32_t*)(ws + p.o_hvy)};
+                       ov_list, 0, 0, (uint32_t*)(ws + p.o_hvy)};
   uint32_t* const ubase = p.nsub <= kScanHere ? (uint32_t*)(ws + p.o_ubase) : nullptr;
   const unsigned cus = (unsigned)std::max(1, p.cus);
   auto phase = [&](auto kern, unsigned grid, size_t lds) {

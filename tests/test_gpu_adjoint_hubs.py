@@ -72,7 +72,8 @@ def test_time():
     """60,000 tetrahedra around a node against as many that share none: what the node's records
     add is two workgroups' reading of them, and an atomic per address would be ten times it."""
     hub = meshgen.fan_mesh(60000)
-    apart = meshgen.Mesh(4, np.arange(240000, dtype=np.int32).reshape(-1, 4), hub.coords[hub.conn.reshape(-1)], hub.coef)
+    apart = meshgen.Mesh(4, np.arange(240000, dtype=np.int32).reshape(-1, 4), hub.coords[hub.conn.reshape(-1)],
+                         hub.coef)
     say("[adjoint hubs] time")
     ms = milliseconds(hub), milliseconds(apart)
     assert ms[0] < 5 * ms[1], ms

@@ -27,7 +27,8 @@ def condition(x):
     out = []
     for p in [(r, s, t) for r in (-g, g) for s in (-g, g) for t in (-g, g)]:
         f = 1 + SIGNS * p
-        dn = np.stack([SIGNS[:, 0] * f[:, 1] * f[:, 2], f[:, 0] * SIGNS[:, 1] * f[:, 2], f[:, 0] * f[:, 1] * SIGNS[:, 2]])
+        dn = np.stack([SIGNS[:, 0] * f[:, 1] * f[:, 2], f[:, 0] * SIGNS[:, 1] * f[:, 2],
+                       f[:, 0] * f[:, 1] * SIGNS[:, 2]])
         out.append(np.linalg.cond(np.einsum("ia,naj->nij", dn / 8, x), np.inf))
     return np.stack(out, 1).reshape(-1, 2, 4).max(2)
 

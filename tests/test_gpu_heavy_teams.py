@@ -24,8 +24,9 @@ def check(conn, n_node, prec, tuning=None):
     rng = np.random.default_rng(conn.size)
     te = conn.shape[1] * (conn.shape[1] + 1) // 2
     klow = rng.integers(-8, 9, (conn.shape[0], te)).astype(np.float64)
-    k = kb.assemble_lower_csr(torch.from_numpy(conn).cuda(), n_node, torch.from_numpy(klow).to("cuda", kb.value_dtype(prec)),
-                              conn.shape[1], prec=prec, tuning=tuning)
+    k = kb.assemble_lower_csr(torch.from_numpy(conn).cuda(), n_node,
+                              torch.from_numpy(klow).to("cuda", kb.value_dtype(prec)), conn.shape[1], prec=prec,
+                              tuning=tuning)
     row_ptr, col, vals = assembled(conn, klow, n_node)
     assert np.array_equal(k.row_ptr.cpu().numpy(), row_ptr) and np.array_equal(k.col_idx.cpu().numpy(), col)
     assert np.array_equal(k.vals.cpu().numpy().astype(np.float64), vals)
