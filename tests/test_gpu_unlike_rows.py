@@ -96,3 +96,24 @@ def test_rows_of_few_elements(elem, shape):
     ms = [milliseconds(x, mesh) for x in b]
     assert_same(*(x.result() for x in b))
     assert ms[0] < 3 * ms[1], ms
+
+
+@pytest.mark.parametrize("n_node,prec", [(161, "fp64"), (161, "fp32"), (1000, "fp64")])
+def test_rows_of_every_length(n_node, prec):
+    """Random tetrahedra over few nodes: rows of every length up to n_node, at the edges of how
+    many columns the ordering takes at a time, against numpy's sums of whole numbers."""
+    rng = np.random.default_rng(n_node)
+    # (of 161 nodes every pair occurs, some 20 times)
+    conn = np.argsort(rng.random((48000 if n_node < 200 else 20000, n_node)), axis=1)[:, :4]
+    klow = rng.integers(-8, 9, (len(conn), 10)).astype(np.float64)
+    a, b = np.tril_indices(4)
+    row, col = (f(conn[:, a], conn[:, b]).astype(np.int64) for f in (np.maximum, np.minimum))
+    key, to = np.unique(row * n_node + col, return_inverse=True)
+    print(f"[every length] {n_node} {prec}", flush=True)
+    k = kb.assemble_lower_csr(torch.from_numpy(conn.astype(np.int32)).cuda(), n_node,
+                              torch.from_numpy(klow).to("cuda", kb.value_dtype(prec)), 4, prec=prec)
+    assert np.array_equal(k.row_ptr.cpu().numpy(), np.searchsorted(key, np.arange(n_node + 1) * n_node))
+    assert np.array_equal(k.col_idx.cpu().numpy(), key % n_node)
+    assert np.array_equal(k.vals.cpu().numpy().astype(np.float64), np.bincount(to.reshape(-1), klow.reshape(-1)))
+    if n_node < 200:
+        assert np.array_equal(np.diff(k.row_ptr.cpu().numpy()), np.arange(1, n_node + 1))
