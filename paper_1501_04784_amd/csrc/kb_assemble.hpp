@@ -1824,7 +1824,7 @@ struct HeavyTable {
   uint32_t* rpair;  // [kHvyRows] pairs of each row
   uint32_t* rsh;    // [kHvyRows] column shift of each row's digits
   uint32_t* rbase;  // [kHvyRows + 1] first digit of each row; rbase[kHvyRows] = digits
-  uint32_t* meta;   // [4] digits; workgroups of the sub-bucket's team done (heavy_team)
+  uint32_t* meta;   // [4] digits; workgroups done (heavy_team) or chunks counted (heavy_hist)
   __device__ HeavyTable(uint32_t* hvy, uint32_t it) {
     st = hvy + (size_t)it * kHvyWords;
     hist = st + kHvyDigits + 1;
@@ -2109,7 +2109,7 @@ __global__ __launch_bounds__(kPass3Threads) void k_pass3(uint32_t* __restrict__ 
 // node, all of it listed, took 128 ms).  In k_pass3 itself the parts made every sub-bucket
 // slower (scalar registers: 27M bricks 13.3 -> 13.7 ms); the launch takes 3 us when nothing
 // is listed.
-constexpr int kPartsGroups = 7;   // workgroups per CU
+constexpr int kPartsGroups = 2;   // workgroups per CU (empty: 3 us, with the seven that fit 4.5)
 template <typename V, int HT, bool RES = false>
 __global__ __launch_bounds__(kPass3Threads) void k_pass3_parts(
     uint32_t* __restrict__ ikey, V* __restrict__ ival, const uint32_t* __restrict__ sbb, const SubBuckets sub,
@@ -2668,6 +2668,7 @@ __device__ void heavy_rows(unsigned char* smem, const HeavyArgs<V>& A, uint32_t 
   for (uint32_t i = blk * kHeavyThreads + threadIdx.x; i < A.npar * (uint32_t)kHvyDigits; i += nblk * kHeavyThreads)
     HeavyTable(A.hvy, i / kHvyDigits).hist[i % kHvyDigits] = 0u;
   if (blk == 0 && threadIdx.x == 0) BigLeaves(A.hvy).list[0] = 0u;
+  if (blk == 0 && threadIdx.x < A.npar) HeavyTable(A.hvy, threadIdx.x).meta[1] = 0u;
   heavy_chunks(A.sbb, A.ov_list, A.npar, blk, nblk, [&](uint32_t it, uint32_t a, uint32_t b) {
     for (int r = threadIdx.x; r < kHvyRows; r += kHeavyThreads) s_rows[r] = 0u;
     __syncthreads();
@@ -2726,32 +2727,6 @@ __device__ __forceinline__ void heavy_load_layout(const HeavyTable& t, uint32_t*
   }
 }
 
-// Pairs per first-level digit, summed over the chunks into the table's hist.  Every
-// workgroup works out the digit layout from the row counts (a scan of 256 words: less
-// than a launch of its own takes); the one with a sub-bucket's first chunk stores it.
-template <typename V>
-__device__ void heavy_hist(unsigned char* smem, const HeavyArgs<V>& A, uint32_t blk, uint32_t nblk) {
-  uint32_t* const s_hist = (uint32_t*)smem;        // [kHvyDigits]
-  uint32_t* const s_rbase = s_hist + kHvyDigits;   // [kHvyRows + 1]
-  uint32_t* const s_rsh = s_rbase + kHvyRows + 1;  // [kHvyRows]
-  uint32_t* const s_scan = s_rsh + kHvyRows;       // [kHeavyThreads / 64 + 1]
-  const int colbits = A.colbits;
-  heavy_chunks(A.sbb, A.ov_list, A.npar, blk, nblk, [&](uint32_t it, uint32_t a, uint32_t b) {
-    const HeavyTable t(A.hvy, it);
-    const uint32_t g = A.ov_list[it];
-    for (int d = threadIdx.x; d < kHvyDigits; d += kHeavyThreads) s_hist[d] = 0u;
-    heavy_layout(t, t.rpair, A.sbb[g + 1] - A.sbb[g], colbits, a == A.sbb[g], s_rbase, s_rsh, s_scan);
-    const uint32_t nd = s_rbase[kHvyRows];
-    heavy_count(A.ikey, a, b, s_hist, [&](uint32_t k) { return heavy_digit(k, colbits, s_rbase, s_rsh); });
-    __syncthreads();
-    for (uint32_t d = threadIdx.x; d < nd; d += kHeavyThreads) {
-      const uint32_t c = s_hist[d];
-      if (c) atomicAdd(&t.hist[d], c);
-    }
-    __syncthreads();
-  });
-}
-
 // the row of digit d: the last r with rbase[r] <= d
 __device__ __forceinline__ uint32_t heavy_row(const uint32_t* rbase, uint32_t d) {
   uint32_t r = 0, n = kHvyRows;
@@ -2771,7 +2746,6 @@ template <typename V>
 __device__ void heavy_starts(unsigned char* smem, const HeavyArgs<V>& A, uint32_t it) {
   uint32_t* const s_off = (uint32_t*)smem;      // [kHvyDigits]
   uint32_t* const s_scan = s_off + kHvyDigits;  // [kHeavyThreads / 64 + 1]
-  if (it >= A.npar) return;
   const int colbits = A.colbits;
   uint32_t* const hvy = A.hvy;
   const HeavyTable t(hvy, it);
@@ -2803,6 +2777,43 @@ __device__ void heavy_starts(unsigned char* smem, const HeavyArgs<V>& A, uint32_
     }
   }
   if (threadIdx.x == 0) t.st[nd] = end;
+}
+
+// Pairs per first-level digit, summed over the chunks into the table's hist.  Every
+// workgroup works out the digit layout from the row counts (a scan of 256 words: less
+// than a launch of its own takes); the one with a sub-bucket's first chunk stores it, the
+// last to finish a chunk of it turns the counts into starts.
+template <typename V>
+__device__ void heavy_hist(unsigned char* smem, const HeavyArgs<V>& A, uint32_t blk, uint32_t nblk) {
+  uint32_t* const s_hist = (uint32_t*)smem;        // [kHvyDigits]
+  uint32_t* const s_rbase = s_hist + kHvyDigits;   // [kHvyRows + 1]
+  uint32_t* const s_rsh = s_rbase + kHvyRows + 1;  // [kHvyRows]
+  uint32_t* const s_scan = s_rsh + kHvyRows;       // [kHeavyThreads / 64 + 1]
+  __shared__ uint32_t s_last;
+  const int colbits = A.colbits;
+  heavy_chunks(A.sbb, A.ov_list, A.npar, blk, nblk, [&](uint32_t it, uint32_t a, uint32_t b) {
+    const HeavyTable t(A.hvy, it);
+    const uint32_t g = A.ov_list[it];
+    for (int d = threadIdx.x; d < kHvyDigits; d += kHeavyThreads) s_hist[d] = 0u;
+    heavy_layout(t, t.rpair, A.sbb[g + 1] - A.sbb[g], colbits, a == A.sbb[g], s_rbase, s_rsh, s_scan);
+    const uint32_t nd = s_rbase[kHvyRows];
+    heavy_count(A.ikey, a, b, s_hist, [&](uint32_t k) { return heavy_digit(k, colbits, s_rbase, s_rsh); });
+    __syncthreads();
+    for (uint32_t d = threadIdx.x; d < nd; d += kHeavyThreads) {
+      const uint32_t c = s_hist[d];
+      if (c) atomicAdd(&t.hist[d], c);
+    }
+    const uint32_t n = A.sbb[g + 1] - A.sbb[g];
+    __threadfence();  // this thread's counts and words of the layout before the arrival
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(&t.meta[1], 1u) == (n - 1) / kSplitChunk ? 1u : 0u;
+    __syncthreads();
+    if (s_last) {
+      __threadfence();
+      heavy_starts<V>(smem, A, it);
+    }
+    __syncthreads();
+  });
 }
 
 // Each chunk's pairs moved from (ikey, ival) to (akey, aval) in first-level digit
@@ -3149,7 +3160,7 @@ __device__ void heavy_team(unsigned char* smem, const HeavyArgs<V>& A, uint32_t 
 // phases are separate launches: one kernel
 // that hands their workgroups out as tickets in order, each phase waiting for the one
 // before, did not finish on a batch with two heavy rows.
-enum HeavyPhase { kHeavyRowsPhase, kHeavyHistPhase, kHeavyStartsPhase, kHeavyScatterPhase, kHeavyBigPhase,
+enum HeavyPhase { kHeavyRowsPhase, kHeavyHistPhase, kHeavyScatterPhase, kHeavyBigPhase,
                   kHeavyRangesPhase, kHeavyFinishPhase, kHeavyTeamPhase };
 constexpr int64_t kHeavySplitPairs = 1 << 16;
 constexpr int kScanHere = 16384;  // sub-buckets whose entry counts the last phase scans itself
@@ -3202,7 +3213,6 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy(HeavyArgs<V> A, const u
   const uint32_t blk = blockIdx.x, nblk = gridDim.x;
   if constexpr (PHASE == kHeavyRowsPhase) heavy_rows<V>(smem, A, blk, nblk);
   if constexpr (PHASE == kHeavyHistPhase) heavy_hist<V>(smem, A, blk, nblk);
-  if constexpr (PHASE == kHeavyStartsPhase) heavy_starts<V>(smem, A, blk);
   if constexpr (PHASE == kHeavyScatterPhase) heavy_scatter<V>(smem, A, blk, nblk);
   if constexpr (PHASE == kHeavyBigPhase) heavy_bigleaf<V>(smem, A, blk, nblk);
   if constexpr (PHASE == kHeavyRangesPhase) {

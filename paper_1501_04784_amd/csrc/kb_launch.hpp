@@ -297,7 +297,6 @@ int launch_pass3(const Plan& p, unsigned char* ws, V* tres, int64_t* nnz_dev, hi
                  std::max<unsigned>(kHeavyPar, (unsigned)std::min<int64_t>(p.nsub, cus)), HeavySmem::bytes());
   KB_TRY(phase(k_heavy<V, RES, kHeavyRowsPhase>, 2 * cus, kTabLds));
   KB_TRY(phase(k_heavy<V, RES, kHeavyHistPhase>, 2 * cus, kTabLds));
-  KB_TRY(phase(k_heavy<V, RES, kHeavyStartsPhase>, kHeavyPar, kTabLds));
   KB_TRY(phase(k_heavy<V, RES, kHeavyScatterPhase>, 2 * cus, kTabLds));
   KB_TRY(phase(k_heavy<V, RES, kHeavyBigPhase>, cus, HeavySmem::bytes()));
   KB_TRY(phase(k_heavy<V, RES, kHeavyRangesPhase>, cus, HeavySmem::bytes()));
