@@ -364,7 +364,8 @@ int kb_build_lower_csr_batched(const kb_batch* batch, int prec, const kb_tuning*
  * integration point sets KB_F_INVERTED; one whose gradients are not finite (degenerate
  * geometry, non-finite coordinates or coefficient) sets KB_F_NONFINITE, and its
  * non-finite node contributions are left out of the sums.  Workspace from
- * kb_plan_adjoint (host only).  Errors: KB_EINVAL (bad argument, nnz < 0), KB_ERANGE
+ * kb_plan_adjoint (host only): about 36 bytes for each element's corner (a record and its
+ * place), and a few megabytes for nodes of very many elements.  Errors: KB_EINVAL (bad argument, nnz < 0), KB_ERANGE
  * (nnz beyond int32 indexing).
  */
 int kb_plan_adjoint(const kb_mesh* mesh, size_t* ws_bytes);

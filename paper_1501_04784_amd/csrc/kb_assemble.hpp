@@ -27,7 +27,8 @@
 //            atomics.  Entries are then ordered by (row, col) and converted once
 //            (correct rounding of the exact sum to the value type).
 //   final    scan of per-sub-bucket unique counts; row_ptr and the compacted col/vals.
-// Sub-buckets whose distinct entries overflow the table are reduced by k_heavy.
+// Sub-buckets whose distinct entries overflow the table are reduced in parts (k_pass3_parts) or
+// by k_heavy.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -297,7 +298,7 @@ __device__ __forceinline__ bool goes_direct(int mode, const uint32_t* __restrict
 // direct way's sub-buckets may fill pass 3's table to kDirectLoad where the two-level
 // way's may not (under a random numbering the last rows are twice the average): 32 rows of
 // bricks instead of 16 (27M bricks FP64, pass 3 5.9 -> 4.9 ms; randomly numbered 1M bricks
-// 0.28 -> 0.33 ms).
+// 0.28 -> 0.33 ms).  Where rows are of unlike length all the same, k_pass3_parts takes over.
 struct SubBuckets {
   int s2[2], nsub[2];
   int mode;
@@ -1799,10 +1800,10 @@ __global__ __launch_bounds__(NT) void k_scatter2(const uint16_t* __restrict__ ir
 }
 
 // The first kHeavyPar heavy sub-buckets of the list are split, and their first-level
-// digit ranges reduced, by many workgroups (the phases of k_heavy: heavy_rows, heavy_layout, heavy_hist,
-// heavy_starts, heavy_scatter, heavy_bigleaf, heavy_ranges); heavy_finish then
-// sums up each one's entries and k_final gathers them from the ranges.
-// heavy_rest clears their tables and takes the other listed sub-buckets whole.
+// digit ranges reduced, by many workgroups (the phases of k_heavy: heavy_rows; heavy_layout,
+// heavy_hist and heavy_starts; heavy_scatter; heavy_bigleaf; heavy_ranges); heavy_finish then
+// sums up each one's entries and k_final gathers them from the ranges.  heavy_rest takes the
+// other listed sub-buckets whole.  (In small builds teams do the same in one launch: heavy_team.)
 // The first-level digits follow the rows: row r of a sub-bucket gets n_r digits (a
 // power of two, none for a row without pairs), each covering 2^(colbits) / n_r columns,
 // with n_r about kHvyShare times the row's share of the pairs, at most one digit per
