@@ -158,7 +158,7 @@ int make_plan(const kb_mesh* m, int prec, const kb_tuning* tu, Plan* p, int dof 
   const double u_wide = std::max(u_row, u_alone * pow(std::max(1.0, avg / u_alone), m->elem == KB_TET4 ? 0.37 : 0.546) +
                                             (p->nn > 0 ? (double)csr_cap / (double)p->nn : 0.0));
   p->s2d = p->s2;
-  if (!sub_bits)
+  if (!sub_bits && p->nsub >= kWideSubs)
     while (p->s2d < s2_max && (double)(2 << p->s2d) * u_wide <= kDirectLoad * p->ht) ++p->s2d;
   auto set_direct = [&](int s2d) {
     p->s2d = s2d;

@@ -27,6 +27,11 @@ constexpr int kSegThreads = 512;   // threads per pass-2 scatter workgroup
 constexpr int kTargetBuckets = 256;  // first-level buckets (pass-1 run length)
 constexpr double kSubEntries = 300;   // target distinct entries per sub-bucket
 constexpr double kDirectLoad = 0.46;  // of pass 3's table, at most, on the direct way
+// (and only where there are more sub-buckets than the device takes at once: fewer, larger ones
+// are then one round of longer workgroups.  64 small boxes of tetrahedra, 1755 sub-buckets: 109 us
+// against 120, in random order, where rows are of unlike length, 112 against 161; 128 boxes of
+// bricks, 27,449: 299 against 278, in random order 362 against 344)
+constexpr int64_t kWideSubs = 4096;
 constexpr int kHTMin = 512, kHTMax = 4096;
 // the direct way for small meshes: at most kDirectRuns runs (tiles x sub-buckets), each of
 // which may take a global atomic when counted and when written (72,000 tets in random order,

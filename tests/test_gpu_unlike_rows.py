@@ -117,3 +117,18 @@ def test_rows_of_every_length(n_node, prec):
     assert np.array_equal(k.vals.cpu().numpy().astype(np.float64), np.bincount(to.reshape(-1), klow.reshape(-1)))
     if n_node < 200:
         assert np.array_equal(np.diff(k.row_ptr.cpu().numpy()), np.arange(1, n_node + 1))
+
+
+def test_small_boxes_in_random_order():
+    """A batch of small boxes, whose last rows are twice the average: with few sub-buckets their
+    tables are not filled further than the two levels' (they took 1.3 times as long)."""
+    rng = np.random.default_rng(8)
+    boxes = [meshgen.box_mesh(4, *(int(x) for x in rng.integers(3, 15, 3)), jitter=0.1, coef=(0.1, 10.0), seed=i,
+                              permute_nodes=True, permute_elems=True) for i in range(64)]
+    batch = kb.pack_batch([(m.conn, m.coords, m.coef) for m in boxes], 4, "cuda")
+    print("[small boxes]", flush=True)
+    b = [kb.BatchBuilder(batch, prec="fp32fb64", tuning=t) for t in (None, TWO_LEVEL)]
+    ms = [milliseconds(x, ()) for x in b]
+    for x, y in zip(*(x.results() for x in b)):
+        assert_same(x, y)
+    assert ms[0] < 1.1 * ms[1], ms
