@@ -532,7 +532,7 @@ def main():
     ms, wall_ms, stages, res, way = time_builds(kb, torch, mesh_dev, m, prec, args.steps, args.warmup,
                                                 stage_events=not args.profile_steps, tuning=tuning, op=args.op,
                                                 groups=groups)
-    direct, tile = way or (False, 0)
+    direct, tile = way or (None, 0)  # (a grouped build decides pass by pass)
     nnz = res.nnz
     print(f"[bench] {prec}: {ms:.3f} ms/step, nnz {nnz}, fallback elements {res.n_fallback}", file=sys.stderr,
           flush=True)
@@ -542,7 +542,7 @@ def main():
     n_fallback = res.n_fallback
     del res
     value = m.n_elem / (ms * 1e-3)
-    ab = algorithmic_bytes(m.elem, m.n_elem, m.n_node, nnz, prec, direct)
+    ab = algorithmic_bytes(m.elem, m.n_elem, m.n_node, nnz, prec, bool(direct))
     out = {
         "metric": METRIC, "value": value, "unit": "elements/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "scaling": "weak",
