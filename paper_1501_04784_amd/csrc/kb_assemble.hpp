@@ -505,8 +505,10 @@ __device__ __forceinline__ void count_elements(const TileSlots<DIRECT>& sl, cons
 }
 
 // Elements of more than 8 rows come in tiles of a few dozen: a lane takes one row of an
-// element (1M bricks of 3 components, 31 elements a tile: 501 -> 436 us).  s_E: LDS for te
-// elements' ids, then a word each (its errors).
+// element (1M bricks of 3 components, 31 elements a tile: 501 -> 436 us).  On two levels only
+// those of more than 16, whose ids and ranks overflow a lane's registers (bricks of 3 components
+// 97 -> 38 us; tetrahedra of 3, 90 elements a tile: 84 with a lane a row, 65 with one an element).
+// s_E: LDS for te elements' ids, then a word each (its errors).
 template <int NEN, bool DIRECT>
 __device__ __forceinline__ void count_rows(const TileSlots<DIRECT>& sl, uint32_t* s_E, const int32_t* __restrict__ conn,
                                            int64_t e0, int64_t e1, int te, int64_t n_node,
@@ -559,7 +561,7 @@ __device__ __forceinline__ void count_tiles(uint32_t* s_h, const int32_t* __rest
     sl.clear(blockDim.x);
     __syncthreads();
     const int64_t e0 = t * te, n = DIRECT ? (t1 - t0) * te : te, e1 = e0 + n < n_elem ? e0 + n : n_elem;
-    if constexpr (NEN > 8)
+    if constexpr (NEN > 8 && (DIRECT || NEN > 16))
       count_rows<NEN>(sl, s_h + slot_words, conn, e0, e1, te, n_node, subcnt, &flags);
     else
       count_elements<NEN>(sl, conn, e0, e1, n_node, subcnt, &flags);
