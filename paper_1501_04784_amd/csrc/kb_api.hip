@@ -152,8 +152,8 @@ int make_plan(const kb_mesh* m, int prec, const kb_tuning* tu, Plan* p, int dof 
   // the direct way's sub-buckets fill the table further, so an entry's average number of
   // elements has to be known better: elements that share no node give a row (nen + 1) / 2
   // entries, each of one element; with more elements a row (1-cell beams, 1-cell sheets, boxes)
-  // its entries grow as the power of its pairs that meets the boxes' figure above (sheet and
-  // beam within 4%: 9.5 and 6.5 entries a row of bricks, 6 and 4.25 of tetrahedra)
+  // its entries grow as the power of its pairs that meets the boxes' figure above (a sheet's and
+  // a beam's within 8%: 9.5 and 6.5 entries a row of bricks, 6 and 4.5 of tetrahedra)
   const double u_alone = 0.5 * (p->nen + 1);
   const double u_wide = std::max(u_row, u_alone * pow(std::max(1.0, avg / u_alone), m->elem == KB_TET4 ? 0.37 : 0.546) +
                                             (p->nn > 0 ? (double)csr_cap / (double)p->nn : 0.0));

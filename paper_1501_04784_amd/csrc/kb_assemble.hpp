@@ -2110,9 +2110,9 @@ __global__ __launch_bounds__(kPass3Threads) void k_pass3(uint32_t* __restrict__ 
 // table; its pairs are read once per part.  What does not fit its table goes to ov_list,
 // for k_heavy (a workgroup of which takes some 0.5 ms: a mesh of 216,000 bricks that share no
 // node, all of it listed, took 128 ms).  In k_pass3 itself the parts made every sub-bucket
-// slower (scalar registers: 27M bricks 13.3 -> 13.7 ms); the launch takes 3 us when nothing
+// slower (scalar registers: 27M bricks 13.3 -> 13.7 ms); the launch takes 4 us when nothing
 // is listed.
-constexpr int kPartsGroups = 2;   // workgroups per CU (empty: 3 us, with the seven that fit 4.5)
+constexpr int kPartsGroups = 2;   // workgroups per CU
 template <typename V, int HT, bool RES = false>
 __global__ __launch_bounds__(kPass3Threads) void k_pass3_parts(
     uint32_t* __restrict__ ikey, V* __restrict__ ival, const uint32_t* __restrict__ sbb, const SubBuckets sub,
@@ -2742,20 +2742,20 @@ __device__ __forceinline__ uint32_t heavy_row(const uint32_t* rbase, uint32_t d)
   return r;
 }
 
-// Per listed sub-bucket, the digit starts (absolute pair positions) from the
-// digit counts, which become the scatter's cursors; digit ranges no wider than a leaf with
-// more than kBigLeafPairs pairs are listed as big leaves
+// A split sub-bucket's digit starts (absolute pair positions) from its digit counts, which become
+// the scatter's cursors; digit ranges no wider than a leaf with more than kBigLeafPairs pairs are
+// listed as big leaves.  s_off: kHvyDigits words; s_rbase, s_rsh: the layout; s_scan as block_scan.
 template <typename V>
-__device__ void heavy_starts(unsigned char* smem, const HeavyArgs<V>& A, uint32_t it) {
-  uint32_t* const s_off = (uint32_t*)smem;      // [kHvyDigits]
-  uint32_t* const s_scan = s_off + kHvyDigits;  // [kHeavyThreads / 64 + 1]
+__device__ __forceinline__ void heavy_starts(const HeavyArgs<V>& A, uint32_t it, uint32_t* s_off,
+                                             const uint32_t* s_rbase, const uint32_t* s_rsh, uint32_t* s_scan) {
   const int colbits = A.colbits;
   uint32_t* const hvy = A.hvy;
   const HeavyTable t(hvy, it);
-  const uint32_t nd = t.meta[0];
+  const uint32_t nd = s_rbase[kHvyRows];
   const uint32_t g = A.ov_list[it];
   const uint32_t beg = A.sbb[g], end = A.sbb[g + 1];
-  for (uint32_t d = threadIdx.x; d < nd; d += kHeavyThreads) s_off[d] = t.hist[d];
+  for (uint32_t d = threadIdx.x; d < nd; d += kHeavyThreads)
+    s_off[d] = __hip_atomic_load(&t.hist[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   block_scan_array(s_off, (int)nd, s_scan);  // (ends with a barrier)
   const BigLeaves big(hvy);
@@ -2764,8 +2764,7 @@ __device__ void heavy_starts(unsigned char* smem, const HeavyArgs<V>& A, uint32_
     t.st[d] = a;
     t.hist[d] = a;
     if (b - a > kBigLeafPairs) {
-      const uint32_t r = heavy_row(t.rbase, d);  // (rare: read from the table)
-      const uint32_t sh = t.rsh[r];
+      const uint32_t r = heavy_row(s_rbase, d), sh = s_rsh[r];
       if ((1u << sh) <= (uint32_t)kLeafKeys) {
         const uint32_t i = atomicAdd(big.list, 1u);
         if (i < (uint32_t)kBigLeaves) {
@@ -2774,7 +2773,7 @@ __device__ void heavy_starts(unsigned char* smem, const HeavyArgs<V>& A, uint32_
           q[1] = d;
           q[2] = a;
           q[3] = b;
-          q[4] = (r << colbits) + ((d - t.rbase[r]) << sh);
+          q[4] = (r << colbits) + ((d - s_rbase[r]) << sh);
         }
       }
     }
@@ -2807,14 +2806,14 @@ __device__ void heavy_hist(unsigned char* smem, const HeavyArgs<V>& A, uint32_t 
       if (c) atomicAdd(&t.hist[d], c);
     }
     const uint32_t n = A.sbb[g + 1] - A.sbb[g];
-    __threadfence();  // this thread's counts and words of the layout before the arrival
+    // this thread's counts done before the arrival (as last_block_starts: nothing but the counts,
+    // which are atomics, passes on; a fence's write-back of the L2 for each chunk took 0.12 ms of a
+    // fan of 1M tetrahedra)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) s_last = atomicAdd(&t.meta[1], 1u) == (n - 1) / kSplitChunk ? 1u : 0u;
     __syncthreads();
-    if (s_last) {
-      __threadfence();
-      heavy_starts<V>(smem, A, it);
-    }
+    if (s_last) heavy_starts<V>(A, it, s_hist, s_rbase, s_rsh, s_scan);
     __syncthreads();
   });
 }
