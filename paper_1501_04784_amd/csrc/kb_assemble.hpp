@@ -1880,8 +1880,10 @@ constexpr int kPass3Threads = 256;
 // (and residual) is kept in place of its low chunk sum, which frees the high chunk sums for
 // the columns grouped by row (one array fewer); a double with its double residual needs both
 // words.  The per-row arrays are sized by the sub-bucket's rows at launch and the columns are
-// grouped by row through cursors (no per-slot index within the row): 22.4 KB at 1024 slots,
-// seven workgroups per CU
+// grouped by row through cursors (no per-slot index within the row): 22.5 KB at 1024 slots,
+// seven workgroups per CU; with a double's residuals 26.5 KB, of which six fit as long as 64 rows
+// take no more than 512 bytes and the two words below none (1.8M tetrahedra in two
+// groups: 91 -> 83 us)
 template <typename V, int HT, bool RES>
 struct Pass3Smem {
   static constexpr bool kSepCols = RES && sizeof(V) == 8;
@@ -1890,7 +1892,7 @@ struct Pass3Smem {
   unsigned long long* hi;  // sum of signed high chunks, then the columns
   uint16_t* slot;          // occupied slots, in insertion order
   uint32_t* lcol;          // columns of the slots, grouped by row
-  uint32_t *rc, *ro, *cur;  // [1 << s2] entries per row, row offsets, cursors
+  uint32_t *rc, *cur;      // [1 << s2] entries per row; cursors, at last each row's end
   uint32_t *over, *nu;     // the table is full; occupied slots
   __device__ __forceinline__ void clear(int rows) const {
     for (int h = threadIdx.x; h < HT; h += kPass3Threads) {
@@ -1963,9 +1965,10 @@ __device__ __forceinline__ void pass3_insert(const Pass3Smem<V, HT, RES>& sm, co
 constexpr uint32_t kLongRow = 128;
 
 // The table's entries rounded, ordered by (row, col) and written from tcol / tval / tres
-// [0, ...) on, and the first entries of rows [row_lo, row_hi), counted from u0, to rowoff
+// [0, ...) on, and the first entries of rows [row_lo, row_hi), counted from u0, to rowoff.
+// Returns their number.
 template <typename V, int HT, bool RES>
-__device__ __forceinline__ void pass3_emit(const Pass3Smem<V, HT, RES>& sm, int F, int colbits, int s2, uint32_t u0,
+__device__ __forceinline__ uint32_t pass3_emit(const Pass3Smem<V, HT, RES>& sm, int F, int colbits, int s2, uint32_t u0,
                                            int row_lo, int row_hi, int32_t* tcol, V* tval, V* tres,
                                            uint32_t* rowoff) {
   constexpr int NT = kPass3Threads;
@@ -2017,10 +2020,7 @@ __device__ __forceinline__ void pass3_emit(const Pass3Smem<V, HT, RES>& sm, int 
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int r = lane * 4 + k;
-      if (r < RB) {
-        sm.ro[r] = run;
-        sm.cur[r] = run;
-      }
+      if (r < RB) sm.cur[r] = run;
       run += v[k];
     }
   }
@@ -2035,7 +2035,7 @@ __device__ __forceinline__ void pass3_emit(const Pass3Smem<V, HT, RES>& sm, int 
     const uint32_t h = sm.slot[f];
     const uint32_t k = sm.key[h];
     const uint32_t row = k >> colbits, col = k & cmask;
-    const uint32_t ro = sm.ro[row], nr = sm.rc[row];
+    const uint32_t nr = sm.rc[row], ro = sm.cur[row] - nr;
     uint32_t rank = 0, q = 0;
     if (nr >= kLongRow)
 #pragma unroll 1
@@ -2056,7 +2056,8 @@ __device__ __forceinline__ void pass3_emit(const Pass3Smem<V, HT, RES>& sm, int 
       if constexpr (RES) tres[pos] = (V)__uint_as_float((uint32_t)(w >> 32));
     }
   }
-  for (int r = row_lo + threadIdx.x; r < row_hi; r += NT) rowoff[r] = u0 + sm.ro[r];
+  for (int r = row_lo + threadIdx.x; r < row_hi; r += NT) rowoff[r] = u0 + sm.cur[r] - sm.rc[r];
+  return U;
 }
 
 template <typename V, int HT, bool RES = false>
@@ -2072,18 +2073,17 @@ __global__ __launch_bounds__(kPass3Threads) void k_pass3(uint32_t* __restrict__ 
   __shared__ unsigned long long s_lo[HT];
   __shared__ unsigned long long s_hi[HT];
   __shared__ uint16_t s_slot[HT];
-  __shared__ uint32_t s_sep[SM::kSepCols ? HT : 1];
-  __shared__ uint32_t s_over, s_nu;
-  extern __shared__ uint32_t s_rows[];  // 3 << s2 words
+  __shared__ uint32_t s_sep[SM::kSepCols ? HT : 2];
+  uint32_t &s_over = s_sep[0], &s_nu = s_sep[1];  // (read before the columns are written)
+  extern __shared__ uint32_t s_rows[];  // 2 << s2 words
   const int64_t g = blockIdx.x;
   const bool either = g < sub.nsub[1];
   if (!either && sub.pick()) return;  // (only the workgroups beyond the direct way's wait for its word here)
   const uint32_t beg = sbb[g], end = sbb[g + 1];
-  SM sm{s_key, s_lo, s_hi, s_slot, SM::kSepCols ? s_sep : (uint32_t*)s_hi, s_rows, nullptr, nullptr, &s_over, &s_nu};
+  SM sm{s_key, s_lo, s_hi, s_slot, SM::kSepCols ? s_sep : (uint32_t*)s_hi, s_rows, nullptr, &s_over, &s_nu};
   sm.clear(1 << (sub.s2[0] > sub.s2[1] ? sub.s2[0] : sub.s2[1]));
   const int s2 = sub.s2[either ? sub.pick() : 0];
-  sm.ro = s_rows + (1 << s2);
-  sm.cur = s_rows + (2 << s2);
+  sm.cur = s_rows + (1 << s2);
   const int F = 1117 - (int)*emax;
   const int64_t r0 = g << s2;
   const int64_t rr = n_node - r0;
@@ -2100,8 +2100,9 @@ __global__ __launch_bounds__(kPass3Threads) void k_pass3(uint32_t* __restrict__ 
     if (threadIdx.x == 0) list[atomicAdd(count, 1u)] = (uint32_t)g;
     return;
   }
-  pass3_emit(sm, F, colbits, s2, 0u, 0, R, tcol + beg, tval + beg, RES ? tres + beg : nullptr, rowoff + r0);
-  if (threadIdx.x == 0) usub[g] = s_nu;
+  const uint32_t U =
+      pass3_emit(sm, F, colbits, s2, 0u, 0, R, tcol + beg, tval + beg, RES ? tres + beg : nullptr, rowoff + r0);
+  if (threadIdx.x == 0) usub[g] = U;
 }
 
 // The sub-buckets that k_pass3 listed, if the direct way's are the wider ones.  Those are
@@ -2125,14 +2126,14 @@ __global__ __launch_bounds__(kPass3Threads) void k_pass3_parts(
   __shared__ unsigned long long s_lo[HT];
   __shared__ unsigned long long s_hi[HT];
   __shared__ uint16_t s_slot[HT];
-  __shared__ uint32_t s_sep[SM::kSepCols ? HT : 1];
-  __shared__ uint32_t s_over, s_nu;
-  extern __shared__ uint32_t s_rows[];  // 3 << s2 words
+  __shared__ uint32_t s_sep[SM::kSepCols ? HT : 2];
+  uint32_t &s_over = s_sep[0], &s_nu = s_sep[1];  // (read before the columns are written)
+  extern __shared__ uint32_t s_rows[];  // 2 << s2 words
   const uint32_t n_list = *count;
   if (blockIdx.x >= n_list) return;
   const int s2 = sub.s2[sub.pick()], s2p = s2 < sub.s2[0] ? s2 : sub.s2[0], np = 1 << (s2 - s2p);
   const SM sm{s_key,  s_lo, s_hi, s_slot, SM::kSepCols ? s_sep : (uint32_t*)s_hi, s_rows, s_rows + (1 << s2),
-              s_rows + (2 << s2), &s_over, &s_nu};
+              &s_over, &s_nu};
   const int F = 1117 - (int)*emax;
   for (uint32_t i = blockIdx.x; i < n_list; i += gridDim.x) {
     const int64_t g = list[i], r0 = g << s2;
@@ -2152,9 +2153,8 @@ __global__ __launch_bounds__(kPass3Threads) void k_pass3_parts(
       __syncthreads();
       if (s_over) break;
       const int lo = p << s2p, hi = lo + (1 << s2p) < R ? lo + (1 << s2p) : R;
-      pass3_emit(sm, F, colbits, s2, U, lo, hi, tcol + beg + U, tval + beg + U, RES ? tres + beg + U : nullptr,
-                 rowoff + r0);
-      U += s_nu;
+      U += pass3_emit(sm, F, colbits, s2, U, lo, hi, tcol + beg + U, tval + beg + U, RES ? tres + beg + U : nullptr,
+                      rowoff + r0);
     }
     if (threadIdx.x == 0) {
       if (p == np)

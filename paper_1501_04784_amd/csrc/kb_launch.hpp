@@ -263,7 +263,7 @@ int launch_pass3(const Plan& p, unsigned char* ws, V* tres, int64_t* nnz_dev, hi
   auto* usub = (uint32_t*)(ws + p.o_usub);
   auto* ov_list = (uint32_t*)(ws + p.o_ovl);
   const SubBuckets sub = sub_buckets(p, ws);
-  const size_t lds3 = (size_t)12 << std::max(p.s2, p.s2d);
+  const size_t lds3 = (size_t)8 << std::max(p.s2, p.s2d);
   const bool parts = p.mode == kAsk && p.s2d > p.s2;
   // (the list of k_pass3_parts lies where the scan of the entry counts goes later)
   auto* list = parts ? (uint32_t*)(ws + p.o_ubase) : ov_list;
